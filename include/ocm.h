@@ -98,14 +98,15 @@ typedef struct {
     int32_t iterations;        /* policy-improvement sweeps, first and last included */
     uint32_t flags;            /* OCM_F_*                                      */
     int32_t connect_rounds;    /* breadth-first connect rounds, all iterations */
-    int32_t jump_rounds;       /* pointer-jumping rounds, all iterations       */
+    int32_t jump_rounds;       /* cycle jump rounds + value_rounds             */
     int32_t fast_iters;        /* iterations resolved by the fused fast path   */
     int64_t W, L;              /* unreduced optimum W/L: weight and length of C */
     int64_t tight_edges;       /* tight non-policy edges at the optimum        */
     int64_t push_frontier;     /* frontier vertices expanded by push rounds    */
     int64_t push_in_edges;     /* in-edges scanned by push rounds              */
     int32_t general_iters;     /* iterations that ran the cycle/select/rebuild phases */
-    int32_t value_rounds;      /* pointer-jumping rounds of the value phases   */
+    int32_t value_rounds;      /* value phases run (one that needs entries of 16
+                                  bytes or more counts its doubling rounds)    */
 } ocm_result;
 
 /* Device time per kernel class, filled when ocm_options.profile is non-null

@@ -231,7 +231,9 @@ __device__ __forceinline__ bool last_arrival(Ctl* c, unsigned long long word,
     const unsigned long long lp = atomicAdd(&c->lane[lane].rpack, word + kArrive);
     if ((unsigned)(lp >> 48) != in_lane - 1) return false;
     __hip_atomic_store(&c->lane[lane].rpack, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long lane_sum = lp + word + kArrive - (unsigned long long)in_lane * kArrive;
+    unsigned long long lane_sum = lp + word + kArrive - (unsigned long long)in_lane * kArrive;
+    // one flag per lane from here on: the top word's flag field cannot spill
+    if ((lane_sum >> 32) & 0xffffu) lane_sum = (lane_sum & 0xffffffffull) | (1ull << 32);
     const unsigned long long tp = atomicAdd(&c->rpack, lane_sum + kArrive);
     if ((unsigned)(tp >> 48) != lanes - 1) return false;
     __hip_atomic_store(&c->rpack, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -78,6 +78,15 @@ struct alignas(128) Ctl {
     unsigned scnt;                 // tie check: special vertices
     unsigned clen;                 // select: edges of the chosen cycle (its L for a mean)
     unsigned ngiant;               // rows longer than kGiantRow
+    // device-driven loop (sweeps and value chases queued ahead of the host)
+    unsigned fmode;                //   kLoopStop / kLoopSweep / kLoopChase: what runs next
+    unsigned fwhy;                 //   once stopped: kWhy*
+    unsigned fopts;                //   kLoop* options of the run
+    unsigned fsweeps, fmax;        //   sweeps run, sweeps allowed
+    unsigned ffast;                //   value phases completed after a sweep of the run
+    unsigned fphases;              //   value phases begun after a sweep of the run
+    unsigned fflags;               //   kChase* events of the running value phase
+    unsigned fwide;                //   the last value phase left a value outside int32
     CtlLane lane[kLanes];
 };
 
@@ -89,6 +98,7 @@ struct CtlView {
     unsigned rmode, rleft, rfront, rerr, rk;
     unsigned jk, jmode, jlast, jstall;
     unsigned xcnt, scnt, clen, ngiant;
+    unsigned fmode, fwhy, fsweeps, ffast, fphases, fwide;
     unsigned long long changed, tight, certain, nondec, pedges, ledges, maxabsw;
     unsigned active, active2, got, left, err, cbroken, overflow, bad;
     unsigned pjc[4];
@@ -114,6 +124,12 @@ __host__ __device__ inline void fold_lanes(const Ctl& c, CtlView& v)
     v.scnt = c.scnt;
     v.clen = c.clen;
     v.ngiant = c.ngiant;
+    v.fmode = c.fmode;
+    v.fwhy = c.fwhy;
+    v.fsweeps = c.fsweeps;
+    v.ffast = c.ffast;
+    v.fphases = c.fphases;
+    v.fwide = c.fwide;
     v.changed = v.tight = v.certain = v.nondec = v.pedges = v.ledges = v.maxabsw = 0;
     v.active = v.active2 = v.got = v.left = v.err = v.cbroken = v.overflow = v.bad = 0;
     v.wide32 = v.ncrit = 0;
@@ -158,6 +174,35 @@ struct alignas(16) Jmp {
     unsigned H;
 };
 
+// Device-driven loop: the host queues (sweep, chase) pairs; each kernel runs
+// only while fmode names it, and its last workgroup decides what comes next
+// or stops the run with a reason.
+constexpr unsigned kLoopStop = 0, kLoopSweep = 1, kLoopChase = 2;   // fmode
+constexpr unsigned kLoopChain = 1;   // fopts: sweeps follow the value phase (else it stops there)
+constexpr unsigned kLoopV32 = 2;     //        the queued sweeps gather the int32 copy
+enum : unsigned {                    // fwhy
+    kWhyNone = 0,
+    kWhyConverged,                   // a sweep changed nothing
+    kWhyBroken,                      // a vertex of C changed policy
+    kWhyStall,                       // some vertex does not reach the source
+    kWhyOverflow,                    // a sum does not fit the packed entries
+    kWhyWide,                        // a value does not fit the int32 copy (values are complete)
+    kWhyIters,                       // fmax sweeps run
+    kWhyOnce                         // value phase complete, no sweep wanted
+};
+constexpr unsigned kChaseStall = 1, kChaseOverflow = 2, kChaseWide = 4;   // fflags
+// The loop's arrivals count workgroups of 256 vertices in 15 bits per lane.
+constexpr int64_t kLoopMaxN = int64_t(1) << 27;
+
+// Packed entry of the value chase: (sum << jb) | vertex reached, jb bits for
+// the vertex and the rest, signed, for the sum.
+inline int chase_bits(int64_t n)
+{
+    int b = 1;
+    while ((int64_t(1) << b) < n) ++b;
+    return b;
+}
+
 // Rows of more than kGiantRow edges are swept by several workgroups: one per
 // chunk of at most kGiantChunk consecutive edges (k_giant_part), then one
 // merge per row in chunk order (k_giant_merge); the tile kernels skip them.
@@ -197,7 +242,33 @@ struct SweepArgs {
     unsigned* xcnt;
     unsigned xcap;
     GiantTab giant;                // rows swept by several workgroups (tile sweeps only)
+    // device-driven loop (counting tile sweeps only; E null: not part of it):
+    // the sweep also writes every vertex's chase entry, and closes the loop's
+    // sweep step unless giant rows follow (launch_loop_close then does)
+    unsigned long long* E = nullptr;
+    int jb = 0;
+    int src = -1;                  // source: its entry is finished
 };
+
+// Device-driven loop.  setup arms it (mode: what runs first; opts: kLoop*;
+// max_sweeps: sweeps allowed) and clears the sweep counters.
+void launch_loop_setup(Ctl* ctl, unsigned mode, unsigned opts, unsigned max_sweeps,
+                       hipStream_t st);
+// Closes a sweep step whose giant rows were merged after the tile kernel.
+void launch_loop_close(Ctl* ctl, hipStream_t st);
+// Chase entries of every vertex from pi (succ = col[pi] is written too).
+void launch_chase_init(int n, const int* col, const int* pi, const void* w, int wtype, int neg,
+                       int s, long long W, long long L, int* succ, unsigned long long* E, int jb,
+                       Ctl* ctl, const int* t, hipStream_t st);
+// One pass of the value chase; a vertex that reaches s gets its sum in V
+// (nullable) and out32.
+void launch_chase(int n, int s, int jb, unsigned long long* E, long long* V, int* out32, Ctl* ctl,
+                  hipStream_t st);
+// Entries whose sums count policy hops (jb = 32).
+void launch_hop_init(int n, int s, const int* succ, unsigned long long* E, hipStream_t st);
+// C's edges by walking succ from s (one thread).
+void launch_cycle_walk(int s, long long L, const int* pi, const int* succ, int* out,
+                       hipStream_t st);
 
 // Giant rows: (vertex, first, end) triples of every row longer than
 // kGiantRow edges, appended in any order (at most cap; ctl->ngiant counts

@@ -312,6 +312,55 @@ __global__ __launch_bounds__(kWG) void k_sweep_tile(SweepArgs a, const WT* __res
     }
 }
 
+// ---------------------------------------------------------------------------
+// Device-driven loop: what follows a sweep.  One thread (the last workgroup's,
+// or k_loop_close's) calls it with the sweep's folded outcome.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void loop_stop(Ctl* c, unsigned why)
+{
+    c->fwhy = why;
+    c->fmode = kLoopStop;
+}
+
+__device__ void loop_after_sweep(Ctl* c, bool changed, bool broken)
+{
+    const unsigned it = c->fsweeps + 1;
+    c->fsweeps = it;
+    if (!changed) {
+        loop_stop(c, kWhyConverged);
+    } else if (it >= c->fmax) {
+        loop_stop(c, kWhyIters);
+    } else if (broken) {
+        loop_stop(c, kWhyBroken);
+    } else {
+        c->jlast = 0xffffffffu;
+        c->fphases += 1;
+        c->fmode = kLoopChase;
+    }
+}
+
+// A chase entry: the sum in the upper 64 - jb bits (signed), the vertex
+// reached below.  Returns false when the sum does not fit.
+__device__ __forceinline__ bool chase_pack(long long d, unsigned j, int jb, unsigned long long* e)
+{
+    const unsigned long long up = (unsigned long long)d << jb;
+    *e = up | j;
+    return ((long long)up >> jb) == d;
+}
+
+// The entry of vertex v with policy edge p and head h.
+template <typename WT, bool RATIO>
+__device__ __forceinline__ bool chase_entry(const SweepArgs& a, const WT* __restrict__ w, int64_t v,
+                                            int p, int h, unsigned long long* e)
+{
+    if (v == a.src) {
+        *e = (unsigned)a.src;
+        return true;
+    }
+    const long long d = a.L * wval(w, p, a.neg) - (RATIO ? a.W * (long long)a.t[p] : a.W);
+    return chase_pack(d, (unsigned)h, a.jb, e);
+}
+
 // Tie scan over a tile (batches as k_sweep_tile; the heads are kept in LDS
 // too).  Counts the tight edges other than the policy edge, those that
 // certainly close a second critical cycle (a tight self-loop, or a tight
@@ -332,6 +381,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(RATIO || VM
 void k_tiescan_tile(SweepArgs a, const WT* __restrict__ w)
 {
     using KT = typename ValT<VM>::type;
+    if (SWEEP && a.E && a.ctl->fmode != kLoopSweep) return;   // uniform: see loop_after_sweep
     __shared__ int beg[kWG + 1];
     __shared__ KT key[kTieTileEdges];
     __shared__ int head[kTieTileEdges];
@@ -463,6 +513,14 @@ void k_tiescan_tile(SweepArgs a, const WT* __restrict__ w)
         changed = 1;
         if (onc) cbroken = 1;
     }
+    if (SWEEP && a.E && t < nv && !giant) {
+        // the vertex's chase entry: its weight is a line the batch just read
+        unsigned long long e;
+        const bool fits = changed ? chase_entry<WT, RATIO>(a, w, v0 + t, pos, bhead, &e)
+                                  : chase_entry<WT, RATIO>(a, w, v0 + t, cur, a.succ[v0 + t], &e);
+        a.E[v0 + t] = e;
+        if (!fits) atomicOr(&a.ctl->fflags, kChaseOverflow);
+    }
     unsigned long long sums[5] = {cnt, certain, nondec, changed, cbroken};
     block_sums_u64(sums);
     if (t == 0) {
@@ -472,7 +530,24 @@ void k_tiescan_tile(SweepArgs a, const WT* __restrict__ w)
         if (sums[2]) atomicAdd(&ln.nondec, sums[2]);
         if (SWEEP && sums[3]) atomicAdd(&ln.changed, sums[3]);
         if (SWEEP && sums[4]) atomicOr(&ln.cbroken, 1u);
+        if (SWEEP && a.E && a.giant.ngiant == 0) {
+            unsigned long long tot;
+            if (last_arrival(a.ctl, arrival_word(sums[3], sums[4] != 0), &tot))
+                loop_after_sweep(a.ctl, (unsigned)tot != 0, ((tot >> 32) & 0xffffu) != 0);
+        }
     }
+}
+
+__global__ void k_loop_close(Ctl* c)
+{
+    if (threadIdx.x != 0 || c->fmode != kLoopSweep) return;
+    unsigned long long changed = 0;
+    unsigned broken = 0;
+    for (int l = 0; l < kLanes; ++l) {
+        changed += c->lane[l].changed;
+        broken |= c->lane[l].cbroken;
+    }
+    loop_after_sweep(c, changed != 0, broken != 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -511,6 +586,7 @@ template <typename WT, int MODE, bool COUNT, int VM, bool RATIO>
 __global__ __launch_bounds__(kWG) void k_giant_part(SweepArgs a, const WT* __restrict__ w)
 {
     using KT = typename ValT<VM>::type;
+    if (MODE == 1 && a.E && a.ctl->fmode != kLoopSweep) return;
     __shared__ KT sk[kWG / 64];
     __shared__ int sp[kWG / 64], sh[kWG / 64];
     const GiantTab& g = a.giant;
@@ -596,29 +672,47 @@ __global__ __launch_bounds__(kWG) void k_giant_part(SweepArgs a, const WT* __res
     }
 }
 
-// Each giant row's best over its chunks (in position order: a strict
-// compare keeps the lowest position), then the sweep's write rule.
-template <int VM, bool FIRST>
-__global__ __launch_bounds__(kWG) void k_giant_merge(SweepArgs a)
+// Each giant row's best over its chunks (equal keys: the earlier chunk, which
+// holds the lower positions), then the sweep's write rule.  A wave per row:
+// its lanes stride over the chunks (one thread walking 128 chunks of a row of
+// 2^20 edges took 51 us on its dependent loads).
+template <typename WT, int VM, bool FIRST, bool RATIO>
+__global__ __launch_bounds__(kWG) void k_giant_merge(SweepArgs a, const WT* __restrict__ w)
 {
     using KT = typename ValT<VM>::type;
+    if (!FIRST && a.E && a.ctl->fmode != kLoopSweep) return;
     const GiantTab& g = a.giant;
     const GiantPart* parts = (const GiantPart*)g.parts;
+    const int lane = threadIdx.x & 63;
     unsigned long long changed = 0, cbroken = 0;
-    for (int i = blockIdx.x * kWG + threadIdx.x; i < g.ngiant; i += gridDim.x * kWG) {
+    for (int i = blockIdx.x * (kWG / 64) + (threadIdx.x >> 6); i < g.ngiant;
+         i += gridDim.x * (kWG / 64)) {
         const int v = g.gv[i];
-        // the best chunk by index, position order (strict keeps the lowest)
-        int bi = -1;
-        for (int c = g.gc0[i]; c < g.gc1[i]; ++c)
-            if (parts[c].pos != INT32_MAX && (bi < 0 || (KT)parts[c].key < (KT)parts[bi].key))
-                bi = c;
-        if (bi < 0) continue;
-        const KT best = (KT)parts[bi].key;
-        if (!FIRST && !(best < load_val<VM>(a.V, a.Vhi, a.V32, v))) continue;
-        a.pi[v] = parts[bi].pos;
-        if (a.succ) a.succ[v] = parts[bi].head;
-        ++changed;
-        if (!FIRST && a.onC && a.onC[v]) cbroken = 1;
+        KT best = val_max<KT>();
+        int bi = INT32_MAX, unused = 0;
+        for (int c = g.gc0[i] + lane; c < g.gc1[i]; c += 64) {
+            const KT k = (KT)parts[c].key;
+            const bool take = parts[c].pos != INT32_MAX && (bi == INT32_MAX || k < best);
+            best = take ? k : best;
+            bi = take ? c : bi;
+        }
+        wave_argmin<KT, false>(best, bi, unused);
+        if (lane != 0) continue;
+        const bool wr = bi != INT32_MAX &&
+                        (FIRST || best < load_val<VM>(a.V, a.Vhi, a.V32, v));
+        if (wr) {
+            a.pi[v] = parts[bi].pos;
+            if (a.succ) a.succ[v] = parts[bi].head;
+            ++changed;
+            if (!FIRST && a.onC && a.onC[v]) cbroken = 1;
+        }
+        if (!FIRST && a.E) {
+            unsigned long long e;
+            if (!chase_entry<WT, RATIO>(a, w, v, wr ? parts[bi].pos : a.pi[v],
+                                        wr ? parts[bi].head : a.succ[v], &e))
+                atomicOr(&a.ctl->fflags, kChaseOverflow);
+            a.E[v] = e;
+        }
     }
     unsigned long long sums[2] = {changed, cbroken};
     block_sums_u64(sums);
@@ -1999,6 +2093,211 @@ __global__ __launch_bounds__(kWG) void k_fill_u32(int64_t len, unsigned* __restr
 }
 
 // ---------------------------------------------------------------------------
+// values: asynchronous chase toward the source over the policy tree cut at s.
+// Every vertex holds one 8-byte entry (sum of L*w - W over the first edges of
+// its path, vertex reached).  A thread follows its own vertex: it reads the
+// entry of the vertex reached, appends it, and publishes the longer entry in
+// place.  Any entry another thread may read, old or new, is a valid summary of
+// a piece of that vertex's path, so the races change how many steps a vertex
+// takes and never a sum; a vertex is finished once it reaches s.
+//   * Bound: line fetches of random 8-byte reads (about 60 G/s past the L2) for
+//     large graphs, the chain of dependent reads for small ones.
+//   * Against synchronous doubling (16-byte entries in two buffers, one kernel
+//     per round, 8 rounds queued): a vertex reads 5 to 7 entries in all, nothing
+//     is written for finished vertices, and a phase is one launch.  Value
+//     phases of optimal policies, doubling -> chase: n = 20,011: about 45 ->
+//     10 us, 2^20 random: 125 -> 80 us, 2^22 random: 343 -> 283 us, 16^6
+//     product: 960 -> 240 us.
+// A pass takes at most kChaseSteps steps per vertex (32 left a few deep
+// vertices of 2^22-vertex graphs for a second pass of 23 us behind a pass of
+// 190 us).  A pass that leaves vertices unfinished is followed by another one; one that finishes nobody
+// proves a stall: an unfinished vertex of C's component nearest to s has
+// reached a finished one and finishes with its next step.  A vertex that
+// reaches itself lies on another cycle, which proves it at once.
+// ---------------------------------------------------------------------------
+constexpr int kChaseSteps = 96;
+
+__global__ void k_loop_setup(Ctl* c, unsigned mode, unsigned opts, unsigned max_sweeps)
+{
+    const int t = threadIdx.x;
+    if (t < kLanes) {
+        CtlLane& ln = c->lane[t];
+        ln.changed = ln.tight = ln.certain = ln.nondec = 0;
+        ln.cbroken = ln.overflow = ln.wide32 = ln.bad = 0;
+        ln.rpack = 0;
+    }
+    if (t == 0) {
+        c->rpack = 0;
+        c->jlast = 0xffffffffu;
+        c->fwhy = kWhyNone;
+        c->fopts = opts;
+        c->fsweeps = c->ffast = c->fphases = c->fflags = c->fwide = 0;
+        c->fmax = max_sweeps;
+        c->fmode = mode;
+    }
+}
+
+template <typename WT>
+__global__ __launch_bounds__(kWG) void k_chase_init(int n, const int* __restrict__ col,
+                                                    const int* __restrict__ pi,
+                                                    const WT* __restrict__ w, int neg, int s,
+                                                    long long W, long long L,
+                                                    int* __restrict__ succ,
+                                                    unsigned long long* __restrict__ E, int jb,
+                                                    Ctl* ctl, const int* __restrict__ tm)
+{
+    constexpr int U = 4;   // independent vertices in flight per thread
+    const int64_t stride = (int64_t)gridDim.x * kWG;
+    bool fits = true;
+    for (int64_t vb = (int64_t)blockIdx.x * kWG + threadIdx.x; vb < n; vb += U * stride) {
+        int e[U], h[U];
+        long long wv[U], tv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t v = vb + u * stride;
+            e[u] = v < n ? pi[v] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t v = vb + u * stride;
+            h[u] = v < n ? col[e[u]] : 0;
+            wv[u] = v < n ? wval(w, e[u], neg) : 0;
+            tv[u] = tm && v < n ? tm[e[u]] : 1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t v = vb + u * stride;
+            if (v >= n) continue;
+            succ[v] = h[u];
+            unsigned long long x = (unsigned)s;
+            if (v != s) fits &= chase_pack(L * wv[u] - W * tv[u], (unsigned)h[u], jb, &x);
+            E[v] = x;
+        }
+    }
+    if (!fits) atomicOr(&ctl->fflags, kChaseOverflow);
+}
+
+__global__ __launch_bounds__(kWG) void k_hop_init(int n, int s, const int* __restrict__ succ,
+                                                  unsigned long long* __restrict__ E)
+{
+    for (int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x; v < n;
+         v += (int64_t)gridDim.x * kWG)
+        E[v] = v == s ? (unsigned long long)(unsigned)s : (1ull << 32) | (unsigned)succ[v];
+}
+
+// What follows a pass: `left` vertices are unfinished.
+__device__ void loop_after_chase(Ctl* c, unsigned left)
+{
+    const unsigned f = __hip_atomic_load(&c->fflags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((f & kChaseStall) || (left && left == c->jlast)) {
+        loop_stop(c, kWhyStall);
+        return;
+    }
+    if (left) {
+        c->jlast = left;
+        return;
+    }
+    if (f & kChaseOverflow) {
+        loop_stop(c, kWhyOverflow);
+        return;
+    }
+    if (c->fsweeps) c->ffast += 1;
+    c->fwide = (f & kChaseWide) ? 1u : 0u;
+    if (!(c->fopts & kLoopChain)) {
+        loop_stop(c, kWhyOnce);
+    } else if ((f & kChaseWide) && (c->fopts & kLoopV32)) {
+        loop_stop(c, kWhyWide);
+    } else {
+        for (int l = 0; l < kLanes; ++l) {
+            CtlLane& ln = c->lane[l];
+            ln.changed = ln.tight = ln.certain = 0;
+            ln.cbroken = 0;
+        }
+        c->fflags = 0;
+        c->fmode = kLoopSweep;
+    }
+}
+
+// Scopes of the entries' relaxed reads and writes: agent scope goes past the
+// XCD's own L2 (fresh entries from every XCD, fewer steps), workgroup scope
+// stays in it (cheaper steps, entries of other XCDs seen late).
+template <int SCOPE>
+__device__ __forceinline__ unsigned long long chase_load(const unsigned long long* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, SCOPE);
+}
+template <int SCOPE>
+__device__ __forceinline__ void chase_store(unsigned long long* p, unsigned long long x)
+{
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, SCOPE);
+}
+
+template <int LD, int ST>
+__global__ __launch_bounds__(kWG) void k_chase(int n, int s, int jb, unsigned long long* E,
+                                               long long* __restrict__ V,
+                                               int* __restrict__ out32, Ctl* ctl)
+{
+    if (ctl->fmode != kLoopChase) return;   // uniform: only the last arrival changes it
+    __shared__ unsigned sleft, sflags;
+    if (threadIdx.x == 0) sleft = sflags = 0;
+    __syncthreads();
+    const unsigned long long jm = (1ull << jb) - 1;
+    const int64_t v = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kWG + threadIdx.x;
+    unsigned long long e = (unsigned)s;
+    if (v < n) e = chase_load<LD>(&E[v]);
+    bool fits = true;
+    for (int k = 1; k <= kChaseSteps; ++k) {
+        const unsigned j = (unsigned)(e & jm);
+        if (j == (unsigned)s) break;
+        const unsigned long long r = chase_load<LD>(&E[j]);
+        const unsigned h = (unsigned)(r & jm);
+        fits &= chase_pack(((long long)e >> jb) + ((long long)r >> jb), h, jb, &e);
+        chase_store<ST>(&E[v], e);
+        if (h == (unsigned)v) {
+            atomicOr(&ctl->fflags, kChaseStall);
+            break;
+        }
+        if ((k & 7) == 0 && (__hip_atomic_load(&ctl->fflags, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT) & kChaseStall))
+            break;
+    }
+    const bool done = (e & jm) == (unsigned)s;
+    bool wide = false;
+    if (v < n && done) {
+        const long long d = (long long)e >> jb;
+        if (V) V[v] = d;
+        out32[v] = (int)d;
+        wide = d != (long long)(int)d;
+    }
+    const unsigned long long open = __ballot(!done);
+    const unsigned flags = (__ballot(!fits) ? kChaseOverflow : 0u) | (__ballot(wide) ? kChaseWide : 0u);
+    if ((threadIdx.x & 63) == 0) {
+        if (open) atomicAdd(&sleft, (unsigned)__popcll(open));
+        if (flags) atomicOr(&sflags, flags);
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    // flags are global before the arrival that lets the last workgroup read them
+    if (sflags) {
+        const unsigned old = atomicOr(&ctl->fflags, sflags);
+        asm volatile("" ::"v"(old));
+    }
+    unsigned long long tot;
+    if (last_arrival(ctl, arrival_word(sleft, 0), &tot)) loop_after_chase(ctl, (unsigned)tot);
+}
+
+__global__ void k_cycle_walk(int s, long long L, const int* __restrict__ pi,
+                             const int* __restrict__ succ, int* __restrict__ out)
+{
+    if (threadIdx.x != 0) return;
+    int v = s;
+    for (long long j = 0; j < L; ++j) {
+        out[j] = pi[v];
+        v = succ[v];
+    }
+}
+
+// ---------------------------------------------------------------------------
 // values: pointer jumping toward the source over the policy tree cut at s.
 // Entry: D = sum of (L*w - W) over the first H edges of v's path, J = the
 // vertex reached.  A vertex is finished once J == s.
@@ -2577,16 +2876,16 @@ static void launch_giant(const SweepArgs& a, const WT* ww, bool first, bool tie,
 {
     if (a.giant.ngiant <= 0) return;
     const unsigned grid = a.giant.nchunks < 2048 ? (unsigned)a.giant.nchunks : 2048u;
-    const unsigned mgrid = blocks_for(a.giant.ngiant);
+    const unsigned mgrid = blocks_for(64 * (int64_t)a.giant.ngiant);
     if (first) {
         k_giant_part<WT, 0, false, 0, false><<<grid, kWG, 0, st>>>(a, ww);
-        k_giant_merge<0, true><<<mgrid, kWG, 0, st>>>(a);
+        k_giant_merge<WT, 0, true, false><<<mgrid, kWG, 0, st>>>(a, ww);
     } else if (tie) {
         k_giant_part<WT, 2, true, VM, RATIO><<<grid, kWG, 0, st>>>(a, ww);
     } else {
         if (fused) k_giant_part<WT, 1, true, VM, RATIO><<<grid, kWG, 0, st>>>(a, ww);
         else k_giant_part<WT, 1, false, VM, RATIO><<<grid, kWG, 0, st>>>(a, ww);
-        k_giant_merge<VM, false><<<mgrid, kWG, 0, st>>>(a);
+        k_giant_merge<WT, VM, false, RATIO><<<mgrid, kWG, 0, st>>>(a, ww);
     }
 }
 
@@ -2665,6 +2964,55 @@ void launch_giant_list(int n, const int* row_ptr, int* triples, unsigned cap, Ct
                        hipStream_t st)
 {
     k_giant_list<<<stride_grid(n), kWG, 0, st>>>(n, row_ptr, triples, cap, ctl);
+}
+
+void launch_loop_setup(Ctl* ctl, unsigned mode, unsigned opts, unsigned max_sweeps,
+                       hipStream_t st)
+{
+    k_loop_setup<<<1, 64, 0, st>>>(ctl, mode, opts, max_sweeps);
+}
+
+void launch_loop_close(Ctl* ctl, hipStream_t st) { k_loop_close<<<1, 64, 0, st>>>(ctl); }
+
+void launch_chase_init(int n, const int* col, const int* pi, const void* w, int wtype, int neg,
+                       int s, long long W, long long L, int* succ, unsigned long long* E, int jb,
+                       Ctl* ctl, const int* t, hipStream_t st)
+{
+    const unsigned grid = stride_grid((n + 3) / 4);
+    if (wtype == kWI64)
+        k_chase_init<long long><<<grid, kWG, 0, st>>>(n, col, pi, (const long long*)w, neg, s, W, L,
+                                                      succ, E, jb, ctl, t);
+    else
+        k_chase_init<int><<<grid, kWG, 0, st>>>(n, col, pi, (const int*)w, neg, s, W, L, succ, E, jb,
+                                                ctl, t);
+}
+
+// Scopes by size (one phase on an optimal policy, us; agent/agent, workgroup
+// reads with agent writes, workgroup/workgroup).  Small graphs sit in every L2
+// and gain from fresh entries: random 2^16: 14.0 / 15.8 / 20.2.  In the middle
+// reads may be late as long as writes go through: 2^20: 82 / 74 / 82, 300,007:
+// 30 / 28 / 33.  On large graphs written-through steps cost more than they
+// save: 2^22: 284 / 269 / 275, 2^23: 436 / 423 / 355, 16^6 product: 501 / 397 /
+// 259.
+void launch_chase(int n, int s, int jb, unsigned long long* E, long long* V, int* out32, Ctl* ctl,
+                  hipStream_t st)
+{
+    constexpr int A = __HIP_MEMORY_SCOPE_AGENT, G = __HIP_MEMORY_SCOPE_WORKGROUP;
+    const unsigned grid = blocks_for(n);
+    if (n < (1 << 18)) k_chase<A, A><<<grid, kWG, 0, st>>>(n, s, jb, E, V, out32, ctl);
+    else if (n <= (1 << 22)) k_chase<G, A><<<grid, kWG, 0, st>>>(n, s, jb, E, V, out32, ctl);
+    else k_chase<G, G><<<grid, kWG, 0, st>>>(n, s, jb, E, V, out32, ctl);
+}
+
+void launch_hop_init(int n, int s, const int* succ, unsigned long long* E, hipStream_t st)
+{
+    k_hop_init<<<stride_grid(n), kWG, 0, st>>>(n, s, succ, E);
+}
+
+void launch_cycle_walk(int s, long long L, const int* pi, const int* succ, int* out,
+                       hipStream_t st)
+{
+    k_cycle_walk<<<1, 64, 0, st>>>(s, L, pi, succ, out);
 }
 
 void launch_pj_init(int n, const int* col, const int* pi, int* succ, bool have_succ,
@@ -3190,6 +3538,12 @@ __global__ void k_post_ctl(const Ctl* __restrict__ c, CtlView* dst, unsigned* se
         v.scnt = c->scnt;
         v.clen = c->clen;
         v.ngiant = c->ngiant;
+        v.fmode = c->fmode;
+        v.fwhy = c->fwhy;
+        v.fsweeps = c->fsweeps;
+        v.ffast = c->ffast;
+        v.fphases = c->fphases;
+        v.fwide = c->fwide;
         *dst = v;
         __threadfence_system();
         __hip_atomic_store(seq_slot, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);

@@ -259,6 +259,10 @@ struct Ctx {
     // rows of more than kGiantRow edges, swept by several workgroups each
     // (tile sweeps only; empty when there are none)
     ocm::GiantTab giant;
+    // values by the packed chase, sweeps and values as one device-driven loop;
+    // off for the rest of the solve once a sum does not fit the entries
+    bool chase = false;
+    bool hop_ok = false;   // ws.hop holds the policy's hops (the chase leaves them out)
 
     Ctx() = default;
     Ctx(const Ctx&) = delete;
@@ -399,11 +403,9 @@ void sweep_done(Ctx& c, bool first, bool tie, bool fused)
 
 // read = false: the caller reads the control block later (after more work
 // queued behind the sweep) and then calls sweep_done.
-ocm_status phase_sweep(Ctx& c, bool first, bool tie, const long long* V, long long W, long long L,
-                       int* pi, const unsigned char* onC, bool collect = false,
-                       bool with_hop = false, bool read = true)
+ocm::SweepArgs sweep_args(Ctx& c, bool first, const long long* V, long long W, long long L,
+                          int* pi, const unsigned char* onC)
 {
-    ocm::launch_ctl_clear(c.ws.ctl, ocm::kClrChanged, c.st);
     ocm::SweepArgs a;
     a.n = c.n;
     a.neg = c.neg;
@@ -420,10 +422,20 @@ ocm_status phase_sweep(Ctx& c, bool first, bool tie, const long long* V, long lo
     a.onC = onC;
     a.ctl = c.ws.ctl;
     a.giant = c.tile_sweep ? c.giant : ocm::GiantTab{};
-    a.hop = tie && with_hop ? c.ws.hop : nullptr;
+    a.hop = nullptr;
     a.xs = a.ys = nullptr;
     a.xcnt = nullptr;
     a.xcap = 0;
+    return a;
+}
+
+ocm_status phase_sweep(Ctx& c, bool first, bool tie, const long long* V, long long W, long long L,
+                       int* pi, const unsigned char* onC, bool collect = false,
+                       bool with_hop = false, bool read = true)
+{
+    ocm::launch_ctl_clear(c.ws.ctl, ocm::kClrChanged, c.st);
+    ocm::SweepArgs a = sweep_args(c, first, V, W, L, pi, onC);
+    a.hop = tie && with_hop ? c.ws.hop : nullptr;
     if (tie && collect) {
         a.xs = c.ws.xs;
         a.ys = c.ws.ys;
@@ -956,10 +968,115 @@ ocm_status phase_values_once(Ctx& c, const int* pi, int s, long long W, long lon
 ocm_status phase_values(Ctx& c, const int* pi, int s, long long W, long long L, long long* V,
                         int* hop, bool probe, bool* stalled, int* rounds, bool gated = false)
 {
+    c.hop_ok = hop != nullptr;
     const ocm_status rc = phase_values_once(c, pi, s, W, L, V, hop, probe, stalled, rounds, gated);
     if (rc != OCM_E_OVERFLOW || c.wide || !c.allow_wide || V != c.ws.V) return rc;
     c.wide = true;
     return phase_values_once(c, pi, s, W, L, V, hop, probe, stalled, rounds, false);
+}
+
+// (sweep, chase) pairs queued between two host reads of the device-driven
+// loop.  Kernels queued behind its end return at once; a pair of them costs
+// about 4 us on small graphs (against 10 us per read), and more where a launch
+// has tens of thousands of workgroups.
+int loop_pairs(const Ctx& c) { return c.prof.out ? 1 : c.n < (1 << 18) ? 4 : 2; }
+
+// Runs the device-driven loop on C's (s, W, L) until it stops: from the value
+// phase (the chase entries are written here from pi) or from a sweep (values
+// current).  c.h holds the outcome (fwhy, fsweeps, ffast).
+ocm_status run_loop(Ctx& c, bool from_values, int s, long long W, long long L, unsigned max_sweeps)
+{
+    Ws& w = c.ws;
+    auto* E = (unsigned long long*)w.Q[0];
+    const int jb = ocm::chase_bits(c.n);
+    const int cls = from_values ? OCM_K_VALUES : OCM_K_FAST;
+    ocm::launch_loop_setup(w.ctl, from_values ? ocm::kLoopChase : ocm::kLoopSweep,
+                           ocm::kLoopChain | (c.v32 ? ocm::kLoopV32 : 0u), max_sweeps, c.st);
+    if (from_values) {
+        c.prof.begin(cls);
+        ocm::launch_chase_init(c.n, c.col, w.pi, c.w, c.wtype, c.neg, s, W, L, w.succ, E, jb, w.ctl,
+                               c.t, c.st);
+        c.prof.end();
+        // pi, col[pi], w[pi], succ, the 8-byte entry
+        c.prof.bytes(cls, (20.0 + c.sw) * c.n);
+    }
+    c.succ_ok = true;
+    c.hop_ok = false;
+    ocm::SweepArgs a = sweep_args(c, false, w.V, W, L, w.pi, w.onC);
+    a.succ = w.succ;
+    a.E = E;
+    a.jb = jb;
+    a.src = s;
+    c.sweep_vbytes = a.V32 ? 4.0 : 8.0;
+    auto chase = [&](int k) {
+        c.prof.begin(k);
+        ocm::launch_chase(c.n, s, jb, E, w.V, w.V32, w.ctl, c.st);
+        c.prof.end();
+        // the entry read and written, an entry gathered, V and its copy
+        c.prof.bytes(k, 36.0 * c.n);
+    };
+    auto sweep = [&]() {
+        c.prof.begin(OCM_K_SWEEP);
+        ocm::launch_sweep(a, c.w, c.wtype, 0, false, false, true, c.sweep_grid, c.st);
+        if (a.giant.ngiant > 0) ocm::launch_loop_close(w.ctl, c.st);
+        c.prof.end();
+        c.prof.bytes(OCM_K_SWEEP, 8.0 * c.n);   // the chase entry
+    };
+    const int pairs = loop_pairs(c);
+    bool chase_next = from_values;
+    c.h.fsweeps = 0;
+    for (;;) {
+        if (c.prof.out) {
+            // profiled: one step per read, so that no launch is an idle one
+            const unsigned before = c.h.fsweeps;
+            if (chase_next) chase(before ? OCM_K_FAST : cls);
+            else sweep();
+            HIP_TRY(hipGetLastError());
+            OCM_TRY(read_ctl(c));
+            if (c.h.fsweeps != before) sweep_done(c, false, false, true);
+        } else {
+            for (int k = 0; k < pairs; ++k) {
+                if (k > 0 || !chase_next) sweep();
+                chase(OCM_K_FAST);
+            }
+            HIP_TRY(hipGetLastError());
+            OCM_TRY(read_ctl(c));
+        }
+        if (c.h.fmode == ocm::kLoopStop) break;
+        chase_next = c.h.fmode == ocm::kLoopChase;
+    }
+    const int phases = (int)c.h.fphases + (from_values ? 1 : 0);
+    c.value_rounds += phases;
+    c.jump_rounds += phases;
+    c.swept_tie = c.h.fwhy == ocm::kWhyConverged;
+    c.swept_tight = c.h.tight;
+    c.swept_certain = c.h.certain;
+    if (c.h.ffast > 0 || c.h.fwhy == ocm::kWhyWide) c.v32 = !c.h.fwide;
+    return OCM_OK;
+}
+
+// Policy hops to s (the tie test and the listing of a long C need them): the
+// chase with a sum of one per edge.
+ocm_status ensure_hops(Ctx& c, int s)
+{
+    if (c.hop_ok) return OCM_OK;
+    Ws& w = c.ws;
+    auto* E = (unsigned long long*)w.Q[0];
+    ocm::launch_loop_setup(w.ctl, ocm::kLoopChase, 0, 0, c.st);
+    c.prof.begin(OCM_K_RESULT);
+    ocm::launch_hop_init(c.n, s, w.succ, E, c.st);
+    for (;;) {
+        ocm::launch_chase(c.n, s, 32, E, nullptr, w.hop, w.ctl, c.st);
+        c.prof.end();
+        HIP_TRY(hipGetLastError());
+        OCM_TRY(read_ctl(c));
+        if (c.h.fmode == ocm::kLoopStop) break;
+        c.prof.begin(OCM_K_RESULT);
+    }
+    c.prof.bytes(OCM_K_RESULT, 32.0 * c.n);
+    if (c.h.fwhy != ocm::kWhyOnce) return fail(OCM_E_HIP, "a policy path does not reach the source");
+    c.hop_ok = true;
+    return OCM_OK;
 }
 
 // Does the small graph (nodes 0..N-1, edges from adjacency lists) hold a
@@ -1002,7 +1119,7 @@ bool has_cycle(int N, const std::vector<int>& head, const std::vector<int>& next
 // graph described at k_tie_mark.
 ocm_status tie_from_list(Ctx& c, unsigned kx, ocm_result* out);
 
-ocm_status tie_check(Ctx& c, long long W, long long L, ocm_result* out)
+ocm_status tie_check(Ctx& c, int s, long long W, long long L, ocm_result* out)
 {
     Ws& w = c.ws;
     // the solve's last sweep changed nothing; if it counted tight edges, its
@@ -1019,6 +1136,7 @@ ocm_status tie_check(Ctx& c, long long W, long long L, ocm_result* out)
         return OCM_OK;
     }
     // second scan, now with the hop test (a random read per tight edge)
+    OCM_TRY(ensure_hops(c, s));
     OCM_TRY(phase_sweep(c, false, true, w.V, W, L, w.pi, w.onC, false, true));
     // With hop = policy hops to s, every policy edge lowers hop by one except
     // s's own; a cycle of tight edges other than C, with no tight edge
@@ -1026,25 +1144,8 @@ ocm_status tie_check(Ctx& c, long long W, long long L, ocm_result* out)
     // not nearer to s than its tail.
     if (c.h.nondec == 0) return OCM_OK;
     {
-        ocm::SweepArgs a;
-        a.n = c.n;
-        a.neg = c.neg;
-        a.row_ptr = c.row_ptr;
-        a.col = c.col;
-        a.V = w.V;
-        a.Vhi = c.wide ? w.Vhi : nullptr;
-        a.V32 = !c.wide && c.v32 ? w.V32 : nullptr;
-        a.t = c.t;
-        a.W = W;
-        a.L = L;
-        a.pi = w.pi;
-        a.onC = w.onC;
-        a.ctl = w.ctl;
+        ocm::SweepArgs a = sweep_args(c, false, w.V, W, L, w.pi, w.onC);
         a.hop = w.hop;
-        a.xs = a.ys = nullptr;
-        a.xcnt = nullptr;
-        a.xcap = 0;
-        a.giant = c.tile_sweep ? c.giant : ocm::GiantTab{};
         c.prof.begin(OCM_K_TIESCAN);
         ocm::launch_tie_short_walk(a, c.w, c.wtype, c.G, w.succ, c.sweep_grid, c.st);
         c.prof.end();
@@ -1344,6 +1445,8 @@ ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t 
     start_reverse_early(c);
     HIP_TRY(hipGetLastError());
 
+    c.chase = c.tile_sweep && o.fast_path && !c.wide && c.n <= ocm::kLoopMaxN;
+    c.v32 = c.chase;   // until a value phase says otherwise
     Ws& w = c.ws;
     const bool warm = o.init_policy != nullptr;
     if (warm) {
@@ -1356,6 +1459,7 @@ ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t 
         HIP_TRY(hipMemcpyAsync(w.pi, o.init_policy, 4 * (size_t)c.n, hipMemcpyDeviceToDevice, c.st));
     }
     int iter = 0, fast = 0;
+    const int iter_cap = o.max_iters > 0 && o.max_iters < kIterCap ? o.max_iters : kIterCap;
     bool have_c = false, need_sweep = !warm;
     int s = -1;
     long long W = 0, L = 1;
@@ -1417,9 +1521,46 @@ ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t 
         // the solve itself needs no layers, only the rewired policy
         rc = phase_connect(c, w.rep, w.onc, s, w.pi, nullptr, w.onC, nullptr);
         if (rc != OCM_OK) break;
+        have_c = true;
+        if (c.chase) {
+            // the values, then sweeps and values until C breaks or the end
+            bool from_values = true, general = false;
+            for (;;) {
+                rc = run_loop(c, from_values, s, W, L, (unsigned)(iter_cap - iter));
+                if (rc != OCM_OK) break;
+                iter += (int)c.h.fsweeps;
+                fast += (int)c.h.ffast;
+                if (c.h.fwhy != ocm::kWhyWide) break;
+                from_values = false;   // go on with int64 gathers
+            }
+            if (rc != OCM_OK) break;
+            const bool swept = !from_values || c.h.fsweeps > 0;
+            if (c.h.fwhy == ocm::kWhyConverged) break;
+            if (c.h.fwhy == ocm::kWhyIters) {
+                rc = fail(OCM_E_NOT_CONVERGED, "max_iters reached");
+                break;
+            }
+            if (c.h.fwhy == ocm::kWhyOverflow) {
+                // entries of 16 bytes from here on; this value phase again
+                c.chase = false;
+                bool stalled = false;
+                rc = phase_values(c, w.pi, s, W, L, w.V, w.hop, swept, &stalled, nullptr);
+                if (rc != OCM_OK) break;
+                if (swept && !stalled) ++fast;
+                general = stalled;
+            } else {
+                if (c.h.fwhy == ocm::kWhyStall && !swept) {
+                    rc = fail(OCM_E_NOT_STRONGLY_CONNECTED, "policy graph does not reach the source");
+                    break;
+                }
+                general = true;
+            }
+            need_sweep = !general;
+            if (general) have_c = false;   // straight to the general phases
+            continue;
+        }
         rc = phase_values(c, w.pi, s, W, L, w.V, w.hop, false, nullptr, nullptr);
         if (rc != OCM_OK) break;
-        have_c = true;
     }
     out->iterations = iter;
     if (c.wide) out->flags |= OCM_F_INT128;
@@ -1446,13 +1587,24 @@ ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t 
         c.prof.finish();
         return fail(OCM_E_CAPACITY, "cycle_cap smaller than the critical cycle");
     }
+    // a short C by walking it (about 0.7 us an edge), a long one by hops (a
+    // chase over all vertices, 10 us and more with n, when the values left none)
+    const bool walk = !c.hop_ok && clen <= 16 + c.n / 16384;
+    if (!walk) {
+        rc = ensure_hops(c, s);
+        if (rc != OCM_OK) {
+            c.prof.finish();
+            return rc;
+        }
+    }
     c.prof.begin(OCM_K_RESULT);
-    ocm::launch_cycle_list(c.n, s, clen, w.onC, w.pi, w.hop, cycle_edges, c.st);
+    if (walk) ocm::launch_cycle_walk(s, clen, w.pi, w.succ, cycle_edges, c.st);
+    else ocm::launch_cycle_list(c.n, s, clen, w.onC, w.pi, w.hop, cycle_edges, c.st);
     c.prof.end();
-    c.prof.bytes(OCM_K_RESULT, (double)c.n + 28.0 * clen);
+    c.prof.bytes(OCM_K_RESULT, walk ? 12.0 * clen : (double)c.n + 28.0 * clen);
     HIP_TRY(hipGetLastError());
     if (o.tie_check) {
-        rc = tie_check(c, W, L, out);
+        rc = tie_check(c, s, W, L, out);
         if (rc != OCM_OK) {
             c.prof.finish();
             return rc;

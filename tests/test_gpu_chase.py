@@ -1,0 +1,108 @@
+"""The value chase and the device-driven loop against the round-by-round
+path (G lanes per vertex, which keeps it) and the oracle, at the sizes and
+values where the chase changes its form: workgroup edges, the scope rule's
+limits, passes that do not finish, stalls, and sums beyond the packed entry."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import native
+from paper_1111_0627_amd import ocm, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def both(g, mode="min", t=None):
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (g.row_ptr, g.col, g.w)]
+    kw = dict(want_policy=True, want_potential=True)
+    if t is None:
+        def fn(**k):
+            return ocm.cycle_mean(*dev, mode=mode, **kw, **k)
+    else:
+        tt = torch.from_numpy(t).cuda()
+
+        def fn(**k):
+            f = ocm.min_cycle_ratio if mode == "min" else ocm.max_cycle_ratio
+            return f(*dev, tt, **kw, **k)
+    a, b = fn(), fn(schedule=8)
+    for r in (a, b):
+        assert r.cycle_edges.numel() > 0
+    same = ("p", "q", "W", "L", "source", "iterations", "flags", "tight_edges", "fast_iters",
+            "connect_rounds")
+    assert [getattr(a, k) for k in same] == [getattr(b, k) for k in same]
+    for k in ("cycle_edges", "policy", "potential"):
+        assert torch.equal(getattr(a, k), getattr(b, k)), k
+    return a
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 4095, 65537, (1 << 18) - 1, 1 << 18, 300007])
+def test_sizes(n):
+    g = synth.random_digraph(n, 1, 4, -1000, 1000, np.int64, seed=[71, n])
+    r = both(g, "min" if n % 2 else "max")
+    if n <= 4095:
+        sol = native.solve(g.row_ptr, g.col, g.w, "min" if n % 2 else "max")
+        assert (r.p, r.q, r.iterations, r.cycle_edges.cpu().tolist()) == \
+            (sol.p, sol.q, sol.iterations, sol.cycle.tolist())
+
+
+@pytest.mark.parametrize("n", [257, 20011])
+def test_times(n):
+    g = synth.random_digraph(n, 1, 5, -500, 500, np.int32, seed=[72, n])
+    t = np.random.default_rng(n).integers(1, 20, g.m).astype(np.int32)
+    both(g, "max" if n == 257 else "min", t)
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_small_weights_stall_and_tie(seed):
+    """Few distinct weights: policy cycles away from C (stalls), ties."""
+    g = synth.random_digraph(5000, 1, 4, 0, 2, np.int32, seed=[73, seed])
+    both(g)
+
+
+def test_long_paths_take_several_passes():
+    """A ring of n vertices with one heavy shortcut: paths of n - 1 edges."""
+    n = 70000
+    rp = np.arange(n + 1, dtype=np.int32)
+    col = ((np.arange(n) + 1) % n).astype(np.int32)
+    w = np.random.default_rng(5).integers(-50, 50, n)
+    rp[1:] += 1                       # vertex 0: a second edge, to vertex 1
+    col = np.insert(col, 1, 1).astype(np.int32)
+    w = np.insert(w, 1, 40).astype(np.int64)
+    g = synth.Graph(rp, col, w, "ring")
+    r = both(g)
+    assert r.cycle_edges.numel() == n
+
+
+@pytest.mark.parametrize("hlo", [2**22, 2**35, 2**47])
+def test_sums_beyond_the_entry(hlo):
+    """Sums of 2^22, of more than the entry's 53 bits, and beyond int64."""
+    g = synth.deep_tail_graph(700, 800, 2, 10, hlo, 2 * hlo, seed=3)
+    dev = [torch.from_numpy(x).cuda() for x in (g.row_ptr, g.col, g.w)]
+    r = ocm.min_cycle_mean(*dev)
+    sol = native.solve(g.row_ptr, g.col, g.w)
+    assert (r.p, r.q, r.iterations, r.cycle_edges.cpu().tolist()) == \
+        (sol.p, sol.q, sol.iterations, sol.cycle.tolist())
+    assert r.int128 == (hlo == 2**47)
+    if hlo < 2**47:
+        both(g)
+
+
+def test_values_leave_int32_in_mid_solve():
+    """int64 weights whose values do not fit the int32 copy."""
+    g = synth.random_digraph(20000, 1, 5, 2**30, 2**31, np.int64, seed=[74, 0])
+    both(g)
+
+
+@pytest.mark.parametrize("cap", [1, 2, 3, 5])
+def test_iteration_cap(cap):
+    g = synth.random_digraph(3000, 1, 4, 1, 1000, np.int32, seed=[75, 0])
+    dev = [torch.from_numpy(x).cuda() for x in (g.row_ptr, g.col, g.w)]
+    need = ocm.min_cycle_mean(*dev).iterations
+    assert need > 5
+    for sched in (0, 8):
+        with pytest.raises(ocm.OCMError) as e:
+            ocm.min_cycle_mean(*dev, max_iters=cap, schedule=sched)
+        assert e.value.status == ocm.OCM_E_NOT_CONVERGED
+    assert ocm.min_cycle_mean(*dev, max_iters=need).iterations == need
