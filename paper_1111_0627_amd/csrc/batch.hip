@@ -38,6 +38,10 @@ constexpr int kActive = 1;    // next: a sweep
 constexpr int kFast = 2;      // next: values with the old cycle (fast path)
 constexpr int kGeneral = 3;   // next: cycles, select, rebuild, values
 constexpr int kTieList = 4;   // after the loop: tie left open by the quick tests
+// the chase left the graph's values to the doubling rounds (kPend + the mode
+// its values are for): a sum that does not fit the packed entries, or a path
+// that two passes did not finish
+constexpr int kPend = 8;
 
 struct GArrays {              // device arrays with one entry per graph
     long long* W;
@@ -72,8 +76,6 @@ struct GArrays {              // device arrays with one entry per graph
 struct BCtl {
     unsigned nchunks;
     unsigned nactive, nfast, ngeneral, ndone;
-    unsigned vrun_round[32];   // value phase: round r has a graph to advance
-    unsigned vlast;            // value phase: slot / buffer parity of the last round's output
     unsigned nspans;           // rebuild: spans holding a rebuilt graph
     unsigned ncyc;
     unsigned overflow;
@@ -81,6 +83,10 @@ struct BCtl {
     unsigned scnt;             // tie test: special vertices
     unsigned rounds_open;      // device-driven rebuild rounds of the iteration left unfinished
     unsigned wide32;           // some value left int32: sweeps gather V, not its int32 copy
+    unsigned npend;            // value chase: graphs left to the doubling rounds
+    // device only from here on (the host reads what is before)
+    unsigned vrun_round[32];   // value phase: round r has a graph to advance
+    unsigned vlast;            // value phase: slot / buffer parity of the last round's output
     unsigned hop_act[34];      // hop phase: entries short of s after round r - 1 (r = 0: 1)
 };
 
@@ -128,6 +134,7 @@ __device__ __forceinline__ bool chunk_range(const int2* __restrict__ chunks, con
 // the list's capacity.  f(g, v0, v1) runs once per chunk; its `return` skips
 // to the next chunk.
 constexpr unsigned kChunkGrid = 2048;
+constexpr unsigned kTileGrid = 32768;   // workgroups of a tile kernel (for_each_tile)
 
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
 // L2: when the grid is a multiple of 8, XCD x takes the x-th eighth of the
@@ -152,6 +159,26 @@ __device__ __forceinline__ void for_each_chunk(const int2* __restrict__ chunks, 
         const int64_t v0 = c.y;
         const int64_t end = vptr[g + 1];
         f(g, v0, v0 + T < end ? v0 + T : end);
+    }
+}
+
+// The tiles (kWG vertices) of the listed chunks, dealt to the XCDs in eighths
+// as above: f(g, v0, nv) runs once per tile, with every thread of the
+// workgroup; launched with tile_grid() workgroups (a multiple of 8).
+template <typename F>
+__device__ __forceinline__ void for_each_tile(const int2* __restrict__ chunks, const unsigned* nch,
+                                              const long long* __restrict__ vptr, int T, F&& f)
+{
+    const unsigned per = (unsigned)((T + kWG - 1) / kWG);
+    const unsigned long long tot = (unsigned long long)*nch * per;
+    const unsigned x = blockIdx.x & 7u;
+    const unsigned lo = (unsigned)(tot * x / 8u), hi = (unsigned)(tot * (x + 1u) / 8u);
+    for (unsigned i = lo + (blockIdx.x >> 3); i < hi; i += gridDim.x >> 3) {
+        const int2 c = chunks[i / per];
+        const int64_t end = vptr[c.x + 1];
+        const int64_t c1 = c.y + (int64_t)T < end ? c.y + (int64_t)T : end;
+        const int64_t v0 = c.y + (int64_t)(i % per) * kWG;
+        if (v0 < c1) f(c.x, v0, c1 - v0 < kWG ? (int)(c1 - v0) : kWG);
     }
 }
 
@@ -417,17 +444,14 @@ __global__ __launch_bounds__(kWG) void k_sweep_tile(const int2* __restrict__ chu
                                                     WT* __restrict__ wsel,
                                                     const int* __restrict__ hop,
                                                     int* __restrict__ xs, int* __restrict__ ys,
-                                                    unsigned* xcnt, unsigned xcap)
+                                                    unsigned* xcnt, unsigned xcap,
+                                                    unsigned long long* __restrict__ E, int jb)
 {
     __shared__ int beg[kWG + 1];
     __shared__ long long key[kBTileEdges];
     constexpr int U = kBTileEdges / kWG;
     const int t = threadIdx.x;
-    const unsigned per = (unsigned)((T + kWG - 1) / kWG);
-    const unsigned ci = blockIdx.x / per;
-    if (ci >= *nch) return;
-    const int2 ch = chunks[ci];
-    const int g = ch.x;
+    for_each_tile(chunks, nch, ga.vptr, T, [&](int g, int64_t tv0, int tnv) {
     if (TIE && ga.status[g] != OCM_OK) return;
     // every value written so far fits int32: gather the 4-byte copy
     const bool use32 = !TIE && bc->wide32 == 0u;
@@ -541,14 +565,18 @@ __global__ __launch_bounds__(kWG) void k_sweep_tile(const int2* __restrict__ chu
             cnt++;
             if (!first && onC[v0 + t]) brk = 1;
         }
+        if (!TIE && E && !first && t < nv) {
+            // the vertex's chase entry (values toward C's source, if C stays)
+            const int64_t v = v0 + t, base = ga.vptr[g];
+            unsigned long long e = (unsigned)(v - base);
+            if (v != ga.s[g] && !chase_pack(L * wval(wsel, v, neg) - W, (unsigned)(succ[v] - base),
+                                            jb, &e))
+                ga.ovf[g] = 1;
+            E[v] = e;
+        }
     };
-    const int64_t end = ga.vptr[g + 1];
-    const int64_t c1 = ch.y + (int64_t)T < end ? ch.y + (int64_t)T : end;
-    const int64_t v0 = ch.y + (int64_t)(blockIdx.x % per) * kWG;
-    if (v0 >= c1) return;
     const bool first = !TIE && ga.iter[g] == 0;
-    tile(v0, c1 - v0 < kWG ? (int)(c1 - v0) : kWG, first, first ? 1 : ga.L[g],
-         first ? 0 : ga.W[g]);
+    tile(tv0, tnv, first, first ? 1 : ga.L[g], first ? 0 : ga.W[g]);
     cnt = block_sum_u64(cnt);
     if (TIE) {
         certain = block_sum_u64(certain);
@@ -565,6 +593,7 @@ __global__ __launch_bounds__(kWG) void k_sweep_tile(const int2* __restrict__ chu
             if (bb) atomicOr(&ga.cbroken[g], 1u);
         }
     }
+    });
 }
 
 // After the sweep: converged graphs retire; the others take the fast path
@@ -607,7 +636,136 @@ __global__ __launch_bounds__(kWG) void k_after_sweep(int G, GArrays ga, int max_
 }
 
 // ---------------------------------------------------------------------------
-// values: pointer jumping toward each graph's source
+// values: chase toward each graph's source
+// ---------------------------------------------------------------------------
+// As k_chase of the single-graph solver, over the listed graphs in mode `want`
+// (entries hold vertex numbers inside the graph): in place, 8 bytes per vertex,
+// two passes instead of ceil(log2 n) rounds over two 12-byte buffers.  The
+// fast path's entries were written by the sweep, a rebuilt graph's by
+// k_chase_init.  Bound by entry reads that stay in one XCD's L2 (a graph's
+// tiles run on one XCD).
+// Per graph: vact[4 g] unfinished after pass 1, vact[4 g + 1] after pass 2,
+// vprog[4 g + 1] some vertex finished in pass 2, vact[4 g + 2] a vertex lies on
+// a cycle other than C; ovf a sum did not fit.  k_chase_close reads and clears
+// them.
+template <typename WT>
+__global__ __launch_bounds__(kWG) void k_chase_init(const int2* __restrict__ chunks,
+                                                    const unsigned* nch, int T, GArrays ga,
+                                                    const int* __restrict__ col,
+                                                    const int* __restrict__ pi,
+                                                    const WT* __restrict__ w, int neg,
+                                                    int* __restrict__ succ, WT* __restrict__ wsel,
+                                                    unsigned long long* __restrict__ E, int jb)
+{
+    for_each_chunk(chunks, nch, ga.vptr, T, [&](int g, int64_t v0, int64_t v1) {
+        const int64_t base = ga.vptr[g];
+        const int s = ga.s[g];
+        const long long W = ga.W[g], L = ga.L[g];
+        for (int64_t v = v0 + threadIdx.x; v < v1; v += kWG) {
+            const int p = pi[v];
+            const WT x = w[p];
+            const int h = col[p];
+            succ[v] = h;
+            wsel[v] = x;
+            unsigned long long e = (unsigned)(v - base);
+            if (v != s && !chase_pack(L * wval(&x, 0, neg) - W, (unsigned)(h - base), jb, &e))
+                ga.ovf[g] = 1;
+            E[v] = e;
+        }
+    });
+}
+
+__global__ __launch_bounds__(kWG) void k_chase(const int2* __restrict__ chunks, const unsigned* nch,
+                                               int T, GArrays ga, int want, int pass, int jb,
+                                               unsigned long long* E, long long* __restrict__ V,
+                                               int* __restrict__ V32, BCtl* bc)
+{
+    constexpr int SC = __HIP_MEMORY_SCOPE_WORKGROUP;
+    const unsigned long long jm = (1ull << jb) - 1;
+    for_each_tile(chunks, nch, ga.vptr, T, [&](int g, int64_t v0, int nv) {
+        if (ga.mode[g] != want) return;
+        unsigned* stall = &ga.vact[4 * g + 2];
+        if (pass == 2 && (!ga.vact[4 * g] || *stall)) return;
+        unsigned long long* Eg = E + ga.vptr[g];
+        const int64_t v = v0 + threadIdx.x;
+        const unsigned me = (unsigned)(v - ga.vptr[g]);
+        const unsigned s = (unsigned)(ga.s[g] - ga.vptr[g]);
+        unsigned long long e = s;
+        if ((int)threadIdx.x < nv) e = chase_load<SC>(&Eg[me]);
+        const bool was = (e & jm) == s;
+        bool fits = true;
+        for (int k = 1; k <= kChaseSteps; ++k) {
+            const unsigned j = (unsigned)(e & jm);
+            if (j == s) break;
+            const unsigned long long r = chase_load<SC>(&Eg[j]);
+            const unsigned h = (unsigned)(r & jm);
+            fits &= chase_pack(((long long)e >> jb) + ((long long)r >> jb), h, jb, &e);
+            chase_store<SC>(&Eg[me], e);
+            if (h == me) {
+                atomicOr(stall, 1u);
+                break;
+            }
+            if ((k & 7) == 0 &&
+                __hip_atomic_load(stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                break;
+        }
+        const bool done = (e & jm) == s;
+        bool wide = false;
+        if ((int)threadIdx.x < nv && done) {
+            const long long d = (long long)e >> jb;
+            V[v] = d;
+            V32[v] = (int)d;
+            wide = d != (long long)(int)d;
+        }
+        const bool open = __ballot(!done) != 0, prog = __ballot(done && !was) != 0;
+        const bool over = __ballot(!fits) != 0, big = __ballot(wide) != 0;
+        if ((threadIdx.x & 63) == 0) {
+            if (open) atomicOr(&ga.vact[4 * g + pass - 1], 1u);
+            if (pass == 2 && prog) atomicOr(&ga.vprog[4 * g + 1], 1u);
+            if (over) atomicOr(&ga.ovf[g], 1u);
+            // sticky: from now on the sweeps gather the int64 values
+            if (big) atomicOr(&bc->wide32, 1u);
+        }
+    });
+}
+
+__global__ __launch_bounds__(kWG) void k_chase_close(int G, GArrays ga, int want, BCtl* bc,
+                                                     const unsigned* halt)
+{
+    if (halt && *halt != 0u) return;
+    for (int g = blockIdx.x * kWG + threadIdx.x; g < G; g += gridDim.x * kWG) {
+        if (ga.mode[g] != want) continue;
+        const unsigned u1 = ga.vact[4 * g], u2 = ga.vact[4 * g + 1], st = ga.vact[4 * g + 2];
+        const unsigned pr = ga.vprog[4 * g + 1], ov = ga.ovf[g];
+        ga.vact[4 * g] = ga.vact[4 * g + 1] = ga.vact[4 * g + 2] = 0;
+        ga.vprog[4 * g + 1] = 0;
+        ga.ovf[g] = 0;
+        if (st || (u1 && u2 && !pr)) {
+            if (want == kFast) {
+                ga.mode[g] = kGeneral;   // C is no longer the only cycle
+            } else {
+                ga.mode[g] = kDone;
+                ga.status[g] = OCM_E_NOT_STRONGLY_CONNECTED;
+            }
+        } else if ((u1 && u2) || ov) {
+            ga.mode[g] = kPend + want;
+            atomicAdd(&bc->npend, 1u);
+        } else {
+            ga.mode[g] = kActive;
+            ga.have_c[g] = 1;
+        }
+    }
+}
+
+// Graphs left to the doubling rounds: back to the mode their values are for.
+__global__ __launch_bounds__(kWG) void k_unpend(int G, GArrays ga, int want)
+{
+    for (int g = blockIdx.x * kWG + threadIdx.x; g < G; g += gridDim.x * kWG)
+        if (ga.mode[g] == kPend + want) ga.mode[g] = want;
+}
+
+// ---------------------------------------------------------------------------
+// values: pointer jumping toward each graph's source (graphs the chase leaves)
 // ---------------------------------------------------------------------------
 // Value init.  SEL (fast path): each vertex's successor and edge weight come
 // from succ and wsel, and the entry already spans two policy edges (succ
@@ -1089,6 +1247,7 @@ __global__ __launch_bounds__(kWG) void k_set_lambda(int G, GArrays ga,
             ga.status[g] = OCM_E_HIP;
             continue;
         }
+        ga.ovf[g] = 0;   // a sweep's entries for the old lambda may have set it
         ga.s[g] = r;
         ga.W[g] = wsum[r];
         ga.L[g] = (long long)lcnt[r];
@@ -1888,6 +2047,7 @@ struct BCtx {
     ocm_profile* prof = nullptr;
     bool rev_built = false;
     bool tile_sweep = true;   // improvement sweeps over vertex tiles (else lanes per vertex)
+    bool chase = false;       // values by the chase (off once a graph needed the rounds)
     bool device_rounds = true;   // iterations after the first decide their rounds on the device
     int max_n = 1;
     int64_t loop_G = 0, loop_n = 0;   // graphs and vertices the loop solves (not the small class)
@@ -1895,7 +2055,7 @@ struct BCtx {
 
 ocm_status bread(BCtx& c)
 {
-    BHIP(ocm::host_read(c.ws.bc, &c.h, sizeof(BCtl), c.st));
+    BHIP(ocm::host_read(c.ws.bc, &c.h, offsetof(BCtl, vrun_round), c.st));
     return OCM_OK;
 }
 
@@ -1905,6 +2065,15 @@ unsigned chunk_grid(const BCtx& c)
 {
     const unsigned most = (unsigned)(c.n / ocm::b::kMinChunk + c.G + 1);
     return most < ocm::b::kChunkGrid ? most : ocm::b::kChunkGrid;
+}
+
+// workgroups of a tile kernel: one per tile of the list's capacity, at most
+// kTileGrid (they stride over the tiles), a multiple of 8
+unsigned tile_grid(const BCtx& c)
+{
+    const int64_t per = (c.sch.chunk + ocm::kWG - 1) / ocm::kWG;
+    const int64_t most = (c.n / c.sch.chunk + c.G + 1) * per;
+    return (unsigned)((std::min<int64_t>(most, ocm::b::kTileGrid) + 7) & ~int64_t(7));
 }
 
 unsigned chunk_grid(unsigned nch) { return nch < ocm::b::kChunkGrid ? nch : ocm::b::kChunkGrid; }
@@ -2016,13 +2185,12 @@ void launch_bsweep(BCtx& c, unsigned nch, bool tie, int* xs = nullptr, int* ys =
     if (c.tile_sweep) {   // improvement sweeps and tie scans over vertex tiles
         BWs& ws = c.ws;
         const int T = c.sch.chunk;
-        const unsigned per = (unsigned)((T + ocm::kWG - 1) / ocm::kWG);
-        // one workgroup per tile: the list's capacity in tiles
-        const unsigned one = (unsigned)(c.n / T + c.G + 1) * per;
+        auto* E = c.chase && !tie ? (unsigned long long*)ws.Q[0] : nullptr;
+        const int jb = ocm::chase_bits(c.max_n);
 #define OCM_BST(WT, TIE, SUCC, WSEL)                                                             \
-    ocm::b::k_sweep_tile<WT, TIE><<<one, ocm::kWG, 0, c.st>>>(                                   \
+    ocm::b::k_sweep_tile<WT, TIE><<<tile_grid(c), ocm::kWG, 0, c.st>>>(                          \
         ws.chunks, &ws.bc->nchunks, T, ws.ga, c.row_ptr, c.col, (const WT*)c.w, c.neg, ws.V,     \
-        ws.pi, ws.onC, ws.V32, ws.bc, SUCC, WSEL, ws.hop, xs, ys, xcnt, xcap)
+        ws.pi, ws.onC, ws.V32, ws.bc, SUCC, WSEL, ws.hop, xs, ys, xcnt, xcap, E, jb)
         int* sc = !tie || walk ? ws.succ : nullptr;
         if (c.wtype == OCM_W_I64) {
             if (tie) OCM_BST(long long, true, sc, nullptr);
@@ -2051,12 +2219,36 @@ int jump_rounds(const BCtx& c)
 // finish every graph that reaches its source.  kFast graphs that stop
 // progressing fall back to the general phases; kGeneral ones fail.
 // halt (nullable): nothing runs while *halt is non-zero.
+// With the chase the fast path takes the sweep's chunk list (the active
+// graphs; those in another mode do nothing) and the sweep's entries.
 void enqueue_values(BCtx& c, int want, const unsigned* halt = nullptr)
 {
     BWs& ws = c.ws;
     GArrays& a = ws.ga;
     const int T = c.sch.chunk;
     const unsigned mc = chunk_grid(c);
+    if (c.chase) {
+        auto* E = (unsigned long long*)ws.Q[0];
+        const int jb = ocm::chase_bits(c.max_n);
+        if (want == ocm::b::kGeneral) {
+            enqueue_chunks(c, want, halt);
+            if (c.wtype == OCM_W_I64)
+                ocm::b::k_chase_init<long long><<<mc, ocm::kWG, 0, c.st>>>(
+                    ws.chunks, &ws.bc->nchunks, T, a, c.col, ws.pi, (const long long*)c.w, c.neg,
+                    ws.succ, (long long*)ws.wsel, E, jb);
+            else
+                ocm::b::k_chase_init<int><<<mc, ocm::kWG, 0, c.st>>>(
+                    ws.chunks, &ws.bc->nchunks, T, a, c.col, ws.pi, (const int*)c.w, c.neg, ws.succ,
+                    (int*)ws.wsel, E, jb);
+        }
+        for (int pass = 1; pass <= 2; ++pass)
+            ocm::b::k_chase<<<tile_grid(c), ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a,
+                                                                 want, pass, jb, E, ws.V, ws.V32,
+                                                                 ws.bc);
+        ocm::b::k_chase_close<<<ocm::stride_grid(c.G), ocm::kWG, 0, c.st>>>((int)c.G, a, want, ws.bc,
+                                                                          halt);
+        return;
+    }
     enqueue_chunks(c, want, halt);
     // vrun_round and vlast (the init books round 0)
     ocm::launch_fill_u32(ws.bc->vrun_round, 33, 0u, c.st);
@@ -2148,7 +2340,7 @@ void enqueue_head(BCtx& c, int max_iters, bool fast_path)
     enqueue_chunks(c, ocm::b::kActive);
     launch_bsweep(c, chunk_grid(c), false);
     ocm::b::k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->nactive, &ws.bc->nfast);
-    ocm::b::k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->ngeneral, nullptr);
+    ocm::b::k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->ngeneral, &ws.bc->npend);
     ocm::b::k_after_sweep<<<ocm::stride_grid(c.G), ocm::kWG, 0, c.st>>>((int)c.G, a, max_iters,
                                                                       ws.bc);
     if (fast_path) enqueue_values(c, ocm::b::kFast);
@@ -2263,6 +2455,27 @@ ocm_status finish_rounds(BCtx& c)
     enqueue_values(c, ocm::b::kGeneral);
     BHIP(hipGetLastError());
     return OCM_OK;
+}
+
+// Graphs whose values the chase left (npend > 0 after an iteration): rebuilt
+// graphs take the doubling rounds, then the fast path's, whose stalled ones go
+// through the general phases.  The batch keeps the rounds from here on.
+ocm_status finish_pending(BCtx& c)
+{
+    BWs& ws = c.ws;
+    GArrays& a = ws.ga;
+    ocm::Ctl* cc = (ocm::Ctl*)ws.vctl;
+    c.chase = false;
+    const unsigned gg = ocm::stride_grid(c.G);
+    ocm::b::k_unpend<<<gg, ocm::kWG, 0, c.st>>>((int)c.G, a, ocm::b::kGeneral);
+    enqueue_values(c, ocm::b::kGeneral);
+    ocm::b::k_unpend<<<gg, ocm::kWG, 0, c.st>>>((int)c.G, a, ocm::b::kFast);
+    enqueue_values(c, ocm::b::kFast);
+    enqueue_general_head(c);
+    ocm::launch_round_setup_dev(cc, c.rev_built ? 0 : 1, kBPushMin, c.st);
+    enqueue_rounds(c, 1, kLoopRounds);
+    BHIP(hipGetLastError());
+    return finish_rounds(c);
 }
 
 // The fixed parts of an iteration as captured hipGraphs: head and tail
@@ -2732,6 +2945,7 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
         BHIP(hipGetLastError());
     }
 
+    c.chase = c.tile_sweep;
     // iterations: [head graph] -> host rebuild rounds -> [tail graph]
     const char* env = getenv("OCM_BATCH_GRAPH");
     const bool use_graph = !(env && env[0] == '0');
@@ -2756,6 +2970,8 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
             if (use_graph) BHIP(hipGraphLaunch(lp.tail, c.st));
             else enqueue_values(c, ocm::b::kGeneral);
             BHIP(hipGetLastError());
+            if (c.chase) BTRY(bread(c));
+            if (c.chase && c.h.npend > 0) BTRY(finish_pending(c));
             continue;
         }
         if (use_graph && !lp.iter)
@@ -2765,7 +2981,15 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
         BHIP(hipGetLastError());
         BTRY(bread(c));
         if (c.h.nactive == 0) break;
-        if (c.h.rounds_open) BTRY(finish_rounds(c));
+        if (c.h.rounds_open) {
+            BTRY(finish_rounds(c));
+            if (c.chase) BTRY(bread(c));   // its values may have left some pending
+        }
+        if (c.h.npend > 0) {
+            BTRY(finish_pending(c));
+            if (lp.iter) (void)hipGraphExecDestroy(lp.iter);   // captured with the chase
+            lp.iter = nullptr;
+        }
     }
 
     // hops to the source for every solved graph (the small class's are

@@ -262,6 +262,32 @@ __device__ __forceinline__ Jmp jmp_combine(Jmp q, const Jmp& r)
     return q;
 }
 
+// Value chase (k_chase): steps a vertex takes per pass.
+constexpr int kChaseSteps = 96;
+
+// A chase entry: the sum in the upper 64 - jb bits (signed), the vertex
+// reached below.  Returns false when the sum does not fit.
+__device__ __forceinline__ bool chase_pack(long long d, unsigned j, int jb, unsigned long long* e)
+{
+    const unsigned long long up = (unsigned long long)d << jb;
+    *e = up | j;
+    return ((long long)up >> jb) == d;
+}
+
+// Scopes of the entries' relaxed reads and writes: agent scope goes past the
+// XCD's own L2 (fresh entries from every XCD, fewer steps), workgroup scope
+// stays in it (cheaper steps, entries of other XCDs seen late).
+template <int SCOPE>
+__device__ __forceinline__ unsigned long long chase_load(const unsigned long long* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, SCOPE);
+}
+template <int SCOPE>
+__device__ __forceinline__ void chase_store(unsigned long long* p, unsigned long long x)
+{
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, SCOPE);
+}
+
 // Rows with more than kLongRow keys in a batch are walked by the vertex's
 // whole wave (64 lanes striding over the keys, then a wave minimum with
 // ties to the lower position) instead of by its own thread alone: a hub's

@@ -339,15 +339,6 @@ __device__ void loop_after_sweep(Ctl* c, bool changed, bool broken)
     }
 }
 
-// A chase entry: the sum in the upper 64 - jb bits (signed), the vertex
-// reached below.  Returns false when the sum does not fit.
-__device__ __forceinline__ bool chase_pack(long long d, unsigned j, int jb, unsigned long long* e)
-{
-    const unsigned long long up = (unsigned long long)d << jb;
-    *e = up | j;
-    return ((long long)up >> jb) == d;
-}
-
 // The entry of vertex v with policy edge p and head h.
 template <typename WT, bool RATIO>
 __device__ __forceinline__ bool chase_entry(const SweepArgs& a, const WT* __restrict__ w, int64_t v,
@@ -2115,8 +2106,6 @@ __global__ __launch_bounds__(kWG) void k_fill_u32(int64_t len, unsigned* __restr
 // reached a finished one and finishes with its next step.  A vertex that
 // reaches itself lies on another cycle, which proves it at once.
 // ---------------------------------------------------------------------------
-constexpr int kChaseSteps = 96;
-
 __global__ void k_loop_setup(Ctl* c, unsigned mode, unsigned opts, unsigned max_sweeps)
 {
     const int t = threadIdx.x;
@@ -2216,20 +2205,6 @@ __device__ void loop_after_chase(Ctl* c, unsigned left)
         c->fflags = 0;
         c->fmode = kLoopSweep;
     }
-}
-
-// Scopes of the entries' relaxed reads and writes: agent scope goes past the
-// XCD's own L2 (fresh entries from every XCD, fewer steps), workgroup scope
-// stays in it (cheaper steps, entries of other XCDs seen late).
-template <int SCOPE>
-__device__ __forceinline__ unsigned long long chase_load(const unsigned long long* p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, SCOPE);
-}
-template <int SCOPE>
-__device__ __forceinline__ void chase_store(unsigned long long* p, unsigned long long x)
-{
-    __hip_atomic_store(p, x, __ATOMIC_RELAXED, SCOPE);
 }
 
 template <int LD, int ST>

@@ -95,6 +95,64 @@ def test_values_leave_int32_in_mid_solve():
     both(g)
 
 
+def batch(gs, mode="min", **kw):
+    u, vptr, eptr = synth.disjoint_union(gs)
+    dev = [torch.from_numpy(x).cuda() for x in (u.row_ptr, u.col, u.w)]
+    r = ocm.cycle_mean_batched(*dev, vptr, eptr, mode=mode, **kw)
+    return r, [tuple(e - int(eptr[k]) for e in r.cycle(k).cpu().tolist()) for k in range(len(gs))]
+
+
+def check_batch(gs, mode="min"):
+    """The loop's chase against its rounds (G lanes per vertex) and the oracle."""
+    (a, ca), (b, cb) = batch(gs, mode), batch(gs, mode, schedule=4)
+    for k in ("p", "q", "iterations", "flags", "status", "cycle_ptr"):
+        assert getattr(a, k) == getattr(b, k), k
+    assert ca == cb
+    for k, g in enumerate(gs):
+        if a.status[k] != ocm.OCM_OK:
+            continue
+        sol = native.solve(g.row_ptr, g.col, g.w, mode)
+        assert (a.p[k], a.q[k], a.iterations[k], list(ca[k])) == \
+            (sol.p, sol.q, sol.iterations, sol.cycle.tolist())
+    return a
+
+
+@pytest.mark.parametrize("sizes", [[1, 2, 3], [255, 256, 257], [511, 512, 513, 1025], [20011, 1, 4097]])
+def test_batched_loop_sizes(sizes, monkeypatch):
+    monkeypatch.setenv("OCM_BATCH_SMALL", "0")
+    check_batch([synth.random_digraph(n, 1, 4, -100, 100, np.int64, seed=[81, n]) for n in sizes],
+                "max" if len(sizes) == 3 else "min")
+
+
+def test_batched_stalls_and_ties(monkeypatch):
+    monkeypatch.setenv("OCM_BATCH_SMALL", "0")
+    check_batch([synth.random_digraph(3000 + k, 1, 4, 0, 2, np.int64, seed=[82, k]) for k in range(8)])
+
+
+@pytest.mark.parametrize("hlo", [2**35, 2**47])
+def test_batched_sums_beyond_the_entry(hlo, monkeypatch):
+    """A graph whose sums do not fit the packed entries goes on with the
+    doubling rounds; one beyond int64 fails alone."""
+    monkeypatch.setenv("OCM_BATCH_SMALL", "0")
+    gs = [synth.random_digraph(n, 1, 5, 1, 1000, np.int64, seed=[83, n]) for n in (300, 5000)]
+    gs.insert(1, synth.deep_tail_graph(700, 800, 2, 10, hlo, 2 * hlo, seed=3))
+    r = check_batch(gs)
+    assert r.status == [0, ocm.OCM_E_OVERFLOW if hlo == 2**47 else 0, 0]
+
+
+def test_batched_long_paths(monkeypatch):
+    """Rings of n vertices with a shortcut: paths of n - 1 edges, cycles of n."""
+    monkeypatch.setenv("OCM_BATCH_SMALL", "0")
+    gs = []
+    for n in (3000, 70000):
+        col = np.insert((np.arange(n) + 1) % n, 1, 1).astype(np.int32)
+        rp = np.arange(n + 1, dtype=np.int32)
+        rp[1:] += 1
+        w = np.insert(np.random.default_rng(n).integers(-50, 50, n), 1, 40).astype(np.int64)
+        gs.append(synth.Graph(rp, col, w, "ring"))
+    check_batch(gs)
+
+
 @pytest.mark.parametrize("cap", [1, 2, 3, 5])
 def test_iteration_cap(cap):
     g = synth.random_digraph(3000, 1, 4, 1, 1000, np.int32, seed=[75, 0])
