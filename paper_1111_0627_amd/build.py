@@ -9,7 +9,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libocm.so")
-SOURCES = ["kernels.hip", "solver.hip", "batch.hip", "general.hip", "multichain.hip"]
+SOURCES = ["kernels.hip", "solver.hip", "batch.hip", "general.hip", "multichain.hip",
+           "small.hip"]
 ARCH = os.environ.get("OCM_OFFLOAD_ARCH", "gfx950")
 
 # Packed-FP32 instructions are switched off for all device code.
@@ -18,7 +19,7 @@ HIPFLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
             "-Wall", "-Wno-unused-function"]
 
 
-def build(verbose: bool = False, jobs: int = 4) -> str:
+def build(verbose: bool = False, jobs: int = 6) -> str:
     objs = []
     procs = []
     for src in SOURCES:

@@ -435,6 +435,12 @@ void launch_exclusive_scan(int64_t len, const unsigned* in, unsigned* out, unsig
 hipError_t host_read(const void* dsrc, void* hdst, size_t bytes, hipStream_t st);
 // Folds a control block's lanes and reads the snapshot.
 hipError_t host_read_ctl(const Ctl* ctl, CtlView* out, hipStream_t st);
+// The calling thread's mailbox as a kernel's target: at most kMailboxBytes at
+// *data, then *want stored (system release) to *seq.  False when reads go
+// through copies; host_mailbox_take waits for the post, and for the stream.
+constexpr size_t kMailboxBytes = 256;
+bool host_mailbox(void** data, unsigned** seq, unsigned* want);
+hipError_t host_mailbox_take(unsigned want, void* dst, size_t bytes, hipStream_t st);
 // The same through a copy into the caller's stack and a stream
 // synchronisation: no pinned mailbox is created (used by the entry point
 // that allocates nothing).

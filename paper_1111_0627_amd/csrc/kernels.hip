@@ -3599,6 +3599,28 @@ hipError_t host_read(const void* dsrc, void* hdst, size_t bytes, hipStream_t st)
     return hipSuccess;
 }
 
+bool host_mailbox(void** data, unsigned** seq, unsigned* want)
+{
+    static_assert(kMailboxBytes == 4 * kPostWords, "the mailbox's data words");
+    Mailbox& mb = mailbox();
+    if (mb.stream_mode) return false;
+    *data = mb.dev;
+    *seq = mb.dev + kPostWords;
+    *want = ++mb.seq;
+    return true;
+}
+
+hipError_t host_mailbox_take(unsigned want, void* dst, size_t bytes, hipStream_t st)
+{
+    Mailbox& mb = mailbox();
+    hipError_t e = wait_post(mb, want, st);
+    if (e != hipSuccess) return e;
+    memcpy(dst, mb.host, bytes);
+    // the kernel that posted is about to end
+    while ((e = hipStreamQuery(st)) == hipErrorNotReady) __builtin_ia32_pause();
+    return e;
+}
+
 hipError_t host_read_ctl_copy(const Ctl* ctl, CtlView* out, hipStream_t st)
 {
     Ctl h;   // on the caller's stack: this path allocates nothing

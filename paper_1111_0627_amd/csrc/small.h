@@ -1,0 +1,64 @@
+// Small graphs solved whole by one workgroup (small.hip).
+#pragma once
+
+#include "kernels.h"
+#include "ocm.h"
+
+namespace ocm {
+
+constexpr int kSmallMaxN = 4096;
+constexpr int kSmallMaxM = 65535;      // edge positions take 16 bits
+constexpr int kSmallFallback = 1;      // status: sums too large, the general path decides
+constexpr int kSmallClasses = 4;
+
+struct SmallOpts {
+    int validate;          // check the CSR (and its column range)
+    int bound;             // apply the weight bound (the batch has done so)
+    int fast_path;
+    int tie_check;
+    int iter_cap;
+    long long cycle_cap;   // room for C's edges (single solves)
+};
+
+struct SmallOut {
+    long long W, L;
+    int status;            // ocm_status or kSmallFallback
+    int s, iterations, fast, general, connect_rounds, jump_rounds, value_rounds;
+    unsigned clen, tight, tie;
+};
+
+struct SmallPtrs {
+    const int* init;       // warm start's policy, or null
+    int* policy;           // outputs of a converged solve, or null
+    long long* potential;
+    int* cycle;
+    SmallOut* out;         // device or mapped host memory
+    unsigned* seq;         // set to want once out is written (mapped host memory), or null
+    unsigned want;
+};
+
+struct SmallBatch {        // the batch's arrays, by graph and by union vertex
+    const long long* vptr;
+    const long long* eptr;
+    long long* W;
+    long long* L;
+    int* s;
+    int* iter;
+    int* status;
+    int* mode;
+    int* pi;
+    int* succ;
+    long long* V;
+    int* hop;
+    unsigned char* onC;
+};
+
+// Class 0 .. kSmallClasses - 1 of a graph (LDS size), or -1.
+int small_class(int64_t n, int64_t m, bool ratio);
+void launch_small_one(int n, int m, const int* row_ptr, const int* col, const void* w, int wtype,
+                      const int* t, int neg, const SmallOpts& o, const SmallPtrs& p, hipStream_t st);
+void launch_small_batch(int cls, const int* list, int nlist, const SmallBatch& b, const int* row_ptr,
+                        const int* col, const void* w, int wtype, int neg, const SmallOpts& o,
+                        hipStream_t st);
+
+}  // namespace ocm

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "kernels.h"
+#include "small.h"
 
 using ocm::Ctl;
 using ocm::Jmp;
@@ -326,7 +327,7 @@ ocm_status check_graph(const ocm_graph* g)
 }
 
 ocm_status setup(Ctx& c, const ocm_graph* g, int neg, void* ws, size_t ws_bytes, void* stream,
-                 ocm_profile* prof)
+                 ocm_profile* prof, bool clear = true)
 {
     OCM_TRY(check_graph(g));
     c.n = (int)g->n;
@@ -345,7 +346,8 @@ ocm_status setup(Ctx& c, const ocm_graph* g, int neg, void* ws, size_t ws_bytes,
     c.prof.st = c.st;
     memset(&c.h, 0, sizeof c.h);
     // the workspace may hold anything: every entry point starts from a clean
-    // control block
+    // control block (a whole solve's validation clears it)
+    if (!clear) return OCM_OK;
     ocm::launch_ctl_clear(c.ws.ctl, ocm::kClrAll | ocm::kClrCount | ocm::kClrChanged, c.st);
     HIP_TRY(hipGetLastError());
     return OCM_OK;
@@ -1409,6 +1411,82 @@ ocm_status solve_mc(Ctx& c, const ocm_options& o, int32_t* cycle_edges, int64_t 
     return OCM_OK;
 }
 
+// A small graph solved by one workgroup in one launch.  *done = false: its sums
+// need more room than the entries have, the general path takes over.
+ocm_status solve_small(Ctx& c, const ocm_options& o, int32_t* cycle_edges, int64_t cap,
+                       ocm_result* out, bool* done)
+{
+    *done = true;
+    ocm::SmallOpts so;
+    so.validate = o.validate != 0;
+    so.bound = 1;
+    so.fast_path = o.fast_path != 0;
+    so.tie_check = o.tie_check != 0;
+    so.iter_cap = o.max_iters > 0 && o.max_iters < kIterCap ? o.max_iters : kIterCap;
+    so.cycle_cap = cap;
+    ocm::SmallPtrs p;
+    p.init = o.init_policy;
+    p.policy = o.policy_out;
+    p.potential = (long long*)o.potential_out;
+    p.cycle = cycle_edges;
+    p.out = (ocm::SmallOut*)c.ws.ctl;
+    p.seq = nullptr;
+    p.want = 0;
+    static_assert(sizeof(ocm::SmallOut) <= ocm::kMailboxBytes && sizeof(ocm::SmallOut) <= sizeof(Ctl),
+                  "the outcome fits the mailbox and the control block");
+    void* data = nullptr;
+    const bool post = !c.noalloc && ocm::host_mailbox(&data, &p.seq, &p.want);
+    if (post) p.out = (ocm::SmallOut*)data;
+    ocm::launch_small_one(c.n, c.m, c.row_ptr, c.col, c.w, c.wtype, c.t, c.neg, so, p, c.st);
+    HIP_TRY(hipGetLastError());
+    ocm::SmallOut r;
+    if (post) {
+        HIP_TRY(ocm::host_mailbox_take(p.want, &r, sizeof r, c.st));
+    } else {
+        HIP_TRY(hipMemcpyAsync(&r, p.out, sizeof r, hipMemcpyDeviceToHost, c.st));
+        HIP_TRY(hipStreamSynchronize(c.st));
+    }
+    if (r.status == ocm::kSmallFallback) {
+        *done = false;
+        return OCM_OK;
+    }
+    out->iterations = r.iterations;
+    out->connect_rounds = r.connect_rounds;
+    out->jump_rounds = r.jump_rounds;
+    out->fast_iters = r.fast;
+    out->general_iters = r.general;
+    out->value_rounds = r.value_rounds;
+    switch (r.status) {
+        case OCM_OK: break;
+        case OCM_E_BAD_CSR: return fail(OCM_E_BAD_CSR, "malformed CSR");
+        case OCM_E_NO_OUT_EDGE: return fail(OCM_E_NO_OUT_EDGE, "a vertex has no out-edge");
+        case OCM_E_INVALID_ARG:
+            return fail(OCM_E_INVALID_ARG, r.tight ? "edge times must be integers >= 1"
+                                                   : "init_policy picks an edge of another vertex");
+        case OCM_E_OVERFLOW: return fail(OCM_E_OVERFLOW, "weights too large for int64 values");
+        case OCM_E_NOT_CONVERGED: return fail(OCM_E_NOT_CONVERGED, "max_iters reached");
+        default:
+            return fail(OCM_E_NOT_STRONGLY_CONNECTED, "some vertex cannot reach the chosen cycle");
+    }
+    const long long gg = gcd_ll(r.W, r.L);
+    out->p = (c.neg ? -r.W : r.W) / gg;
+    out->q = r.L / gg;
+    out->W = c.neg ? -r.W : r.W;
+    out->L = r.L;
+    out->source = r.s;
+    out->cycle_len = r.clen;
+    if (cap < (int64_t)r.clen) return fail(OCM_E_CAPACITY, "cycle_cap smaller than the critical cycle");
+    if (o.tie_check) {
+        out->tight_edges = r.tight;
+        if (r.tight) out->flags |= OCM_F_TIGHT_EDGES;
+        if (r.tie) out->flags |= OCM_F_TIE;
+    } else {
+        out->flags |= OCM_F_TIE_UNCHECKED;
+        out->tight_edges = -1;
+    }
+    return OCM_OK;
+}
+
 // t (nullable): edge times, the optimal cycle ratio instead of the mean.
 ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t ws_bytes,
                  int32_t* cycle_edges, int64_t cap, ocm_result* out, void* stream, int neg,
@@ -1423,7 +1501,7 @@ ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t 
     Ctx c;
     c.noalloc = noalloc;
     c.t = t;
-    OCM_TRY(setup(c, g, neg, wsp, ws_bytes, stream, o.profile));
+    OCM_TRY(setup(c, g, neg, wsp, ws_bytes, stream, o.profile, false));
     if (cap > 0 && !cycle_edges) return fail(OCM_E_INVALID_ARG, "cycle_edges is null");
     c.G = choose_lanes(c.n, c.m, o.schedule);
     if (!valid_lanes(c.G)) return fail(OCM_E_INVALID_ARG, "schedule must be a power of two <= 64");
@@ -1438,6 +1516,18 @@ ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t 
     if (o.multichain && (o.init_policy || t || o.int128_values))
         return fail(OCM_E_INVALID_ARG,
                     "multichain runs without init_policy, edge times or int128 values");
+    // small graphs go to one workgroup: a phase launched by itself costs more
+    // than an iteration there.  OCM_SMALL=0 keeps them on the general path
+    // (same results); so do the options that name a part of that path.
+    if (ocm::small_class(c.n, c.m, t != nullptr) >= 0 && o.schedule <= 0 && !o.connect_mode &&
+        !o.profile && !o.multichain && !o.int128_values) {
+        const char* env = getenv("OCM_SMALL");
+        if (!(env && env[0] == '0')) {
+            bool done = true;
+            const ocm_status s = solve_small(c, o, cycle_edges, cap, out, &done);
+            if (done || s != OCM_OK) return s;
+        }
+    }
     ocm_status rc = validate(c, o.validate != 0);
     if (rc == OCM_OK) rc = build_giant(c);
     if (rc != OCM_OK) { c.prof.finish(); return rc; }
