@@ -2601,12 +2601,20 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
         BHIP(hipGetLastError());
     }
 
+    // a batch of small graphs alone has nothing left for the loop, unless one
+    // fell back
+    bool loop = c.loop_G > 0;
+    if (!loop) {
+        unsigned nch = 0;
+        BTRY(build_chunks(c, ocm::b::kActive, &nch));
+        loop = nch > 0;
+    }
     c.chase = c.tile_sweep;
     // iterations: [head graph] -> host rebuild rounds -> [tail graph]
     const char* env = getenv("OCM_BATCH_GRAPH");
     const bool use_graph = !(env && env[0] == '0');
     Loop lp;
-    if (use_graph) {
+    if (use_graph && loop) {
         BHIP(hipStreamCreate(&lp.cs));
         BTRY(capture(c, lp, &lp.head, [&] { enqueue_head(c, o.max_iters, o.fast_path != 0); }));
         BTRY(capture(c, lp, &lp.tail, [&] { enqueue_values(c, ocm::b::kGeneral); }));
@@ -2614,7 +2622,7 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
     // the first iteration (every graph rebuilds) with host-driven rounds,
     // which build the reverse CSR when push rounds pay; then whole
     // iterations with device-driven rounds, one host read each
-    for (int guard = 0;; ++guard) {
+    for (int guard = 0; loop; ++guard) {
         if (guard > (1 << 20)) return bfail(OCM_E_NOT_CONVERGED, "iteration guard");
         if (guard == 0 || !c.device_rounds) {
             if (use_graph) BHIP(hipGraphLaunch(lp.head, c.st));
@@ -2648,9 +2656,9 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
         }
     }
 
-    // hops to the source for every solved graph (the small class's are
-    // recomputed, equal), then the per-graph results
-    {
+    // hops to the source for the loop's graphs (the small ones' are written),
+    // then the per-graph results
+    if (loop) {
         unsigned nch = 0;
         BTRY(build_chunks(c, -2, &nch));
         if (nch > 0) {

@@ -58,6 +58,7 @@ struct Lds {
     unsigned short layer[N];             // rebuild round (0xffff unattached); heads; alive
     unsigned char onc[N];                // 1 on a policy cycle, 3 on C
     unsigned acc[2][4];                  // sweep: changed, broken, tight, certain (by parity)
+    unsigned got[3];                     // rebuild rounds: vertices attached
     unsigned stall, over, cnt, flag;
     unsigned long long maxw;
     unsigned maxt, err, cap;
@@ -92,27 +93,41 @@ struct View {
 
 // In-place chase of every vertex to s (see k_chase): at most n steps, each at
 // least one policy edge, so a vertex that has not arrived by then never does.
+// A thread's vertices step together, so that their reads overlap.
+template <int N>
+constexpr int kVpt = N == 4096 ? 4 : 2;   // vertices per thread at most
+
 template <int N, int M, bool RATIO>
 __device__ __forceinline__ void chase(Lds<N, M, RATIO>& S, int n, unsigned s)
 {
-    constexpr int WGS = __HIP_MEMORY_SCOPE_WORKGROUP;
-    for (int v = threadIdx.x; v < n; v += blockDim.x) {
-        unsigned long long e = S.E[v];
-        bool fits = true;
-        int k = 0;
-        while ((e & kMask) != s) {
-            const unsigned long long r = chase_load<WGS>(&S.E[e & kMask]);
-            const unsigned h = (unsigned)(r & kMask);
-            fits &= chase_pack(((long long)e >> kBits) + ((long long)r >> kBits), h, kBits, &e);
-            chase_store<WGS>(&S.E[v], e);
-            if (h == (unsigned)v || ++k > n) {
-                S.stall = 1;
-                break;
-            }
-            if (__hip_atomic_load(&S.stall, __ATOMIC_RELAXED, WGS)) break;
+    constexpr int WGS = __HIP_MEMORY_SCOPE_WORKGROUP, VPT = kVpt<N>;
+    const int t = threadIdx.x, B = blockDim.x;
+    unsigned long long e[VPT];
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) e[i] = t + i * B < n ? S.E[t + i * B] : (unsigned long long)s;
+    bool fits = true;
+    for (int k = 1;; ++k) {
+        unsigned long long r[VPT];
+        bool open = false;
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) {
+            r[i] = chase_load<WGS>(&S.E[e[i] & kMask]);   // a finished vertex rereads s
+            open |= (e[i] & kMask) != s;
         }
-        if (!fits) S.over = 1;
+        if (!open) break;
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) {
+            if ((e[i] & kMask) == s) continue;
+            const unsigned h = (unsigned)(r[i] & kMask);
+            fits &= chase_pack(((long long)e[i] >> kBits) + ((long long)r[i] >> kBits), h, kBits,
+                               &e[i]);
+            chase_store<WGS>(&S.E[t + i * B], e[i]);
+            if (h == (unsigned)(t + i * B)) S.stall = 1;
+        }
+        if (k > n) S.stall = 1;
+        if ((k & 3) == 0 && __hip_atomic_load(&S.stall, __ATOMIC_RELAXED, WGS)) break;
     }
+    if (!fits) S.over = 1;
 }
 
 struct Run {
@@ -132,7 +147,7 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
                           const SmallOpts& o, const int* __restrict__ init, Run& R)
 {
     const int t = threadIdx.x, B = blockDim.x;
-    constexpr int VPT = N == 4096 ? 4 : 2;   // vertices per thread
+    constexpr int VPT = kVpt<N>;
     R = Run{};
     R.status = OCM_OK;
     R.s = 0;
@@ -338,12 +353,13 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
             unsigned left = __popcll(__ballot(mine & 1)) + 2 * __popcll(__ballot(mine & 2)) +
                             4 * __popcll(__ballot(mine & 4));
             if ((t & 63) == 0 && left) atomicAdd(&S.cnt, left);
+            if (t < 2) S.got[t + 1] = 0;
             __syncthreads();
             left = S.cnt;
             for (int k = 1; left > 0; ++k) {
-                __syncthreads();   // cnt is read by all
-                if (t == 0) S.cnt = 0;
-                __syncthreads();
+                // counters take turns: round k adds to got[k % 3], which all
+                // read after its barrier, and clears the next round's
+                if (t == 0 && k > 1) S.got[(k + 1) % 3] = 0;
                 unsigned got = 0;
                 for (int v = t; v < n; v += B) {
                     if (S.layer[v] != 0xffffu) continue;
@@ -358,9 +374,9 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
                         }
                     }
                 }
-                if (got) atomicAdd(&S.cnt, got);
+                if (got) atomicAdd(&S.got[k % 3], got);
                 __syncthreads();
-                got = S.cnt;
+                got = S.got[k % 3];
                 ++R.connect;
                 if (got == 0) {
                     R.status = OCM_E_NOT_STRONGLY_CONNECTED;
@@ -415,18 +431,31 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
                 const bool onC = S.onc[v] == 3;
                 long long best = INT64_MAX;
                 int arg = 0, bh = 0;
-                for (int e = S.rb[v]; e < (int)S.rb[v + 1]; ++e) {
-                    const int x = g.head(e);
-                    const long long key = ((long long)S.E[x] >> kBits) + L * g.weight(e) -
-                                          (RATIO ? W * g.time(e) : W);
-                    if (key < best) {
-                        best = key;
-                        arg = e;
-                        bh = x;
+                const int end = S.rb[v + 1];
+                for (int eb = S.rb[v]; eb < end; eb += 4) {
+                    // four edges in flight (past the row: its last edge again)
+                    int x[4];
+                    long long key[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int e = eb + u < end ? eb + u : end - 1;
+                        x[u] = g.head(e);
+                        key[u] = L * g.weight(e) - (RATIO ? W * g.time(e) : W);
                     }
-                    if (key == own && e != cur) {
-                        ++tight;
-                        certain += x == v || onC;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) key[u] += (long long)S.E[x[u]] >> kBits;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (eb + u >= end) break;
+                        if (key[u] < best) {
+                            best = key[u];
+                            arg = eb + u;
+                            bh = x[u];
+                        }
+                        if (key[u] == own && eb + u != cur) {
+                            ++tight;
+                            certain += x[u] == v || onC;
+                        }
                     }
                 }
                 ch = best < own;
@@ -635,10 +664,10 @@ static void launch_one(int cls, int n, int m, const int* row_ptr, const int* col
 {
     switch (cls) {
         case 0:
-            sm::k_small_one<WT, 512, 4096, RATIO><<<1, 256, 0, st>>>(n, m, row_ptr, col, w, t, neg, o, p);
+            sm::k_small_one<WT, 512, 4096, RATIO><<<1, n <= 128 ? 128 : n <= 256 ? 256 : 512, 0, st>>>(n, m, row_ptr, col, w, t, neg, o, p);
             break;
         case 1:
-            sm::k_small_one<WT, 1024, 8192, RATIO><<<1, 512, 0, st>>>(n, m, row_ptr, col, w, t, neg, o, p);
+            sm::k_small_one<WT, 1024, 8192, RATIO><<<1, 1024, 0, st>>>(n, m, row_ptr, col, w, t, neg, o, p);
             break;
         case 2:
             sm::k_small_one<WT, 2048, RATIO ? 8192 : 16384, RATIO>
