@@ -18,7 +18,6 @@ constexpr unsigned kClrChanged = 1u;
 constexpr unsigned kClrCount = 2u;
 constexpr unsigned kClrAll = 4u;
 constexpr unsigned kClrActive2 = 8u;
-constexpr unsigned kClrGiant = 16u;
 
 // |V| must stay within 2^62 so that V[u] + (L*w - W) cannot leave int64 when
 // |L*w - W| < 2^62 as well.
@@ -174,10 +173,12 @@ struct alignas(16) Jmp {
     unsigned H;
 };
 
-// Device-driven loop: the host queues (sweep, chase) pairs; each kernel runs
-// only while fmode names it, and its last workgroup decides what comes next
-// or stops the run with a reason.
+// Device-driven loop: the host queues the general phases and (sweep, chase)
+// pairs; each kernel runs only while fmode names its step, and its last
+// workgroup decides what comes next or stops the run with a reason.  lambda and
+// the source are read from the control block.
 constexpr unsigned kLoopStop = 0, kLoopSweep = 1, kLoopChase = 2;   // fmode
+constexpr unsigned kLoopCycles = 3, kLoopSelect = 4, kLoopConn = 5, kLoopRounds = 6;
 constexpr unsigned kLoopChain = 1;   // fopts: sweeps follow the value phase (else it stops there)
 constexpr unsigned kLoopV32 = 2;     //        the queued sweeps gather the int32 copy
 enum : unsigned {                    // fwhy
@@ -188,7 +189,8 @@ enum : unsigned {                    // fwhy
     kWhyOverflow,                    // a sum does not fit the packed entries
     kWhyWide,                        // a value does not fit the int32 copy (values are complete)
     kWhyIters,                       // fmax sweeps run
-    kWhyOnce                         // value phase complete, no sweep wanted
+    kWhyOnce,                        // value phase complete, no sweep wanted
+    kWhyDisconnected                 // a rebuild round attached nobody, vertices were left
 };
 constexpr unsigned kChaseStall = 1, kChaseOverflow = 2, kChaseWide = 4;   // fflags
 // The loop's arrivals count workgroups of 256 vertices in 15 bits per lane.
@@ -246,8 +248,7 @@ struct SweepArgs {
     // the sweep also writes every vertex's chase entry, and closes the loop's
     // sweep step unless giant rows follow (launch_loop_close then does)
     unsigned long long* E = nullptr;
-    int jb = 0;
-    int src = -1;                  // source: its entry is finished
+    int jb = 0;                    // (lambda and the source come from ctl then)
 };
 
 // Device-driven loop.  setup arms it (mode: what runs first; opts: kLoop*;
@@ -256,16 +257,35 @@ void launch_loop_setup(Ctl* ctl, unsigned mode, unsigned opts, unsigned max_swee
                        hipStream_t st);
 // Closes a sweep step whose giant rows were merged after the tile kernel.
 void launch_loop_close(Ctl* ctl, hipStream_t st);
-// Chase entries of every vertex from pi (succ = col[pi] is written too).
+// Chase entries of every vertex from pi (succ = col[pi] is written too), once
+// the rebuild rounds are over.
 void launch_chase_init(int n, const int* col, const int* pi, const void* w, int wtype, int neg,
-                       int s, long long W, long long L, int* succ, unsigned long long* E, int jb,
-                       Ctl* ctl, const int* t, hipStream_t st);
-// One pass of the value chase; a vertex that reaches s gets its sum in V
-// (nullable) and out32.
-void launch_chase(int n, int s, int jb, unsigned long long* E, long long* V, int* out32, Ctl* ctl,
+                       int* succ, unsigned long long* E, int jb, Ctl* ctl, const int* t,
+                       hipStream_t st);
+// One pass of the value chase; a vertex that reaches the source gets its sum in
+// V (nullable) and out32.
+void launch_chase(int n, int jb, unsigned long long* E, long long* V, int* out32, Ctl* ctl,
                   hipStream_t st);
-// Entries whose sums count policy hops (jb = 32).
-void launch_hop_init(int n, int s, const int* succ, unsigned long long* E, hipStream_t st);
+// The general phases as steps of the loop (mode kLoopCycles first): the cycles'
+// final (both tag arrays are left clear), the per-cycle sums and the select,
+// the rebuild's start (policy and push_min as launch_round).
+void launch_loop_cycles_final(int n, const unsigned long long* P0, const unsigned long long* P1,
+                              int K, int* rep, unsigned char* onc, unsigned char* tag0,
+                              unsigned char* tag1, long long* wsum, unsigned* lcnt, long long* tsum,
+                              int* cyc_list, Ctl* ctl, hipStream_t st);
+void launch_loop_select(int n, const int* rep, const unsigned char* onc, const int* pi,
+                        const void* w, int wtype, int neg, const int* t, long long* wsum,
+                        unsigned* lcnt, long long* tsum, const int* cyc_list, void* scratch,
+                        Ctl* ctl, hipStream_t st);
+void launch_loop_conn_init(int n, const int* rep, const unsigned char* onc, unsigned char* onC,
+                           unsigned* a1, unsigned* a0, Ctl* ctl, int policy, unsigned push_min,
+                           hipStream_t st);
+// Pull round k with a thread per vertex (see k_round_vertex).
+void launch_round_vertex(int k, int n, const int* row_ptr, const int* col, const unsigned* acur,
+                         unsigned* anext, int* pi, Ctl* ctl, hipStream_t st);
+// Entries whose sums count policy hops to the source (jb = 32).
+void launch_hop_init(int n, const int* succ, unsigned long long* E, const Ctl* ctl,
+                     hipStream_t st);
 // C's edges by walking succ from s (one thread).
 void launch_cycle_walk(int s, long long L, const int* pi, const int* succ, int* out,
                        hipStream_t st);

@@ -344,11 +344,13 @@ template <typename WT, bool RATIO>
 __device__ __forceinline__ bool chase_entry(const SweepArgs& a, const WT* __restrict__ w, int64_t v,
                                             int p, int h, unsigned long long* e)
 {
-    if (v == a.src) {
-        *e = (unsigned)a.src;
+    const int s = a.ctl->s;
+    if (v == s) {
+        *e = (unsigned)s;
         return true;
     }
-    const long long d = a.L * wval(w, p, a.neg) - (RATIO ? a.W * (long long)a.t[p] : a.W);
+    const long long W = a.ctl->W;
+    const long long d = a.ctl->L * wval(w, p, a.neg) - (RATIO ? W * (long long)a.t[p] : W);
     return chase_pack(d, (unsigned)h, a.jb, e);
 }
 
@@ -376,7 +378,7 @@ void k_tiescan_tile(SweepArgs a, const WT* __restrict__ w)
     __shared__ int beg[kWG + 1];
     __shared__ KT key[kTieTileEdges];
     __shared__ int head[kTieTileEdges];
-    const int64_t L = a.L, W = a.W;
+    const int64_t L = SWEEP && a.E ? a.ctl->L : a.L, W = SWEEP && a.E ? a.ctl->W : a.W;
     const int64_t v0 = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kWG;
     const int nv = a.n - v0 < kWG ? (int)(a.n - v0) : kWG;
     const int t = threadIdx.x;
@@ -582,6 +584,7 @@ __global__ __launch_bounds__(kWG) void k_giant_part(SweepArgs a, const WT* __res
     __shared__ int sp[kWG / 64], sh[kWG / 64];
     const GiantTab& g = a.giant;
     GiantPart* parts = (GiantPart*)g.parts;
+    const long long gL = MODE == 1 && a.E ? a.ctl->L : a.L, gW = MODE == 1 && a.E ? a.ctl->W : a.W;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     unsigned long long cnt = 0, certain = 0, nondec = 0;
     for (int c = blockIdx.x; c < g.nchunks; c += gridDim.x) {
@@ -605,7 +608,7 @@ __global__ __launch_bounds__(kWG) void k_giant_part(SweepArgs a, const WT* __res
             if (MODE == 0) k = (KT)wl;
             else
                 k = load_val<VM>(a.V, a.Vhi, a.V32, h) +
-                    (KT)(a.L * wl - (RATIO ? a.W * (long long)a.t[e] : a.W));
+                    (KT)(gL * wl - (RATIO ? gW * (long long)a.t[e] : gW));
             if (MODE != 2 && k < best) {
                 best = k;
                 pos = e;
@@ -924,6 +927,49 @@ __global__ __launch_bounds__(kWG) void k_pj_final_dev(int n, const unsigned long
     onc[c] = 1;
 }
 
+// The same as a step of the device-driven loop, with k_cyc_zero's work: the
+// cycles' heads (rep[v] == v only at a cycle's smallest vertex) are listed and
+// their sums cleared.  Both tag arrays are left clear for the next phase.
+__global__ __launch_bounds__(kWG) void k_loop_cycles_final(
+    int n, const unsigned long long* __restrict__ P0, const unsigned long long* __restrict__ P1, int K,
+    int* __restrict__ rep, unsigned char* __restrict__ onc, unsigned char* __restrict__ tag0,
+    unsigned char* __restrict__ tag1, long long* __restrict__ wsum, unsigned* __restrict__ lcnt,
+    long long* __restrict__ tsum, int* __restrict__ cyc_list, Ctl* ctl)
+{
+    if (ctl->fmode != kLoopCycles || (ctl->jmode != 0 && ctl->jk != (unsigned)K)) return;
+    const unsigned long long* __restrict__ P = (ctl->jk & 1) ? P1 : P0;
+    const int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x;
+    bool head = false;
+    if (v < n) {
+        const int c = (int)(P[v] >> 32);
+        const int r = (int)(unsigned)P[c];
+        rep[v] = r;
+        onc[c] = 1;
+        tag0[v] = tag1[v] = 0;
+        head = r == v;
+        if (head) {
+            wsum[v] = 0;
+            lcnt[v] = 0;
+            if (tsum) tsum[v] = 0;
+        }
+    }
+    __shared__ unsigned nh, base;
+    if (threadIdx.x == 0) nh = 0;
+    __syncthreads();
+    const unsigned long long mask = __ballot(head);
+    const unsigned lane = threadIdx.x & 63;
+    unsigned at = 0;
+    if (lane == 0 && mask) at = atomicAdd(&nh, (unsigned)__popcll(mask));
+    at = __shfl(at, 0, 64);
+    __syncthreads();
+    if (threadIdx.x == 0) base = nh ? atomicAdd(&ctl->ncyc, nh) : 0u;
+    __syncthreads();
+    if (head) cyc_list[base + at + __popcll(mask & ((1ull << lane) - 1ull))] = (int)v;
+    if (threadIdx.x != 0) return;
+    unsigned long long tot;
+    if (last_arrival(ctl, 0, &tot)) ctl->fmode = kLoopSelect;
+}
+
 // ---------------------------------------------------------------------------
 // select: per-cycle (W, L) keyed by rep, then the minimum in exact order
 // ---------------------------------------------------------------------------
@@ -962,8 +1008,9 @@ __global__ __launch_bounds__(kWG) void k_cyc_sum(int n, const int* __restrict__ 
                                                  long long* __restrict__ wsum,
                                                  unsigned* __restrict__ lcnt,
                                                  const int* __restrict__ tm,
-                                                 long long* __restrict__ tsum)
+                                                 long long* __restrict__ tsum, const Ctl* loop)
 {
+    if (loop && loop->fmode != kLoopSelect) return;   // loop: as a step of the loop
     const int v = blockIdx.x * kWG + threadIdx.x;
     if (v >= n || !onc[v]) return;
     const int r = rep[v];
@@ -1019,8 +1066,10 @@ __global__ __launch_bounds__(kWG) void k_select_part(const int* __restrict__ cyc
                                                      const long long* __restrict__ wsum,
                                                      const unsigned* __restrict__ lcnt,
                                                      const long long* __restrict__ tsum,
-                                                     const Ctl* ctl, Cand* __restrict__ part)
+                                                     const Ctl* ctl, Cand* __restrict__ part,
+                                                     int loop)
 {
+    if (loop && ctl->fmode != kLoopSelect) return;
     const unsigned nc = ctl->ncyc;
     Cand best{0, 1, -1};
     for (unsigned i = blockIdx.x * kWG + threadIdx.x; i < nc; i += gridDim.x * kWG) {
@@ -1033,8 +1082,10 @@ __global__ __launch_bounds__(kWG) void k_select_part(const int* __restrict__ cyc
 }
 
 __global__ __launch_bounds__(kWG) void k_select_final(const Cand* __restrict__ part, int nparts,
-                                                      const unsigned* __restrict__ lcnt, Ctl* ctl)
+                                                      const unsigned* __restrict__ lcnt, Ctl* ctl,
+                                                      int loop)
 {
+    if (loop && ctl->fmode != kLoopSelect) return;
     Cand best{0, 1, -1};
     for (int i = threadIdx.x; i < nparts; i += kWG)
         if (cand_less(part[i], best)) best = part[i];
@@ -1044,6 +1095,7 @@ __global__ __launch_bounds__(kWG) void k_select_final(const Cand* __restrict__ p
         ctl->W = best.W;
         ctl->L = best.L;
         ctl->clen = best.r >= 0 ? lcnt[best.r] : 0u;
+        if (loop) ctl->fmode = kLoopConn;
     }
 }
 
@@ -1116,6 +1168,17 @@ __device__ __forceinline__ unsigned valid_bits(int64_t word, int n)
     return lo + 32 <= n ? 0xffffffffu : (lo >= n ? 0u : (1u << (unsigned)(n - lo)) - 1u);
 }
 
+// Direction of the next round: policy 0 pushes while many vertices are left
+// and the frontier is small against them, 1 always pulls, 2 always pushes.
+__device__ __forceinline__ unsigned round_mode(unsigned left, unsigned front, int policy,
+                                               unsigned push_min)
+{
+    if (left == 0) return 0;
+    if (policy == 1) return 2;
+    if (policy == 2) return front > 0 ? 1 : 2;
+    return left >= push_min && 2ull * front < left ? 1 : 2;
+}
+
 // Rebuild init: C's component (rep == s) keeps pi (layer 0), every other
 // vertex is unattached (layer -1).  Writes the round-1 bitmaps (a1 = layer
 // 0, a0 = empty) and counts both sets into the lanes (got, left).
@@ -1124,8 +1187,13 @@ __global__ __launch_bounds__(kWG) void k_conn_init(int n, const int* __restrict_
                                                    int* __restrict__ layer,
                                                    unsigned char* __restrict__ onC,
                                                    unsigned* __restrict__ a1,
-                                                   unsigned* __restrict__ a0, Ctl* ctl)
+                                                   unsigned* __restrict__ a0, Ctl* ctl, int loop,
+                                                   int policy, unsigned push_min)
 {
+    if (loop) {   // as a step of the loop: the source from ctl, then the rounds' start
+        if (ctl->fmode != kLoopConn) return;
+        s = ctl->s;
+    }
     const int64_t words = ((int64_t)n + 31) / 32;
     const int64_t span = (int64_t)gridDim.x * kWG;
     const int lane = threadIdx.x & 63;
@@ -1154,10 +1222,19 @@ __global__ __launch_bounds__(kWG) void k_conn_init(int n, const int* __restrict_
     }
     ncomp = block_sum_u64(ncomp);
     nleft = block_sum_u64(nleft);
-    if (threadIdx.x == 0) {
+    if (threadIdx.x != 0) return;
+    if (!loop) {
         if (ncomp) atomicAdd(&my_lane(ctl).got, (unsigned)ncomp);
         if (nleft) atomicAdd(&my_lane(ctl).left, (unsigned)nleft);
+        return;
     }
+    unsigned long long tot;
+    if (!last_arrival(ctl, arrival_word(nleft, 0), &tot)) return;
+    const unsigned left = (unsigned)tot, front = (unsigned)n - left;
+    ctl->rleft = left;
+    ctl->rfront = front;
+    ctl->rmode = round_mode(left, front, policy, push_min);
+    ctl->fmode = kLoopRounds;
 }
 
 // LDS of the mark step: the frontier of a workgroup's words is processed
@@ -1632,17 +1709,6 @@ __global__ __launch_bounds__(kWG) void k_conn_claim(int k, int n, const int* __r
 // rmode names them.  The last workgroup of a round's final kernel books the
 // round (round_close).
 
-// Direction of the next round: policy 0 pushes while many vertices are left
-// and the frontier is small against them, 1 always pulls, 2 always pushes.
-__device__ __forceinline__ unsigned round_mode(unsigned left, unsigned front, int policy,
-                                               unsigned push_min)
-{
-    if (left == 0) return 0;
-    if (policy == 1) return 2;
-    if (policy == 2) return front > 0 ? 1 : 2;
-    return left >= push_min && 2ull * front < left ? 1 : 2;
-}
-
 // Called by thread 0 of every workgroup of round k's final kernel with the
 // workgroup's attachment count g.  The last workgroup to arrive books the
 // round's attachments and picks round k + 1's direction (a round that
@@ -1693,6 +1759,62 @@ __global__ __launch_bounds__(kWG) void k_round_mark_pull(
                       left_marks ? marks : nullptr, L.wave);
         if (threadIdx.x == 0) round_close(ctl, k, g, policy, push_min, false);
     }
+}
+
+// A whole pull round with a thread per vertex, for graphs whose rounds never
+// push: every unattached vertex scans its row for the first head attached
+// before the round (rows beyond kLongRow edges by the whole wave).  A wave owns
+// two bitmap words.  The span kernels above own 8192 vertices per workgroup, so
+// a graph of 20,000 vertices filled 3 of them and a round took 57 us on their
+// rows' dependent reads; a thread per vertex takes 5 us.
+__global__ __launch_bounds__(kWG) void k_round_vertex(int k, int n, const int* __restrict__ row_ptr,
+                                                      const int* __restrict__ col,
+                                                      const unsigned* __restrict__ acur,
+                                                      unsigned* __restrict__ anext,
+                                                      int* __restrict__ pi, Ctl* ctl)
+{
+    if (!round_is(ctl, k, 2u)) return;
+    const int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const unsigned word = v < n ? acur[v >> 5] : 0xffffffffu;
+    const bool un = v < n && !((word >> (v & 31)) & 1u);
+    int b = 0, end = 0, found = -1;
+    if (un) {
+        b = row_ptr[v];
+        end = row_ptr[v + 1];
+    }
+    const bool long_row = end - b > kLongRow;
+    if (!long_row)
+        for (int e = b; e < end && found < 0; e += 4) {
+            int h[4];
+            unsigned bit[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) h[u] = col[e + u < end ? e + u : end - 1];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) bit[u] = attached(acur, h[u]);
+#pragma unroll
+            for (int u = 3; u >= 0; --u)
+                if (bit[u] && e + u < end) found = e + u;
+        }
+    for (unsigned long long lm = __ballot(long_row); lm; lm &= lm - 1) {
+        const int l = __ffsll((long long)lm) - 1;
+        const int rb = __shfl(b, l, 64), re = __shfl(end, l, 64);
+        int f = -1;
+        for (int e = rb; e < re && f < 0; e += 64) {
+            const unsigned long long hit = __ballot(e + lane < re && attached(acur, col[e + lane]));
+            if (hit) f = e + __ffsll((long long)hit) - 1;
+        }
+        if (lane == l) found = f;
+    }
+    if (found >= 0) pi[v] = found;
+    const unsigned long long got = __ballot(found >= 0);
+    if ((lane & 31) == 0 && v < n) anext[v >> 5] = word | (unsigned)(got >> (lane & 32));
+    __shared__ unsigned sum;
+    if (threadIdx.x == 0) sum = 0;
+    __syncthreads();
+    if (lane == 0 && got) atomicAdd(&sum, (unsigned)__popcll(got));
+    __syncthreads();
+    if (threadIdx.x == 0) round_close(ctl, k, sum, 1, 0, false);
 }
 
 // Round k's second kernel: the claims of a push round, and the marks of
@@ -2113,10 +2235,16 @@ __global__ void k_loop_setup(Ctl* c, unsigned mode, unsigned opts, unsigned max_
         CtlLane& ln = c->lane[t];
         ln.changed = ln.tight = ln.certain = ln.nondec = 0;
         ln.cbroken = ln.overflow = ln.wide32 = ln.bad = 0;
+        ln.active = ln.active2 = ln.got = ln.left = 0;
         ln.rpack = 0;
     }
     if (t == 0) {
         c->rpack = 0;
+        if (mode == kLoopCycles) {
+            c->ncyc = c->rmode = c->rleft = c->rfront = c->rerr = c->rk = c->rmarks = 0;
+            c->jk = c->jstall = 0;
+            c->jmode = 1;
+        }
         c->jlast = 0xffffffffu;
         c->fwhy = kWhyNone;
         c->fopts = opts;
@@ -2129,12 +2257,14 @@ __global__ void k_loop_setup(Ctl* c, unsigned mode, unsigned opts, unsigned max_
 template <typename WT>
 __global__ __launch_bounds__(kWG) void k_chase_init(int n, const int* __restrict__ col,
                                                     const int* __restrict__ pi,
-                                                    const WT* __restrict__ w, int neg, int s,
-                                                    long long W, long long L,
+                                                    const WT* __restrict__ w, int neg,
                                                     int* __restrict__ succ,
                                                     unsigned long long* __restrict__ E, int jb,
                                                     Ctl* ctl, const int* __restrict__ tm)
 {
+    if (ctl->fmode != kLoopRounds || ctl->rmode != 0) return;
+    const int s = ctl->s;
+    const long long W = ctl->W, L = ctl->L;
     constexpr int U = 4;   // independent vertices in flight per thread
     const int64_t stride = (int64_t)gridDim.x * kWG;
     bool fits = true;
@@ -2164,11 +2294,20 @@ __global__ __launch_bounds__(kWG) void k_chase_init(int n, const int* __restrict
         }
     }
     if (!fits) atomicOr(&ctl->fflags, kChaseOverflow);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    unsigned long long tot;
+    if (!last_arrival(ctl, 0, &tot)) return;
+    ctl->jlast = 0xffffffffu;
+    if (ctl->rerr) loop_stop(ctl, kWhyDisconnected);
+    else ctl->fmode = kLoopChase;
 }
 
-__global__ __launch_bounds__(kWG) void k_hop_init(int n, int s, const int* __restrict__ succ,
-                                                  unsigned long long* __restrict__ E)
+__global__ __launch_bounds__(kWG) void k_hop_init(int n, const int* __restrict__ succ,
+                                                  unsigned long long* __restrict__ E,
+                                                  const Ctl* __restrict__ ctl)
 {
+    const int s = ctl->s;
     for (int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x; v < n;
          v += (int64_t)gridDim.x * kWG)
         E[v] = v == s ? (unsigned long long)(unsigned)s : (1ull << 32) | (unsigned)succ[v];
@@ -2208,11 +2347,12 @@ __device__ void loop_after_chase(Ctl* c, unsigned left)
 }
 
 template <int LD, int ST>
-__global__ __launch_bounds__(kWG) void k_chase(int n, int s, int jb, unsigned long long* E,
+__global__ __launch_bounds__(kWG) void k_chase(int n, int jb, unsigned long long* E,
                                                long long* __restrict__ V,
                                                int* __restrict__ out32, Ctl* ctl)
 {
     if (ctl->fmode != kLoopChase) return;   // uniform: only the last arrival changes it
+    const int s = ctl->s;
     __shared__ unsigned sleft, sflags;
     if (threadIdx.x == 0) sleft = sflags = 0;
     __syncthreads();
@@ -2757,7 +2897,6 @@ __global__ void k_ctl_clear(Ctl* ctl, unsigned what)
         if (what & kClrActive2) ln.active2 = 0;
     }
     if (t == 0) {
-        if (what & kClrGiant) ctl->ngiant = 0;
         if (what & kClrChanged) {
             ctl->xcnt = 0;
             ctl->scnt = 0;
@@ -2950,16 +3089,15 @@ void launch_loop_setup(Ctl* ctl, unsigned mode, unsigned opts, unsigned max_swee
 void launch_loop_close(Ctl* ctl, hipStream_t st) { k_loop_close<<<1, 64, 0, st>>>(ctl); }
 
 void launch_chase_init(int n, const int* col, const int* pi, const void* w, int wtype, int neg,
-                       int s, long long W, long long L, int* succ, unsigned long long* E, int jb,
-                       Ctl* ctl, const int* t, hipStream_t st)
+                       int* succ, unsigned long long* E, int jb, Ctl* ctl, const int* t,
+                       hipStream_t st)
 {
     const unsigned grid = stride_grid((n + 3) / 4);
     if (wtype == kWI64)
-        k_chase_init<long long><<<grid, kWG, 0, st>>>(n, col, pi, (const long long*)w, neg, s, W, L,
-                                                      succ, E, jb, ctl, t);
+        k_chase_init<long long><<<grid, kWG, 0, st>>>(n, col, pi, (const long long*)w, neg, succ, E,
+                                                      jb, ctl, t);
     else
-        k_chase_init<int><<<grid, kWG, 0, st>>>(n, col, pi, (const int*)w, neg, s, W, L, succ, E, jb,
-                                                ctl, t);
+        k_chase_init<int><<<grid, kWG, 0, st>>>(n, col, pi, (const int*)w, neg, succ, E, jb, ctl, t);
 }
 
 // Scopes by size (one phase on an optimal policy, us; agent/agent, workgroup
@@ -2969,19 +3107,19 @@ void launch_chase_init(int n, const int* col, const int* pi, const void* w, int 
 // 30 / 28 / 33.  On large graphs written-through steps cost more than they
 // save: 2^22: 284 / 269 / 275, 2^23: 436 / 423 / 355, 16^6 product: 501 / 397 /
 // 259.
-void launch_chase(int n, int s, int jb, unsigned long long* E, long long* V, int* out32, Ctl* ctl,
+void launch_chase(int n, int jb, unsigned long long* E, long long* V, int* out32, Ctl* ctl,
                   hipStream_t st)
 {
     constexpr int A = __HIP_MEMORY_SCOPE_AGENT, G = __HIP_MEMORY_SCOPE_WORKGROUP;
     const unsigned grid = blocks_for(n);
-    if (n < (1 << 18)) k_chase<A, A><<<grid, kWG, 0, st>>>(n, s, jb, E, V, out32, ctl);
-    else if (n <= (1 << 22)) k_chase<G, A><<<grid, kWG, 0, st>>>(n, s, jb, E, V, out32, ctl);
-    else k_chase<G, G><<<grid, kWG, 0, st>>>(n, s, jb, E, V, out32, ctl);
+    if (n < (1 << 18)) k_chase<A, A><<<grid, kWG, 0, st>>>(n, jb, E, V, out32, ctl);
+    else if (n <= (1 << 22)) k_chase<G, A><<<grid, kWG, 0, st>>>(n, jb, E, V, out32, ctl);
+    else k_chase<G, G><<<grid, kWG, 0, st>>>(n, jb, E, V, out32, ctl);
 }
 
-void launch_hop_init(int n, int s, const int* succ, unsigned long long* E, hipStream_t st)
+void launch_hop_init(int n, const int* succ, unsigned long long* E, const Ctl* ctl, hipStream_t st)
 {
-    k_hop_init<<<stride_grid(n), kWG, 0, st>>>(n, s, succ, E);
+    k_hop_init<<<stride_grid(n), kWG, 0, st>>>(n, succ, E, ctl);
 }
 
 void launch_cycle_walk(int s, long long L, const int* pi, const int* succ, int* out,
@@ -3077,18 +3215,45 @@ void launch_cyc_sum(int n, const int* rep, const unsigned char* onc, const int* 
 {
     if (wtype == kWI64)
         k_cyc_sum<long long><<<blocks_for(n), kWG, 0, st>>>(n, rep, onc, pi, (const long long*)w,
-                                                            neg, wsum, lcnt, t, tsum);
+                                                            neg, wsum, lcnt, t, tsum, nullptr);
     else
         k_cyc_sum<int><<<blocks_for(n), kWG, 0, st>>>(n, rep, onc, pi, (const int*)w, neg, wsum,
-                                                      lcnt, t, tsum);
+                                                      lcnt, t, tsum, nullptr);
 }
 
 void launch_select(const int* cyc_list, const long long* wsum, const unsigned* lcnt, Ctl* ctl,
                    void* scratch, hipStream_t st, const long long* tsum)
 {
     Cand* part = (Cand*)scratch;
-    k_select_part<<<kSelectParts, kWG, 0, st>>>(cyc_list, wsum, lcnt, tsum, ctl, part);
-    k_select_final<<<1, kWG, 0, st>>>(part, kSelectParts, lcnt, ctl);
+    k_select_part<<<kSelectParts, kWG, 0, st>>>(cyc_list, wsum, lcnt, tsum, ctl, part, 0);
+    k_select_final<<<1, kWG, 0, st>>>(part, kSelectParts, lcnt, ctl, 0);
+}
+
+void launch_loop_cycles_final(int n, const unsigned long long* P0, const unsigned long long* P1,
+                              int K, int* rep, unsigned char* onc, unsigned char* tag0,
+                              unsigned char* tag1, long long* wsum, unsigned* lcnt, long long* tsum,
+                              int* cyc_list, Ctl* ctl, hipStream_t st)
+{
+    k_loop_cycles_final<<<blocks_for(n), kWG, 0, st>>>(n, P0, P1, K, rep, onc, tag0, tag1, wsum, lcnt,
+                                                       tsum, cyc_list, ctl);
+}
+
+void launch_loop_select(int n, const int* rep, const unsigned char* onc, const int* pi,
+                        const void* w, int wtype, int neg, const int* t, long long* wsum,
+                        unsigned* lcnt, long long* tsum, const int* cyc_list, void* scratch,
+                        Ctl* ctl, hipStream_t st)
+{
+    if (wtype == kWI64)
+        k_cyc_sum<long long><<<blocks_for(n), kWG, 0, st>>>(n, rep, onc, pi, (const long long*)w,
+                                                            neg, wsum, lcnt, t, tsum, ctl);
+    else
+        k_cyc_sum<int><<<blocks_for(n), kWG, 0, st>>>(n, rep, onc, pi, (const int*)w, neg, wsum,
+                                                      lcnt, t, tsum, ctl);
+    Cand* part = (Cand*)scratch;
+    // at most n cycles
+    const int parts = (int)(blocks_for(n) < (unsigned)kSelectParts ? blocks_for(n) : kSelectParts);
+    k_select_part<<<parts, kWG, 0, st>>>(cyc_list, wsum, lcnt, tsum, ctl, part, 1);
+    k_select_final<<<1, kWG, 0, st>>>(part, parts, lcnt, ctl, 1);
 }
 
 void launch_validate_t(int m, const int* t, Ctl* ctl, hipStream_t st)
@@ -3099,7 +3264,21 @@ void launch_validate_t(int m, const int* t, Ctl* ctl, hipStream_t st)
 void launch_conn_init(int n, const int* rep, const unsigned char* onc, int s, int* layer,
                       unsigned char* onC, unsigned* a1, unsigned* a0, Ctl* ctl, hipStream_t st)
 {
-    k_conn_init<<<stride_grid(n), kWG, 0, st>>>(n, rep, onc, s, layer, onC, a1, a0, ctl);
+    k_conn_init<<<stride_grid(n), kWG, 0, st>>>(n, rep, onc, s, layer, onC, a1, a0, ctl, 0, 0, 0);
+}
+
+void launch_loop_conn_init(int n, const int* rep, const unsigned char* onc, unsigned char* onC,
+                           unsigned* a1, unsigned* a0, Ctl* ctl, int policy, unsigned push_min,
+                           hipStream_t st)
+{
+    k_conn_init<<<stride_grid(n), kWG, 0, st>>>(n, rep, onc, -1, nullptr, onC, a1, a0, ctl, 1, policy,
+                                                push_min);
+}
+
+void launch_round_vertex(int k, int n, const int* row_ptr, const int* col, const unsigned* acur,
+                         unsigned* anext, int* pi, Ctl* ctl, hipStream_t st)
+{
+    k_round_vertex<<<blocks_for(n), kWG, 0, st>>>(k, n, row_ptr, col, acur, anext, pi, ctl);
 }
 
 // Words per thread of the round kernels: 2 when one word per thread would

@@ -260,9 +260,11 @@ struct Ctx {
     // rows of more than kGiantRow edges, swept by several workgroups each
     // (tile sweeps only; empty when there are none)
     ocm::GiantTab giant;
+    unsigned ngiant = 0;
     // values by the packed chase, sweeps and values as one device-driven loop;
     // off for the rest of the solve once a sum does not fit the entries
     bool chase = false;
+    bool tags_clear = false;   // the cycle phase's tag arrays (in ws.layer) are clear
     bool hop_ok = false;   // ws.hop holds the policy's hops (the chase leaves them out)
 
     Ctx() = default;
@@ -362,8 +364,13 @@ ocm_status validate(Ctx& c, int check_csr)
     ocm::launch_validate(c.n, c.m, c.row_ptr, c.col, c.w, c.wtype, check_csr, c.ws.ctl, c.st);
     c.prof.end();
     c.prof.bytes(OCM_K_VALIDATE, 4.0 * (c.n + 1) + (check_csr ? 4.0 * c.m : 0.0) + c.sw * (double)c.m);
+    // the giant rows' list rides on the same read (an unsound CSR only fills it
+    // with nonsense, up to its capacity)
+    if (c.tile_sweep && c.m > ocm::kGiantRow)
+        ocm::launch_giant_list(c.n, c.row_ptr, c.ws.gtri, c.ws.gcap, c.ws.ctl, c.st);
     HIP_TRY(hipGetLastError());
     OCM_TRY(read_ctl(c));
+    c.ngiant = c.h.ngiant;
     if (c.h.err & ocm::kErrBadCsr) return fail(OCM_E_BAD_CSR, "malformed CSR");
     if (c.h.err & ocm::kErrNoOut) return fail(OCM_E_NO_OUT_EDGE, "a vertex has no out-edge");
     const unsigned long long maxw = c.h.maxabsw;
@@ -474,11 +481,7 @@ ocm_status build_giant(Ctx& c)
     Ws& w = c.ws;
     c.giant = ocm::GiantTab{};
     if (!c.tile_sweep || c.m <= ocm::kGiantRow) return OCM_OK;
-    ocm::launch_ctl_clear(w.ctl, ocm::kClrGiant, c.st);
-    ocm::launch_giant_list(c.n, c.row_ptr, w.gtri, w.gcap, w.ctl, c.st);
-    HIP_TRY(hipGetLastError());
-    OCM_TRY(read_ctl(c));
-    const unsigned ng = c.h.ngiant;
+    const unsigned ng = c.ngiant;   // listed with the validation
     if (ng == 0) return OCM_OK;
     if (ng > w.gcap) return fail(OCM_E_HIP, "more giant rows than the edges allow");
     std::vector<int> tri(3 * (size_t)ng);
@@ -559,6 +562,7 @@ ocm_status phase_cycles(Ctx& c, const int* pi, int* rep, unsigned char* onc)
     while ((int64_t(1) << K) < c.n) ++K;
     const double n = c.n;
     // the two tag arrays live in the layer array, which the rebuild rewrites
+    c.tags_clear = false;
     unsigned char* tag[2] = {(unsigned char*)c.ws.layer, (unsigned char*)c.ws.layer + c.n};
     const bool stop_test = K > 2;
     c.prof.begin(OCM_K_CYCLES);
@@ -983,36 +987,84 @@ ocm_status phase_values(Ctx& c, const int* pi, int s, long long W, long long L, 
 // has tens of thousands of workgroups.
 int loop_pairs(const Ctx& c) { return c.prof.out ? 1 : c.n < (1 << 18) ? 4 : 2; }
 
-// Runs the device-driven loop on C's (s, W, L) until it stops: from the value
-// phase (the chase entries are written here from pi) or from a sweep (values
-// current).  c.h holds the outcome (fwhy, fsweeps, ffast).
-ocm_status run_loop(Ctx& c, bool from_values, int s, long long W, long long L, unsigned max_sweeps)
+// Rebuild rounds without pushes below this size: a thread per vertex pulls a
+// whole round in 5 us there, where the span kernels of the pushes fill only a
+// few compute units.
+constexpr int kVertexRoundsN = 1 << 17;
+
+// Runs the device-driven loop until it stops, from `start`: the general phases
+// (kLoopCycles: C, its lambda and the policy around it are found, then the
+// values), the values after them (kLoopRounds) or a sweep (kLoopSweep).  c.h
+// holds the outcome (fwhy, fsweeps, ffast; s, W, L and clen of C).
+ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
 {
     Ws& w = c.ws;
     auto* E = (unsigned long long*)w.Q[0];
+    auto* P0 = (unsigned long long*)w.Q[0];
+    auto* P1 = (unsigned long long*)w.Q[1];
     const int jb = ocm::chase_bits(c.n);
-    const int cls = from_values ? OCM_K_VALUES : OCM_K_FAST;
-    ocm::launch_loop_setup(w.ctl, from_values ? ocm::kLoopChase : ocm::kLoopSweep,
-                           ocm::kLoopChain | (c.v32 ? ocm::kLoopV32 : 0u), max_sweeps, c.st);
-    if (from_values) {
-        c.prof.begin(cls);
-        ocm::launch_chase_init(c.n, c.col, w.pi, c.w, c.wtype, c.neg, s, W, L, w.succ, E, jb, w.ctl,
-                               c.t, c.st);
-        c.prof.end();
-        // pi, col[pi], w[pi], succ, the 8-byte entry
-        c.prof.bytes(cls, (20.0 + c.sw) * c.n);
+    const bool from_values = start != ocm::kLoopSweep;
+    const bool small = c.n < kVertexRoundsN;
+    unsigned char* tag[2] = {(unsigned char*)w.layer, (unsigned char*)w.layer + c.n};
+    int K = 0;
+    while ((int64_t(1) << K) < c.n) ++K;
+    if (start == ocm::kLoopCycles && !c.tags_clear) {
+        ocm::launch_fill_u32((unsigned*)w.layer, ((int64_t)c.n * 2 + 3) / 4, 0u, c.st);
+        c.tags_clear = true;   // each cycle phase leaves them clear
     }
-    c.succ_ok = true;
-    c.hop_ok = false;
-    ocm::SweepArgs a = sweep_args(c, false, w.V, W, L, w.pi, w.onC);
+    ocm::launch_loop_setup(w.ctl, start, ocm::kLoopChain | (c.v32 ? ocm::kLoopV32 : 0u), max_sweeps,
+                           c.st);
+    ocm::SweepArgs a = sweep_args(c, false, w.V, 0, 1, w.pi, w.onC);
     a.succ = w.succ;
     a.E = E;
     a.jb = jb;
-    a.src = s;
     c.sweep_vbytes = a.V32 ? 4.0 : 8.0;
+    int kc = 0, kr = 0;   // cycle and rebuild rounds queued
+    // the steps from `mode` up to the chase
+    auto general = [&](unsigned mode) {
+        if (mode == ocm::kLoopCycles) {
+            kr = 0;   // no rebuild round has run yet
+            if (kc == 0) {
+                const bool have_succ = c.succ_ok;
+                ocm::launch_pj_init(c.n, c.col, w.pi, w.succ, have_succ, P0, w.onc, tag[0], nullptr,
+                                    c.st);
+            }
+            for (int j = 0; j < 12 && kc < K; ++j) {
+                ++kc;
+                ocm::launch_pj_round_dev(c.n, kc, kc & 1 ? P0 : P1, kc & 1 ? P1 : P0,
+                                         tag[(kc - 1) & 1], tag[kc & 1], w.ctl, c.st);
+            }
+            ocm::launch_loop_cycles_final(c.n, P0, P1, K, w.rep, w.onc, tag[0], tag[1], w.wsum, w.lcnt,
+                                          c.t ? w.tsum : nullptr, w.cyc, w.ctl, c.st);
+            ocm::launch_loop_select(c.n, w.rep, w.onc, w.pi, c.w, c.wtype, c.neg, c.t, w.wsum, w.lcnt,
+                                    c.t ? w.tsum : nullptr, w.cyc, w.sel, w.ctl, c.st);
+            ocm::launch_loop_conn_init(c.n, w.rep, w.onc, w.onC, w.abits[1], w.abits[0], w.ctl,
+                                       small ? 1 : 0, kPushMinUnattached, c.st);
+        }
+        if (mode != ocm::kLoopChase && start == ocm::kLoopCycles) {
+            if (!small && !c.rev_built) build_reverse(c);
+            for (int j = 0; j < kRoundsPerRead; ++j) {
+                ++kr;
+                if (small)
+                    ocm::launch_round_vertex(kr, c.n, c.row_ptr, c.col, w.abits[kr & 1],
+                                             w.abits[(kr + 1) & 1], w.pi, w.ctl, c.st);
+                else
+                    ocm::launch_round(kr, c.n, c.row_ptr, c.col, w.rin_ptr, w.rin, w.abits[kr & 1],
+                                      w.abits[(kr + 1) & 1], w.marks[kr & 1], w.marks[(kr + 1) & 1],
+                                      w.pi, nullptr, w.ctl, &w.ctl->lane[0].pedges, 0,
+                                      kPushMinUnattached, true, kr > 1, c.st);
+            }
+        }
+        const int cls = OCM_K_VALUES;
+        c.prof.begin(cls);
+        ocm::launch_chase_init(c.n, c.col, w.pi, c.w, c.wtype, c.neg, w.succ, E, jb, w.ctl, c.t, c.st);
+        c.prof.end();
+        // pi, col[pi], w[pi], succ, the 8-byte entry
+        c.prof.bytes(cls, (20.0 + c.sw) * c.n);
+    };
     auto chase = [&](int k) {
         c.prof.begin(k);
-        ocm::launch_chase(c.n, s, jb, E, w.V, w.V32, w.ctl, c.st);
+        ocm::launch_chase(c.n, jb, E, w.V, w.V32, w.ctl, c.st);
         c.prof.end();
         // the entry read and written, an entry gathered, V and its copy
         c.prof.bytes(k, 36.0 * c.n);
@@ -1025,29 +1077,42 @@ ocm_status run_loop(Ctx& c, bool from_values, int s, long long W, long long L, u
         c.prof.bytes(OCM_K_SWEEP, 8.0 * c.n);   // the chase entry
     };
     const int pairs = loop_pairs(c);
-    bool chase_next = from_values;
+    unsigned mode = start;
     c.h.fsweeps = 0;
     for (;;) {
+        const bool gen = mode != ocm::kLoopSweep && mode != ocm::kLoopChase;
+        if (gen) {
+            general(mode);
+            c.succ_ok = true;
+        }
+        c.hop_ok = false;
         if (c.prof.out) {
             // profiled: one step per read, so that no launch is an idle one
             const unsigned before = c.h.fsweeps;
-            if (chase_next) chase(before ? OCM_K_FAST : cls);
+            if (mode != ocm::kLoopSweep) chase(before ? OCM_K_FAST : OCM_K_VALUES);
             else sweep();
             HIP_TRY(hipGetLastError());
             OCM_TRY(read_ctl(c));
             if (c.h.fsweeps != before) sweep_done(c, false, false, true);
         } else {
             for (int k = 0; k < pairs; ++k) {
-                if (k > 0 || !chase_next) sweep();
+                if (k > 0 || mode == ocm::kLoopSweep) sweep();
                 chase(OCM_K_FAST);
             }
             HIP_TRY(hipGetLastError());
             OCM_TRY(read_ctl(c));
         }
         if (c.h.fmode == ocm::kLoopStop) break;
-        chase_next = c.h.fmode == ocm::kLoopChase;
+        mode = c.h.fmode;
+        if (mode == ocm::kLoopCycles && kc >= K) return fail(OCM_E_HIP, "cycle rounds did not finish");
+        if (kr > c.n + 2 * kRoundsPerRead) return fail(OCM_E_HIP, "rebuild rounds did not finish");
     }
-    const int phases = (int)c.h.fphases + (from_values ? 1 : 0);
+    if (start == ocm::kLoopCycles) {
+        c.jump_rounds += (int)c.h.jk;
+        c.connect_rounds += (int)c.h.rk;
+    }
+    // the chase wrote succ if it ran (it does not when the rebuild failed)
+    const int phases = (int)c.h.fphases + (from_values && c.h.fwhy != ocm::kWhyDisconnected ? 1 : 0);
     c.value_rounds += phases;
     c.jump_rounds += phases;
     c.swept_tie = c.h.fwhy == ocm::kWhyConverged;
@@ -1059,16 +1124,16 @@ ocm_status run_loop(Ctx& c, bool from_values, int s, long long W, long long L, u
 
 // Policy hops to s (the tie test and the listing of a long C need them): the
 // chase with a sum of one per edge.
-ocm_status ensure_hops(Ctx& c, int s)
+ocm_status ensure_hops(Ctx& c)
 {
     if (c.hop_ok) return OCM_OK;
     Ws& w = c.ws;
     auto* E = (unsigned long long*)w.Q[0];
     ocm::launch_loop_setup(w.ctl, ocm::kLoopChase, 0, 0, c.st);
     c.prof.begin(OCM_K_RESULT);
-    ocm::launch_hop_init(c.n, s, w.succ, E, c.st);
+    ocm::launch_hop_init(c.n, w.succ, E, w.ctl, c.st);
     for (;;) {
-        ocm::launch_chase(c.n, s, 32, E, nullptr, w.hop, w.ctl, c.st);
+        ocm::launch_chase(c.n, 32, E, nullptr, w.hop, w.ctl, c.st);
         c.prof.end();
         HIP_TRY(hipGetLastError());
         OCM_TRY(read_ctl(c));
@@ -1121,7 +1186,7 @@ bool has_cycle(int N, const std::vector<int>& head, const std::vector<int>& next
 // graph described at k_tie_mark.
 ocm_status tie_from_list(Ctx& c, unsigned kx, ocm_result* out);
 
-ocm_status tie_check(Ctx& c, int s, long long W, long long L, ocm_result* out)
+ocm_status tie_check(Ctx& c, long long W, long long L, ocm_result* out)
 {
     Ws& w = c.ws;
     // the solve's last sweep changed nothing; if it counted tight edges, its
@@ -1138,7 +1203,7 @@ ocm_status tie_check(Ctx& c, int s, long long W, long long L, ocm_result* out)
         return OCM_OK;
     }
     // second scan, now with the hop test (a random read per tight edge)
-    OCM_TRY(ensure_hops(c, s));
+    OCM_TRY(ensure_hops(c));
     OCM_TRY(phase_sweep(c, false, true, w.V, W, L, w.pi, w.onC, false, true));
     // With hop = policy hops to s, every policy edge lowers hop by one except
     // s's own; a cycle of tight edges other than C, with no tight edge
@@ -1600,34 +1665,54 @@ ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t 
             }
         }
         ++c.general_iters;
-        rc = phase_cycles(c, w.pi, w.rep, w.onc);
-        if (rc != OCM_OK) break;
-        rc = phase_select(c, w.pi, w.rep, w.onc);
-        if (rc != OCM_OK) break;
-        s = c.h.s;
-        W = c.h.W;
-        L = c.h.L;
-        clen = c.h.clen;
-        // the solve itself needs no layers, only the rewired policy
-        rc = phase_connect(c, w.rep, w.onc, s, w.pi, nullptr, w.onC, nullptr);
-        if (rc != OCM_OK) break;
+        // the general phases and the loop after them without a host read in
+        // between, unless every kernel is timed or the rounds are forced
+        const bool queued = c.chase && !c.prof.out && c.connect_mode == 0;
+        if (!queued) {
+            rc = phase_cycles(c, w.pi, w.rep, w.onc);
+            if (rc != OCM_OK) break;
+            rc = phase_select(c, w.pi, w.rep, w.onc);
+            if (rc != OCM_OK) break;
+            s = c.h.s;
+            W = c.h.W;
+            L = c.h.L;
+            clen = c.h.clen;
+            // the solve itself needs no layers, only the rewired policy
+            rc = phase_connect(c, w.rep, w.onc, s, w.pi, nullptr, w.onC, nullptr);
+            if (rc != OCM_OK) break;
+        }
         have_c = true;
         if (c.chase) {
             // the values, then sweeps and values until C breaks or the end
-            bool from_values = true, general = false;
+            unsigned start = queued ? ocm::kLoopCycles : ocm::kLoopRounds;
+            bool general = false, swept = false;
             for (;;) {
-                rc = run_loop(c, from_values, s, W, L, (unsigned)(iter_cap - iter));
+                rc = run_loop(c, start, (unsigned)(iter_cap - iter));
                 if (rc != OCM_OK) break;
+                if (start == ocm::kLoopCycles) {
+                    if (c.h.ncyc == 0 || c.h.s < 0) {
+                        rc = fail(OCM_E_HIP, "no policy cycle found");
+                        break;
+                    }
+                    s = c.h.s;
+                    W = c.h.W;
+                    L = c.h.L;
+                    clen = c.h.clen;
+                }
                 iter += (int)c.h.fsweeps;
                 fast += (int)c.h.ffast;
+                swept = swept || c.h.fsweeps > 0;
                 if (c.h.fwhy != ocm::kWhyWide) break;
-                from_values = false;   // go on with int64 gathers
+                start = ocm::kLoopSweep;   // go on with int64 gathers
             }
             if (rc != OCM_OK) break;
-            const bool swept = !from_values || c.h.fsweeps > 0;
             if (c.h.fwhy == ocm::kWhyConverged) break;
             if (c.h.fwhy == ocm::kWhyIters) {
                 rc = fail(OCM_E_NOT_CONVERGED, "max_iters reached");
+                break;
+            }
+            if (c.h.fwhy == ocm::kWhyDisconnected) {
+                rc = fail(OCM_E_NOT_STRONGLY_CONNECTED, "some vertex cannot reach the chosen cycle");
                 break;
             }
             if (c.h.fwhy == ocm::kWhyOverflow) {
@@ -1681,7 +1766,7 @@ ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t 
     // chase over all vertices, 10 us and more with n, when the values left none)
     const bool walk = !c.hop_ok && clen <= 16 + c.n / 16384;
     if (!walk) {
-        rc = ensure_hops(c, s);
+        rc = ensure_hops(c);
         if (rc != OCM_OK) {
             c.prof.finish();
             return rc;
@@ -1694,7 +1779,7 @@ ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t 
     c.prof.bytes(OCM_K_RESULT, walk ? 12.0 * clen : (double)c.n + 28.0 * clen);
     HIP_TRY(hipGetLastError());
     if (o.tie_check) {
-        rc = tie_check(c, s, W, L, out);
+        rc = tie_check(c, W, L, out);
         if (rc != OCM_OK) {
             c.prof.finish();
             return rc;

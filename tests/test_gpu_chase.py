@@ -37,8 +37,10 @@ def both(g, mode="min", t=None):
     return a
 
 
-@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 4095, 65537, (1 << 18) - 1, 1 << 18, 300007])
-def test_sizes(n):
+@pytest.mark.parametrize("n", [1, 2, 5, 255, 256, 257, 4095, 4097, 65537, (1 << 17) - 1, 1 << 17,
+                               (1 << 18) - 1, 1 << 18, 300007])
+def test_sizes(n, monkeypatch):
+    monkeypatch.setenv("OCM_SMALL", "0")
     g = synth.random_digraph(n, 1, 4, -1000, 1000, np.int64, seed=[71, n])
     r = both(g, "min" if n % 2 else "max")
     if n <= 4095:
@@ -48,14 +50,16 @@ def test_sizes(n):
 
 
 @pytest.mark.parametrize("n", [257, 20011])
-def test_times(n):
+def test_times(n, monkeypatch):
+    monkeypatch.setenv("OCM_SMALL", "0")
     g = synth.random_digraph(n, 1, 5, -500, 500, np.int32, seed=[72, n])
     t = np.random.default_rng(n).integers(1, 20, g.m).astype(np.int32)
     both(g, "max" if n == 257 else "min", t)
 
 
 @pytest.mark.parametrize("seed", range(4))
-def test_small_weights_stall_and_tie(seed):
+def test_small_weights_stall_and_tie(seed, monkeypatch):
+    monkeypatch.setenv("OCM_SMALL", "0")
     """Few distinct weights: policy cycles away from C (stalls), ties."""
     g = synth.random_digraph(5000, 1, 4, 0, 2, np.int32, seed=[73, seed])
     both(g)
@@ -76,8 +80,9 @@ def test_long_paths_take_several_passes():
 
 
 @pytest.mark.parametrize("hlo", [2**22, 2**35, 2**47])
-def test_sums_beyond_the_entry(hlo):
+def test_sums_beyond_the_entry(hlo, monkeypatch):
     """Sums of 2^22, of more than the entry's 53 bits, and beyond int64."""
+    monkeypatch.setenv("OCM_SMALL", "0")
     g = synth.deep_tail_graph(700, 800, 2, 10, hlo, 2 * hlo, seed=3)
     dev = [torch.from_numpy(x).cuda() for x in (g.row_ptr, g.col, g.w)]
     r = ocm.min_cycle_mean(*dev)
@@ -87,6 +92,24 @@ def test_sums_beyond_the_entry(hlo):
     assert r.int128 == (hlo == 2**47)
     if hlo < 2**47:
         both(g)
+
+
+@pytest.mark.parametrize("hubs,deg", [(1, 100), (3, 33), (2, 9000)])
+def test_rebuild_rounds_over_long_rows(hubs, deg):
+    """Rows around the whole-wave limit and beyond the giant-row limit."""
+    both(synth.hub_graph(9000, hubs, deg, 1, 3, -20, 20, np.int64, seed=[76, deg]))
+
+
+def test_disconnected(monkeypatch):
+    monkeypatch.setenv("OCM_SMALL", "0")
+    for n in (6000, 1 << 17):
+        v = np.arange(n)
+        col = np.where(v % (n // 2) == n // 2 - 1, v - (n // 2 - 1), v + 1).astype(np.int32)
+        dev = [torch.from_numpy(x).cuda() for x in (np.arange(n + 1, dtype=np.int32), col, (v < n // 2).astype(np.int32))]
+        for sched in (0, 8):
+            with pytest.raises(ocm.OCMError) as e:
+                ocm.min_cycle_mean(*dev, schedule=sched)
+            assert e.value.status == ocm.OCM_E_NOT_STRONGLY_CONNECTED
 
 
 def test_values_leave_int32_in_mid_solve():
@@ -154,7 +177,8 @@ def test_batched_long_paths(monkeypatch):
 
 
 @pytest.mark.parametrize("cap", [1, 2, 3, 5])
-def test_iteration_cap(cap):
+def test_iteration_cap(cap, monkeypatch):
+    monkeypatch.setenv("OCM_SMALL", "0")
     g = synth.random_digraph(3000, 1, 4, 1, 1000, np.int32, seed=[75, 0])
     dev = [torch.from_numpy(x).cuda() for x in (g.row_ptr, g.col, g.w)]
     need = ocm.min_cycle_mean(*dev).iterations
