@@ -1497,6 +1497,43 @@ __global__ __launch_bounds__(kWG) void k_rebase(int n, int m, const int* __restr
     }
 }
 
+// A graph solved on its own: its rebased policy and cycle go to the batch's
+// arrays (V is there already), so the results and tie tests after the loop
+// treat it like the loop's.
+__global__ __launch_bounds__(kWG) void k_solo_out(int g, int n, int v0, int e0,
+                                                  const int* __restrict__ col,
+                                                  const int* __restrict__ pol, long long W,
+                                                  long long L, int s, int iter, int status,
+                                                  GArrays ga, int* __restrict__ pi,
+                                                  int* __restrict__ succ,
+                                                  unsigned char* __restrict__ onC)
+{
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ga.W[g] = W;
+        ga.L[g] = L;
+        ga.s[g] = v0 + s;
+        ga.iter[g] = iter;
+        ga.status[g] = status;
+        ga.mode[g] = kDone;
+        ga.have_c[g] = status == OCM_OK;
+    }
+    if (status != OCM_OK) return;
+    for (int v = blockIdx.x * kWG + threadIdx.x; v < n; v += gridDim.x * kWG) {
+        const int e = e0 + pol[v];
+        pi[v0 + v] = e;
+        succ[v0 + v] = col[e];
+        onC[v0 + v] = 0;
+    }
+}
+
+__global__ __launch_bounds__(kWG) void k_solo_cycle(int len, int e0, const int* __restrict__ col,
+                                                    const int* __restrict__ cyc,
+                                                    unsigned char* __restrict__ onC)
+{
+    for (int i = blockIdx.x * kWG + threadIdx.x; i < len; i += gridDim.x * kWG)
+        onC[col[e0 + cyc[i]]] = 1;
+}
+
 __global__ __launch_bounds__(kWG) void k_tie_init(int G, GArrays ga)
 {
     for (int g = blockIdx.x * kWG + threadIdx.x; g < G; g += gridDim.x * kWG) {
@@ -2472,6 +2509,52 @@ ocm_status exact_tie(BCtx& c, int64_t g, const int64_t* vptr, const int64_t* ept
     return OCM_OK;
 }
 
+// The loop's graphs one after the other by the single-graph solver, when there
+// are at most this many: an iteration of the loop is about 60 kernels whatever
+// it holds, a fast iteration of the solver two.  One component of 120,000
+// vertices (general_200k): 6.4 ms in the loop, 1.5 ms alone.
+constexpr int64_t kSoloGraphs = 4;
+
+ocm_status solve_solo(BCtx& c, int64_t g, const int64_t* vptr, const int64_t* eptr,
+                      const ocm_options& bo)
+{
+    const int64_t v0 = vptr[g], e0 = eptr[g];
+    const int n = (int)(vptr[g + 1] - v0), m = (int)(eptr[g + 1] - e0);
+    char* b = (char*)c.ws.sub;
+    int* rp = (int*)b;
+    int* cl = (int*)(b + bal(4 * (size_t)(n + 1)));
+    int* pol = (int*)((char*)cl + bal(4 * (size_t)m));
+    int32_t* cyc = (int32_t*)((char*)pol + bal(4 * (size_t)n));
+    char* ws = (char*)cyc + bal(4 * (size_t)n);
+    const size_t ws_bytes = c.ws.sub_bytes - (size_t)(ws - b);
+    // pi is not set yet: the rebased policy is ignored
+    ocm::b::k_rebase<<<ocm::stride_grid(m + 1), ocm::kWG, 0, c.st>>>(
+        n, m, c.row_ptr + v0, c.col + e0, c.ws.pi + v0, (int)v0, (int)e0, rp, cl, pol);
+    BHIP(hipGetLastError());
+    ocm_graph sg{n, m, rp, cl, (const char*)c.w + (size_t)c.sw * (size_t)e0, c.wtype};
+    ocm_options o;
+    ocm_default_options(&o);
+    o.validate = 0;
+    o.tie_check = 0;
+    o.max_iters = bo.max_iters;
+    o.fast_path = bo.fast_path;
+    o.policy_out = pol;
+    o.potential_out = (int64_t*)c.ws.V + v0;
+    ocm_result r;
+    const ocm_status rc = ocm::solve_int64(&sg, &o, ws, ws_bytes, cyc, n, &r, c.st, c.neg);
+    if (rc != OCM_OK && rc != OCM_E_OVERFLOW && rc != OCM_E_NOT_CONVERGED &&
+        rc != OCM_E_NOT_STRONGLY_CONNECTED)
+        return rc;
+    ocm::b::k_solo_out<<<ocm::stride_grid(n), ocm::kWG, 0, c.st>>>(
+        (int)g, n, (int)v0, (int)e0, c.col, pol, c.neg ? -r.W : r.W, r.L, r.source, r.iterations, rc,
+        c.ws.ga, c.ws.pi, c.ws.succ, c.ws.onC);
+    if (rc == OCM_OK)
+        ocm::b::k_solo_cycle<<<ocm::stride_grid(r.cycle_len), ocm::kWG, 0, c.st>>>(
+            (int)r.cycle_len, (int)e0, c.col, cyc, c.ws.onC);
+    BHIP(hipGetLastError());
+    return OCM_OK;
+}
+
 ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, const ocm_graph* u,
                          const ocm_options* o_in, void* wsp, size_t ws_bytes, int64_t* p,
                          int64_t* q, int64_t* cycle_ptr, int32_t* cycle_edges, int64_t cycle_cap,
@@ -2550,6 +2633,7 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
     // solved one per workgroup in LDS (OCM_BATCH_SMALL=0 sends them through
     // the loop too; same results), the others by the loop
     std::vector<int> small[ocm::kSmallClasses];
+    std::vector<int64_t> solo;   // the loop's graphs, if few
     {
         const char* se = getenv("OCM_BATCH_SMALL");
         const bool use_small = !(se && se[0] == '0');
@@ -2560,14 +2644,17 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
             } else {
                 ++c.loop_G;
                 c.loop_n += ng;
+                if ((int64_t)solo.size() <= kSoloGraphs) solo.push_back(g);
             }
         }
+        const char* env = getenv("OCM_BATCH_SOLO");   // 0: keep them in the loop
+        if (!c.tile_sweep || c.loop_G > kSoloGraphs || (env && env[0] == '0')) solo.clear();
     }
 
     // schedule of the loop: given (lanes, tile), or autotuned and cached per
     // size class
     int tuned = 0;
-    if ((o.schedule <= 0 || o.tile <= 0) && c.loop_G > 0) {
+    if ((o.schedule <= 0 || o.tile <= 0) && c.loop_G > 0 && solo.empty()) {
         Schedule t;
         BTRY(autotune(c, &t, &tuned));
         if (o.schedule <= 0) c.sch.lanes = t.lanes;
@@ -2601,9 +2688,10 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
         BHIP(hipGetLastError());
     }
 
+    for (int64_t g : solo) BTRY(solve_solo(c, g, vptr, eptr, o));
     // a batch of small graphs alone has nothing left for the loop, unless one
     // fell back
-    bool loop = c.loop_G > 0;
+    bool loop = c.loop_G > 0 && solo.empty();
     if (!loop) {
         unsigned nch = 0;
         BTRY(build_chunks(c, ocm::b::kActive, &nch));
@@ -2658,7 +2746,7 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
 
     // hops to the source for the loop's graphs (the small ones' are written),
     // then the per-graph results
-    if (loop) {
+    if (loop || !solo.empty()) {
         unsigned nch = 0;
         BTRY(build_chunks(c, -2, &nch));
         if (nch > 0) {

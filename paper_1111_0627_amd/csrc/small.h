@@ -61,4 +61,9 @@ void launch_small_batch(int cls, const int* list, int nlist, const SmallBatch& b
                         const int* col, const void* w, int wtype, int neg, const SmallOpts& o,
                         hipStream_t st);
 
+// ocm_min / ocm_max (neg) without the int128 fallback: a value that leaves int64
+// gives OCM_E_OVERFLOW, as in the batch.
+ocm_status solve_int64(const ocm_graph* g, const ocm_options* o, void* ws, size_t ws_bytes,
+                       int32_t* cycle_edges, int64_t cap, ocm_result* out, void* stream, int neg);
+
 }  // namespace ocm

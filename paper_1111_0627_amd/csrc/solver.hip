@@ -1555,7 +1555,7 @@ ocm_status solve_small(Ctx& c, const ocm_options& o, int32_t* cycle_edges, int64
 // t (nullable): edge times, the optimal cycle ratio instead of the mean.
 ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t ws_bytes,
                  int32_t* cycle_edges, int64_t cap, ocm_result* out, void* stream, int neg,
-                 bool noalloc = false, const int32_t* t = nullptr)
+                 bool noalloc = false, const int32_t* t = nullptr, bool allow_wide = true)
 {
     if (!out) return fail(OCM_E_INVALID_ARG, "result pointer is null");
     memset(out, 0, sizeof *out);
@@ -1574,7 +1574,7 @@ ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t 
     c.tile_sweep = o.schedule <= 0;
     c.count_tight = o.tie_check != 0;
     c.connect_mode = o.connect_mode;
-    c.allow_wide = true;
+    c.allow_wide = allow_wide;
     c.wide = o.int128_values != 0;
     if (c.connect_mode < 0 || c.connect_mode > 2) return fail(OCM_E_INVALID_ARG, "bad connect_mode");
 
@@ -1845,6 +1845,13 @@ ocm_status scratch_slot(ScratchSlot** out)
 }
 
 }  // namespace
+
+ocm_status ocm::solve_int64(const ocm_graph* g, const ocm_options* o, void* ws, size_t ws_bytes,
+                            int32_t* cycle_edges, int64_t cap, ocm_result* out, void* stream,
+                            int neg)
+{
+    return solve(g, o, ws, ws_bytes, cycle_edges, cap, out, stream, neg, false, nullptr, false);
+}
 
 extern "C" {
 

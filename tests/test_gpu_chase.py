@@ -143,12 +143,38 @@ def check_batch(gs, mode="min"):
 @pytest.mark.parametrize("sizes", [[1, 2, 3], [255, 256, 257], [511, 512, 513, 1025], [20011, 1, 4097]])
 def test_batched_loop_sizes(sizes, monkeypatch):
     monkeypatch.setenv("OCM_BATCH_SMALL", "0")
+    monkeypatch.setenv("OCM_BATCH_SOLO", "0")
     check_batch([synth.random_digraph(n, 1, 4, -100, 100, np.int64, seed=[81, n]) for n in sizes],
                 "max" if len(sizes) == 3 else "min")
 
 
+@pytest.mark.parametrize("sizes", [[1], [5000], [2, 30000, 257, 6000], [100, 4000, 200, 7000, 300]])
+def test_few_large_graphs_solved_alone(sizes, monkeypatch):
+    """At most four graphs beyond the small class leave the loop; failing ones
+    keep the batch's statuses."""
+    gs = [synth.random_digraph(n, 1, 4, -100, 100, np.int64, seed=[84, n]) for n in sizes]
+    if len(sizes) == 5:
+        gs.append(synth.deep_tail_graph(700, 1500, 2, 10, 2**47, 2**48, seed=3))
+        n = 6000                            # two rings
+        v = np.arange(n)
+        col = np.where(v % 3000 == 2999, v - 2999, v + 1).astype(np.int32)
+        gs.append(synth.Graph(np.arange(n + 1, dtype=np.int32), col, (v < 3000).astype(np.int64), "rings"))
+    got = []
+    for solo in ("1", "0"):
+        monkeypatch.setenv("OCM_BATCH_SOLO", solo)
+        if len(sizes) == 1:
+            monkeypatch.setenv("OCM_BATCH_SMALL", "0")
+        r = check_batch(gs, "max" if len(sizes) == 4 else "min")
+        got.append((r.p, r.q, r.flags, r.status, r.cycle_ptr, r.cycle_edges.cpu().tolist(),
+                    r.iterations))
+    assert got[0] == got[1]
+    if len(sizes) == 5:
+        assert got[0][3] == [0] * 5 + [ocm.OCM_E_OVERFLOW, ocm.OCM_E_NOT_STRONGLY_CONNECTED]
+
+
 def test_batched_stalls_and_ties(monkeypatch):
     monkeypatch.setenv("OCM_BATCH_SMALL", "0")
+    monkeypatch.setenv("OCM_BATCH_SOLO", "0")
     check_batch([synth.random_digraph(3000 + k, 1, 4, 0, 2, np.int64, seed=[82, k]) for k in range(8)])
 
 
@@ -157,6 +183,7 @@ def test_batched_sums_beyond_the_entry(hlo, monkeypatch):
     """A graph whose sums do not fit the packed entries goes on with the
     doubling rounds; one beyond int64 fails alone."""
     monkeypatch.setenv("OCM_BATCH_SMALL", "0")
+    monkeypatch.setenv("OCM_BATCH_SOLO", "0")
     gs = [synth.random_digraph(n, 1, 5, 1, 1000, np.int64, seed=[83, n]) for n in (300, 5000)]
     gs.insert(1, synth.deep_tail_graph(700, 800, 2, 10, hlo, 2 * hlo, seed=3))
     r = check_batch(gs)
@@ -166,6 +193,7 @@ def test_batched_sums_beyond_the_entry(hlo, monkeypatch):
 def test_batched_long_paths(monkeypatch):
     """Rings of n vertices with a shortcut: paths of n - 1 edges, cycles of n."""
     monkeypatch.setenv("OCM_BATCH_SMALL", "0")
+    monkeypatch.setenv("OCM_BATCH_SOLO", "0")
     gs = []
     for n in (3000, 70000):
         col = np.insert((np.arange(n) + 1) % n, 1, 1).astype(np.int32)
