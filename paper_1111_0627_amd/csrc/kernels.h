@@ -243,6 +243,7 @@ struct SweepArgs {
     int* ys;                       //           and head
     unsigned* xcnt;
     unsigned xcap;
+    bool xnondec = false;          //           list only those whose head is not nearer (hop given)
     GiantTab giant;                // rows swept by several workgroups (tile sweeps only)
     // device-driven loop (counting tile sweeps only; E null: not part of it):
     // the sweep also writes every vertex's chase entry, and closes the loop's
@@ -443,6 +444,9 @@ void launch_cycle_list(int n, int s, long long L, const unsigned char* onC, cons
                        const int* hop, int* out, hipStream_t st);
 void launch_tie_short_walk(const SweepArgs& a, const void* w, int wtype, int G, const int* succ,
                            unsigned grid, hipStream_t st);
+// The short walk over k listed edges (lanes' certain counts the ones that close).
+void launch_tie_list_walk(unsigned k, const int* xs, const int* ys, const int* succ, Ctl* ctl,
+                          hipStream_t st);
 void launch_ctl_clear(Ctl* ctl, unsigned what, hipStream_t st);
 void launch_ctl_set(Ctl* ctl, int s, long long W, long long L, hipStream_t st);
 void launch_zero2(unsigned* a, unsigned* b, hipStream_t st);

@@ -440,7 +440,7 @@ ocm::SweepArgs sweep_args(Ctx& c, bool first, const long long* V, long long W, l
 
 ocm_status phase_sweep(Ctx& c, bool first, bool tie, const long long* V, long long W, long long L,
                        int* pi, const unsigned char* onC, bool collect = false,
-                       bool with_hop = false, bool read = true)
+                       bool with_hop = false, bool read = true, bool nondec = false)
 {
     ocm::launch_ctl_clear(c.ws.ctl, ocm::kClrChanged, c.st);
     ocm::SweepArgs a = sweep_args(c, first, V, W, L, pi, onC);
@@ -450,6 +450,7 @@ ocm_status phase_sweep(Ctx& c, bool first, bool tie, const long long* V, long lo
         a.ys = c.ws.ys;
         a.xcnt = &c.ws.ctl->xcnt;
         a.xcap = c.ws.xcap;
+        a.xnondec = nondec;
     }
     const int cls = tie ? OCM_K_TIESCAN : OCM_K_SWEEP;
     const bool fused = !tie && !first && c.tile_sweep && c.count_tight;
@@ -1005,6 +1006,10 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
     const int jb = ocm::chase_bits(c.n);
     const bool from_values = start != ocm::kLoopSweep;
     const bool small = c.n < kVertexRoundsN;
+    // on large graphs idle kernels cost more than a read (a chase of 65,536
+    // workgroups that returns at once 15 us): the values and the loop are
+    // queued once the rounds are over
+    const bool apart = c.n >= (1 << 18);
     unsigned char* tag[2] = {(unsigned char*)w.layer, (unsigned char*)w.layer + c.n};
     int K = 0;
     while ((int64_t(1) << K) < c.n) ++K;
@@ -1020,8 +1025,8 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
     a.jb = jb;
     c.sweep_vbytes = a.V32 ? 4.0 : 8.0;
     int kc = 0, kr = 0;   // cycle and rebuild rounds queued
-    // the steps from `mode` up to the chase
-    auto general = [&](unsigned mode) {
+    // the steps from `mode` up to the chase (true), or part of them
+    auto general = [&](unsigned mode) -> bool {
         if (mode == ocm::kLoopCycles) {
             kr = 0;   // no rebuild round has run yet
             if (kc == 0) {
@@ -1041,7 +1046,7 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
             ocm::launch_loop_conn_init(c.n, w.rep, w.onc, w.onC, w.abits[1], w.abits[0], w.ctl,
                                        small ? 1 : 0, kPushMinUnattached, c.st);
         }
-        if (mode != ocm::kLoopChase && start == ocm::kLoopCycles) {
+        if (start == ocm::kLoopCycles && (mode == ocm::kLoopCycles || c.h.rmode != 0)) {
             if (!small && !c.rev_built) build_reverse(c);
             for (int j = 0; j < kRoundsPerRead; ++j) {
                 ++kr;
@@ -1055,12 +1060,15 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
                                       kPushMinUnattached, true, kr > 1, c.st);
             }
         }
+        if (apart && mode == ocm::kLoopCycles) return false;
+        if (apart && start == ocm::kLoopCycles && c.h.rmode != 0) return false;
         const int cls = OCM_K_VALUES;
         c.prof.begin(cls);
         ocm::launch_chase_init(c.n, c.col, w.pi, c.w, c.wtype, c.neg, w.succ, E, jb, w.ctl, c.t, c.st);
         c.prof.end();
         // pi, col[pi], w[pi], succ, the 8-byte entry
         c.prof.bytes(cls, (20.0 + c.sw) * c.n);
+        return true;
     };
     auto chase = [&](int k) {
         c.prof.begin(k);
@@ -1082,8 +1090,18 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
     for (;;) {
         const bool gen = mode != ocm::kLoopSweep && mode != ocm::kLoopChase;
         if (gen) {
-            general(mode);
+            const bool whole = general(mode);
             c.succ_ok = true;
+            if (!whole) {
+                HIP_TRY(hipGetLastError());
+                OCM_TRY(read_ctl(c));
+                mode = c.h.fmode;
+                if (mode == ocm::kLoopCycles && kc >= K)
+                    return fail(OCM_E_HIP, "cycle rounds did not finish");
+                if (kr > c.n + 2 * kRoundsPerRead)
+                    return fail(OCM_E_HIP, "rebuild rounds did not finish");
+                continue;
+            }
         }
         c.hop_ok = false;
         if (c.prof.out) {
@@ -1204,24 +1222,28 @@ ocm_status tie_check(Ctx& c, long long W, long long L, ocm_result* out)
     }
     // second scan, now with the hop test (a random read per tight edge)
     OCM_TRY(ensure_hops(c));
-    OCM_TRY(phase_sweep(c, false, true, w.V, W, L, w.pi, w.onC, false, true));
+    OCM_TRY(phase_sweep(c, false, true, w.V, W, L, w.pi, w.onC, true, true, true, true));
     // With hop = policy hops to s, every policy edge lowers hop by one except
     // s's own; a cycle of tight edges other than C, with no tight edge
     // leaving C (certain == 0), needs a tight non-policy edge whose head is
     // not nearer to s than its tail.
     if (c.h.nondec == 0) return OCM_OK;
-    {
+    const bool listed = c.h.nondec <= w.xcap;
+    if (listed) {
+        c.prof.begin(OCM_K_TIESCAN);
+        ocm::launch_tie_list_walk((unsigned)c.h.nondec, w.xs, w.ys, w.succ, w.ctl, c.st);
+    } else {
         ocm::SweepArgs a = sweep_args(c, false, w.V, W, L, w.pi, w.onC);
         a.hop = w.hop;
         c.prof.begin(OCM_K_TIESCAN);
         ocm::launch_tie_short_walk(a, c.w, c.wtype, c.G, w.succ, c.sweep_grid, c.st);
-        c.prof.end();
-        HIP_TRY(hipGetLastError());
-        OCM_TRY(read_ctl(c));
-        if (c.h.certain > 0) {
-            out->flags |= OCM_F_TIE;
-            return OCM_OK;
-        }
+    }
+    c.prof.end();
+    HIP_TRY(hipGetLastError());
+    OCM_TRY(read_ctl(c));
+    if (c.h.certain > 0) {
+        out->flags |= OCM_F_TIE;
+        return OCM_OK;
     }
     if (k > w.xcap) {
         out->flags |= OCM_F_TIE_UNCHECKED;
