@@ -342,15 +342,14 @@ __device__ void loop_after_sweep(Ctl* c, bool changed, bool broken)
 // The entry of vertex v with policy edge p and head h.
 template <typename WT, bool RATIO>
 __device__ __forceinline__ bool chase_entry(const SweepArgs& a, const WT* __restrict__ w, int64_t v,
-                                            int p, int h, unsigned long long* e)
+                                            int p, int h, int s, long long W, long long L,
+                                            unsigned long long* e)
 {
-    const int s = a.ctl->s;
+    const long long d = L * wval(w, p, a.neg) - (RATIO ? W * (long long)a.t[p] : W);
     if (v == s) {
         *e = (unsigned)s;
         return true;
     }
-    const long long W = a.ctl->W;
-    const long long d = a.ctl->L * wval(w, p, a.neg) - (RATIO ? W * (long long)a.t[p] : W);
     return chase_pack(d, (unsigned)h, a.jb, e);
 }
 
@@ -374,25 +373,30 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(RATIO || VM
 void k_tiescan_tile(SweepArgs a, const WT* __restrict__ w)
 {
     using KT = typename ValT<VM>::type;
-    if (SWEEP && a.E && a.ctl->fmode != kLoopSweep) return;   // uniform: see loop_after_sweep
     __shared__ int beg[kWG + 1];
     __shared__ KT key[kTieTileEdges];
     __shared__ int head[kTieTileEdges];
-    const int64_t L = SWEEP && a.E ? a.ctl->L : a.L, W = SWEEP && a.E ? a.ctl->W : a.W;
+    // the loop's step and lambda, on the way together with the rows' first loads
+    const bool loop = SWEEP && a.E;
+    const unsigned mode = loop ? a.ctl->fmode : kLoopSweep;
+    const int64_t L = loop ? a.ctl->L : a.L, W = loop ? a.ctl->W : a.W;
     const int64_t v0 = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kWG;
     const int nv = a.n - v0 < kWG ? (int)(a.n - v0) : kWG;
     const int t = threadIdx.x;
     KT own = 0;
-    int cur = -1, hv = 0;
+    int cur = -1, hv = 0, rb = 0, rl = 0;
     bool onc = false;
     if (t < nv) {
-        beg[t] = a.row_ptr[v0 + t];
+        rb = a.row_ptr[v0 + t];
         own = load_val<VM>(a.V, a.Vhi, a.V32, v0 + t);
         cur = a.pi[v0 + t];
         if (a.hop) hv = a.hop[v0 + t];
         onc = a.onC && a.onC[v0 + t];
     }
-    if (t == 0) beg[nv] = a.row_ptr[v0 + nv];
+    if (t == 0) rl = a.row_ptr[v0 + nv];
+    if (SWEEP && mode != kLoopSweep) return;   // uniform: see loop_after_sweep
+    if (t < nv) beg[t] = rb;
+    if (t == 0) beg[nv] = rl;
     __syncthreads();
     const int e0 = beg[0], e1 = beg[nv];
     // giant rows are left to k_giant_part / k_giant_merge
@@ -511,8 +515,9 @@ void k_tiescan_tile(SweepArgs a, const WT* __restrict__ w)
     if (SWEEP && a.E && t < nv && !giant) {
         // the vertex's chase entry: its weight is a line the batch just read
         unsigned long long e;
-        const bool fits = changed ? chase_entry<WT, RATIO>(a, w, v0 + t, pos, bhead, &e)
-                                  : chase_entry<WT, RATIO>(a, w, v0 + t, cur, a.succ[v0 + t], &e);
+        const bool fits = chase_entry<WT, RATIO>(a, w, v0 + t, changed ? pos : cur,
+                                                 changed ? bhead : a.succ[v0 + t], a.ctl->s, W, L,
+                                                 &e);
         a.E[v0 + t] = e;
         if (!fits) atomicOr(&a.ctl->fflags, kChaseOverflow);
     }
@@ -706,7 +711,8 @@ __global__ __launch_bounds__(kWG) void k_giant_merge(SweepArgs a, const WT* __re
         if (!FIRST && a.E) {
             unsigned long long e;
             if (!chase_entry<WT, RATIO>(a, w, v, wr ? parts[bi].pos : a.pi[v],
-                                        wr ? parts[bi].head : a.succ[v], &e))
+                                        wr ? parts[bi].head : a.succ[v], a.ctl->s, a.ctl->W,
+                                        a.ctl->L, &e))
                 atomicOr(&a.ctl->fflags, kChaseOverflow);
             a.E[v] = e;
         }
@@ -2354,15 +2360,18 @@ __global__ __launch_bounds__(kWG) void k_chase(int n, int jb, unsigned long long
                                                long long* __restrict__ V,
                                                int* __restrict__ out32, Ctl* ctl)
 {
-    if (ctl->fmode != kLoopChase) return;   // uniform: only the last arrival changes it
+    // the step, the source and the own entry are on the way together
+    const unsigned mode = ctl->fmode;
     const int s = ctl->s;
+    const unsigned long long jm = (1ull << jb) - 1;
+    const int64_t v = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kWG + threadIdx.x;
+    unsigned long long e = 0;
+    if (v < n) e = chase_load<LD>(&E[v]);
+    if (mode != kLoopChase) return;   // uniform: only the last arrival changes it
     __shared__ unsigned sleft, sflags;
     if (threadIdx.x == 0) sleft = sflags = 0;
     __syncthreads();
-    const unsigned long long jm = (1ull << jb) - 1;
-    const int64_t v = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kWG + threadIdx.x;
-    unsigned long long e = (unsigned)s;
-    if (v < n) e = chase_load<LD>(&E[v]);
+    if (v >= n) e = (unsigned)s;
     bool fits = true;
     for (int k = 1; k <= kChaseSteps; ++k) {
         const unsigned j = (unsigned)(e & jm);

@@ -264,6 +264,7 @@ struct Ctx {
     // values by the packed chase, sweeps and values as one device-driven loop;
     // off for the rest of the solve once a sum does not fit the entries
     bool chase = false;
+    bool warm = false;     // started from a given policy
     bool tags_clear = false;   // the cycle phase's tag arrays (in ws.layer) are clear
     bool hop_ok = false;   // ws.hop holds the policy's hops (the chase leaves them out)
 
@@ -357,7 +358,7 @@ ocm_status setup(Ctx& c, const ocm_graph* g, int neg, void* ws, size_t ws_bytes,
 
 // Validation kernel, then the bound that keeps every value inside int64:
 // |L*w - W| <= 2 n max|w| must stay below 2^62.
-ocm_status validate(Ctx& c, int check_csr)
+ocm_status validate(Ctx& c, int check_csr, const int* policy = nullptr, bool* bad_policy = nullptr)
 {
     ocm::launch_ctl_clear(c.ws.ctl, ocm::kClrAll | ocm::kClrCount | ocm::kClrChanged, c.st);
     c.prof.begin(OCM_K_VALIDATE);
@@ -368,8 +369,10 @@ ocm_status validate(Ctx& c, int check_csr)
     // with nonsense, up to its capacity)
     if (c.tile_sweep && c.m > ocm::kGiantRow)
         ocm::launch_giant_list(c.n, c.row_ptr, c.ws.gtri, c.ws.gcap, c.ws.ctl, c.st);
+    if (policy) ocm::launch_check_policy(c.n, c.row_ptr, policy, &c.ws.ctl->lane[0].bad, c.st);
     HIP_TRY(hipGetLastError());
     OCM_TRY(read_ctl(c));
+    if (policy) *bad_policy = c.h.bad != 0;
     c.ngiant = c.h.ngiant;
     if (c.h.err & ocm::kErrBadCsr) return fail(OCM_E_BAD_CSR, "malformed CSR");
     if (c.h.err & ocm::kErrNoOut) return fail(OCM_E_NO_OUT_EDGE, "a vertex has no out-edge");
@@ -1005,7 +1008,9 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
     auto* P1 = (unsigned long long*)w.Q[1];
     const int jb = ocm::chase_bits(c.n);
     const bool from_values = start != ocm::kLoopSweep;
-    const bool small = c.n < kVertexRoundsN;
+    // a warm start's policy mostly reaches C already: its rebuilds do without
+    // the reverse CSR that pushes need
+    const bool small = c.n < kVertexRoundsN || c.warm;
     // on large graphs idle kernels cost more than a read (a chase of 65,536
     // workgroups that returns at once 15 us): the values and the loop are
     // queued once the rounds are over
@@ -1048,7 +1053,8 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
         }
         if (start == ocm::kLoopCycles && (mode == ocm::kLoopCycles || c.h.rmode != 0)) {
             if (!small && !c.rev_built) build_reverse(c);
-            for (int j = 0; j < kRoundsPerRead; ++j) {
+            const int rounds = c.warm && kr == 0 ? 2 : kRoundsPerRead;
+            for (int j = 0; j < rounds; ++j) {
                 ++kr;
                 if (small)
                     ocm::launch_round_vertex(kr, c.n, c.row_ptr, c.col, w.abits[kr & 1],
@@ -1615,24 +1621,22 @@ ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t 
             if (done || s != OCM_OK) return s;
         }
     }
-    ocm_status rc = validate(c, o.validate != 0);
+    const bool warm = o.init_policy != nullptr;
+    bool bad_policy = false;
+    ocm_status rc = validate(c, o.validate != 0, o.init_policy, &bad_policy);
     if (rc == OCM_OK) rc = build_giant(c);
     if (rc != OCM_OK) { c.prof.finish(); return rc; }
     if (o.multichain) return solve_mc(c, o, cycle_edges, cap, out);
-    start_reverse_early(c);
+    if (bad_policy) return fail(OCM_E_INVALID_ARG, "init_policy picks an edge of another vertex");
+    c.warm = warm;
+    if (!warm) start_reverse_early(c);
     HIP_TRY(hipGetLastError());
 
     c.chase = c.tile_sweep && o.fast_path && !c.wide && c.n <= ocm::kLoopMaxN;
     c.v32 = c.chase;   // until a value phase says otherwise
     Ws& w = c.ws;
-    const bool warm = o.init_policy != nullptr;
     if (warm) {
         // warm start: the given policy replaces the first sweep
-        ocm::launch_ctl_clear(w.ctl, ocm::kClrChanged, c.st);
-        ocm::launch_check_policy(c.n, c.row_ptr, o.init_policy, &w.ctl->lane[0].bad, c.st);
-        HIP_TRY(hipGetLastError());
-        OCM_TRY(read_ctl(c));
-        if (c.h.bad) return fail(OCM_E_INVALID_ARG, "init_policy picks an edge of another vertex");
         HIP_TRY(hipMemcpyAsync(w.pi, o.init_policy, 4 * (size_t)c.n, hipMemcpyDeviceToDevice, c.st));
     }
     int iter = 0, fast = 0;
@@ -1784,9 +1788,10 @@ ocm_status solve(const ocm_graph* g, const ocm_options* o_in, void* wsp, size_t 
         c.prof.finish();
         return fail(OCM_E_CAPACITY, "cycle_cap smaller than the critical cycle");
     }
-    // a short C by walking it (about 0.7 us an edge), a long one by hops (a
-    // chase over all vertices, 10 us and more with n, when the values left none)
-    const bool walk = !c.hop_ok && clen <= 16 + c.n / 16384;
+    // a short C by walking it (about 0.7 us an edge), a long one by hops: a
+    // chase over all vertices and a read, 35 us at n = 20,000, 65 at 300,000,
+    // 110 at 2^20, 320 at 2^22 and beyond
+    const bool walk = !c.hop_ok && clen <= 50 + std::min<int64_t>(c.n / 8192, 400);
     if (!walk) {
         rc = ensure_hops(c);
         if (rc != OCM_OK) {
