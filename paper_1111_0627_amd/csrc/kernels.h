@@ -51,7 +51,8 @@ struct alignas(128) CtlLane {
                                    //   the running round kernel, and their counts
     unsigned wide32;               // values: some value does not fit int32 (no int32 copy)
     unsigned ncrit;                // multichain tie check: policy cycles of optimal gain
-    unsigned pad_[2];
+    unsigned fpass;                // filtered sweep: edges whose value was gathered
+    unsigned pad_[1];
 };
 static_assert(sizeof(CtlLane) == 4 * kLaneWords, "one lane per 128-byte line");
 
@@ -86,6 +87,13 @@ struct alignas(128) Ctl {
     unsigned fphases;              //   value phases begun after a sweep of the run
     unsigned fflags;               //   kChase* events of the running value phase
     unsigned fwide;                //   the last value phase left a value outside int32
+    unsigned hlines;               // validation: distinct lines in samples of 64 heads
+    unsigned fpass;                // edges the last filtered sweep gathered values for
+    // byte codes of the values (k_sweep_filter): the scale the next value phase
+    // uses, the one the codes at hand were made with, and the sampled range
+    long long qbase, dbase, qlo, qhi;
+    long long slo, shi, sL;        //   the scale's range, and the L its values were scaled by
+    unsigned qshift, dshift, qvalid, dvalid;
     CtlLane lane[kLanes];
 };
 
@@ -97,7 +105,7 @@ struct CtlView {
     unsigned rmode, rleft, rfront, rerr, rk;
     unsigned jk, jmode, jlast, jstall;
     unsigned xcnt, scnt, clen, ngiant;
-    unsigned fmode, fwhy, fsweeps, ffast, fphases, fwide;
+    unsigned fmode, fwhy, fsweeps, ffast, fphases, fwide, hlines, fpass;
     unsigned long long changed, tight, certain, nondec, pedges, ledges, maxabsw;
     unsigned active, active2, got, left, err, cbroken, overflow, bad;
     unsigned pjc[4];
@@ -129,6 +137,8 @@ __host__ __device__ inline void fold_lanes(const Ctl& c, CtlView& v)
     v.ffast = c.ffast;
     v.fphases = c.fphases;
     v.fwide = c.fwide;
+    v.hlines = c.hlines;
+    v.fpass = c.fpass;
     v.changed = v.tight = v.certain = v.nondec = v.pedges = v.ledges = v.maxabsw = 0;
     v.active = v.active2 = v.got = v.left = v.err = v.cbroken = v.overflow = v.bad = 0;
     v.wide32 = v.ncrit = 0;
@@ -181,6 +191,7 @@ constexpr unsigned kLoopStop = 0, kLoopSweep = 1, kLoopChase = 2;   // fmode
 constexpr unsigned kLoopCycles = 3, kLoopSelect = 4, kLoopConn = 5, kLoopRounds = 6;
 constexpr unsigned kLoopChain = 1;   // fopts: sweeps follow the value phase (else it stops there)
 constexpr unsigned kLoopV32 = 2;     //        the queued sweeps gather the int32 copy
+constexpr unsigned kLoopScale = 4;   //        the codes' scale of an earlier loop of this solve holds on
 enum : unsigned {                    // fwhy
     kWhyNone = 0,
     kWhyConverged,                   // a sweep changed nothing
@@ -264,9 +275,16 @@ void launch_chase_init(int n, const int* col, const int* pi, const void* w, int 
                        int* succ, unsigned long long* E, int jb, Ctl* ctl, const int* t,
                        hipStream_t st);
 // One pass of the value chase; a vertex that reaches the source gets its sum in
-// V (nullable) and out32.
-void launch_chase(int n, int jb, unsigned long long* E, long long* V, int* out32, Ctl* ctl,
-                  hipStream_t st);
+// V (nullable) and out32, and its code in q8 (nullable).
+void launch_chase(int n, int jb, unsigned long long* E, long long* V, int* out32, unsigned char* q8,
+                  Ctl* ctl, hipStream_t st);
+// The loop's sweep with gathers filtered by the codes (int32 values only).
+void launch_sweep_filter(const SweepArgs& a, const void* w, int wtype, const unsigned char* q8,
+                         hipStream_t st);
+// ctl->hlines: distinct 128-byte lines of int32 values that kHeadSamples samples
+// of 64 consecutive heads name.
+constexpr int kHeadSamples = 64;
+void launch_head_lines(int m, const int* col, Ctl* ctl, hipStream_t st);
 // The general phases as steps of the loop (mode kLoopCycles first): the cycles'
 // final (both tag arrays are left clear), the per-cycle sums and the select,
 // the rebuild's start (policy and push_min as launch_round).

@@ -538,6 +538,201 @@ void k_tiescan_tile(SweepArgs a, const WT* __restrict__ w)
     }
 }
 
+// The loop's sweep on large graphs whose heads are scattered: a plain sweep
+// gathers 4 bytes of V per edge and is bound by the lines that miss the L2 (276
+// us a sweep over 16.8M edges of a 2^22-vertex graph, 61 G gathers/s).  An edge
+// can only improve its tail, or be tight, if the head's value lies low enough,
+// and a byte per vertex says so for most: the codes are a quarter of the table
+// (4 MB for 2^22 vertices, an XCD's L2), and V is read for the few edges left
+// (27 % of them in the first sweeps, below 1 % in the last, the policy edges
+// not counted, whose key is the tail's own value).  177 us a sweep, bound by the
+// codes' gathers (95 G/s) and the edges' stream.  Same results: an edge is left
+// out only if its key exceeds V(tail).
+template <typename WT, bool RATIO>
+__global__ __launch_bounds__(kWG) void k_sweep_filter(SweepArgs a, const WT* __restrict__ w,
+                                                      const unsigned char* __restrict__ q8)
+{
+    __shared__ int beg[kWG + 1];
+    __shared__ long long add[kTieTileEdges];   // L * w - W (* t)
+    __shared__ int head[kTieTileEdges];
+    __shared__ unsigned char code[kTieTileEdges];
+    const unsigned mode = a.ctl->fmode;
+    const int64_t L = a.ctl->L, W = a.ctl->W;
+    const long long base = a.ctl->dbase;
+    const unsigned shift = a.ctl->dshift;
+    const bool coded = a.ctl->dvalid != 0;   // else every value is gathered
+    const int64_t v0 = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kWG;
+    const int nv = a.n - v0 < kWG ? (int)(a.n - v0) : kWG;
+    const int t = threadIdx.x;
+    long long own = 0;
+    int cur = -1, rb = 0, rl = 0;
+    bool onc = false;
+    if (t < nv) {
+        rb = a.row_ptr[v0 + t];
+        own = a.V32[v0 + t];
+        cur = a.pi[v0 + t];
+        onc = a.onC[v0 + t];
+    }
+    if (t == 0) rl = a.row_ptr[v0 + nv];
+    if (mode != kLoopSweep) return;   // uniform: see loop_after_sweep
+    if (t < nv) beg[t] = rb;
+    if (t == 0) beg[nv] = rl;
+    __syncthreads();
+    const int e0 = beg[0], e1 = beg[nv];
+    // giant rows are left to k_giant_part / k_giant_merge
+    const bool giant = a.giant.ngiant > 0 && t < nv && beg[t + 1] - beg[t] > kGiantRow;
+    const bool skip = a.giant.ngiant > 0 && __syncthreads_or(giant);
+    const int mb = t < nv && !giant ? beg[t] : 0, me = t < nv && !giant ? beg[t + 1] : 0;
+    unsigned cnt = 0, certain = 0, pass = 0;
+    long long best = INT64_MAX;
+    int pos = INT32_MAX, bhead = 0;
+    constexpr int U = kTieTileEdges / kWG;
+    auto low = [&](int j, long long o) {   // may the edge's key be o or less?
+        const unsigned q = code[j];
+        return q == 0 || add[j] + base + ((long long)(q - 1) << shift) <= o;
+    };
+    for (int eb = skip ? skip_giant(beg, nv, e0, e1) : e0; eb < e1;) {
+        const int n_e = e1 - eb < kTieTileEdges ? e1 - eb : kTieTileEdges;
+        int c[U];
+        WT wr[U];
+        int tl[U];
+        unsigned char q[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = t + u * kWG;
+            c[u] = j < n_e ? a.col[eb + j] : 0;
+            wr[u] = j < n_e ? w[eb + j] : 0;
+            tl[u] = RATIO && j < n_e ? a.t[eb + j] : 1;
+        }
+        if (coded) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) q[u] = t + u * kWG < n_e ? q8[c[u]] : 0;
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) q[u] = 0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = t + u * kWG;
+            if (j < n_e) {
+                add[j] = L * wval(&wr[u], 0, a.neg) - (RATIO ? W * (long long)tl[u] : W);
+                head[j] = c[u];
+                code[j] = q[u];
+            }
+        }
+        __syncthreads();
+        const int lo = mb > eb ? mb : eb, hi = me < eb + n_e ? me : eb + n_e;
+        const bool long_row = hi - lo > kLongRow;
+        auto take = [&](int e, int h, long long k) {
+            if (k < best) {
+                best = k;
+                pos = e;
+                bhead = h;
+            }
+            if (k == own) {
+                ++cnt;
+                certain += h == v0 + t || onc;
+            }
+        };
+        if (!long_row) {
+            unsigned mask = 0;
+            for (int e = lo; e < hi; ++e)
+                if (low(e - eb, own) && e != cur) mask |= 1u << (e - lo);
+            pass += __popc(mask);
+            while (mask) {   // two values on the way at once, in CSR order
+                const int x = lo + __ffs(mask) - 1;
+                mask &= mask - 1;
+                const int y = mask ? lo + __ffs(mask) - 1 : x;
+                const int hx = head[x - eb], hy = head[y - eb];
+                const int vx = a.V32[hx], vy = a.V32[hy];
+                take(x, hx, (long long)vx + add[x - eb]);
+                if (mask) take(y, hy, (long long)vy + add[y - eb]);
+                mask &= mask - 1;
+            }
+        }
+        // the wave's long rows, one after the other, by all its lanes
+        for (unsigned long long lm = __ballot(long_row); lm; lm &= lm - 1) {
+            const int l = __ffsll((long long)lm) - 1;
+            const int rlo = __shfl(lo, l, 64), rhi = __shfl(hi, l, 64);
+            const long long rown = __shfl(own, l, 64);
+            const int rcur = __shfl(cur, l, 64);
+            const bool ronc = __shfl((int)onc, l, 64) != 0;
+            const int rv = (int)(v0 + (t & ~63) + l);
+            long long k = INT64_MAX;
+            int kp = INT32_MAX, kh = 0;
+            for (int e = rlo + (t & 63); e < rhi; e += 64) {
+                if (e == rcur || !low(e - eb, rown)) continue;
+                ++pass;
+                const int h = head[e - eb];
+                const long long x = (long long)a.V32[h] + add[e - eb];
+                if (x < k) {
+                    k = x;
+                    kp = e;
+                    kh = h;
+                }
+                if (x == rown) {
+                    ++cnt;
+                    certain += h == rv || ronc;
+                }
+            }
+            wave_argmin<long long, true>(k, kp, kh);
+            if ((t & 63) == l && k < best) {   // earlier batches hold lower positions
+                best = k;
+                pos = kp;
+                bhead = kh;
+            }
+        }
+        __syncthreads();
+        eb += n_e;
+        if (skip) eb = skip_giant(beg, nv, eb, e1);
+    }
+    const bool changed = t < nv && pos != INT32_MAX && best < own;
+    if (changed) {
+        a.pi[v0 + t] = pos;
+        a.succ[v0 + t] = bhead;
+    }
+    if (t < nv && !giant) {
+        unsigned long long e;
+        if (!chase_entry<WT, RATIO>(a, w, v0 + t, changed ? pos : cur, changed ? bhead : a.succ[v0 + t],
+                                    a.ctl->s, W, L, &e))
+            atomicOr(&a.ctl->fflags, kChaseOverflow);
+        a.E[v0 + t] = e;
+    }
+    unsigned long long sums[3] = {((unsigned long long)changed << 32) | (unsigned long long)(changed && onc),
+                                  ((unsigned long long)cnt << 32) | certain, pass};
+    block_sums_u64(sums);
+    if (t == 0) {
+        CtlLane& ln = my_lane(a.ctl);
+        const unsigned long long ch = sums[0] >> 32;
+        const bool br = (unsigned)sums[0] != 0;
+        if (sums[1] >> 32) atomicAdd(&ln.tight, sums[1] >> 32);
+        if ((unsigned)sums[1]) atomicAdd(&ln.certain, (unsigned long long)(unsigned)sums[1]);
+        if (coded && sums[2]) atomicAdd(&ln.fpass, (unsigned)sums[2]);
+        if (ch) atomicAdd(&ln.changed, ch);
+        if (br) atomicOr(&ln.cbroken, 1u);
+        if (a.giant.ngiant == 0) {
+            unsigned long long tot;
+            if (last_arrival(a.ctl, arrival_word(ch, br), &tot))
+                loop_after_sweep(a.ctl, (unsigned)tot != 0, ((tot >> 32) & 0xffffu) != 0);
+        }
+    }
+}
+
+// One wave per sample of 64 consecutive heads: how many different lines of
+// int32 values they name.
+__global__ __launch_bounds__(64) void k_head_lines(int m, const int* __restrict__ col, Ctl* ctl)
+{
+    const int64_t e = (int64_t)blockIdx.x * (m / kHeadSamples) + threadIdx.x;
+    const int line = e < m ? col[e] >> 5 : -1 - (int)threadIdx.x;
+    bool seen = false;
+    for (int l = 0; l < 63; ++l) {
+        const int other = __shfl(line, l, 64);
+        seen |= l < (int)threadIdx.x && other == line;
+    }
+    const unsigned long long mask = __ballot(!seen);
+    if (threadIdx.x == 0) atomicAdd(&ctl->hlines, (unsigned)__popcll(mask));
+}
+
 __global__ void k_loop_close(Ctl* c)
 {
     if (threadIdx.x != 0 || c->fmode != kLoopSweep) return;
@@ -2244,7 +2439,7 @@ __global__ void k_loop_setup(Ctl* c, unsigned mode, unsigned opts, unsigned max_
         CtlLane& ln = c->lane[t];
         ln.changed = ln.tight = ln.certain = ln.nondec = 0;
         ln.cbroken = ln.overflow = ln.wide32 = ln.bad = 0;
-        ln.active = ln.active2 = ln.got = ln.left = 0;
+        ln.active = ln.active2 = ln.got = ln.left = ln.fpass = 0;
         ln.rpack = 0;
     }
     if (t == 0) {
@@ -2259,8 +2454,22 @@ __global__ void k_loop_setup(Ctl* c, unsigned mode, unsigned opts, unsigned max_
         c->fopts = opts;
         c->fsweeps = c->ffast = c->fphases = c->fflags = c->fwide = 0;
         c->fmax = max_sweeps;
+        c->fpass = 0;
+        c->qlo = INT64_MAX;
+        c->qhi = INT64_MIN;
+        c->dvalid = 0;
+        if (!(opts & kLoopScale)) c->qvalid = 0;
         c->fmode = mode;
     }
+}
+
+// The next codes' scale for values from lo to hi (int32 values: 32 bits apart).
+__device__ __forceinline__ void code_scale(Ctl* c, long long lo, long long hi)
+{
+    unsigned sh = 0;
+    while (sh < 31 && (hi - lo) >> sh > 253) ++sh;
+    c->qbase = lo;
+    c->qshift = sh;
 }
 
 template <typename WT>
@@ -2274,6 +2483,11 @@ __global__ __launch_bounds__(kWG) void k_chase_init(int n, const int* __restrict
     if (ctl->fmode != kLoopRounds || ctl->rmode != 0) return;
     const int s = ctl->s;
     const long long W = ctl->W, L = ctl->L;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && ctl->qvalid && ctl->sL != L) {
+        // another C: its values are scaled by another L
+        const double f = (double)L / (double)ctl->sL;
+        code_scale(ctl, (long long)(f * (double)ctl->slo), (long long)(f * (double)ctl->shi));
+    }
     constexpr int U = 4;   // independent vertices in flight per thread
     const int64_t stride = (int64_t)gridDim.x * kWG;
     bool fits = true;
@@ -2345,20 +2559,52 @@ __device__ void loop_after_chase(Ctl* c, unsigned left)
     } else if ((f & kChaseWide) && (c->fopts & kLoopV32)) {
         loop_stop(c, kWhyWide);
     } else {
+        unsigned pass = 0;
         for (int l = 0; l < kLanes; ++l) {
             CtlLane& ln = c->lane[l];
+            pass += ln.fpass;
             ln.changed = ln.tight = ln.certain = 0;
-            ln.cbroken = 0;
+            ln.cbroken = ln.fpass = 0;
+        }
+        // what the last sweep let through; the codes just written, and the next
+        // phase's scale from the sampled range
+        c->fpass = pass;
+        c->dbase = c->qbase;
+        c->dshift = c->qshift;
+        c->dvalid = c->qvalid;
+        const long long lo = __hip_atomic_load(&c->qlo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const long long hi = __hip_atomic_load(&c->qhi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lo <= hi) {
+            code_scale(c, lo, hi);
+            c->slo = lo;
+            c->shi = hi;
+            c->sL = c->L;
+            c->qvalid = 1;
+            c->qlo = INT64_MAX;
+            c->qhi = INT64_MIN;
         }
         c->fflags = 0;
         c->fmode = kLoopSweep;
     }
 }
 
-template <int LD, int ST>
+// Code of a value: 0 says nothing, q >= 1 says value >= base + ((q - 1) << shift).
+__device__ __forceinline__ unsigned char value_code(long long d, long long base, unsigned shift,
+                                                    bool valid)
+{
+    if (!valid || d < base) return 0;
+    const long long q = (d - base) >> shift;
+    return (unsigned char)(q < 254 ? q + 1 : 255);
+}
+
+// CODE: also the values' byte codes, with the range of the values of some 32
+// waves as the sample the next phase's scale is taken from (2048 waves, whose
+// atomics meet on one line, cost 50 us).
+template <int LD, int ST, bool CODE>
 __global__ __launch_bounds__(kWG) void k_chase(int n, int jb, unsigned long long* E,
                                                long long* __restrict__ V,
-                                               int* __restrict__ out32, Ctl* ctl)
+                                               int* __restrict__ out32,
+                                               unsigned char* __restrict__ q8, Ctl* ctl)
 {
     // the step, the source and the own entry are on the way together
     const unsigned mode = ctl->fmode;
@@ -2395,6 +2641,22 @@ __global__ __launch_bounds__(kWG) void k_chase(int n, int jb, unsigned long long
         if (V) V[v] = d;
         out32[v] = (int)d;
         wide = d != (long long)(int)d;
+        if (CODE) q8[v] = value_code(d, ctl->qbase, ctl->qshift, ctl->qvalid != 0);
+    }
+    if (CODE && threadIdx.x < 64 && blockIdx.x % (gridDim.x / 32 + 1) == 0) {
+        long long lo = v < n && done ? (long long)e >> jb : INT64_MAX;
+        long long hi = v < n && done ? (long long)e >> jb : INT64_MIN;
+        for (int off = 32; off > 0; off >>= 1) {
+            const long long a = __shfl_xor(lo, off, 64), b = __shfl_xor(hi, off, 64);
+            lo = a < lo ? a : lo;
+            hi = b > hi ? b : hi;
+        }
+        if (threadIdx.x == 0 && lo <= hi) {
+            atomicMin(&ctl->qlo, lo);
+            // the returned value orders the update before the arrival below
+            const long long old = atomicMax(&ctl->qhi, hi);
+            asm volatile("" ::"v"((int)old));
+        }
     }
     const unsigned long long open = __ballot(!done);
     const unsigned flags = (__ballot(!fits) ? kChaseOverflow : 0u) | (__ballot(wide) ? kChaseWide : 0u);
@@ -3104,6 +3366,32 @@ void launch_sweep(const SweepArgs& a, const void* w, int wtype, int G, bool firs
     else launch_sweep_t<int>(a, w, G, first, tie, grid, st);
 }
 
+template <typename WT>
+static void launch_sweep_filter_t(const SweepArgs& a, const WT* w, const unsigned char* q8,
+                                  hipStream_t st)
+{
+    const unsigned tiles = blocks_for(a.n);
+    if (a.t) {
+        k_sweep_filter<WT, true><<<tiles, kWG, 0, st>>>(a, w, q8);
+        launch_giant<WT, 2, true>(a, w, false, false, true, st);
+    } else {
+        k_sweep_filter<WT, false><<<tiles, kWG, 0, st>>>(a, w, q8);
+        launch_giant<WT, 2, false>(a, w, false, false, true, st);
+    }
+}
+
+void launch_sweep_filter(const SweepArgs& a, const void* w, int wtype, const unsigned char* q8,
+                         hipStream_t st)
+{
+    if (wtype == kWI64) launch_sweep_filter_t(a, (const long long*)w, q8, st);
+    else launch_sweep_filter_t(a, (const int*)w, q8, st);
+}
+
+void launch_head_lines(int m, const int* col, Ctl* ctl, hipStream_t st)
+{
+    k_head_lines<<<kHeadSamples, 64, 0, st>>>(m, col, ctl);
+}
+
 void launch_giant_list(int n, const int* row_ptr, int* triples, unsigned cap, Ctl* ctl,
                        hipStream_t st)
 {
@@ -3137,14 +3425,17 @@ void launch_chase_init(int n, const int* col, const int* pi, const void* w, int 
 // 30 / 28 / 33.  On large graphs written-through steps cost more than they
 // save: 2^22: 284 / 269 / 275, 2^23: 436 / 423 / 355, 16^6 product: 501 / 397 /
 // 259.
-void launch_chase(int n, int jb, unsigned long long* E, long long* V, int* out32, Ctl* ctl,
-                  hipStream_t st)
+void launch_chase(int n, int jb, unsigned long long* E, long long* V, int* out32, unsigned char* q8,
+                  Ctl* ctl, hipStream_t st)
 {
     constexpr int A = __HIP_MEMORY_SCOPE_AGENT, G = __HIP_MEMORY_SCOPE_WORKGROUP;
     const unsigned grid = blocks_for(n);
-    if (n < (1 << 18)) k_chase<A, A><<<grid, kWG, 0, st>>>(n, jb, E, V, out32, ctl);
-    else if (n <= (1 << 22)) k_chase<G, A><<<grid, kWG, 0, st>>>(n, jb, E, V, out32, ctl);
-    else k_chase<G, G><<<grid, kWG, 0, st>>>(n, jb, E, V, out32, ctl);
+    if (q8) {   // large graphs only
+        if (n <= (1 << 22)) k_chase<G, A, true><<<grid, kWG, 0, st>>>(n, jb, E, V, out32, q8, ctl);
+        else k_chase<G, G, true><<<grid, kWG, 0, st>>>(n, jb, E, V, out32, q8, ctl);
+    } else if (n < (1 << 18)) k_chase<A, A, false><<<grid, kWG, 0, st>>>(n, jb, E, V, out32, q8, ctl);
+    else if (n <= (1 << 22)) k_chase<G, A, false><<<grid, kWG, 0, st>>>(n, jb, E, V, out32, q8, ctl);
+    else k_chase<G, G, false><<<grid, kWG, 0, st>>>(n, jb, E, V, out32, q8, ctl);
 }
 
 void launch_hop_init(int n, const int* succ, unsigned long long* E, const Ctl* ctl, hipStream_t st)
@@ -3734,6 +4025,8 @@ __global__ void k_post_ctl(const Ctl* __restrict__ c, CtlView* dst, unsigned* se
         v.ffast = c->ffast;
         v.fphases = c->fphases;
         v.fwide = c->fwide;
+        v.hlines = c->hlines;
+        v.fpass = c->fpass;
         *dst = v;
         __threadfence_system();
         __hip_atomic_store(seq_slot, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);

@@ -63,6 +63,7 @@ struct Ws {
     Ctl* ctl;
     long long* V;        // values scaled by L (int128 values: their low words)
     long long* Vhi;      // int128 values: high words
+    unsigned char* q8;   // byte codes of V (filtered sweeps; in wsum, which only the cycle phase uses)
     int* V32;            // int32 copy of V (valid while every value fits int32)
     long long* Dhi[2];   // int128 value rounds: high words of the jump entries' sums
     int* pi;             // policy: CSR position of each vertex's edge
@@ -148,6 +149,7 @@ Ws carve(void* base, int64_t n, int64_t m)
     w.xs = (int*)take(4 * (size_t)w.xcap);
     w.ys = (int*)take(4 * (size_t)w.xcap);
     w.wsum = (long long*)take(8 * N);
+    w.q8 = (unsigned char*)w.wsum;
     w.lcnt = (unsigned*)take(4 * N);
     w.tsum = (long long*)take(8 * N);
     w.cyc = (int*)take(4 * N);
@@ -264,6 +266,8 @@ struct Ctx {
     // values by the packed chase, sweeps and values as one device-driven loop;
     // off for the rest of the solve once a sum does not fit the entries
     bool chase = false;
+    bool filter = false;   // sweeps filtered by the values' byte codes (k_sweep_filter)
+    bool coded = false;    // the codes have a scale
     bool warm = false;     // started from a given policy
     bool tags_clear = false;   // the cycle phase's tag arrays (in ws.layer) are clear
     bool hop_ok = false;   // ws.hop holds the policy's hops (the chase leaves them out)
@@ -356,6 +360,14 @@ ocm_status setup(Ctx& c, const ocm_graph* g, int neg, void* ws, size_t ws_bytes,
     return OCM_OK;
 }
 
+// Sweeps gather through byte codes from this size on, if 64 consecutive heads
+// name at least 45 different lines of values on average (random heads: 53 to
+// 64; the 16^6 product graph: about 12, its gathers mostly hit the L2 as they
+// are).  Random graphs of degree 2 to 6, whole solve without / with codes, ms:
+// 786,432 vertices 4.47 / 4.50 (int32), 2^20 11.02 / 11.07, 3 * 2^19 10.37 /
+// 9.93, 2^21 6.45 / 5.76, 2^22 22.3 / 19.4, 2^23 25.6 / 22.7.
+constexpr int kFilterN = 3 << 19;
+
 // Validation kernel, then the bound that keeps every value inside int64:
 // |L*w - W| <= 2 n max|w| must stay below 2^62.
 ocm_status validate(Ctx& c, int check_csr, const int* policy = nullptr, bool* bad_policy = nullptr)
@@ -369,10 +381,12 @@ ocm_status validate(Ctx& c, int check_csr, const int* policy = nullptr, bool* ba
     // with nonsense, up to its capacity)
     if (c.tile_sweep && c.m > ocm::kGiantRow)
         ocm::launch_giant_list(c.n, c.row_ptr, c.ws.gtri, c.ws.gcap, c.ws.ctl, c.st);
+    if (c.n >= kFilterN) ocm::launch_head_lines(c.m, c.col, c.ws.ctl, c.st);
     if (policy) ocm::launch_check_policy(c.n, c.row_ptr, policy, &c.ws.ctl->lane[0].bad, c.st);
     HIP_TRY(hipGetLastError());
     OCM_TRY(read_ctl(c));
     if (policy) *bad_policy = c.h.bad != 0;
+    c.filter = c.n >= kFilterN && 10 * c.h.hlines >= 7u * 64 * ocm::kHeadSamples;
     c.ngiant = c.h.ngiant;
     if (c.h.err & ocm::kErrBadCsr) return fail(OCM_E_BAD_CSR, "malformed CSR");
     if (c.h.err & ocm::kErrNoOut) return fail(OCM_E_NO_OUT_EDGE, "a vertex has no out-edge");
@@ -1022,8 +1036,8 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
         ocm::launch_fill_u32((unsigned*)w.layer, ((int64_t)c.n * 2 + 3) / 4, 0u, c.st);
         c.tags_clear = true;   // each cycle phase leaves them clear
     }
-    ocm::launch_loop_setup(w.ctl, start, ocm::kLoopChain | (c.v32 ? ocm::kLoopV32 : 0u), max_sweeps,
-                           c.st);
+    ocm::launch_loop_setup(w.ctl, start, ocm::kLoopChain | (c.v32 ? ocm::kLoopV32 : 0u) |
+                                             (c.coded ? ocm::kLoopScale : 0u), max_sweeps, c.st);
     ocm::SweepArgs a = sweep_args(c, false, w.V, 0, 1, w.pi, w.onC);
     a.succ = w.succ;
     a.E = E;
@@ -1078,14 +1092,15 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
     };
     auto chase = [&](int k) {
         c.prof.begin(k);
-        ocm::launch_chase(c.n, jb, E, w.V, w.V32, w.ctl, c.st);
+        ocm::launch_chase(c.n, jb, E, w.V, w.V32, c.filter ? w.q8 : nullptr, w.ctl, c.st);
         c.prof.end();
         // the entry read and written, an entry gathered, V and its copy
         c.prof.bytes(k, 36.0 * c.n);
     };
-    auto sweep = [&]() {
+    auto sweep = [&](bool coded) {
         c.prof.begin(OCM_K_SWEEP);
-        ocm::launch_sweep(a, c.w, c.wtype, 0, false, false, true, c.sweep_grid, c.st);
+        if (c.filter && coded && a.V32) ocm::launch_sweep_filter(a, c.w, c.wtype, w.q8, c.st);
+        else ocm::launch_sweep(a, c.w, c.wtype, 0, false, false, true, c.sweep_grid, c.st);
         if (a.giant.ngiant > 0) ocm::launch_loop_close(w.ctl, c.st);
         c.prof.end();
         c.prof.bytes(OCM_K_SWEEP, 8.0 * c.n);   // the chase entry
@@ -1114,18 +1129,22 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
             // profiled: one step per read, so that no launch is an idle one
             const unsigned before = c.h.fsweeps;
             if (mode != ocm::kLoopSweep) chase(before ? OCM_K_FAST : OCM_K_VALUES);
-            else sweep();
+            else sweep(c.coded);
             HIP_TRY(hipGetLastError());
             OCM_TRY(read_ctl(c));
             if (c.h.fsweeps != before) sweep_done(c, false, false, true);
         } else {
             for (int k = 0; k < pairs; ++k) {
-                if (k > 0 || mode == ocm::kLoopSweep) sweep();
+                // the second value phase is the first with a scale
+                if (k > 0 || mode == ocm::kLoopSweep) sweep(c.coded || k > 1);
                 chase(OCM_K_FAST);
             }
             HIP_TRY(hipGetLastError());
             OCM_TRY(read_ctl(c));
         }
+        // a filter that lets most edges through is not worth its bytes
+        if (c.h.fpass > (unsigned)c.m / 4 * 3) c.filter = false;
+        c.coded = c.coded || c.h.fsweeps > 0;
         if (c.h.fmode == ocm::kLoopStop) break;
         mode = c.h.fmode;
         if (mode == ocm::kLoopCycles && kc >= K) return fail(OCM_E_HIP, "cycle rounds did not finish");
@@ -1157,7 +1176,7 @@ ocm_status ensure_hops(Ctx& c)
     c.prof.begin(OCM_K_RESULT);
     ocm::launch_hop_init(c.n, w.succ, E, w.ctl, c.st);
     for (;;) {
-        ocm::launch_chase(c.n, 32, E, nullptr, w.hop, w.ctl, c.st);
+        ocm::launch_chase(c.n, 32, E, nullptr, w.hop, nullptr, w.ctl, c.st);
         c.prof.end();
         HIP_TRY(hipGetLastError());
         OCM_TRY(read_ctl(c));
