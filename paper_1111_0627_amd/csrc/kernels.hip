@@ -2263,6 +2263,7 @@ __global__ __launch_bounds__(kPlaceWG) void k_rev_place(int n, int64_t m, int B,
     }
     __syncthreads();
     for (int64_t v = lo + threadIdx.x; v < hi; v += kPlaceWG) rin_ptr[v] = (int)(start + cnt[v - lo]);
+    __syncthreads();   // the placement below moves the cursors on
     if (bkt == B - 1 && threadIdx.x == 0) rin_ptr[n] = (int)m;
     const bool staged = end - start <= cap;   // uniform
     int* out = staged ? stage : rin + start;
