@@ -94,6 +94,7 @@ struct alignas(128) Ctl {
     long long qbase, dbase, qlo, qhi;
     long long slo, shi, sL;        //   the scale's range, and the L its values were scaled by
     unsigned qshift, dshift, qvalid, dvalid;
+    unsigned lfail;                // cycles by records: a path or a cycle was too long
     CtlLane lane[kLanes];
 };
 
@@ -288,6 +289,13 @@ void launch_head_lines(int m, const int* col, Ctl* ctl, hipStream_t st);
 // The general phases as steps of the loop (mode kLoopCycles first): the cycles'
 // final (both tag arrays are left clear), the per-cycle sums and the select,
 // the rebuild's start (policy and push_min as launch_round).
+// The policy's cycles by records (see k_low_next): N, T, marks in onc and the
+// cycles' sums; the smallest vertex of v's cycle is rep[T[v]].  ctl->lfail if
+// that gave up, then the loop still stands at its cycle step.
+void launch_loop_low_cycles(int n, const int* col, const int* pi, int* succ, bool have_succ,
+                            unsigned* N, unsigned* T, int* rep, unsigned char* onc, const void* w,
+                            int wtype, int neg, const int* t, long long* wsum, unsigned* lcnt,
+                            long long* tsum, int* cyc_list, Ctl* ctl, hipStream_t st);
 void launch_loop_cycles_final(int n, const unsigned long long* P0, const unsigned long long* P1,
                               int K, int* rep, unsigned char* onc, unsigned char* tag0,
                               unsigned char* tag1, long long* wsum, unsigned* lcnt, long long* tsum,
@@ -295,10 +303,10 @@ void launch_loop_cycles_final(int n, const unsigned long long* P0, const unsigne
 void launch_loop_select(int n, const int* rep, const unsigned char* onc, const int* pi,
                         const void* w, int wtype, int neg, const int* t, long long* wsum,
                         unsigned* lcnt, long long* tsum, const int* cyc_list, void* scratch,
-                        Ctl* ctl, hipStream_t st);
-void launch_loop_conn_init(int n, const int* rep, const unsigned char* onc, unsigned char* onC,
-                           unsigned* a1, unsigned* a0, Ctl* ctl, int policy, unsigned push_min,
-                           hipStream_t st);
+                        Ctl* ctl, bool have_sums, hipStream_t st);
+void launch_loop_conn_init(int n, const int* rep, const unsigned* T, const unsigned char* onc,
+                           unsigned char* onC, unsigned* a1, unsigned* a0, Ctl* ctl, int policy,
+                           unsigned push_min, hipStream_t st);
 // Pull round k with a thread per vertex (see k_round_vertex).
 void launch_round_vertex(int k, int n, const int* row_ptr, const int* col, const unsigned* acur,
                          unsigned* anext, int* pi, Ctl* ctl, hipStream_t st);

@@ -1175,6 +1175,240 @@ __global__ __launch_bounds__(kWG) void k_loop_cycles_final(
 }
 
 // ---------------------------------------------------------------------------
+// cycles by records, the loop's cycle step.  Jump rounds touch every vertex
+// some log2(depth) + 3 times, each time a gather of 8 bytes and a barrier of a
+// launch (2^22 vertices: 12 to 15 rounds, 560 to 1390 us; 20,000: 13 launches).  Here vertices are
+// ordered by a multiplicative hash of their index, and each finds
+//   N: the first vertex on its path that is lower than itself (k_low_next), by
+//      jumping along the entries of the vertices in between, in place (a vertex
+//      below its whole path, hence on no cycle, ends at the cycle's lowest);
+//   T: the lowest vertex its path reaches (k_low_root), along the N's;
+// a vertex with N = itself is the lowest of its cycle.  Expected 2 to 4 gathers
+// of 4 bytes per vertex and step whatever the numbering, in two launches: as in
+// the value chase an entry seen late is still a vertex of the path with nothing
+// lower before it, so every order of the updates ends in the same N and T.
+// 2^22 vertices: 290 to 600 us with the marks, bound by the gathers; 20,000: 42 us.
+// Sets lfail, for the jump rounds to take over, if a path takes more than
+// kLowSteps steps or a cycle has more than kLowQueue vertices.
+// ---------------------------------------------------------------------------
+constexpr int kLowSteps = 256;
+constexpr int kLowFirst = 8;   // steps of a large graph's first pass
+constexpr int kLowQueue = 8192;
+
+__device__ __forceinline__ unsigned low_key(unsigned v) { return v * 0x9E3779B1u; }
+
+__global__ __launch_bounds__(kWG) void k_low_init(int n, const int* __restrict__ col,
+                                                  const int* __restrict__ pi, int* __restrict__ succ,
+                                                  int have_succ, unsigned* __restrict__ N,
+                                                  unsigned char* __restrict__ onc)
+{
+    const int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x;
+    if (v >= n) return;
+    int s;
+    if (have_succ) {
+        s = succ[v];
+    } else {
+        s = col[pi[v]];
+        succ[v] = s;
+    }
+    N[v] = (unsigned)s;
+    onc[v] = 0;
+}
+
+template <int LD, int ST>
+__global__ __launch_bounds__(kWG) void k_low_next(int n, int steps, int last, unsigned* N,
+                                                  unsigned* __restrict__ T, Ctl* ctl)
+{
+    const int64_t v = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kWG + threadIdx.x;
+    if (v >= n) return;
+    const unsigned own = low_key((unsigned)v);
+    unsigned j = __hip_atomic_load(&N[v], __ATOMIC_RELAXED, LD);
+    unsigned low = j;   // the lowest vertex passed since the last restart
+    bool open = low_key(j) > own;
+    for (int k = 1; k <= steps && open; ++k) {
+        const unsigned r = __hip_atomic_load(&N[j], __ATOMIC_RELAXED, LD);
+        // at the cycle's lowest, or back at the lowest passed, which is that
+        // (unless it is off the cycle: hence the restarts): a vertex off the
+        // cycle, below its whole path
+        open = r != j && r != low && low_key(r) > own;
+        if (low_key(r) < low_key(low) || (k & 31) == 0) low = r;
+        j = r;
+        __hip_atomic_store(&N[v], j, __ATOMIC_RELAXED, ST);
+    }
+    if (!last) return;
+    T[v] = j;
+    if (open) ctl->lfail = 1;
+}
+
+template <int LD, int ST>
+__global__ __launch_bounds__(kWG) void k_low_root(int n, unsigned* T, int* __restrict__ roots,
+                                                  Ctl* ctl)
+{
+    __shared__ unsigned nr, base, fail;
+    if (threadIdx.x == 0) fail = ctl->lfail;   // other workgroups may set it meanwhile
+    __syncthreads();
+    if (fail) return;
+    const int64_t v = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kWG + threadIdx.x;
+    bool root = false, open = false;
+    if (v < n) {
+        unsigned j = __hip_atomic_load(&T[v], __ATOMIC_RELAXED, LD);
+        root = j == (unsigned)v;
+        open = !root;
+        for (int k = 0; k < kLowSteps && open; ++k) {
+            const unsigned r = __hip_atomic_load(&T[j], __ATOMIC_RELAXED, LD);
+            open = r != j;
+            if (open) {
+                j = r;
+                __hip_atomic_store(&T[v], j, __ATOMIC_RELAXED, ST);
+            }
+        }
+    }
+    if (threadIdx.x == 0) nr = 0;
+    __syncthreads();
+    const unsigned long long mask = __ballot(root), late = __ballot(open);
+    const unsigned lane = threadIdx.x & 63;
+    unsigned at = 0;
+    if (lane == 0) {
+        if (mask) at = atomicAdd(&nr, (unsigned)__popcll(mask));
+        if (late) atomicOr(&nr, 1u << 31);
+    }
+    at = __shfl(at, 0, 64) & 0x7fffffffu;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned c = nr & 0x7fffffffu;
+        base = c ? atomicAdd(&ctl->ncyc, c) : 0u;
+        if (nr >> 31) ctl->lfail = 1;
+    }
+    __syncthreads();
+    if (root) roots[base + at + __popcll(mask & ((1ull << lane) - 1ull))] = (int)v;
+}
+
+// Marks the cycles from their lowest vertices and adds up their edges; rep of
+// the lowest becomes the cycle's smallest index (of the other vertices it is
+// rep[T[v]]).  A thread walks a cycle of up to kLowWalk vertices (0.6 us a step
+// on a large graph); longer ones are left to the workgroup: the vertices between
+// v and N[v] are the chain succ(v), N(succ(v)), ... up to N[v], each with those
+// between itself and its own N, which spreads a cycle of l random vertices over
+// the threads in some 2 ln l levels (1000 vertices: 60 us, not 600).  With a
+// workgroup per cycle the walk is given up after kLowWalkFew steps.
+constexpr int kLowWalk = 48, kLowWalkFew = 8;
+
+template <typename WT>
+__global__ __launch_bounds__(kWG) void k_low_mark(const int* __restrict__ succ,
+                                                  const unsigned* __restrict__ N,
+                                                  const int* __restrict__ pi,
+                                                  const WT* __restrict__ w, int neg,
+                                                  const int* __restrict__ tm, int* __restrict__ cyc,
+                                                  int* __restrict__ rep, unsigned char* __restrict__ onc,
+                                                  long long* __restrict__ wsum,
+                                                  unsigned* __restrict__ lcnt,
+                                                  long long* __restrict__ tsum, Ctl* ctl)
+{
+    __shared__ int q[kLowQueue];
+    __shared__ int longs[kWG];
+    __shared__ unsigned nlong, tail, over;
+    __shared__ int low;
+    const int t = threadIdx.x;
+    if (ctl->fmode != kLoopCycles || ctl->lfail) return;   // uniform: only the last arrival changes them
+    const unsigned nroots = ctl->ncyc;
+    const unsigned walk = nroots <= gridDim.x ? kLowWalkFew : kLowWalk;
+    auto visit = [&](int u, int& mn, long long& W, long long& T) {
+        onc[u] = 1;
+        mn = u < mn ? u : mn;
+        const int e = pi[u];
+        W += wval(w, e, neg);
+        if (tm) T += tm[e];
+    };
+    auto close = [&](unsigned i, int r, int mn, long long W, long long T, unsigned len) {
+        rep[r] = mn;
+        cyc[i] = mn;
+        wsum[mn] = W;
+        lcnt[mn] = len;
+        if (tm) tsum[mn] = T;
+    };
+    bool failed = false;   // uniform
+    for (unsigned b = 0; !failed && b * gridDim.x + blockIdx.x < nroots; b += kWG) {
+        if (t == 0) nlong = 0;
+        __syncthreads();
+        const unsigned i = (b + t) * gridDim.x + blockIdx.x;   // neighbours go to different workgroups
+        if (i < nroots) {
+            const int r = cyc[i];
+            int u = r, mn = r;
+            unsigned len = 0;
+            long long W = 0, T = 0;
+            do {
+                visit(u, mn, W, T);
+                u = succ[u];
+                ++len;
+            } while (u != r && len < walk);
+            if (u == r) close(i, r, mn, W, T, len);
+            else longs[atomicAdd(&nlong, 1u)] = (int)i;
+        }
+        __syncthreads();
+        const unsigned nl = nlong;
+        for (unsigned x = 0; x < nl; ++x) {
+            const unsigned li = (unsigned)longs[x];
+            const int r = cyc[li];
+            __syncthreads();   // every thread has read the entry it may overwrite below
+            if (t == 0) {
+                q[0] = r;
+                tail = 1;
+                over = 0;
+                low = r;
+            }
+            __syncthreads();
+            int mn = r;
+            long long W = 0, T = 0;
+            if (t == 0) visit(r, mn, W, T);
+            unsigned lo = 0, hi = 1;
+            while (lo < hi) {
+                for (unsigned y = lo + t; y < hi; y += kWG) {
+                    const int v = q[y], end = (int)N[v];
+                    int u = succ[v];
+                    while (u != end) {
+                        visit(u, mn, W, T);
+                        const unsigned slot = atomicAdd(&tail, 1u);
+                        if (slot >= (unsigned)kLowQueue) {
+                            over = 1;
+                            break;
+                        }
+                        q[slot] = u;
+                        u = (int)N[u];
+                    }
+                }
+                __syncthreads();
+                lo = hi;
+                hi = tail;
+                const bool stop = over != 0;
+                __syncthreads();
+                if (stop) break;
+            }
+            if (over) {   // uniform: read after the barrier
+                failed = true;
+                break;
+            }
+            atomicMin(&low, mn);
+            unsigned long long sums[2] = {(unsigned long long)W, (unsigned long long)T};
+            block_sums_u64(sums);   // two's complement sums
+            __syncthreads();
+            if (t == 0) close(li, r, low, (long long)sums[0], (long long)sums[1], hi);
+            __syncthreads();
+        }
+        __syncthreads();
+    }
+    if (t != 0) return;
+    unsigned long long tot;
+    if (last_arrival(ctl, arrival_word(0, failed), &tot)) {
+        if ((tot >> 32) & 0xffffu) {
+            ctl->lfail = 1;
+        } else {
+            ctl->jk = 2;
+            ctl->fmode = kLoopSelect;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // select: per-cycle (W, L) keyed by rep, then the minimum in exact order
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kWG) void k_cyc_zero(int n, const int* __restrict__ rep,
@@ -1386,7 +1620,9 @@ __device__ __forceinline__ unsigned round_mode(unsigned left, unsigned front, in
 // Rebuild init: C's component (rep == s) keeps pi (layer 0), every other
 // vertex is unattached (layer -1).  Writes the round-1 bitmaps (a1 = layer
 // 0, a0 = empty) and counts both sets into the lanes (got, left).
+// T (nullable): rep is that of T[v].
 __global__ __launch_bounds__(kWG) void k_conn_init(int n, const int* __restrict__ rep,
+                                                   const unsigned* __restrict__ T,
                                                    const unsigned char* __restrict__ onc, int s,
                                                    int* __restrict__ layer,
                                                    unsigned char* __restrict__ onC,
@@ -1408,7 +1644,7 @@ __global__ __launch_bounds__(kWG) void k_conn_init(int n, const int* __restrict_
         const int64_t v = vb + lane;
         bool comp = false;
         if (v < n) {
-            comp = rep[v] == s;
+            comp = rep[T ? (int64_t)T[v] : v] == s;
             if (layer) layer[v] = comp ? 0 : -1;
             if (onC) onC[v] = (unsigned char)(comp && onc && onc[v]);
         }
@@ -2447,7 +2683,7 @@ __global__ void k_loop_setup(Ctl* c, unsigned mode, unsigned opts, unsigned max_
         c->rpack = 0;
         if (mode == kLoopCycles) {
             c->ncyc = c->rmode = c->rleft = c->rfront = c->rerr = c->rk = c->rmarks = 0;
-            c->jk = c->jstall = 0;
+            c->jk = c->jstall = c->lfail = 0;
             c->jmode = 1;
         }
         c->jlast = 0xffffffffu;
@@ -3560,12 +3796,49 @@ void launch_loop_cycles_final(int n, const unsigned long long* P0, const unsigne
                                                        tsum, cyc_list, ctl);
 }
 
+void launch_loop_low_cycles(int n, const int* col, const int* pi, int* succ, bool have_succ,
+                            unsigned* N, unsigned* T, int* rep, unsigned char* onc, const void* w,
+                            int wtype, int neg, const int* t, long long* wsum, unsigned* lcnt,
+                            long long* tsum, int* cyc_list, Ctl* ctl, hipStream_t st)
+{
+    constexpr int A = __HIP_MEMORY_SCOPE_AGENT, G = __HIP_MEMORY_SCOPE_WORKGROUP;
+    const unsigned grid = blocks_for(n);
+    k_low_init<<<grid, kWG, 0, st>>>(n, col, pi, succ, have_succ, N, onc);
+    // Every vertex runs at once up to 2^18 of them: one pass.  Beyond, the first
+    // ones meet many vertices that have not begun and whose entries are single
+    // edges; a pass of a few steps for all, then one that finishes the rest.
+    // Scopes: written through and read fresh, or the walks around a cycle find
+    // its lowest vertex late (2^22: over 256 steps); above 2^22 the first pass
+    // and the roots' cheaper steps win (16^6 product: 608 us against 899).
+    if (n < (1 << 18)) {
+        k_low_next<A, A><<<grid, kWG, 0, st>>>(n, kLowSteps, 1, N, T, ctl);
+        k_low_root<A, A><<<grid, kWG, 0, st>>>(n, T, cyc_list, ctl);
+    } else if (n <= (1 << 22)) {
+        k_low_next<A, A><<<grid, kWG, 0, st>>>(n, kLowFirst, 0, N, T, ctl);
+        k_low_next<A, A><<<grid, kWG, 0, st>>>(n, kLowSteps, 1, N, T, ctl);
+        k_low_root<G, A><<<grid, kWG, 0, st>>>(n, T, cyc_list, ctl);
+    } else {
+        k_low_next<G, G><<<grid, kWG, 0, st>>>(n, kLowFirst, 0, N, T, ctl);
+        k_low_next<A, A><<<grid, kWG, 0, st>>>(n, kLowSteps, 1, N, T, ctl);
+        k_low_root<G, G><<<grid, kWG, 0, st>>>(n, T, cyc_list, ctl);
+    }
+    const unsigned mgrid = grid < 256 ? grid : 256;
+    if (wtype == kWI64)
+        k_low_mark<long long><<<mgrid, kWG, 0, st>>>(succ, N, pi, (const long long*)w, neg, t, cyc_list,
+                                                     rep, onc, wsum, lcnt, tsum, ctl);
+    else
+        k_low_mark<int><<<mgrid, kWG, 0, st>>>(succ, N, pi, (const int*)w, neg, t, cyc_list, rep, onc,
+                                               wsum, lcnt, tsum, ctl);
+}
+
 void launch_loop_select(int n, const int* rep, const unsigned char* onc, const int* pi,
                         const void* w, int wtype, int neg, const int* t, long long* wsum,
                         unsigned* lcnt, long long* tsum, const int* cyc_list, void* scratch,
-                        Ctl* ctl, hipStream_t st)
+                        Ctl* ctl, bool have_sums, hipStream_t st)
 {
-    if (wtype == kWI64)
+    if (have_sums)
+        ;
+    else if (wtype == kWI64)
         k_cyc_sum<long long><<<blocks_for(n), kWG, 0, st>>>(n, rep, onc, pi, (const long long*)w,
                                                             neg, wsum, lcnt, t, tsum, ctl);
     else
@@ -3586,14 +3859,14 @@ void launch_validate_t(int m, const int* t, Ctl* ctl, hipStream_t st)
 void launch_conn_init(int n, const int* rep, const unsigned char* onc, int s, int* layer,
                       unsigned char* onC, unsigned* a1, unsigned* a0, Ctl* ctl, hipStream_t st)
 {
-    k_conn_init<<<stride_grid(n), kWG, 0, st>>>(n, rep, onc, s, layer, onC, a1, a0, ctl, 0, 0, 0);
+    k_conn_init<<<stride_grid(n), kWG, 0, st>>>(n, rep, nullptr, onc, s, layer, onC, a1, a0, ctl, 0, 0, 0);
 }
 
-void launch_loop_conn_init(int n, const int* rep, const unsigned char* onc, unsigned char* onC,
-                           unsigned* a1, unsigned* a0, Ctl* ctl, int policy, unsigned push_min,
+void launch_loop_conn_init(int n, const int* rep, const unsigned* T, const unsigned char* onc,
+                           unsigned char* onC, unsigned* a1, unsigned* a0, Ctl* ctl, int policy, unsigned push_min,
                            hipStream_t st)
 {
-    k_conn_init<<<stride_grid(n), kWG, 0, st>>>(n, rep, onc, -1, nullptr, onC, a1, a0, ctl, 1, policy,
+    k_conn_init<<<stride_grid(n), kWG, 0, st>>>(n, rep, T, onc, -1, nullptr, onC, a1, a0, ctl, 1, policy,
                                                 push_min);
 }
 

@@ -268,6 +268,7 @@ struct Ctx {
     bool chase = false;
     bool filter = false;   // sweeps filtered by the values' byte codes (k_sweep_filter)
     bool coded = false;    // the codes have a scale
+    bool low = true;       // the loop's cycle step by records (k_low_next)
     bool warm = false;     // started from a given policy
     bool tags_clear = false;   // the cycle phase's tag arrays (in ws.layer) are clear
     bool hop_ok = false;   // ws.hop holds the policy's hops (the chase leaves them out)
@@ -1020,6 +1021,8 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
     auto* E = (unsigned long long*)w.Q[0];
     auto* P0 = (unsigned long long*)w.Q[0];
     auto* P1 = (unsigned long long*)w.Q[1];
+    auto* N = (unsigned*)w.Q[0];
+    auto* T = (unsigned*)w.Q[1];
     const int jb = ocm::chase_bits(c.n);
     const bool from_values = start != ocm::kLoopSweep;
     // a warm start's policy mostly reaches C already: its rebuilds do without
@@ -1032,12 +1035,15 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
     unsigned char* tag[2] = {(unsigned char*)w.layer, (unsigned char*)w.layer + c.n};
     int K = 0;
     while ((int64_t(1) << K) < c.n) ++K;
-    if (start == ocm::kLoopCycles && !c.tags_clear) {
-        ocm::launch_fill_u32((unsigned*)w.layer, ((int64_t)c.n * 2 + 3) / 4, 0u, c.st);
-        c.tags_clear = true;   // each cycle phase leaves them clear
-    }
-    ocm::launch_loop_setup(w.ctl, start, ocm::kLoopChain | (c.v32 ? ocm::kLoopV32 : 0u) |
+    auto setup = [&]() {
+        if (start == ocm::kLoopCycles && !c.low && !c.tags_clear) {
+            ocm::launch_fill_u32((unsigned*)w.layer, ((int64_t)c.n * 2 + 3) / 4, 0u, c.st);
+            c.tags_clear = true;   // each cycle phase leaves them clear
+        }
+        ocm::launch_loop_setup(w.ctl, start, ocm::kLoopChain | (c.v32 ? ocm::kLoopV32 : 0u) |
                                              (c.coded ? ocm::kLoopScale : 0u), max_sweeps, c.st);
+    };
+    setup();
     ocm::SweepArgs a = sweep_args(c, false, w.V, 0, 1, w.pi, w.onC);
     a.succ = w.succ;
     a.E = E;
@@ -1048,22 +1054,26 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
     auto general = [&](unsigned mode) -> bool {
         if (mode == ocm::kLoopCycles) {
             kr = 0;   // no rebuild round has run yet
-            if (kc == 0) {
-                const bool have_succ = c.succ_ok;
-                ocm::launch_pj_init(c.n, c.col, w.pi, w.succ, have_succ, P0, w.onc, tag[0], nullptr,
-                                    c.st);
+            if (c.low) {
+                ocm::launch_loop_low_cycles(c.n, c.col, w.pi, w.succ, c.succ_ok, N, T, w.rep, w.onc,
+                                            c.w, c.wtype, c.neg, c.t, w.wsum, w.lcnt,
+                                            c.t ? w.tsum : nullptr, w.cyc, w.ctl, c.st);
+            } else {
+                if (kc == 0)
+                    ocm::launch_pj_init(c.n, c.col, w.pi, w.succ, c.succ_ok, P0, w.onc, tag[0],
+                                        nullptr, c.st);
+                for (int j = 0; j < 12 && kc < K; ++j) {
+                    ++kc;
+                    ocm::launch_pj_round_dev(c.n, kc, kc & 1 ? P0 : P1, kc & 1 ? P1 : P0,
+                                             tag[(kc - 1) & 1], tag[kc & 1], w.ctl, c.st);
+                }
+                ocm::launch_loop_cycles_final(c.n, P0, P1, K, w.rep, w.onc, tag[0], tag[1], w.wsum,
+                                              w.lcnt, c.t ? w.tsum : nullptr, w.cyc, w.ctl, c.st);
             }
-            for (int j = 0; j < 12 && kc < K; ++j) {
-                ++kc;
-                ocm::launch_pj_round_dev(c.n, kc, kc & 1 ? P0 : P1, kc & 1 ? P1 : P0,
-                                         tag[(kc - 1) & 1], tag[kc & 1], w.ctl, c.st);
-            }
-            ocm::launch_loop_cycles_final(c.n, P0, P1, K, w.rep, w.onc, tag[0], tag[1], w.wsum, w.lcnt,
-                                          c.t ? w.tsum : nullptr, w.cyc, w.ctl, c.st);
             ocm::launch_loop_select(c.n, w.rep, w.onc, w.pi, c.w, c.wtype, c.neg, c.t, w.wsum, w.lcnt,
-                                    c.t ? w.tsum : nullptr, w.cyc, w.sel, w.ctl, c.st);
-            ocm::launch_loop_conn_init(c.n, w.rep, w.onc, w.onC, w.abits[1], w.abits[0], w.ctl,
-                                       small ? 1 : 0, kPushMinUnattached, c.st);
+                                    c.t ? w.tsum : nullptr, w.cyc, w.sel, w.ctl, c.low, c.st);
+            ocm::launch_loop_conn_init(c.n, w.rep, c.low ? T : nullptr, w.onc, w.onC, w.abits[1],
+                                       w.abits[0], w.ctl, small ? 1 : 0, kPushMinUnattached, c.st);
         }
         if (start == ocm::kLoopCycles && (mode == ocm::kLoopCycles || c.h.rmode != 0)) {
             if (!small && !c.rev_built) build_reverse(c);
@@ -1107,6 +1117,16 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
     };
     const int pairs = loop_pairs(c);
     unsigned mode = start;
+    auto check_cycles = [&]() -> ocm_status {
+        if (mode != ocm::kLoopCycles) return OCM_OK;
+        if (c.low) {   // jump rounds from here on, and in the solve's later phases
+            c.low = false;
+            setup();
+        } else if (kc >= K) {
+            return fail(OCM_E_HIP, "cycle rounds did not finish");
+        }
+        return OCM_OK;
+    };
     c.h.fsweeps = 0;
     for (;;) {
         const bool gen = mode != ocm::kLoopSweep && mode != ocm::kLoopChase;
@@ -1117,8 +1137,7 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
                 HIP_TRY(hipGetLastError());
                 OCM_TRY(read_ctl(c));
                 mode = c.h.fmode;
-                if (mode == ocm::kLoopCycles && kc >= K)
-                    return fail(OCM_E_HIP, "cycle rounds did not finish");
+                OCM_TRY(check_cycles());
                 if (kr > c.n + 2 * kRoundsPerRead)
                     return fail(OCM_E_HIP, "rebuild rounds did not finish");
                 continue;
@@ -1147,7 +1166,7 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
         c.coded = c.coded || c.h.fsweeps > 0;
         if (c.h.fmode == ocm::kLoopStop) break;
         mode = c.h.fmode;
-        if (mode == ocm::kLoopCycles && kc >= K) return fail(OCM_E_HIP, "cycle rounds did not finish");
+        OCM_TRY(check_cycles());
         if (kr > c.n + 2 * kRoundsPerRead) return fail(OCM_E_HIP, "rebuild rounds did not finish");
     }
     if (start == ocm::kLoopCycles) {
