@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "device_util.h"
+#include "low.h"
 #include "small.h"
 #include "kernels.h"
 
@@ -43,6 +44,8 @@ constexpr int kTieList = 4;   // after the loop: tie left open by the quick test
 // its values are for): a sum that does not fit the packed entries, or a path
 // that two passes did not finish
 constexpr int kPend = 8;
+// cycles by records gave the graph up: left to the jump rounds
+constexpr int kPendCycles = 16;
 
 struct GArrays {              // device arrays with one entry per graph
     long long* W;
@@ -85,6 +88,7 @@ struct BCtl {
     unsigned rounds_open;      // device-driven rebuild rounds of the iteration left unfinished
     unsigned wide32;           // some value left int32: sweeps gather V, not its int32 copy
     unsigned npend;            // value chase: graphs left to the doubling rounds
+    unsigned npendc;           // cycles by records: graphs left to the jump rounds
     // device only from here on (the host reads what is before)
     unsigned vrun_round[32];   // value phase: round r has a graph to advance
     unsigned vlast;            // value phase: slot / buffer parity of the last round's output
@@ -758,11 +762,11 @@ __global__ __launch_bounds__(kWG) void k_chase_close(int G, GArrays ga, int want
     }
 }
 
-// Graphs left to the doubling rounds: back to the mode their values are for.
-__global__ __launch_bounds__(kWG) void k_unpend(int G, GArrays ga, int want)
+// Graphs left to the doubling or the jump rounds: back to their mode.
+__global__ __launch_bounds__(kWG) void k_unpend(int G, GArrays ga, int from, int want)
 {
     for (int g = blockIdx.x * kWG + threadIdx.x; g < G; g += gridDim.x * kWG)
-        if (ga.mode[g] == kPend + want) ga.mode[g] = want;
+        if (ga.mode[g] == from) ga.mode[g] = want;
 }
 
 // ---------------------------------------------------------------------------
@@ -1102,6 +1106,81 @@ __global__ __launch_bounds__(kWG) void k_pj_init(const int2* __restrict__ chunks
     });
 }
 
+// Cycles by records (low.h) of the listed graphs, in place of the jump rounds;
+// vact[4 g + 3]: the graph is given up (k_set_lambda sets it aside).  Entries
+// are read past the L1, or a vertex that circles its cycle sees the lowest one's
+// late.
+__global__ __launch_bounds__(kWG) void k_low_init(const int2* __restrict__ chunks,
+                                                  const unsigned* nch, int T, GArrays ga,
+                                                  const int* __restrict__ succ,
+                                                  unsigned* __restrict__ N,
+                                                  unsigned char* __restrict__ onc)
+{
+    for_each_chunk(chunks, nch, ga.vptr, T, [&](int g, int64_t v0, int64_t v1) {
+        for (int64_t v = v0 + threadIdx.x; v < v1; v += kWG) {
+            N[v] = (unsigned)succ[v];
+            onc[v] = 0;
+        }
+        if (threadIdx.x == 0) ga.best[g] = -1;
+    });
+}
+
+// The first pass's stores may stay in the XCD's L2 (a graph's tiles run on one,
+// but for those the eighths of the list cut through).
+template <bool LAST>
+__global__ __launch_bounds__(kWG) void k_low_next(const int2* __restrict__ chunks,
+                                                  const unsigned* nch, int T, GArrays ga, int steps,
+                                                  unsigned* N, unsigned* __restrict__ Tp)
+{
+    constexpr int A = __HIP_MEMORY_SCOPE_AGENT, ST = LAST ? A : __HIP_MEMORY_SCOPE_WORKGROUP;
+    for_each_tile(chunks, nch, ga.vptr, T, [&](int g, int64_t v0, int nv) {
+        if ((int)threadIdx.x >= nv) return;
+        const int64_t v = v0 + threadIdx.x;
+        bool open;
+        const unsigned j = low_next<A, ST>(N, (unsigned)v, steps, &open);
+        if (!LAST) return;
+        Tp[v] = j;
+        if (open) ga.vact[4 * g + 3] = 1;
+    });
+}
+
+__global__ __launch_bounds__(kWG) void k_low_root(const int2* __restrict__ chunks,
+                                                  const unsigned* nch, int T, GArrays ga,
+                                                  unsigned* Tp, int2* __restrict__ heads, BCtl* bc)
+{
+    constexpr int A = __HIP_MEMORY_SCOPE_AGENT, G = __HIP_MEMORY_SCOPE_WORKGROUP;
+    for_each_tile(chunks, nch, ga.vptr, T, [&](int g, int64_t v0, int nv) {
+        const int64_t v = v0 + threadIdx.x;
+        const bool given_up = __hip_atomic_load(&ga.vact[4 * g + 3], __ATOMIC_RELAXED, A) != 0;
+        bool root = false, open = false;
+        if ((int)threadIdx.x < nv && !given_up) root = low_root<A, G>(Tp, (unsigned)v, &open);
+        if (open) ga.vact[4 * g + 3] = 1;
+        const unsigned slot = wave_append(root, &bc->ncyc);
+        if (root) heads[slot] = make_int2((int)v, g);
+    });
+}
+
+template <typename WT>
+__global__ __launch_bounds__(kWG) void k_low_mark(GArrays ga, const int* __restrict__ succ,
+                                                  const unsigned* __restrict__ N,
+                                                  const int* __restrict__ pi,
+                                                  const WT* __restrict__ w, int neg,
+                                                  int2* __restrict__ heads, int* __restrict__ rep,
+                                                  unsigned char* __restrict__ onc,
+                                                  long long* __restrict__ wsum,
+                                                  unsigned* __restrict__ lcnt, BCtl* bc)
+{
+    low_mark<WT>(
+        bc->ncyc, succ, N, pi, w, neg, nullptr, onc, [&](unsigned i) { return heads[i].x; },
+        [&](unsigned i, int r, int mn, long long W, long long, unsigned len) {
+            rep[r] = mn;
+            heads[i].x = mn;
+            wsum[mn] = W;
+            lcnt[mn] = len;
+        },
+        [&](unsigned i) { ga.vact[4 * heads[i].y + 3] = 1; });
+}
+
 // Rounds a graph of n vertices needs: ceil(log2 n) (2^K >= n covers every
 // policy path and cycle in it).
 __device__ __forceinline__ int graph_rounds(const long long* __restrict__ vptr, int g)
@@ -1227,6 +1306,7 @@ __global__ __launch_bounds__(kWG) void k_vote(const int2* __restrict__ heads, co
     const unsigned nc = bc->ncyc;
     for (unsigned i = blockIdx.x * kWG + threadIdx.x; i < nc; i += gridDim.x * kWG) {
         const int2 h = heads[i];
+        if (ga.vact[4 * h.y + 3]) continue;   // given up: no sums
         int cur = ga.best[h.y];
         while (cur < 0 || rep_less(h.x, cur, wsum, lcnt)) {
             const int prev = atomicCAS(&ga.best[h.y], cur, h.x);
@@ -1238,10 +1318,16 @@ __global__ __launch_bounds__(kWG) void k_vote(const int2* __restrict__ heads, co
 
 __global__ __launch_bounds__(kWG) void k_set_lambda(int G, GArrays ga,
                                                     const long long* __restrict__ wsum,
-                                                    const unsigned* __restrict__ lcnt)
+                                                    const unsigned* __restrict__ lcnt, BCtl* bc)
 {
     for (int g = blockIdx.x * kWG + threadIdx.x; g < G; g += gridDim.x * kWG) {
         if (ga.mode[g] != kGeneral) continue;
+        if (ga.vact[4 * g + 3]) {
+            ga.vact[4 * g + 3] = 0;
+            ga.mode[g] = kPendCycles;
+            atomicAdd(&bc->npendc, 1u);
+            continue;
+        }
         const int r = ga.best[g];
         if (r < 0) {
             ga.mode[g] = kDone;
@@ -1283,9 +1369,11 @@ __device__ __forceinline__ void clear_wave_bits(unsigned* bits, int64_t vb, bool
 // ones (every other graph counts as attached); here every vertex leaves a0
 // and every unattached one leaves a1, so round 1 sees the components as its
 // frontier.  Counts go to cc's lanes (got = components, left = unattached).
+// Tp (nullable): rep is that of Tp[v].
 __global__ __launch_bounds__(kWG) void k_conn_init(const int2* __restrict__ chunks,
                                                    const unsigned* nch, int T, GArrays ga,
                                                    const int* __restrict__ rep,
+                                                   const unsigned* __restrict__ Tp,
                                                    const unsigned char* __restrict__ onc,
                                                    int* __restrict__ layer,
                                                    unsigned char* __restrict__ onC,
@@ -1299,7 +1387,7 @@ __global__ __launch_bounds__(kWG) void k_conn_init(const int2* __restrict__ chun
             const bool live = v < v1;
             bool comp = false;
             if (live) {
-                comp = rep[v] == s;
+                comp = rep[Tp ? (int64_t)Tp[v] : v] == s;
                 if (layer) layer[v] = comp ? 0 : -1;
                 onC[v] = (unsigned char)(comp && onc[v]);
                 ncomp += comp;
@@ -1745,6 +1833,7 @@ struct BCtx {
     bool rev_built = false;
     bool tile_sweep = true;   // improvement sweeps over vertex tiles (else lanes per vertex)
     bool chase = false;       // values by the chase (off once a graph needed the rounds)
+    bool low = false;         // cycles by records
     bool device_rounds = true;   // iterations after the first decide their rounds on the device
     int max_n = 1;
     int64_t loop_G = 0, loop_n = 0;   // graphs and vertices the loop solves (not the small class)
@@ -1985,31 +2074,53 @@ void enqueue_general_head(BCtx& c)
     const int T = c.sch.chunk;
     const unsigned mc = chunk_grid(c);
     enqueue_chunks(c, ocm::b::kGeneral);
-    auto* P0 = (unsigned long long*)ws.Q[0];
-    auto* P1 = (unsigned long long*)ws.Q[1];
-    const int K = jump_rounds(c);
-    ocm::b::k_pj_init<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, ws.succ, P0,
-                                                 ws.onc);
-    for (int k = 0; k < K; ++k)
-        ocm::b::k_pj_round<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, k,
-                                                      k & 1 ? P1 : P0, k & 1 ? P0 : P1);
-    ocm::b::k_pj_final<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, P0, P1, ws.rep,
-                                                  ws.onc);
-    ocm::b::k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->ncyc, nullptr);
-    ocm::b::k_cyc_zero<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, ws.rep, ws.onc,
-                                                  ws.wsum, ws.lcnt, ws.heads, ws.bc);
-    if (c.wtype == OCM_W_I64)
-        ocm::b::k_cyc_sum<long long><<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a,
-                                                                ws.rep, ws.onc, ws.pi,
-                                                                (const long long*)c.w, c.neg,
-                                                                ws.wsum, ws.lcnt);
-    else
-        ocm::b::k_cyc_sum<int><<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, ws.rep,
-                                                          ws.onc, ws.pi, (const int*)c.w, c.neg,
-                                                          ws.wsum, ws.lcnt);
+    auto* N = (unsigned*)ws.Q[0];
+    auto* Tp = (unsigned*)ws.Q[1];
+    if (c.low) {
+        const unsigned tg = tile_grid(c);
+        ocm::b::k_low_init<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, ws.succ, N,
+                                                      ws.onc);
+        ocm::b::k_low_next<false><<<tg, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a,
+                                                             ocm::kLowFirst, N, Tp);
+        ocm::b::k_low_next<true><<<tg, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a,
+                                                            ocm::kLowSteps, N, Tp);
+        ocm::b::k_low_root<<<tg, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, Tp, ws.heads,
+                                                      ws.bc);
+        const unsigned mg = std::min(mc, 512u);
+        if (c.wtype == OCM_W_I64)
+            ocm::b::k_low_mark<long long><<<mg, ocm::kWG, 0, c.st>>>(
+                a, ws.succ, N, ws.pi, (const long long*)c.w, c.neg, ws.heads, ws.rep, ws.onc, ws.wsum,
+                ws.lcnt, ws.bc);
+        else
+            ocm::b::k_low_mark<int><<<mg, ocm::kWG, 0, c.st>>>(a, ws.succ, N, ws.pi, (const int*)c.w,
+                                                               c.neg, ws.heads, ws.rep, ws.onc,
+                                                               ws.wsum, ws.lcnt, ws.bc);
+    } else {
+        auto* P0 = (unsigned long long*)ws.Q[0];
+        auto* P1 = (unsigned long long*)ws.Q[1];
+        const int K = jump_rounds(c);
+        ocm::b::k_pj_init<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, ws.succ, P0,
+                                                     ws.onc);
+        for (int k = 0; k < K; ++k)
+            ocm::b::k_pj_round<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, k,
+                                                          k & 1 ? P1 : P0, k & 1 ? P0 : P1);
+        ocm::b::k_pj_final<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, P0, P1, ws.rep,
+                                                      ws.onc);
+        ocm::b::k_cyc_zero<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, ws.rep, ws.onc,
+                                                      ws.wsum, ws.lcnt, ws.heads, ws.bc);
+        if (c.wtype == OCM_W_I64)
+            ocm::b::k_cyc_sum<long long><<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a,
+                                                                    ws.rep, ws.onc, ws.pi,
+                                                                    (const long long*)c.w, c.neg,
+                                                                    ws.wsum, ws.lcnt);
+        else
+            ocm::b::k_cyc_sum<int><<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, ws.rep,
+                                                              ws.onc, ws.pi, (const int*)c.w, c.neg,
+                                                              ws.wsum, ws.lcnt);
+    }
     ocm::b::k_vote<<<2048, ocm::kWG, 0, c.st>>>(ws.heads, ws.bc, a, ws.wsum, ws.lcnt);
     ocm::b::k_set_lambda<<<ocm::stride_grid(c.G), ocm::kWG, 0, c.st>>>((int)c.G, a, ws.wsum,
-                                                                     ws.lcnt);
+                                                                     ws.lcnt, ws.bc);
     enqueue_chunks(c, ocm::b::kGeneral);   // graphs whose vote failed retired
     // rebuild init: counters and both bitmaps reset (all ones: graphs that
     // are not rebuilt count as attached)
@@ -2018,8 +2129,8 @@ void enqueue_general_head(BCtx& c)
     const int64_t words = ((int64_t)c.n + 31) / 32;
     ocm::launch_fill_u32(ws.abits[0], words, 0xffffffffu, c.st);
     ocm::launch_fill_u32(ws.abits[1], words, 0xffffffffu, c.st);
-    ocm::b::k_conn_init<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, ws.rep, ws.onc,
-                                                   nullptr, ws.onC, ws.abits[1], ws.abits[0], cc);
+    ocm::b::k_conn_init<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, ws.rep,
+                                                   c.low ? Tp : nullptr, ws.onc, nullptr, ws.onC, ws.abits[1], ws.abits[0], cc);
     // the rounds visit only the spans that hold a rebuilt graph
     const int64_t span_verts = (int64_t)32 * ocm::kWG * ocm::round_wpt(c.n);
     ocm::b::k_span_flag<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, span_verts,
@@ -2038,6 +2149,7 @@ void enqueue_head(BCtx& c, int max_iters, bool fast_path)
     launch_bsweep(c, chunk_grid(c), false);
     ocm::b::k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->nactive, &ws.bc->nfast);
     ocm::b::k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->ngeneral, &ws.bc->npend);
+    ocm::b::k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->ncyc, &ws.bc->npendc);
     ocm::b::k_after_sweep<<<ocm::stride_grid(c.G), ocm::kWG, 0, c.st>>>((int)c.G, a, max_iters,
                                                                       ws.bc);
     if (fast_path) enqueue_values(c, ocm::b::kFast);
@@ -2156,23 +2268,32 @@ ocm_status finish_rounds(BCtx& c)
 
 // Graphs whose values the chase left (npend > 0 after an iteration): rebuilt
 // graphs take the doubling rounds, then the fast path's, whose stalled ones go
-// through the general phases.  The batch keeps the rounds from here on.
+// through the general phases, with those whose cycles the records left.  The
+// batch keeps the doubling rounds from here on if it needed them.
 ocm_status finish_pending(BCtx& c)
 {
     BWs& ws = c.ws;
     GArrays& a = ws.ga;
     ocm::Ctl* cc = (ocm::Ctl*)ws.vctl;
-    c.chase = false;
     const unsigned gg = ocm::stride_grid(c.G);
-    ocm::b::k_unpend<<<gg, ocm::kWG, 0, c.st>>>((int)c.G, a, ocm::b::kGeneral);
-    enqueue_values(c, ocm::b::kGeneral);
-    ocm::b::k_unpend<<<gg, ocm::kWG, 0, c.st>>>((int)c.G, a, ocm::b::kFast);
-    enqueue_values(c, ocm::b::kFast);
+    using namespace ocm::b;
+    if (c.h.npend > 0) {
+        c.chase = false;
+        k_unpend<<<gg, ocm::kWG, 0, c.st>>>((int)c.G, a, kPend + kGeneral, kGeneral);
+        enqueue_values(c, kGeneral);
+        k_unpend<<<gg, ocm::kWG, 0, c.st>>>((int)c.G, a, kPend + kFast, kFast);
+        enqueue_values(c, kFast);
+    }
+    k_unpend<<<gg, ocm::kWG, 0, c.st>>>((int)c.G, a, kPendCycles, kGeneral);
+    k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->npend, &ws.bc->npendc);
+    c.low = false;
     enqueue_general_head(c);
     ocm::launch_round_setup_dev(cc, c.rev_built ? 0 : 1, kBPushMin, c.st);
     enqueue_rounds(c, 1, kLoopRounds);
     BHIP(hipGetLastError());
-    return finish_rounds(c);
+    c.low = true;
+    BTRY(finish_rounds(c));
+    return bread(c);
 }
 
 // The fixed parts of an iteration as captured hipGraphs: head and tail
@@ -2697,7 +2818,7 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
         BTRY(build_chunks(c, ocm::b::kActive, &nch));
         loop = nch > 0;
     }
-    c.chase = c.tile_sweep;
+    c.chase = c.low = c.tile_sweep;
     // iterations: [head graph] -> host rebuild rounds -> [tail graph]
     const char* env = getenv("OCM_BATCH_GRAPH");
     const bool use_graph = !(env && env[0] == '0');
@@ -2723,7 +2844,7 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
             else enqueue_values(c, ocm::b::kGeneral);
             BHIP(hipGetLastError());
             if (c.chase) BTRY(bread(c));
-            if (c.chase && c.h.npend > 0) BTRY(finish_pending(c));
+            while (c.h.npend > 0 || c.h.npendc > 0) BTRY(finish_pending(c));
             continue;
         }
         if (use_graph && !lp.iter)
@@ -2737,8 +2858,9 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
             BTRY(finish_rounds(c));
             if (c.chase) BTRY(bread(c));   // its values may have left some pending
         }
-        if (c.h.npend > 0) {
-            BTRY(finish_pending(c));
+        const bool chased = c.chase;
+        while (c.h.npend > 0 || c.h.npendc > 0) BTRY(finish_pending(c));
+        if (chased && !c.chase) {
             if (lp.iter) (void)hipGraphExecDestroy(lp.iter);   // captured with the chase
             lp.iter = nullptr;
         }

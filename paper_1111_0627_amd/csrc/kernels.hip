@@ -15,6 +15,7 @@
 
 #include "kernels.h"
 #include "device_util.h"
+#include "low.h"
 
 namespace ocm {
 
@@ -1175,28 +1176,9 @@ __global__ __launch_bounds__(kWG) void k_loop_cycles_final(
 }
 
 // ---------------------------------------------------------------------------
-// cycles by records, the loop's cycle step.  Jump rounds touch every vertex
-// some log2(depth) + 3 times, each time a gather of 8 bytes and a barrier of a
-// launch (2^22 vertices: 12 to 15 rounds, 560 to 1390 us; 20,000: 13 launches).  Here vertices are
-// ordered by a multiplicative hash of their index, and each finds
-//   N: the first vertex on its path that is lower than itself (k_low_next), by
-//      jumping along the entries of the vertices in between, in place (a vertex
-//      below its whole path, hence on no cycle, ends at the cycle's lowest);
-//   T: the lowest vertex its path reaches (k_low_root), along the N's;
-// a vertex with N = itself is the lowest of its cycle.  Expected 2 to 4 gathers
-// of 4 bytes per vertex and step whatever the numbering, in two launches: as in
-// the value chase an entry seen late is still a vertex of the path with nothing
-// lower before it, so every order of the updates ends in the same N and T.
-// 2^22 vertices: 290 to 600 us with the marks, bound by the gathers; 20,000: 42 us.
-// Sets lfail, for the jump rounds to take over, if a path takes more than
-// kLowSteps steps or a cycle has more than kLowQueue vertices.
+// cycles by records (low.h), the loop's cycle step.  Sets lfail for the jump
+// rounds to take over.
 // ---------------------------------------------------------------------------
-constexpr int kLowSteps = 256;
-constexpr int kLowFirst = 8;   // steps of a large graph's first pass
-constexpr int kLowQueue = 8192;
-
-__device__ __forceinline__ unsigned low_key(unsigned v) { return v * 0x9E3779B1u; }
-
 __global__ __launch_bounds__(kWG) void k_low_init(int n, const int* __restrict__ col,
                                                   const int* __restrict__ pi, int* __restrict__ succ,
                                                   int have_succ, unsigned* __restrict__ N,
@@ -1221,20 +1203,8 @@ __global__ __launch_bounds__(kWG) void k_low_next(int n, int steps, int last, un
 {
     const int64_t v = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kWG + threadIdx.x;
     if (v >= n) return;
-    const unsigned own = low_key((unsigned)v);
-    unsigned j = __hip_atomic_load(&N[v], __ATOMIC_RELAXED, LD);
-    unsigned low = j;   // the lowest vertex passed since the last restart
-    bool open = low_key(j) > own;
-    for (int k = 1; k <= steps && open; ++k) {
-        const unsigned r = __hip_atomic_load(&N[j], __ATOMIC_RELAXED, LD);
-        // at the cycle's lowest, or back at the lowest passed, which is that
-        // (unless it is off the cycle: hence the restarts): a vertex off the
-        // cycle, below its whole path
-        open = r != j && r != low && low_key(r) > own;
-        if (low_key(r) < low_key(low) || (k & 31) == 0) low = r;
-        j = r;
-        __hip_atomic_store(&N[v], j, __ATOMIC_RELAXED, ST);
-    }
+    bool open;
+    const unsigned j = low_next<LD, ST>(N, (unsigned)v, steps, &open);
     if (!last) return;
     T[v] = j;
     if (open) ctl->lfail = 1;
@@ -1245,54 +1215,31 @@ __global__ __launch_bounds__(kWG) void k_low_root(int n, unsigned* T, int* __res
                                                   Ctl* ctl)
 {
     __shared__ unsigned nr, base, fail;
-    if (threadIdx.x == 0) fail = ctl->lfail;   // other workgroups may set it meanwhile
+    if (threadIdx.x == 0) {
+        fail = ctl->lfail;   // other workgroups may set it meanwhile
+        nr = 0;
+    }
     __syncthreads();
     if (fail) return;
     const int64_t v = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kWG + threadIdx.x;
     bool root = false, open = false;
-    if (v < n) {
-        unsigned j = __hip_atomic_load(&T[v], __ATOMIC_RELAXED, LD);
-        root = j == (unsigned)v;
-        open = !root;
-        for (int k = 0; k < kLowSteps && open; ++k) {
-            const unsigned r = __hip_atomic_load(&T[j], __ATOMIC_RELAXED, LD);
-            open = r != j;
-            if (open) {
-                j = r;
-                __hip_atomic_store(&T[v], j, __ATOMIC_RELAXED, ST);
-            }
-        }
-    }
-    if (threadIdx.x == 0) nr = 0;
-    __syncthreads();
+    if (v < n) root = low_root<LD, ST>(T, (unsigned)v, &open);
     const unsigned long long mask = __ballot(root), late = __ballot(open);
     const unsigned lane = threadIdx.x & 63;
     unsigned at = 0;
     if (lane == 0) {
         if (mask) at = atomicAdd(&nr, (unsigned)__popcll(mask));
-        if (late) atomicOr(&nr, 1u << 31);
+        if (late) ctl->lfail = 1;
     }
-    at = __shfl(at, 0, 64) & 0x7fffffffu;
+    at = __shfl(at, 0, 64);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned c = nr & 0x7fffffffu;
-        base = c ? atomicAdd(&ctl->ncyc, c) : 0u;
-        if (nr >> 31) ctl->lfail = 1;
-    }
+    if (threadIdx.x == 0) base = nr ? atomicAdd(&ctl->ncyc, nr) : 0u;
     __syncthreads();
     if (root) roots[base + at + __popcll(mask & ((1ull << lane) - 1ull))] = (int)v;
 }
 
-// Marks the cycles from their lowest vertices and adds up their edges; rep of
-// the lowest becomes the cycle's smallest index (of the other vertices it is
-// rep[T[v]]).  A thread walks a cycle of up to kLowWalk vertices (0.6 us a step
-// on a large graph); longer ones are left to the workgroup: the vertices between
-// v and N[v] are the chain succ(v), N(succ(v)), ... up to N[v], each with those
-// between itself and its own N, which spreads a cycle of l random vertices over
-// the threads in some 2 ln l levels (1000 vertices: 60 us, not 600).  With a
-// workgroup per cycle the walk is given up after kLowWalkFew steps.
-constexpr int kLowWalk = 48, kLowWalkFew = 8;
-
+// The cycles' list changes from their lowest vertices to their smallest indices;
+// rep of the lowest becomes that index (of the other vertices it is rep[T[v]]).
 template <typename WT>
 __global__ __launch_bounds__(kWG) void k_low_mark(const int* __restrict__ succ,
                                                   const unsigned* __restrict__ N,
@@ -1304,107 +1251,26 @@ __global__ __launch_bounds__(kWG) void k_low_mark(const int* __restrict__ succ,
                                                   unsigned* __restrict__ lcnt,
                                                   long long* __restrict__ tsum, Ctl* ctl)
 {
-    __shared__ int q[kLowQueue];
-    __shared__ int longs[kWG];
-    __shared__ unsigned nlong, tail, over;
-    __shared__ int low;
-    const int t = threadIdx.x;
-    if (ctl->fmode != kLoopCycles || ctl->lfail) return;   // uniform: only the last arrival changes them
-    const unsigned nroots = ctl->ncyc;
-    const unsigned walk = nroots <= gridDim.x ? kLowWalkFew : kLowWalk;
-    auto visit = [&](int u, int& mn, long long& W, long long& T) {
-        onc[u] = 1;
-        mn = u < mn ? u : mn;
-        const int e = pi[u];
-        W += wval(w, e, neg);
-        if (tm) T += tm[e];
-    };
-    auto close = [&](unsigned i, int r, int mn, long long W, long long T, unsigned len) {
-        rep[r] = mn;
-        cyc[i] = mn;
-        wsum[mn] = W;
-        lcnt[mn] = len;
-        if (tm) tsum[mn] = T;
-    };
+    if (ctl->fmode != kLoopCycles || ctl->lfail) return;   // only the last arrival changes them
     bool failed = false;   // uniform
-    for (unsigned b = 0; !failed && b * gridDim.x + blockIdx.x < nroots; b += kWG) {
-        if (t == 0) nlong = 0;
-        __syncthreads();
-        const unsigned i = (b + t) * gridDim.x + blockIdx.x;   // neighbours go to different workgroups
-        if (i < nroots) {
-            const int r = cyc[i];
-            int u = r, mn = r;
-            unsigned len = 0;
-            long long W = 0, T = 0;
-            do {
-                visit(u, mn, W, T);
-                u = succ[u];
-                ++len;
-            } while (u != r && len < walk);
-            if (u == r) close(i, r, mn, W, T, len);
-            else longs[atomicAdd(&nlong, 1u)] = (int)i;
-        }
-        __syncthreads();
-        const unsigned nl = nlong;
-        for (unsigned x = 0; x < nl; ++x) {
-            const unsigned li = (unsigned)longs[x];
-            const int r = cyc[li];
-            __syncthreads();   // every thread has read the entry it may overwrite below
-            if (t == 0) {
-                q[0] = r;
-                tail = 1;
-                over = 0;
-                low = r;
-            }
-            __syncthreads();
-            int mn = r;
-            long long W = 0, T = 0;
-            if (t == 0) visit(r, mn, W, T);
-            unsigned lo = 0, hi = 1;
-            while (lo < hi) {
-                for (unsigned y = lo + t; y < hi; y += kWG) {
-                    const int v = q[y], end = (int)N[v];
-                    int u = succ[v];
-                    while (u != end) {
-                        visit(u, mn, W, T);
-                        const unsigned slot = atomicAdd(&tail, 1u);
-                        if (slot >= (unsigned)kLowQueue) {
-                            over = 1;
-                            break;
-                        }
-                        q[slot] = u;
-                        u = (int)N[u];
-                    }
-                }
-                __syncthreads();
-                lo = hi;
-                hi = tail;
-                const bool stop = over != 0;
-                __syncthreads();
-                if (stop) break;
-            }
-            if (over) {   // uniform: read after the barrier
-                failed = true;
-                break;
-            }
-            atomicMin(&low, mn);
-            unsigned long long sums[2] = {(unsigned long long)W, (unsigned long long)T};
-            block_sums_u64(sums);   // two's complement sums
-            __syncthreads();
-            if (t == 0) close(li, r, low, (long long)sums[0], (long long)sums[1], hi);
-            __syncthreads();
-        }
-        __syncthreads();
-    }
-    if (t != 0) return;
+    low_mark<WT>(
+        ctl->ncyc, succ, N, pi, w, neg, tm, onc, [&](unsigned i) { return cyc[i]; },
+        [&](unsigned i, int r, int mn, long long W, long long T, unsigned len) {
+            rep[r] = mn;
+            cyc[i] = mn;
+            wsum[mn] = W;
+            lcnt[mn] = len;
+            if (tm) tsum[mn] = T;
+        },
+        [&](unsigned) { failed = true; });
+    if (threadIdx.x != 0) return;
     unsigned long long tot;
-    if (last_arrival(ctl, arrival_word(0, failed), &tot)) {
-        if ((tot >> 32) & 0xffffu) {
-            ctl->lfail = 1;
-        } else {
-            ctl->jk = 2;
-            ctl->fmode = kLoopSelect;
-        }
+    if (!last_arrival(ctl, arrival_word(0, failed), &tot)) return;
+    if ((tot >> 32) & 0xffffu) {
+        ctl->lfail = 1;
+    } else {
+        ctl->jk = 2;
+        ctl->fmode = kLoopSelect;
     }
 }
 

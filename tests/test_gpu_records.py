@@ -104,3 +104,31 @@ def test_paths_in_the_order_of_the_records(down):
     f[order[:-1]] = order[1:]
     f[order[-1]] = order[-1]
     both(f, np.int64, seed=2)
+
+
+def test_batched(monkeypatch):
+    """One batch of such policies against the jump rounds (kept by sweeps with
+    lanes per vertex); two graphs' cycles are too long for the records."""
+    monkeypatch.setenv("OCM_BATCH_SMALL", "0")
+    monkeypatch.setenv("OCM_BATCH_SOLO", "0")
+    r = np.random.default_rng(5)
+    fs = [cycles(4000, length, True, tails=700) for length in (1, 2, 47, 48, 49, 257, 3000)]
+    fs += [cycles(9000, 8192, True), cycles(9000, 8193, True), cycles(20000, 20000, True)]
+    fs += [r.integers(0, n, n).astype(np.int32) for n in (1, 2, 255, 257, 5000, 60000)]
+    fs += [(np.arange(5000) + d).clip(0, 4999).astype(np.int32) for d in (1, -1)]
+    ns = [len(f) for f in fs]
+    vptr = np.concatenate([[0], np.cumsum(ns)])
+    col = np.empty(2 * vptr[-1], np.int32)
+    w = np.empty(2 * vptr[-1], np.int32)
+    for f, v0 in zip(fs, vptr):
+        at = 2 * (v0 + np.arange(len(f)))
+        col[at], w[at] = v0 + f, r.integers(-40, 40, len(f))
+        col[at + 1], w[at + 1] = v0 + (np.arange(len(f)) + 1) % len(f), r.integers(60, 900, len(f))
+    rp = np.arange(0, 2 * vptr[-1] + 1, 2, dtype=np.int32)
+    dev = [torch.from_numpy(x).cuda() for x in (rp, col, w)]
+    got = []
+    for kw in (dict(), dict(schedule=8)):
+        x = ocm.cycle_mean_batched(*dev, vptr, 2 * vptr, **kw)
+        assert x.status == [0] * len(fs)
+        got.append((x.p, x.q, x.iterations, x.flags, x.cycle_ptr, x.cycle_edges.cpu().tolist()))
+    assert got[0] == got[1]
