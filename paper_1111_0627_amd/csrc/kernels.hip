@@ -1459,6 +1459,7 @@ __global__ __launch_bounds__(kWG) void k_validate_t(int m, const int* __restrict
 // all their in-edges over its threads (every in-edge is visited, and spread
 // rows give coalesced loads; measured faster than the per-wave scheme here).
 constexpr int kLaneRow = 32;
+constexpr int kHeavyUnroll = 8;   // steps in flight past a heavy row's first
 constexpr int kWaves = kWG / 64;
 
 __device__ __forceinline__ bool attached(const unsigned* __restrict__ abits, int v)
@@ -1764,14 +1765,30 @@ __device__ __forceinline__ unsigned wave_attach(int k, int64_t v0, unsigned mask
             const int src = __ffsll((long long)hv) - 1;
             const int hb = __shfl(b, src), he = __shfl(end, src);
             int found = INT32_MAX;
-            for (int e0 = hb; e0 < he; e0 += 64) {
-                const int e = e0 + lane;
-                const unsigned long long bal = __ballot(e < he && attached(acur, col[e]));
-                if (lane == src) *scanned += (unsigned)(he - e0 < 64 ? he - e0 : 64);
-                if (bal) {
-                    found = e0 + __ffsll((long long)bal) - 1;
-                    break;
+            // most rows hit in their first edges; a hub's may scan a million
+            // (a round of one such row, one step of 64 at a time: 3560 us, eight
+            // in flight: 941 us; sixteen, 780 us, spill in k_round_claim, which
+            // cost the 16^6 product 7 %)
+            for (int e0 = hb; e0 < he && found == INT32_MAX;) {
+                constexpr int U = kHeavyUnroll;
+                const int steps = e0 == hb ? 1 : U;
+                int h[U];
+                unsigned a[U];
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    const int e = e0 + 64 * j + lane;
+                    h[j] = j < steps && e < he && e >= e0 ? col[e] : -1;
                 }
+#pragma unroll
+                for (int j = 0; j < U; ++j) a[j] = h[j] >= 0 ? acur[h[j] >> 5] : 0u;
+                const int len = he - e0 < 64 * steps ? he - e0 : 64 * steps;
+                if (lane == src) *scanned += (unsigned)len;
+#pragma unroll
+                for (int j = U - 1; j >= 0; --j) {
+                    const unsigned long long bal = __ballot((a[j] >> (h[j] & 31)) & 1u);
+                    if (bal) found = e0 + 64 * j + __ffsll((long long)bal) - 1;
+                }
+                e0 += len;
             }
             if (lane == src) best = found;
         }
