@@ -27,116 +27,144 @@ struct GCtl {
     unsigned ncomp;     // components that hold a cycle
 };
 
-__global__ __launch_bounds__(kWG) void k_init(int n, unsigned char* __restrict__ alive,
-                                              int* __restrict__ scc)
+// A vertex is unassigned while its scc is -1.  label, for the colouring of one
+// pass: a vertex's colour c while it is unassigned, ~c once it is known to lie in
+// the component of c's root, kAssigned if an earlier pass assigned it; one gather
+// of 4 bytes per edge tells a round all it needs of the head.
+constexpr int kAssigned = INT32_MIN;
+
+// label[v] = v for unassigned vertices
+__global__ __launch_bounds__(kWG) void k_label_init(int n, const int* __restrict__ scc,
+                                                    int* __restrict__ label,
+                                                    int* __restrict__ pushed)
 {
     for (int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x; v < n; v += (int64_t)gridDim.x * kWG) {
-        alive[v] = 1;
-        scc[v] = -1;
+        label[v] = scc[v] < 0 ? (int)v : kAssigned;
+        pushed[v] = kAssigned;
     }
 }
 
-// label[v] = v for unassigned vertices; member[v]: v is its label's root
-__global__ __launch_bounds__(kWG) void k_label_init(int n, const unsigned char* __restrict__ alive,
-                                                    int* __restrict__ label,
-                                                    unsigned char* __restrict__ member)
+// The heads of row [e, end), four at a time: f(u, x[u]) until it returns true.
+template <typename F>
+__device__ __forceinline__ void for_heads(int e, int end, const int* __restrict__ col, const int* x,
+                                          F&& f)
+{
+    for (; e < end; e += 4) {
+        int u[4], y[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) u[j] = e + j < end ? col[e + j] : -1;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = u[j] >= 0 ? x[u[j]] : 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (u[j] >= 0 && f(u[j], y[j])) return;
+    }
+}
+
+// Trim round: an unassigned vertex without an out-edge to another unassigned one
+// is a component of its own.  In place, and not run to its end: what it leaves
+// the colouring finds too.  Chains of such vertices took a colouring pass each
+// (three host reads and some 30 launches; on a sparse graph of 200,000 vertices
+// half of the 84 colouring rounds went).
+__global__ __launch_bounds__(kWG) void k_trim_round(int n, const int* __restrict__ row_ptr,
+                                                    const int* __restrict__ col, int* scc)
 {
     for (int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x; v < n; v += (int64_t)gridDim.x * kWG) {
-        label[v] = alive[v] ? (int)v : INT32_MAX;
-        member[v] = 0;
+        if (scc[v] >= 0) continue;
+        bool stays = false;
+        for_heads(row_ptr[v], row_ptr[v + 1], col, scc,
+                  [&](int u, int x) { return stays = x < 0 && u != (int)v; });
+        if (!stays) scc[v] = (int)v;
     }
 }
 
 // Rounds are queued kRoundsPerRead at a time (r = 1, 2, ...); round r runs only
 // if round r - 1 changed something, so the ones behind the fixpoint return at
-// once.  A read per round cost about 25 us against a round's 15.
-constexpr int kRoundsPerRead = 6;
+// once.  A read costs about 20 us, a round 3 to 8, an idle one 2 (200,000 vertices
+// whole, 6 / 12 rounds per read: 4.38 / 4.31 ms).
+constexpr int kRoundsPerRead = 12;
+constexpr int kTrimRounds = 6;   // at the start of each pass
 
 __device__ __forceinline__ bool round_due(const GCtl* ctl, int r) { return ctl->changed + 1 >= (unsigned)r; }
 
+// Round r changed something.  The word is read first: an atomic per wave of a
+// busy round queued on it for 20 us.
+__device__ __forceinline__ void note_change(GCtl* ctl, int r)
+{
+    if (__hip_atomic_load(&ctl->changed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (unsigned)r)
+        atomicMax(&ctl->changed, (unsigned)r);
+}
+
 // Forward colouring round: every unassigned vertex pushes its label along its
-// out-edges into unassigned heads (atomic minimum).  The fixpoint is unique:
-// label[v] = smallest unassigned vertex that reaches v.
+// out-edges into unassigned heads (atomic minimum), once per label (pushed).  The
+// fixpoint is unique: label[v] = smallest unassigned vertex that reaches v.
 __global__ __launch_bounds__(kWG) void k_label_round(int n, const int* __restrict__ row_ptr,
-                                                     const int* __restrict__ col,
-                                                     const unsigned char* __restrict__ alive,
-                                                     int* __restrict__ label, GCtl* ctl, int r)
+                                                     const int* __restrict__ col, int* label,
+                                                     int* __restrict__ pushed, GCtl* ctl, int r)
 {
     if (block_bcast(!round_due(ctl, r))) return;
-    unsigned ch = 0;
+    bool ch = false;
     for (int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x; v < n; v += (int64_t)gridDim.x * kWG) {
-        if (!alive[v]) continue;
         const int lv = label[v];
-        const int e1 = row_ptr[v + 1];
-        for (int e = row_ptr[v]; e < e1; ++e) {
-            const int u = col[e];
-            if (alive[u] && lv < label[u] && atomicMin(&label[u], lv) > lv) ch = 1;
-        }
+        if (lv < 0 || pushed[v] == lv) continue;
+        pushed[v] = lv;
+        for_heads(row_ptr[v], row_ptr[v + 1], col, label, [&](int u, int x) {
+            if (lv < x && atomicMin(&label[u], lv) > lv) ch = true;
+            return false;
+        });
     }
-    if (__ballot(ch != 0) && (threadIdx.x & 63) == 0) atomicMax(&ctl->changed, (unsigned)r);
+    if (ch) note_change(ctl, r);
 }
 
 // Roots: vertices whose label is their own index.
-__global__ __launch_bounds__(kWG) void k_roots(int n, const unsigned char* __restrict__ alive,
-                                               const int* __restrict__ label,
-                                               unsigned char* __restrict__ member)
+__global__ __launch_bounds__(kWG) void k_roots(int n, int* __restrict__ label)
 {
     for (int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x; v < n; v += (int64_t)gridDim.x * kWG)
-        if (alive[v] && label[v] == (int)v) member[v] = 1;
+        if (label[v] == (int)v) label[v] = ~(int)v;
 }
 
 // Backward closure round: an unassigned vertex with the root's label joins
 // the root's component when one of its out-edges enters a member of that
 // label (it reaches the root, and the root reaches it).
 __global__ __launch_bounds__(kWG) void k_member_round(int n, const int* __restrict__ row_ptr,
-                                                      const int* __restrict__ col,
-                                                      const unsigned char* __restrict__ alive,
-                                                      const int* __restrict__ label,
-                                                      unsigned char* __restrict__ member, GCtl* ctl,
-                                                      int r)
+                                                      const int* __restrict__ col, int* label,
+                                                      GCtl* ctl, int r)
 {
     if (block_bcast(!round_due(ctl, r))) return;
-    unsigned ch = 0;
+    bool ch = false;
     for (int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x; v < n; v += (int64_t)gridDim.x * kWG) {
-        if (!alive[v] || member[v]) continue;
         const int lv = label[v];
-        const int e1 = row_ptr[v + 1];
-        for (int e = row_ptr[v]; e < e1; ++e) {
-            const int u = col[e];
-            if (alive[u] && label[u] == lv && member[u]) {
-                member[v] = 1;
-                ch = 1;
-                break;
-            }
+        if (lv < 0) continue;
+        bool joins = false;
+        for_heads(row_ptr[v], row_ptr[v + 1], col, label, [&](int, int x) { return joins = x == ~lv; });
+        if (joins) {
+            label[v] = ~lv;
+            ch = true;
         }
     }
-    if (__ballot(ch != 0) && (threadIdx.x & 63) == 0) atomicMax(&ctl->changed, (unsigned)r);
+    if (ch) note_change(ctl, r);
 }
 
 // Members take their label (the component's smallest vertex) as component id.
-__global__ __launch_bounds__(kWG) void k_assign(int n, unsigned char* __restrict__ alive,
-                                                const int* __restrict__ label,
-                                                const unsigned char* __restrict__ member,
+__global__ __launch_bounds__(kWG) void k_assign(int n, const int* __restrict__ label,
                                                 int* __restrict__ scc, GCtl* ctl)
 {
     unsigned left = 0;
     for (int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x; v < n; v += (int64_t)gridDim.x * kWG) {
-        if (!alive[v]) continue;
-        if (member[v]) {
-            scc[v] = label[v];
-            alive[v] = 0;
-        } else {
-            ++left;
-        }
+        const int lv = label[v];
+        if (lv == kAssigned) continue;
+        if (lv < 0) scc[v] = ~lv;
+        else ++left;
     }
     const unsigned long long t = block_sum_u64(left);
     if (threadIdx.x == 0 && t) atomicAdd(&ctl->alive, (unsigned)t);
 }
 
 // Component sizes and self-loops (a one-vertex component holds a cycle only
-// through a self-loop).  The lanes of a wave whose component is the first
-// lane's add together: one atomic per vertex of a large component serialised
-// on its counter (1.31 ms on 120,000 vertices, 30 us so).
+// through a self-loop).  The lanes of a wave with the same component add
+// together: one atomic per vertex of a large component serialises on its counter
+// (1.31 ms on 120,000 vertices; 590 us on 200,000 when only those of the first
+// lane's component did, which may be a vertex of its own; 41 us so).
 __global__ __launch_bounds__(kWG) void k_comp_stats(int n, const int* __restrict__ row_ptr,
                                                     const int* __restrict__ col,
                                                     const int* __restrict__ scc,
@@ -145,11 +173,12 @@ __global__ __launch_bounds__(kWG) void k_comp_stats(int n, const int* __restrict
 {
     for (int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x; v < n; v += (int64_t)gridDim.x * kWG) {
         const int c = scc[v];
-        const int c0 = __builtin_amdgcn_readfirstlane(c);
-        const unsigned long long same = __ballot(c == c0);
-        if (c != c0) atomicAdd(&size[c], 1u);
-        else if ((threadIdx.x & 63) == (unsigned)__ffsll((long long)same) - 1u)
-            atomicAdd(&size[c], (unsigned)__popcll(same));
+        for (unsigned long long left = __ballot(true); left;) {
+            const int lead = __ffsll((long long)left) - 1;
+            const unsigned long long same = __ballot(c == __shfl(c, lead, 64)) & left;
+            if ((int)(threadIdx.x & 63) == lead) atomicAdd(&size[c], (unsigned)__popcll(same));
+            left &= ~same;
+        }
         const int e1 = row_ptr[v + 1];
         for (int e = row_ptr[v]; e < e1; ++e)
             if (col[e] == (int)v) self[c] = 1;
@@ -302,7 +331,7 @@ size_t gal(size_t x) { return (x + 255) & ~size_t(255); }
 struct GWs {
     GCtl* ctl;
     void* vctl;                 // control block of the validation kernel
-    unsigned char *alive, *member, *self;
+    unsigned char* self;
     int *label, *scc, *keys, *vals, *keys_s, *perm, *pos;
     unsigned *size, *first, *idx, *stot, *deg, *urp;
     long long *vptr, *eptr;
@@ -339,8 +368,6 @@ GWs gcarve(void* base, int64_t n, int64_t m)
     GWs w;
     w.ctl = (GCtl*)take(sizeof(GCtl));
     w.vctl = take(sizeof(ocm::Ctl));
-    w.alive = (unsigned char*)take(N);
-    w.member = (unsigned char*)take(N);
     w.self = (unsigned char*)take(N);
     w.label = (int*)take(4 * N);
     w.scc = (int*)take(4 * N);
@@ -415,33 +442,35 @@ ocm_status solve_general(const ocm_graph* g, const ocm_options* o_in, void* wsp,
     // components: colour from the smallest unassigned vertex forward, close
     // each root's component backward, repeat on what is left
     GCtl h;
-    ocm::gen::k_init<<<grid, ocm::kWG, 0, st>>>(n, w.alive, w.scc);
+    ocm::launch_fill_u32((unsigned*)w.scc, n, 0xffffffffu, st);
     for (int pass = 0;; ++pass) {
         if (pass > n) return gfail(OCM_E_HIP, "component passes did not finish");
-        ocm::gen::k_label_init<<<grid, ocm::kWG, 0, st>>>(n, w.alive, w.label, w.member);
+        for (int j = 0; j < ocm::gen::kTrimRounds; ++j)
+            ocm::gen::k_trim_round<<<grid, ocm::kWG, 0, st>>>(n, g->row_ptr, g->col, w.scc);
+        ocm::gen::k_label_init<<<grid, ocm::kWG, 0, st>>>(n, w.scc, w.label, w.keys);
         ocm::launch_fill_u32(&w.ctl->changed, 1, 0u, st);
         for (int r = 1;;) {
             if (r > n + 2) return gfail(OCM_E_HIP, "colouring did not converge");
             for (int j = 0; j < ocm::gen::kRoundsPerRead; ++j, ++r)
-                ocm::gen::k_label_round<<<grid, ocm::kWG, 0, st>>>(n, g->row_ptr, g->col, w.alive,
-                                                                   w.label, w.ctl, r);
+                ocm::gen::k_label_round<<<grid, ocm::kWG, 0, st>>>(n, g->row_ptr, g->col, w.label,
+                                                                   w.keys, w.ctl, r);
             GHIP(hipGetLastError());
             if (read_gctl(w, &h, st) != OCM_OK) return OCM_E_HIP;
             if (h.changed + 1 < (unsigned)r) break;   // the last round queued changed nothing
         }
-        ocm::gen::k_roots<<<grid, ocm::kWG, 0, st>>>(n, w.alive, w.label, w.member);
+        ocm::gen::k_roots<<<grid, ocm::kWG, 0, st>>>(n, w.label);
         ocm::launch_fill_u32(&w.ctl->changed, 1, 0u, st);
         for (int r = 1;;) {
             if (r > n + 2) return gfail(OCM_E_HIP, "backward closure did not converge");
             for (int j = 0; j < ocm::gen::kRoundsPerRead; ++j, ++r)
-                ocm::gen::k_member_round<<<grid, ocm::kWG, 0, st>>>(n, g->row_ptr, g->col, w.alive,
-                                                                    w.label, w.member, w.ctl, r);
+                ocm::gen::k_member_round<<<grid, ocm::kWG, 0, st>>>(n, g->row_ptr, g->col, w.label,
+                                                                    w.ctl, r);
             GHIP(hipGetLastError());
             if (read_gctl(w, &h, st) != OCM_OK) return OCM_E_HIP;
             if (h.changed + 1 < (unsigned)r) break;
         }
         ocm::launch_fill_u32(&w.ctl->alive, 1, 0u, st);
-        ocm::gen::k_assign<<<grid, ocm::kWG, 0, st>>>(n, w.alive, w.label, w.member, w.scc, w.ctl);
+        ocm::gen::k_assign<<<grid, ocm::kWG, 0, st>>>(n, w.label, w.scc, w.ctl);
         GHIP(hipGetLastError());
         if (read_gctl(w, &h, st) != OCM_OK) return OCM_E_HIP;
         if (h.alive == 0) break;
