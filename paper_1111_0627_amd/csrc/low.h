@@ -69,19 +69,20 @@ __device__ __forceinline__ bool low_root(unsigned* T, unsigned v, bool* open)
     return root;
 }
 
-// Marks the cycles from their lowest vertices and adds up their edges.  A
-// thread walks a cycle of up to kLowWalk vertices (0.6 us a step on a large
-// graph); longer ones are left to the workgroup: the vertices between v and
-// N[v] are the chain succ(v), N(succ(v)), ... up to N[v], each with those
-// between itself and its own N, which spreads a cycle of l random vertices over
-// the threads in some 2 ln l levels (1000 vertices: 60 us, not 600).  With a
-// workgroup per cycle the walk is given up after kLowWalkFew steps.
+// Marks the cycles from their lowest vertices and adds up their edges: dependent
+// reads, so the loads of a step are issued together and the sums a step behind.
+// A thread walks a cycle of up to kLowWalk vertices; longer ones are left to the
+// workgroup: the vertices between v and N[v] are the chain succ(v), N(succ(v)),
+// ... up to N[v], each with those between itself and its own N, which spreads a
+// cycle of l random vertices over the threads in some 2 ln l levels (1000
+// vertices of 2^20: 46 us, not 600).  With a workgroup per cycle the walk is given up
+// after kLowWalkFew steps.
 constexpr int kLowWalk = 48, kLowWalkFew = 8;
+constexpr int kLowLevel = 2048;   // vertices of two consecutive levels
 
 // All threads of every workgroup call it.  root(i) is the lowest vertex of cycle
 // i < nroots; close(i, r, smallest index, W, T, length) is called once per cycle,
-// or fail(i) (by every thread of a workgroup, with t = threadIdx.x == 0) if it is
-// too long.
+// or fail(i) (by every thread of a workgroup) if it is too long.
 template <typename WT, typename Root, typename Close, typename Fail>
 __device__ __forceinline__ void low_mark(unsigned nroots, const int* __restrict__ succ,
                                          const unsigned* __restrict__ N, const int* __restrict__ pi,
@@ -89,34 +90,34 @@ __device__ __forceinline__ void low_mark(unsigned nroots, const int* __restrict_
                                          const int* __restrict__ tm, unsigned char* __restrict__ onc,
                                          Root&& root, Close&& close, Fail&& fail)
 {
-    __shared__ int q[kLowQueue];
+    __shared__ int all[kLowQueue];                            // the cycle's vertices
+    __shared__ int qn[kLowLevel], qs[kLowLevel];   // their N and succ, by slot mod kLowLevel
     __shared__ int longs[kWG];
     __shared__ unsigned nlong, tail, over;
     __shared__ int low;
     const int t = threadIdx.x;
     const unsigned walk = nroots <= gridDim.x ? kLowWalkFew : kLowWalk;
-    auto visit = [&](int u, int& mn, long long& W, long long& T) {
-        onc[u] = 1;
-        mn = u < mn ? u : mn;
-        const int e = pi[u];
-        W += wval(w, e, neg);
-        if (tm) T += tm[e];
-    };
     for (unsigned b = 0; b * gridDim.x + blockIdx.x < nroots; b += kWG) {
         if (t == 0) nlong = 0;
         __syncthreads();
         const unsigned i = (b + t) * gridDim.x + blockIdx.x;   // neighbours go to different workgroups
         if (i < nroots) {
             const int r = root(i);
-            int u = r, mn = r;
+            int u = r, mn = r, e = -1;
             unsigned len = 0;
             long long W = 0, T = 0;
             do {
-                visit(u, mn, W, T);
-                u = succ[u];
+                const int next = succ[u], e1 = pi[u];
+                const long long we = e >= 0 ? wval(w, e, neg) : 0, te = tm && e >= 0 ? tm[e] : 0;
+                onc[u] = 1;
+                mn = u < mn ? u : mn;
+                W += we;
+                T += te;
+                e = e1;
+                u = next;
                 ++len;
             } while (u != r && len < walk);
-            if (u == r) close(i, r, mn, W, T, len);
+            if (u == r) close(i, r, mn, W + wval(w, e, neg), tm ? T + tm[e] : 0, len);
             else longs[atomicAdd(&nlong, 1u)] = (int)i;
         }
         __syncthreads();
@@ -126,30 +127,31 @@ __device__ __forceinline__ void low_mark(unsigned nroots, const int* __restrict_
             const int r = root(li);
             __syncthreads();   // every thread has read what close() may overwrite
             if (t == 0) {
-                q[0] = r;
+                all[0] = qn[0] = low = r;
+                qs[0] = succ[r];
+                onc[r] = 1;
                 tail = 1;
                 over = 0;
-                low = r;
             }
             __syncthreads();
-            int mn = r;
-            long long W = 0, T = 0;
-            if (t == 0) visit(r, mn, W, T);
             unsigned lo = 0, hi = 1;
             bool stop = false;
             while (lo < hi && !stop) {
                 for (unsigned y = lo + t; y < hi; y += kWG) {
-                    const int v = q[y], end = (int)N[v];
-                    int u = succ[v];
+                    const int end = qn[y % kLowLevel];
+                    int u = qs[y % kLowLevel];
                     while (u != end) {
-                        visit(u, mn, W, T);
+                        const int n = (int)N[u], s = succ[u];
+                        onc[u] = 1;
                         const unsigned slot = atomicAdd(&tail, 1u);
-                        if (slot >= (unsigned)kLowQueue) {
+                        if (slot >= (unsigned)kLowQueue || slot - lo >= (unsigned)kLowLevel) {
                             over = 1;
                             break;
                         }
-                        q[slot] = u;
-                        u = (int)N[u];
+                        all[slot] = u;
+                        qn[slot % kLowLevel] = n;
+                        qs[slot % kLowLevel] = s;
+                        u = n;
                     }
                 }
                 __syncthreads();
@@ -161,6 +163,14 @@ __device__ __forceinline__ void low_mark(unsigned nroots, const int* __restrict_
             if (stop) {   // uniform
                 fail(li);
                 continue;
+            }
+            int mn = r;
+            long long W = 0, T = 0;
+            for (unsigned y = t; y < hi; y += kWG) {
+                const int u = all[y], e = pi[u];
+                mn = u < mn ? u : mn;
+                W += wval(w, e, neg);
+                if (tm) T += tm[e];
             }
             atomicMin(&low, mn);
             unsigned long long sums[2] = {(unsigned long long)W, (unsigned long long)T};
