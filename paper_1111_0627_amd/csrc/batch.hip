@@ -2173,7 +2173,7 @@ ocm_status host_connect(BCtx& c)
         const bool push = left >= (1u << 16) && (uint64_t)front * 2 < left;
         if (push && !c.rev_built) {
             ocm::launch_rev_build(c.n, c.m, c.row_ptr, c.col, ws.rdeg, ws.stot, ws.rin_ptr, ws.rin,
-                                  ws.marks, ws.rscratch, c.st);
+                                  ws.marks, ws.rscratch, false, c.st);
             c.rev_built = true;
         }
         const unsigned* acur = ws.abits[k & 1];

@@ -449,7 +449,7 @@ RevPlan rev_plan(int64_t n, int64_t m);
 size_t rev_scratch_bytes(int64_t n, int64_t m);
 void launch_rev_build(int n, int m, const int* row_ptr, const int* col, unsigned* deg,
                       unsigned* tot, int* rin_ptr, int* rin, unsigned char* marks, void* scratch,
-                      hipStream_t st);
+                      bool scattered, hipStream_t st);
 // gate (nullable): the init does nothing while *gate is 0.  have_succ: succ
 // already holds col[pi]; otherwise it is written.
 // Dhi (nullable): int128 entries, whose high words start sign-extended.

@@ -266,6 +266,7 @@ struct Ctx {
     // values by the packed chase, sweeps and values as one device-driven loop;
     // off for the rest of the solve once a sum does not fit the entries
     bool chase = false;
+    bool scattered = false;   // a large graph whose neighbouring heads lie far apart
     bool filter = false;   // sweeps filtered by the values' byte codes (k_sweep_filter)
     bool coded = false;    // the codes have a scale
     bool low = true;       // the loop's cycle step by records (k_low_next)
@@ -387,7 +388,8 @@ ocm_status validate(Ctx& c, int check_csr, const int* policy = nullptr, bool* ba
     HIP_TRY(hipGetLastError());
     OCM_TRY(read_ctl(c));
     if (policy) *bad_policy = c.h.bad != 0;
-    c.filter = c.n >= kFilterN && 10 * c.h.hlines >= 7u * 64 * ocm::kHeadSamples;
+    c.scattered = c.n >= kFilterN && 10 * c.h.hlines >= 7u * 64 * ocm::kHeadSamples;
+    c.filter = c.scattered;
     c.ngiant = c.h.ngiant;
     if (c.h.err & ocm::kErrBadCsr) return fail(OCM_E_BAD_CSR, "malformed CSR");
     if (c.h.err & ocm::kErrNoOut) return fail(OCM_E_NO_OUT_EDGE, "a vertex has no out-edge");
@@ -658,7 +660,7 @@ void launch_reverse(Ctx& c, hipStream_t st)
 {
     Ws& w = c.ws;
     ocm::launch_rev_build(c.n, c.m, c.row_ptr, c.col, w.rdeg, w.stot, w.rin_ptr, w.rin,
-                          w.marks[0], w.rscratch, st);
+                          w.marks[0], w.rscratch, c.scattered && c.ngiant == 0, st);
     ocm::launch_fill_u32((unsigned*)w.marks[1], ((int64_t)c.n + 3) / 4, 0u, st);
 }
 

@@ -88,3 +88,12 @@ def test_warm_start():
                        schedule=8)
     assert (x.p, x.q, x.iterations, x.tight_edges) == (y.p, y.q, y.iterations, y.tight_edges)
     assert torch.equal(x.potential, y.potential) and torch.equal(x.policy, y.policy)
+
+
+@pytest.mark.parametrize("n,long_rows", [(N, ()), (N + 1, (9, 8192, 7000, 33)), ((1 << 21) + 5, (8191,))])
+def test_reverse_csr_of_scattered_heads(n, long_rows):
+    """Push rounds (which read the reverse CSR) against pull rounds."""
+    dev = [torch.from_numpy(x).cuda() for x in graph(n, (-1000, 1000, np.int32), [85, n], long_rows)]
+    a, b = (ocm.cycle_mean(*dev, connect=k, want_policy=True, want_potential=True) for k in ("auto", "pull"))
+    assert (a.p, a.q, a.iterations, a.connect_rounds) == (b.p, b.q, b.iterations, b.connect_rounds)
+    assert torch.equal(a.policy, b.policy) and torch.equal(a.potential, b.potential)
