@@ -29,7 +29,7 @@ def log(*a):
 
 
 KERNEL_NAMES = {
-    "sweep": "k_sweep_tile / k_tiescan_tile<SWEEP> (policy improvement)",
+    "sweep": "k_sweep_tile / k_tiescan_tile<SWEEP> / k_sweep_filter (policy improvement)",
     "tiescan": "k_tiescan_tile (tight-edge count)",
     "cycles": "k_pj_init/round/final (policy-graph cycles)",
     "select": "k_cyc_zero/sum + k_select (minimum-mean cycle)",
@@ -37,8 +37,8 @@ KERNEL_NAMES = {
     "conn_mark": "k_conn_mark (rebuild, push marks)",
     "conn_claim": "k_conn_claim (rebuild, push claims)",
     "reverse": "k_rev_hist/scatter/place (reverse CSR)",
-    "values": "k_val_init/round/final (values after a rebuild)",
-    "fast": "k_val_init/round/final (values, fast path)",
+    "values": "k_chase_init, k_chase (values after a rebuild)",
+    "fast": "k_chase (values, fast path)",
     "result": "k_cycle_list",
     "validate": "k_validate",
 }
@@ -49,16 +49,17 @@ KERNEL_NAMES = {
 SRC_ROOT = ROOT
 # profile class -> the kernels whose counters give its traffic: the kernels
 # the per-phase profile launches (the device-driven round loops use
-# k_round_*, k_val_round_dev and k_pj_round_dev instead).  Each entry is
-# (kernel, (template argument index, value) or None): the first sweep is
-# k_sweep_tile, the later ones also count tight edges (k_tiescan_tile whose
-# second template argument, SWEEP, is true).
+# k_round_* and k_low_* instead).  Each entry is (kernel, (template argument
+# index, value) or None): the first sweep is k_sweep_tile, the later ones also
+# count tight edges (k_tiescan_tile whose second template argument, SWEEP, is
+# true; k_sweep_filter on large graphs with scattered heads).
 KERNEL_SYMBOL = {
-    "sweep": [("k_sweep_tile", None), ("k_tiescan_tile", (1, "true"))],
+    "sweep": [("k_sweep_tile", None), ("k_tiescan_tile", (1, "true")),
+              ("k_sweep_filter", None)],
     "tiescan": [("k_tiescan_tile", (1, "false"))],
     "conn_mark": [("k_conn_mark", None)], "conn_claim": [("k_conn_claim", None)],
-    "conn_pull": [("k_conn_pull", None)], "values": [("k_val_round", None)],
-    "fast": [("k_val_round", None)], "cycles": [("k_pj_round_tagged", None)],
+    "conn_pull": [("k_conn_pull", None)], "values": [("k_chase", None)],
+    "fast": [("k_chase", None)], "cycles": [("k_pj_round_tagged", None)],
     "reverse": [("k_rev_place", None)],
 }
 
@@ -93,7 +94,8 @@ def class_kernels(table, cls):
 # The sources the single-graph solve is built from (the batched, general and
 # multichain files do not change its kernels).
 DIGEST_FILES = ("include/ocm.h", "paper_1111_0627_amd/csrc/kernels.h",
-                "paper_1111_0627_amd/csrc/device_util.h", "paper_1111_0627_amd/csrc/kernels.hip",
+                "paper_1111_0627_amd/csrc/device_util.h", "paper_1111_0627_amd/csrc/low.h",
+                "paper_1111_0627_amd/csrc/kernels.hip",
                 "paper_1111_0627_amd/csrc/solver.hip", "paper_1111_0627_amd/csrc/batch.hip")
 
 

@@ -2633,7 +2633,7 @@ ocm_status exact_tie(BCtx& c, int64_t g, const int64_t* vptr, const int64_t* ept
 // The loop's graphs one after the other by the single-graph solver, when there
 // are at most this many: an iteration of the loop is about 60 kernels whatever
 // it holds, a fast iteration of the solver two.  One component of 120,000
-// vertices (general_200k): 6.4 ms in the loop, 1.5 ms alone.
+// vertices (of a sparse graph of 200,000): 6.4 ms in the loop, 1.5 ms alone.
 constexpr int64_t kSoloGraphs = 4;
 
 ocm_status solve_solo(BCtx& c, int64_t g, const int64_t* vptr, const int64_t* eptr,

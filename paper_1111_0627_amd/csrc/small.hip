@@ -13,7 +13,7 @@ namespace sm {
 // path included): R1's first sweep; cycles by pointer jumping; per-cycle sums
 // and the (W/L, rep) minimum; breadth-first rebuild rounds; values by the
 // in-place chase; the improvement sweep, a thread per vertex over its row.
-//   * Bound: barriers and LDS latency, about 4 us an iteration at n = 1000.
+//   * Bound: barriers and LDS latency, 8 to 10 us an iteration at n = 1000.
 //     A launch per phase costs about 5 us each on such graphs, and reading the
 //     CSR from L2 in every sweep 6 us, so everything stays on the CU: vertex
 //     numbers and edge positions in 16 bits, weights (and times) in 32.
@@ -21,9 +21,10 @@ namespace sm {
 //   * One array serves as chase entries and as values: a finished entry is
 //     (value << kBits) | s.  A sweep reads the values, and after a barrier its
 //     threads write the next entries.
-//   * Classes (vertices, edges, threads; LDS): 512, 4096, 256 (36 KB, 4 per
-//     CU); 1024, 8192, 512 (71 KB, 2 per CU); 2048, 16384, 1024 (142 KB);
-//     4096, edges in memory, 1024 (92 KB).
+//   * Classes (vertices, edges, threads in a batch; LDS): 512, 4096, 256 (36
+//     KB, 4 per CU); 1024, 8192, 512 (71 KB, 2 per CU); 2048, 16384, 1024 (142
+//     KB); 4096, edges in memory, 1024 (92 KB).  A single solve, alone on its
+//     CU, takes 128 to 512 threads up to 512 vertices and 1024 beyond.
 // Sums that do not fit an entry (kBits for the vertex, 51 and a sign for the
 // sum) end the solve with kSmallFallback: the general path takes the graph.
 // ---------------------------------------------------------------------------
