@@ -440,6 +440,8 @@ void launch_round(int k, int n, const int* row_ptr, const int* col, const int* r
 // rev_scratch_bytes(n, m) bytes (0 when the plan does not apply) the build
 // is partitioned by head bucket; otherwise it counts and fills with global
 // atomics (deg and tot are its counters).  Also clears the mark bytes.
+// scattered: neighbouring edges' heads lie far apart, and no row is giant (the
+// scatter stages its edges in LDS).
 struct RevPlan {
     int64_t buckets, chunk, nblk, hist_len;
     int bits;   // heads per bucket = 2^bits

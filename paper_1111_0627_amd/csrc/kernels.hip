@@ -2215,9 +2215,10 @@ __global__ __launch_bounds__(kWG) void k_rev_fill(int n, const int* __restrict__
 // Partitioned build (no global atomics): edges are binned by head bucket
 // (2^bits heads, bits = 12..14) in LDS, scattered bucket by bucket as
 // (head offset in the bucket: 16 bits, tail: 32 bits) in two arrays, and one
-// workgroup per bucket then counts its edges per head and places them.  When the bucket's in-edges fit in LDS they are
-// placed there and written out in order (scattered 4-byte stores over a
-// bucket's region in HBM cost several times their size in write traffic).
+// workgroup per bucket then counts its edges per head and places them.  When
+// the bucket's in-edges fit in LDS they are placed there and written out in
+// order (scattered 4-byte stores over a bucket's region in HBM cost several
+// times their size in write traffic).
 // The order of a vertex's in-edges is arbitrary; the rounds only test
 // membership.
 constexpr int kRevMinBits = 12;
