@@ -435,7 +435,7 @@ void launch_round(int k, int n, const int* row_ptr, const int* col, const int* r
                   const int* rin, const unsigned* acur, unsigned* anext, unsigned char* marks,
                   unsigned char* marks_next, int* pi, int* layer, Ctl* ctl,
                   unsigned long long* pedges, int policy, unsigned push_min, bool may_push,
-                  bool single, hipStream_t st);
+                  bool single, bool giants, hipStream_t st);
 // Reverse CSR (rin_ptr, rin) of the graph.  With `scratch` of
 // rev_scratch_bytes(n, m) bytes (0 when the plan does not apply) the build
 // is partitioned by head bucket; otherwise it counts and fills with global

@@ -1671,6 +1671,16 @@ struct WaveLds {
     unsigned nb[kWaves][64];    // vertices attached in the round, per word
 };
 
+// Giant rows that a wave leaves to its workgroup: vertex, first edge not tested,
+// row end, and where its bit goes.
+constexpr int kHeavyRows = 16;
+struct HeavyLds {
+    int u[kHeavyRows], e[kHeavyRows], end[kHeavyRows], word[kHeavyRows], bit[kHeavyRows];
+    int wave[kHeavyRows];
+    unsigned n;
+    int pos;
+};
+
 // LDS of a round kernel that claims and then marks (used one after the other).
 union RoundLds {
     WaveLds wave;
@@ -1731,13 +1741,14 @@ __device__ __forceinline__ void wave_candidate(const unsigned* pre, const unsign
 // attaches with its lowest out-edge whose head is in acur, if it has one
 // (pi, layer = k, bit in nb).  Returns the lane's attachments; out-edges
 // examined are added to *scanned.
+template <bool GIANT>
 __device__ __forceinline__ unsigned wave_attach(int k, int64_t v0, unsigned mask,
                                                 const int* __restrict__ row_ptr,
                                                 const int* __restrict__ col,
                                                 const unsigned* __restrict__ acur,
                                                 int* __restrict__ pi, int* __restrict__ layer,
                                                 unsigned* pre, unsigned* msk, unsigned* nb,
-                                                unsigned long long* scanned)
+                                                unsigned long long* scanned, HeavyLds* H)
 {
     const int lane = threadIdx.x & 63;
     nb[lane] = 0;
@@ -1778,6 +1789,7 @@ __device__ __forceinline__ unsigned wave_attach(int k, int64_t v0, unsigned mask
             const int src = __ffsll((long long)hv) - 1;
             const int hb = __shfl(b, src), he = __shfl(end, src);
             int found = INT32_MAX;
+            bool full = false;
             // most rows hit in their first edges; a hub's may scan a million
             // (a round of one such row, one step of 64 at a time: 3560 us, eight
             // in flight: 941 us; sixteen, 780 us, spill in k_round_claim, which
@@ -1802,6 +1814,23 @@ __device__ __forceinline__ unsigned wave_attach(int k, int64_t v0, unsigned mask
                     if (bal) found = e0 + 64 * j + __ffsll((long long)bal) - 1;
                 }
                 e0 += len;
+                if (GIANT && !full && found == INT32_MAX && he - e0 > kGiantRow) {
+                    unsigned slot = 0;
+                    if (lane == src) slot = atomicAdd(&H->n, 1u);
+                    slot = __shfl(slot, src);
+                    full = slot >= (unsigned)kHeavyRows;
+                    if (!full) {
+                        if (lane == src) {
+                            H->u[slot] = u;
+                            H->e[slot] = e0;
+                            H->end[slot] = he;
+                            H->word[slot] = word;
+                            H->bit[slot] = bit;
+                            H->wave[slot] = threadIdx.x >> 6;
+                        }
+                        break;
+                    }
+                }
             }
             if (lane == src) best = found;
         }
@@ -1813,6 +1842,55 @@ __device__ __forceinline__ unsigned wave_attach(int k, int64_t v0, unsigned mask
         }
     }
     wave_lds_sync();
+    return got;
+}
+
+// The rows that the waves of a workgroup left in H, one after the other by all of
+// them (a round of one row of a million edges: 941 us by one wave, 341 so).  All
+// threads call it; it ends with a barrier and H empty.  Returns the attachments in
+// thread 0.
+__device__ __forceinline__ unsigned block_attach(int k, const int* __restrict__ col,
+                                                 const unsigned* __restrict__ acur,
+                                                 int* __restrict__ pi, int* __restrict__ layer,
+                                                 unsigned (*nb)[64], HeavyLds& H)
+{
+    __syncthreads();
+    const unsigned n = H.n < (unsigned)kHeavyRows ? H.n : (unsigned)kHeavyRows;
+    const int t = threadIdx.x, lane = t & 63;
+    unsigned got = 0;
+    for (unsigned i = 0; i < n; ++i) {
+        const int he = H.end[i];
+        int p = INT32_MAX;
+        constexpr int U = kHeavyUnroll;
+        for (int64_t e0 = H.e[i]; e0 < he && p == INT32_MAX; e0 += U * kWG) {
+            if (t == 0) H.pos = INT32_MAX;
+            __syncthreads();
+            const int64_t b = e0 + (t >> 6) * (U * 64) + lane;   // each wave a run of U * 64 edges
+            int h[U];
+            unsigned a[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) h[j] = b + 64 * j < he ? col[b + 64 * j] : -1;
+#pragma unroll
+            for (int j = 0; j < U; ++j) a[j] = h[j] >= 0 ? acur[h[j] >> 5] : 0u;
+            int found = INT32_MAX;
+#pragma unroll
+            for (int j = U - 1; j >= 0; --j)
+                if ((a[j] >> (h[j] & 31)) & 1u) found = (int)(b + 64 * j);
+            if (found != INT32_MAX) atomicMin(&H.pos, found);
+            __syncthreads();
+            p = H.pos;
+            __syncthreads();
+        }
+        if (t == 0 && p != INT32_MAX) {
+            pi[H.u[i]] = p;
+            if (layer) layer[H.u[i]] = k;
+            nb[H.wave[i]][H.word[i]] |= 1u << H.bit[i];
+            ++got;
+        }
+    }
+    __syncthreads();
+    if (t == 0) H.n = 0;
+    __syncthreads();
     return got;
 }
 
@@ -1858,23 +1936,29 @@ __device__ __forceinline__ unsigned take_marks(unsigned char* __restrict__ marks
 // becomes acur plus this round's attachments.  With stale (marks left by a
 // push round before it for this round), their bytes are cleared.  Returns (in
 // thread 0) the workgroup's attachment count.
+template <bool GIANT>
 __device__ __forceinline__ unsigned long long pull_body(
     int k, int n, const int* __restrict__ row_ptr, const int* __restrict__ col,
     const unsigned* __restrict__ acur, unsigned* __restrict__ anext, int* __restrict__ layer,
     int* __restrict__ pi, unsigned long long* ledges, const int* __restrict__ spans,
-    const unsigned* nspans, unsigned char* __restrict__ stale, WaveLds& L)
+    const unsigned* nspans, unsigned char* __restrict__ stale, WaveLds& L, HeavyLds* H)
 {
     const int64_t words = ((int64_t)n + 31) / 32;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     unsigned got = 0;
     unsigned long long scanned = 0;
+    if (GIANT) {
+        if (threadIdx.x == 0) H->n = 0;
+        __syncthreads();
+    }
     for_each_span(spans, nspans, (words + kWG - 1) / kWG, [&](int64_t span) {
         const int64_t w = span * kWG + threadIdx.x;
         const unsigned a = w < words ? acur[w] : 0u;
         const unsigned mask = w < words ? ~a & valid_bits(w, n) : 0u;
         if (stale && w < words) (void)take_marks(stale, w, n);
-        got += wave_attach(k, (w - lane) * 32, mask, row_ptr, col, acur, pi, layer, L.pre[wave],
-                           L.msk[wave], L.nb[wave], &scanned);
+        got += wave_attach<GIANT>(k, (w - lane) * 32, mask, row_ptr, col, acur, pi, layer,
+                                  L.pre[wave], L.msk[wave], L.nb[wave], &scanned, H);
+        if (GIANT) got += block_attach(k, col, acur, pi, layer, L.nb, *H);
         if (w < words) anext[w] = a | L.nb[wave][lane];
     });
     const unsigned long long g = block_sum_u64(got);
@@ -1953,25 +2037,31 @@ __device__ __forceinline__ void mark_body(int n, const int* __restrict__ rin_ptr
 // tails of its attachments, the next round's frontier, in marks_next (the
 // next round's mark array; this round's is marks).  Returns (in thread 0)
 // the workgroup's attachment count.
+template <bool GIANT>
 __device__ __forceinline__ unsigned long long claim_body(
     int k, int n, const int* __restrict__ row_ptr, const int* __restrict__ col,
     const unsigned* __restrict__ acur, unsigned* __restrict__ anext,
     unsigned char* __restrict__ marks, int* __restrict__ pi, int* __restrict__ layer,
     unsigned long long* cedges, const int* __restrict__ spans, const unsigned* nspans,
     const int* __restrict__ rin_ptr, const int* __restrict__ rin,
-    unsigned char* __restrict__ marks_next, unsigned long long* pedges, RoundLds& L)
+    unsigned char* __restrict__ marks_next, unsigned long long* pedges, RoundLds& L, HeavyLds* H)
 {
     const int64_t words = ((int64_t)n + 31) / 32;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     unsigned got = 0;
     unsigned long long scanned = 0, marked = 0;
+    if (GIANT) {
+        if (threadIdx.x == 0) H->n = 0;
+        __syncthreads();
+    }
     for_each_span(spans, nspans, (words + kWG - 1) / kWG, [&](int64_t span) {
         const int64_t w = span * kWG + threadIdx.x;
         const unsigned a = w < words ? acur[w] : 0u;
         // marked tails that are already attached drop out
         const unsigned mask = w < words ? take_marks(marks, w, n) & ~a : 0u;
-        got += wave_attach(k, (w - lane) * 32, mask, row_ptr, col, acur, pi, layer,
-                           L.wave.pre[wave], L.wave.msk[wave], L.wave.nb[wave], &scanned);
+        got += wave_attach<GIANT>(k, (w - lane) * 32, mask, row_ptr, col, acur, pi, layer,
+                                  L.wave.pre[wave], L.wave.msk[wave], L.wave.nb[wave], &scanned, H);
+        if (GIANT) got += block_attach(k, col, acur, pi, layer, L.wave.nb, *H);
         const unsigned x = L.wave.nb[wave][lane];
         if (w < words) anext[w] = a | x;
         if (marks_next) {
@@ -2001,7 +2091,8 @@ __global__ __launch_bounds__(kWG) void k_conn_pull(int k, int n, const int* __re
 {
     __shared__ WaveLds L;
     const unsigned long long g =
-        pull_body(k, n, row_ptr, col, acur, anext, layer, pi, ledges, spans, nspans, stale, L);
+        pull_body<false>(k, n, row_ptr, col, acur, anext, layer, pi, ledges, spans, nspans, stale, L,
+                         nullptr);
     if (threadIdx.x == 0 && g) atomicAdd(&my_lane(ctl).got, (unsigned)g);
 }
 
@@ -2033,9 +2124,9 @@ __global__ __launch_bounds__(kWG) void k_conn_claim(int k, int n, const int* __r
                                                     unsigned long long* pedges)
 {
     __shared__ RoundLds L;
-    const unsigned long long g = claim_body(k, n, row_ptr, col, acur, anext, marks, pi, layer,
+    const unsigned long long g = claim_body<false>(k, n, row_ptr, col, acur, anext, marks, pi, layer,
                                             cedges, spans, nspans, rin_ptr, rin, marks_next,
-                                            pedges, L);
+                                            pedges, L, nullptr);
     if (threadIdx.x == 0 && g) atomicAdd(&my_lane(ctl).got, (unsigned)g);
 }
 
@@ -2078,6 +2169,7 @@ __device__ __forceinline__ bool round_is(const Ctl* c, int k, unsigned mode)
 // them), or a whole pull round (clearing marks round k-1 left).  marks is
 // round k's mark array (marks[k & 1] of the pair).  Not launched when the
 // host expects pushes with their marks left (single, below).
+template <bool GIANT>
 __global__ __launch_bounds__(kWG) void k_round_mark_pull(
     int k, int n, const int* __restrict__ row_ptr, const int* __restrict__ col,
     const int* __restrict__ rin_ptr, const int* __restrict__ rin, const unsigned* __restrict__ acur,
@@ -2085,14 +2177,15 @@ __global__ __launch_bounds__(kWG) void k_round_mark_pull(
     int* __restrict__ layer, Ctl* ctl, unsigned long long* pedges, int policy, unsigned push_min)
 {
     __shared__ RoundLds L;
+    __shared__ HeavyLds H;
     const bool left_marks = ctl->rmarks == (unsigned)k;
     if (round_is(ctl, k, 1u)) {
         if (!left_marks)
             mark_body(n, rin_ptr, rin, acur, anext, marks, pedges, nullptr, nullptr, L.mark);
     } else if (round_is(ctl, k, 2u)) {
         const unsigned long long g =
-            pull_body(k, n, row_ptr, col, acur, anext, layer, pi, nullptr, nullptr, nullptr,
-                      left_marks ? marks : nullptr, L.wave);
+            pull_body<GIANT>(k, n, row_ptr, col, acur, anext, layer, pi, nullptr, nullptr, nullptr,
+                      left_marks ? marks : nullptr, L.wave, &H);
         if (threadIdx.x == 0) round_close(ctl, k, g, policy, push_min, false);
     }
 }
@@ -2159,6 +2252,7 @@ __global__ __launch_bounds__(kWG) void k_round_vertex(int k, int n, const int* _
 // this kernel then runs a pull round itself, and a push round that finds no
 // marks left (a pull came first) as a pull round too, which attaches the
 // same vertices by the same edges.
+template <bool GIANT>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_round_claim(
     int k, int n, const int* __restrict__ row_ptr, const int* __restrict__ col,
     const int* __restrict__ rin_ptr, const int* __restrict__ rin, const unsigned* __restrict__ acur,
@@ -2169,16 +2263,17 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     const bool push = round_is(ctl, k, 1u);
     if (!push && !(single && round_is(ctl, k, 2u))) return;
     __shared__ RoundLds L;
+    __shared__ HeavyLds H;
     const bool left_marks = ctl->rmarks == (unsigned)k;
     if (push && (!single || left_marks)) {
-        const unsigned long long g = claim_body(k, n, row_ptr, col, acur, anext, marks, pi, layer,
+        const unsigned long long g = claim_body<GIANT>(k, n, row_ptr, col, acur, anext, marks, pi, layer,
                                                 nullptr, nullptr, nullptr, rin_ptr, rin,
-                                                marks_next, pedges, L);
+                                                marks_next, pedges, L, &H);
         if (threadIdx.x == 0) round_close(ctl, k, g, policy, push_min, true);
     } else {
         const unsigned long long g =
-            pull_body(k, n, row_ptr, col, acur, anext, layer, pi, nullptr, nullptr, nullptr,
-                      left_marks ? marks : nullptr, L.wave);
+            pull_body<GIANT>(k, n, row_ptr, col, acur, anext, layer, pi, nullptr, nullptr, nullptr,
+                      left_marks ? marks : nullptr, L.wave, &H);
         if (threadIdx.x == 0) round_close(ctl, k, g, policy, push_min, false);
     }
 }
@@ -3995,15 +4090,17 @@ void launch_round(int k, int n, const int* row_ptr, const int* col, const int* r
                   const int* rin, const unsigned* acur, unsigned* anext, unsigned char* marks,
                   unsigned char* marks_next, int* pi, int* layer, Ctl* ctl,
                   unsigned long long* pedges, int policy, unsigned push_min, bool may_push,
-                  bool single, hipStream_t st)
+                  bool single, bool giants, hipStream_t st)
 {
     const unsigned grid = (unsigned)round_spans(n);
     const bool one = single && may_push;
+    auto mark_pull = giants ? k_round_mark_pull<true> : k_round_mark_pull<false>;
+    auto claim = giants ? k_round_claim<true> : k_round_claim<false>;
     if (!one)
-        k_round_mark_pull<<<grid, kWG, 0, st>>>(k, n, row_ptr, col, rin_ptr, rin, acur, anext,
+        mark_pull<<<grid, kWG, 0, st>>>(k, n, row_ptr, col, rin_ptr, rin, acur, anext,
                                                 marks, pi, layer, ctl, pedges, policy, push_min);
     if (may_push)
-        k_round_claim<<<grid, kWG, 0, st>>>(k, n, row_ptr, col, rin_ptr, rin, acur, anext, marks,
+        claim<<<grid, kWG, 0, st>>>(k, n, row_ptr, col, rin_ptr, rin, acur, anext, marks,
                                             marks_next, pi, layer, ctl, pedges, policy, push_min,
                                             one ? 1 : 0);
 }

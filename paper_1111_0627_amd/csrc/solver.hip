@@ -744,7 +744,7 @@ ocm_status connect_rounds_on_device(Ctx& c, int* pi, int* layer, unsigned left, 
             ocm::launch_round(k, c.n, c.row_ptr, c.col, w.rin_ptr, w.rin, w.abits[k & 1],
                               w.abits[(k + 1) & 1], w.marks[k & 1], w.marks[(k + 1) & 1], pi,
                               layer, w.ctl, pedges, policy, kPushMinUnattached, may_push,
-                              k > 1 && guess_push, c.st);
+                              k > 1 && guess_push, c.ngiant > 0, c.st);
         }
         HIP_TRY(hipGetLastError());
         OCM_TRY(read_ctl(c));
@@ -1089,7 +1089,7 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
                     ocm::launch_round(kr, c.n, c.row_ptr, c.col, w.rin_ptr, w.rin, w.abits[kr & 1],
                                       w.abits[(kr + 1) & 1], w.marks[kr & 1], w.marks[(kr + 1) & 1],
                                       w.pi, nullptr, w.ctl, &w.ctl->lane[0].pedges, 0,
-                                      kPushMinUnattached, true, kr > 1, c.st);
+                                      kPushMinUnattached, true, kr > 1, c.ngiant > 0, c.st);
             }
         }
         if (apart && mode == ocm::kLoopCycles) return false;
