@@ -2084,6 +2084,9 @@ void enqueue_general_head(BCtx& c)
     enqueue_chunks(c, ocm::b::kGeneral);
     auto* N = (unsigned*)ws.Q[0];
     auto* Tp = (unsigned*)ws.Q[1];
+    // the heads' list starts empty each time: heads of an earlier pass (of a
+    // graph given up, without sums) must not vote, nor push the list past its end
+    ocm::b::k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->ncyc, &ws.bc->npendc);
     if (c.low) {
         const unsigned tg = tile_grid(c);
         ocm::b::k_low_init<<<mc, ocm::kWG, 0, c.st>>>(ws.chunks, &ws.bc->nchunks, T, a, ws.succ, N,
@@ -2156,7 +2159,6 @@ void enqueue_head(BCtx& c, int max_iters, bool fast_path)
     launch_bsweep(c, chunk_grid(c), false);
     ocm::b::k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->nactive, &ws.bc->nfast);
     ocm::b::k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->ngeneral, &ws.bc->npend);
-    ocm::b::k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->ncyc, &ws.bc->npendc);
     ocm::b::k_after_sweep<<<ocm::stride_grid(c.G), ocm::kWG, 0, c.st>>>((int)c.G, a, max_iters,
                                                                       ws.bc);
     if (fast_path) enqueue_values(c, ocm::b::kFast);
@@ -2294,7 +2296,7 @@ ocm_status finish_pending(BCtx& c)
         enqueue_values(c, kFast);
     }
     k_unpend<<<gg, ocm::kWG, 0, c.st>>>((int)c.G, a, kPendCycles, kGeneral);
-    k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->npend, &ws.bc->npendc);
+    k_bctl_zero<<<1, 64, 0, c.st>>>(&ws.bc->npend, nullptr);
     c.low = false;
     enqueue_general_head(c);
     ocm::launch_round_setup_dev(cc, c.rev_built ? 0 : 1, kBPushMin, c.st);

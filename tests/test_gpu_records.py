@@ -132,3 +132,59 @@ def test_batched(monkeypatch):
         assert x.status == [0] * len(fs)
         got.append((x.p, x.q, x.iterations, x.flags, x.cycle_ptr, x.cycle_edges.cpu().tolist()))
     assert got[0] == got[1]
+
+
+def batch_of(fs, weight):
+    """The graphs of both(), as one batch; weight(g) gives graph g's light edges."""
+    vptr = np.concatenate([[0], np.cumsum([len(f) for f in fs])])
+    col = np.empty(2 * vptr[-1], np.int32)
+    w = np.empty(2 * vptr[-1], np.int32)
+    for g, (f, v0) in enumerate(zip(fs, vptr)):
+        at = 2 * (v0 + np.arange(len(f)))
+        col[at], w[at] = v0 + f, weight(g)
+        col[at + 1], w[at + 1] = v0 + (np.arange(len(f)) + 1) % len(f), 900
+    rp = np.arange(0, 2 * vptr[-1] + 1, 2, dtype=np.int32)
+    return [torch.from_numpy(x).cuda() for x in (rp, col, w)], vptr
+
+
+@pytest.mark.parametrize("fill", [0x00, 0xA5, 0x5A])
+def test_batched_long_cycles_among_others(fill, monkeypatch):
+    """Graphs left to the jump rounds whose long cycle competes with others, of
+    better and worse mean at lower and higher indices, and so many of them that
+    the heads of two passes together would be more than the vertices; whatever
+    the workspace holds before."""
+    monkeypatch.setenv("OCM_BATCH_SMALL", "0")
+    r = np.random.default_rng(11)
+    fs = []
+    for g in range(6):
+        n, long = 24000, 8193 + 97 * g
+        lo = (3000, 0, 11000, 5, 6000, 11001)[g]       # where the long cycle begins
+        body = lo + r.permutation(long)                # its successors shuffled
+        f = np.empty(n, np.int32)
+        f[body] = np.roll(body, -1)
+        rest = np.setdiff1d(np.arange(n), body)
+        f[rest] = rest
+        if g == 0:                                     # cycles of seven, else self-loops
+            k = len(rest) // 7 * 7
+            f[rest[:k]] = np.roll(rest[:k].reshape(-1, 7), -1, 1).ravel()
+        fs.append(f)
+    fs.append(np.arange(40000, dtype=np.int32))        # nothing but self-loops
+
+    def weight(g):
+        x = r.integers(10, 500, len(fs[g]))
+        if g in (0, 3, 5):   # the long cycle wins
+            x[np.arange(len(x)) == fs[g]] = 500
+            x[fs[g] != np.arange(len(x))] //= 2
+        return x
+
+    dev, vptr = batch_of(fs, weight)
+    got = []
+    for kw in (dict(), dict(schedule=8)):
+        ocm.release_workspace()
+        ocm.cycle_mean_batched(*dev, vptr, 2 * vptr, max_iters=1)   # makes the workspace
+        for ws in ocm._bws_cache.values():
+            ws.fill_(fill)
+        x = ocm.cycle_mean_batched(*dev, vptr, 2 * vptr, **kw)
+        assert x.status == [0] * len(fs)
+        got.append((x.p, x.q, x.iterations, x.flags, x.cycle_ptr, x.cycle_edges.cpu().tolist()))
+    assert got[0] == got[1]
