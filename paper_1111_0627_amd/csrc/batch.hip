@@ -1710,16 +1710,18 @@ struct BWs {
     int* small;          // graphs of the small class (solved one per workgroup in LDS)
     void* vctl;          // control block of the validation kernel
     void* sub;           // exact tie test of one graph: its rebased CSR, policy and
-    size_t sub_bytes;    //   single-graph workspace (sized for the largest graph)
+    size_t sub_bytes;    //   single-graph workspace (room for any graph of the batch)
     size_t total;
 };
 
-// Bytes to solve the largest graph of the batch on its own (rebased CSR and
-// policy, then ocm_min's workspace).
+// Bytes to solve any graph of the batch, of at most max_n vertices and max_m
+// edges, on its own (rebased CSR and policy, then ocm_min's workspace, whose
+// reverse build may need more for a graph of fewer edges).
 size_t sub_bytes_for(int64_t max_n, int64_t max_m)
 {
     ocm_graph g{max_n, max_m, (const int32_t*)16, (const int32_t*)16, (const void*)16, OCM_W_I64};
-    const size_t ws = ocm_workspace_size(&g, nullptr);
+    const size_t ws = ocm_workspace_size(&g, nullptr) + ocm::rev_scratch_bound(max_n, max_m) -
+                      ocm::rev_scratch_bytes(max_n, max_m);
     return ws + 4 * (size_t)(max_n + 1) + 4 * (size_t)max_m + 8 * (size_t)max_n + 4 * 256;
 }
 

@@ -449,6 +449,10 @@ struct RevPlan {
 };
 RevPlan rev_plan(int64_t n, int64_t m);
 size_t rev_scratch_bytes(int64_t n, int64_t m);
+// At least rev_scratch_bytes of every graph of at most n vertices and m edges
+// (that is not monotone: past 1024 histogram blocks, and past kRevMaxBuckets
+// buckets, the next larger chunk or bucket halves the histograms).
+size_t rev_scratch_bound(int64_t n, int64_t m);
 void launch_rev_build(int n, int m, const int* row_ptr, const int* col, unsigned* deg,
                       unsigned* tot, int* rin_ptr, int* rin, unsigned char* marks, void* scratch,
                       bool scattered, hipStream_t st);

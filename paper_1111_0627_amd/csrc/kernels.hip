@@ -2653,13 +2653,24 @@ RevPlan rev_plan(int64_t n, int64_t m)
     return p;
 }
 
+static size_t rev_bytes(int64_t m, int64_t hist_len)
+{
+    auto al = [](size_t b) { return (b + 255) / 256 * 256; };
+    return al(4 * (size_t)m) + al(2 * (size_t)m) + 2 * al(4 * (size_t)hist_len) +
+           al(4 * ((size_t)hist_len / 2048 + 2));
+}
+
 size_t rev_scratch_bytes(int64_t n, int64_t m)
 {
     const RevPlan p = rev_plan(n, m);
-    if (!p.partition) return 0;
-    auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-    return al(4 * (size_t)m) + al(2 * (size_t)m) + 2 * al(4 * (size_t)p.hist_len) +
-           al(4 * ((size_t)p.hist_len / 2048 + 2));
+    return p.partition ? rev_bytes(m, p.hist_len) : 0;
+}
+
+size_t rev_scratch_bound(int64_t n, int64_t m)
+{
+    const int64_t heads = (int64_t)1 << kRevMinBits;
+    const int64_t buckets = std::min<int64_t>((n + heads - 1) / heads, kRevMaxBuckets);
+    return rev_bytes(m, buckets * std::min<int64_t>((m + 4095) / 4096, 1024));
 }
 
 // Exclusive prefix sum of len unsigned values (three launches: per-block

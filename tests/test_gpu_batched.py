@@ -430,3 +430,31 @@ def test_more_graphs_than_one_workgroup_lists(monkeypatch):
         cyc = [c - eptr[k] for c in cyc_all[cptr[k]:cptr[k + 1]]]
         assert (p[k], q[k], cyc, iters[k]) == (sol.p, sol.q, sol.cycle.tolist(), sol.iterations), k
         assert bool(flags[k] & ocm.OCM_F_TIE) == bool(sol.tie), k
+
+
+def test_graphs_either_side_of_the_reverse_builds_chunk():
+    """Few large graphs are solved one after the other in one region.  The
+    reverse build's scratch halves where its chunk doubles, at 4096 * 1024
+    edges: the graph with fewer edges needs more room than the larger one."""
+    n, rng = 5000, np.random.default_rng(61)
+    ms = [(4096 << 10) + 1, 4096 << 10, (4096 << 10) - n]
+    rows, cols, ws = [], [], []
+    for k, m in enumerate(ms):
+        deg = np.full(n, m // n) + (np.arange(n) < m % n)
+        rp = np.concatenate([[0], np.cumsum(deg)])
+        col = rng.integers(0, n, m)
+        col[rp[:-1]] = (np.arange(n) + 1) % n
+        rows.append(rp[:-1] + sum(ms[:k]))
+        cols.append(col + k * n)
+        ws.append(rng.integers(1, 1 << 20, m))
+    i32 = np.int32
+    rp, col, w = (np.concatenate(x).astype(i32) for x in (rows + [[sum(ms)]], cols, ws))
+    eptr, vptr = np.concatenate([[0], np.cumsum(ms)]), n * np.arange(len(ms) + 1)
+    dev = [torch.from_numpy(x).cuda() for x in (rp, col, w)]
+    r = ocm.cycle_mean_batched(*dev, vptr, eptr)
+    assert r.status == [ocm.OCM_OK] * len(ms)
+    for k, (e0, e1) in enumerate(zip(eptr[:-1], eptr[1:])):
+        one = ocm.min_cycle_mean((dev[0][k * n:k * n + n + 1] - int(e0)).contiguous(),
+                                 (dev[1][e0:e1] - k * n).contiguous(), dev[2][e0:e1].contiguous())
+        assert (r.p[k], r.q[k], r.iterations[k]) == (one.p, one.q, one.iterations)
+        assert (r.cycle(k) - int(e0)).tolist() == one.cycle_edges.tolist()
