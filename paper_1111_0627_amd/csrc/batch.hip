@@ -348,7 +348,7 @@ __global__ __launch_bounds__(kWG) void k_sweep(const int2* __restrict__ chunks,
             }
             long long best = INT64_MAX;
             int bpos = INT32_MAX;
-            for (int e = beg + lane; e < end; e += G) {
+            for (unsigned e = (unsigned)beg + lane; e < (unsigned)end; e += G) {
                 const long long we = wval(w, e, neg);
                 const long long key = first ? we : V[col[e]] + L * we - W;
                 if (TIE) {
@@ -542,13 +542,13 @@ __global__ __launch_bounds__(kWG) void k_sweep_tile(const int2* __restrict__ chu
                     const long long rown = __shfl(own, l, 64);
                     const int rcur = __shfl(cur, l, 64);
                     const int64_t rv = v0 + (t & ~63) + l;
-                    for (int e = rlo + (t & 63); e < rhi; e += 64)
+                    for (unsigned e = (unsigned)rlo + (t & 63); e < (unsigned)rhi; e += 64)
                         if (key[e - eb] == rown && e != rcur) tight_edge(rv, e);
                     continue;
                 }
                 long long rb = INT64_MAX;
                 int rp = INT32_MAX, rh = 0;
-                for (int e = rlo + (t & 63); e < rhi; e += 64) {
+                for (unsigned e = (unsigned)rlo + (t & 63); e < (unsigned)rhi; e += 64) {
                     const long long k = key[e - eb];
                     if (k < rb) {
                         rb = k;
@@ -2626,7 +2626,7 @@ ocm_status exact_tie(BCtx& c, int64_t g, const int64_t* vptr, const int64_t* ept
     int32_t* cyc = (int32_t*)((char*)pol + bal(4 * (size_t)n));
     char* ws = (char*)cyc + bal(4 * (size_t)n);
     const size_t ws_bytes = c.ws.sub_bytes - (size_t)(ws - b);
-    ocm::b::k_rebase<<<ocm::stride_grid(m + 1), ocm::kWG, 0, c.st>>>(
+    ocm::b::k_rebase<<<ocm::stride_grid((int64_t)m + 1), ocm::kWG, 0, c.st>>>(
         n, m, c.row_ptr + v0, c.col + e0, c.ws.pi + v0, (int)v0, (int)e0, rp, cl, pol);
     BHIP(hipGetLastError());
     ocm_graph sg{n, m, rp, cl, (const char*)c.w + (size_t)c.sw * (size_t)e0, c.wtype};
@@ -2662,7 +2662,7 @@ ocm_status solve_solo(BCtx& c, int64_t g, const int64_t* vptr, const int64_t* ep
     char* ws = (char*)cyc + bal(4 * (size_t)n);
     const size_t ws_bytes = c.ws.sub_bytes - (size_t)(ws - b);
     // pi is not set yet: the rebased policy is ignored
-    ocm::b::k_rebase<<<ocm::stride_grid(m + 1), ocm::kWG, 0, c.st>>>(
+    ocm::b::k_rebase<<<ocm::stride_grid((int64_t)m + 1), ocm::kWG, 0, c.st>>>(
         n, m, c.row_ptr + v0, c.col + e0, c.ws.pi + v0, (int)v0, (int)e0, rp, cl, pol);
     BHIP(hipGetLastError());
     ocm_graph sg{n, m, rp, cl, (const char*)c.w + (size_t)c.sw * (size_t)e0, c.wtype};

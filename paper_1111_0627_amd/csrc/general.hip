@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "device_util.h"
+#include "rows.h"
 #include "kernels.h"
 
 namespace ocm {
@@ -49,16 +50,9 @@ template <typename F>
 __device__ __forceinline__ void for_heads(int e, int end, const int* __restrict__ col, const int* x,
                                           F&& f)
 {
-    for (; e < end; e += 4) {
-        int u[4], y[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) u[j] = e + j < end ? col[e + j] : -1;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) y[j] = u[j] >= 0 ? x[u[j]] : 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (u[j] >= 0 && f(u[j], y[j])) return;
-    }
+    for_row<4>(
+        e, end, [&](unsigned i) { return col[i]; }, [&](int u) { return x[u]; },
+        [&](unsigned, int u, int y) { return f(u, y); });
 }
 
 // Trim round: an unassigned vertex without an out-edge to another unassigned one

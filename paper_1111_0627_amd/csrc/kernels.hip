@@ -120,27 +120,27 @@ __global__ __launch_bounds__(kWG) void k_sweep_u(SweepArgs a, const WT* __restri
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int e = beg[u] + lane;
+            const unsigned e = (unsigned)beg[u] + lane;
             c0[u] = 0;
             w0[u] = 0;
-            if (e < end[u]) {
+            if (e < (unsigned)end[u]) {
                 w0[u] = wval(w, e, a.neg);
                 if (!FIRST) c0[u] = a.col[e];
             }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int e = beg[u] + lane;
+            const unsigned e = (unsigned)beg[u] + lane;
             best[u] = INT64_MAX;
             bpos[u] = INT32_MAX;
-            if (e < end[u]) {
+            if (e < (unsigned)end[u]) {
                 best[u] = FIRST ? w0[u] : a.V[c0[u]] + L * w0[u] - W;
                 bpos[u] = e;
             }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            for (int e = beg[u] + lane + G; e < end[u]; e += G) {
+            for (unsigned e = (unsigned)beg[u] + lane + G; e < (unsigned)end[u]; e += G) {
                 const int64_t we = wval(w, e, a.neg);
                 const int64_t key = FIRST ? we : a.V[a.col[e]] + L * we - W;
                 if (key < best[u]) {
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kWG) void k_sweep_tile(SweepArgs a, const WT* __res
             const int rlo = __shfl(lo, l, 64), rhi = __shfl(hi, l, 64);
             KT rb = val_max<KT>();
             int rp = INT32_MAX, rh = 0;
-            for (int e = rlo + (t & 63); e < rhi; e += 64) {
+            for (unsigned e = (unsigned)rlo + (t & 63); e < (unsigned)rhi; e += 64) {
                 const KT k = key[e - eb];
                 if (k < rb) {
                     rb = k;
@@ -482,7 +482,7 @@ void k_tiescan_tile(SweepArgs a, const WT* __restrict__ w)
             const int rv = (int)(v0 + (t & ~63) + l);
             KT rb = val_max<KT>();
             int rp = INT32_MAX, rh = 0;
-            for (int e = rlo + (t & 63); e < rhi; e += 64) {
+            for (unsigned e = (unsigned)rlo + (t & 63); e < (unsigned)rhi; e += 64) {
                 const KT k = key[e - eb];
                 const int h = head[e - eb];
                 if (SWEEP && k < rb) {
@@ -674,7 +674,7 @@ __global__ __launch_bounds__(kWG) void k_sweep_filter(SweepArgs a, const WT* __r
             const int rv = (int)(v0 + (t & ~63) + l);
             long long k = INT64_MAX;
             int kp = INT32_MAX, kh = 0;
-            for (int e = rlo + (t & 63); e < rhi; e += 64) {
+            for (unsigned e = (unsigned)rlo + (t & 63); e < (unsigned)rhi; e += 64) {
                 if (e == rcur || !low(e - eb, rown)) continue;
                 ++pass;
                 const int h = head[e - eb];
@@ -817,7 +817,7 @@ __global__ __launch_bounds__(kWG) void k_giant_part(SweepArgs a, const WT* __res
         int pos = INT32_MAX, bh = 0;
         // lanes stride over the chunk: each keeps its lowest position among
         // equal keys
-        for (int e = c0 + t; e < c1; e += kWG) {
+        for (unsigned e = (unsigned)c0 + t; e < (unsigned)c1; e += kWG) {
             const int h = a.col[e];
             const long long wl = wval(w, e, a.neg);
             KT k;
@@ -1766,20 +1766,20 @@ __device__ __forceinline__ unsigned wave_attach(int k, int64_t v0, unsigned mask
         const bool heavy = end - b > kLaneRow;
         int best = INT32_MAX;
         if (u >= 0 && !heavy) {
-            for (int e = b; e < end; e += 4) {
+            for (unsigned e = b; e < (unsigned)end; e += 4) {
                 int h[4];
                 unsigned a[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) h[j] = e + j < end ? col[e + j] : -1;
+                for (int j = 0; j < 4; ++j) h[j] = e + j < (unsigned)end ? col[e + j] : -1;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) a[j] = h[j] >= 0 ? acur[h[j] >> 5] : 0u;
                 int hit = -1;
 #pragma unroll
                 for (int j = 3; j >= 0; --j)
                     if ((a[j] >> (h[j] & 31)) & 1u) hit = j;
-                *scanned += (unsigned)(end - e < 4 ? end - e : 4);
+                *scanned += end - e < 4 ? end - e : 4;
                 if (hit >= 0) {
-                    best = e + hit;
+                    best = (int)e + hit;
                     break;
                 }
             }
@@ -1801,8 +1801,8 @@ __device__ __forceinline__ unsigned wave_attach(int k, int64_t v0, unsigned mask
                 unsigned a[U];
 #pragma unroll
                 for (int j = 0; j < U; ++j) {
-                    const int e = e0 + 64 * j + lane;
-                    h[j] = j < steps && e < he && e >= e0 ? col[e] : -1;
+                    const unsigned e = (unsigned)e0 + 64 * j + lane;
+                    h[j] = j < steps && e < (unsigned)he ? col[e] : -1;
                 }
 #pragma unroll
                 for (int j = 0; j < U; ++j) a[j] = h[j] >= 0 ? acur[h[j] >> 5] : 0u;
@@ -2214,24 +2214,25 @@ __global__ __launch_bounds__(kWG) void k_round_vertex(int k, int n, const int* _
     }
     const bool long_row = end - b > kLongRow;
     if (!long_row)
-        for (int e = b; e < end && found < 0; e += 4) {
+        for (unsigned e = b; e < (unsigned)end && found < 0; e += 4) {
             int h[4];
             unsigned bit[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) h[u] = col[e + u < end ? e + u : end - 1];
+            for (int u = 0; u < 4; ++u) h[u] = col[e + u < (unsigned)end ? e + u : end - 1];
 #pragma unroll
             for (int u = 0; u < 4; ++u) bit[u] = attached(acur, h[u]);
 #pragma unroll
             for (int u = 3; u >= 0; --u)
-                if (bit[u] && e + u < end) found = e + u;
+                if (bit[u] && e + u < (unsigned)end) found = (int)e + u;
         }
     for (unsigned long long lm = __ballot(long_row); lm; lm &= lm - 1) {
         const int l = __ffsll((long long)lm) - 1;
         const int rb = __shfl(b, l, 64), re = __shfl(end, l, 64);
         int f = -1;
-        for (int e = rb; e < re && f < 0; e += 64) {
-            const unsigned long long hit = __ballot(e + lane < re && attached(acur, col[e + lane]));
-            if (hit) f = e + __ffsll((long long)hit) - 1;
+        for (unsigned e = rb; e < (unsigned)re && f < 0; e += 64) {
+            const unsigned long long hit =
+                __ballot(e + lane < (unsigned)re && attached(acur, col[e + lane]));
+            if (hit) f = (int)e + __ffsll((long long)hit) - 1;
         }
         if (lane == l) found = f;
     }
@@ -2300,7 +2301,7 @@ __global__ __launch_bounds__(kWG) void k_rev_fill(int n, const int* __restrict__
     const int lane = threadIdx.x & (G - 1);
     const int64_t ngroups = (int64_t)gridDim.x * (kWG / G);
     for (int64_t u = ((int64_t)blockIdx.x * kWG + threadIdx.x) / G; u < n; u += ngroups) {
-        for (int e = row_ptr[u] + lane, end = row_ptr[u + 1]; e < end; e += G) {
+        for (unsigned e = (unsigned)row_ptr[u] + lane, end = row_ptr[u + 1]; e < end; e += G) {
             const unsigned pos = atomicAdd(&cursor[col[e]], 1u);
             rin[pos] = (int)u;
         }
@@ -2424,7 +2425,7 @@ __global__ __launch_bounds__(kWG) void k_rev_scatter(int n, const int* __restric
         }
         int v[U];
 #pragma unroll
-        for (int j = 0; j < U; ++j) v[j] = lo[j] + lane < hi[j] ? col[lo[j] + lane] : -1;
+        for (int j = 0; j < U; ++j) v[j] = lane < hi[j] - lo[j] ? col[lo[j] + lane] : -1;
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             const int u = ub + j * kGroups;
@@ -2433,7 +2434,7 @@ __global__ __launch_bounds__(kWG) void k_rev_scatter(int n, const int* __restric
                 hlo[pos] = (unsigned short)(v[j] & hmask);
                 tails[pos] = u;
             }
-            for (int e = lo[j] + lane + G; e < hi[j]; e += G) {   // out-degree above G
+            for (unsigned e = (unsigned)lo[j] + lane + G; e < (unsigned)hi[j]; e += G) {   // out-degree above G
                 const int x = col[e];
                 const unsigned pos = atomicAdd(&cur[x >> bits], 1u);
                 hlo[pos] = (unsigned short)(x & hmask);
@@ -2525,7 +2526,7 @@ __global__ __launch_bounds__(kScatterWG) void k_rev_scatter_lds(int n, const int
             }
             int v[U];
 #pragma unroll
-            for (int j = 0; j < U; ++j) v[j] = lo[j] + lane < hi[j] ? col[lo[j] + lane] : -1;
+            for (int j = 0; j < U; ++j) v[j] = lane < hi[j] - lo[j] ? col[lo[j] + lane] : -1;
 #pragma unroll
             for (int j = 0; j < U; ++j) {
                 const int u = ub + j * kGroups;
@@ -2534,7 +2535,7 @@ __global__ __launch_bounds__(kScatterWG) void k_rev_scatter_lds(int n, const int
                     head[pos] = v[j];
                     tail[pos] = u;
                 }
-                for (int e = lo[j] + lane + G; e < hi[j]; e += G) {   // out-degree above G
+                for (unsigned e = (unsigned)lo[j] + lane + G; e < (unsigned)hi[j]; e += G) {   // out-degree above G
                     const int x = col[e];
                     const unsigned q = atomicAdd(&cur[x >> bits], 1u);
                     head[q] = x;
@@ -3296,7 +3297,7 @@ __global__ __launch_bounds__(kWG) void k_tie_short_walk(SweepArgs a, const WT* _
         if (a.giant.ngiant > 0 && end - beg > kGiantRow) continue;   // k_giant_short_walk
         const KT own = load_val<VM>(a.V, a.Vhi, a.V32, v);
         const int cur = a.pi[v];
-        for (int e = beg + lane; e < end; e += G) {
+        for (unsigned e = (unsigned)beg + lane; e < (unsigned)end; e += G) {
             if (e == cur) continue;
             const int y = a.col[e];
             if (a.hop[y] < a.hop[v]) continue;
@@ -3342,7 +3343,7 @@ __global__ __launch_bounds__(kWG) void k_giant_short_walk(SweepArgs a, const WT*
         const int v = g.cv[c];
         const KT own = load_val<VM>(a.V, a.Vhi, a.V32, v);
         const int cur = a.pi[v], hv = a.hop[v];
-        for (int e = g.cs[c] + (int)threadIdx.x; e < g.ce[c]; e += kWG) {
+        for (unsigned e = (unsigned)g.cs[c] + threadIdx.x; e < (unsigned)g.ce[c]; e += kWG) {
             if (e == cur) continue;
             const int y = a.col[e];
             if (a.hop[y] < hv) continue;

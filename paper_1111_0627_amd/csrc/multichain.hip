@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kWG) void k_mc_sweep(McArgs a, const WT* __restrict
             const bool on_c = TIE && a.onC[v];
             // giant rows are left to k_mc_giant_part / k_mc_giant_merge
             const bool giant = a.giant.ngiant > 0 && e1 - e0 > kGiantRow;
-            for (int e = opt && !giant ? e0 + lane : e1; e < e1; e += G) {
+            for (unsigned e = opt && !giant ? (unsigned)e0 + lane : e1; e < (unsigned)e1; e += G) {
                 const int u = a.col[e];
                 const Jmp ru = a.R[u];
                 const long long gw = a.wsum[ru.J], gl = (long long)a.lcnt[ru.J];
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(kWG) void k_mc_giant_part(McArgs a, const WT* __res
         const bool on_c = TIE && a.onC[v];
         long long bw = 0, bl = 1, bb = 0;
         int pos = INT_MAX, bh = 0;
-        for (int e = opt ? g.cs[c] + t : g.ce[c]; e < g.ce[c]; e += kWG) {
+        for (unsigned e = opt ? (unsigned)g.cs[c] + t : g.ce[c]; e < (unsigned)g.ce[c]; e += kWG) {
             const int u = a.col[e];
             const Jmp ru = a.R[u];
             const long long gw = a.wsum[ru.J], gl = (long long)a.lcnt[ru.J];
