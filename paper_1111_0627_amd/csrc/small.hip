@@ -25,12 +25,26 @@ namespace sm {
 //     KB, 4 per CU); 1024, 8192, 512 (71 KB, 2 per CU); 2048, 16384, 1024 (142
 //     KB); 4096, edges in memory, 1024 (92 KB).  A single solve, alone on its
 //     CU, takes 128 to 512 threads up to 512 vertices and 1024 beyond.
+//   * A thread walks its vertex's row, a wave the rows of more than kLongEdges
+//     edges, the whole workgroup those of more than kWideEdges: see below.
 // Sums that do not fit an entry (kBits for the vertex, 51 and a sign for the
 // sum) end the solve with kSmallFallback: the general path takes the graph.
 // ---------------------------------------------------------------------------
 constexpr int kBits = 12;
 constexpr unsigned long long kMask = (1ull << kBits) - 1;
 static_assert(kSmallMaxN <= (1 << kBits), "vertex numbers fit the entry");
+
+// Rows that one thread would keep the others waiting for, four edges at a time:
+// long ones take a wave each, wide ones all waves.  Whole solves, by a thread / so
+// (launches per phase: the general path), us: 4000 vertices with a hub to all of
+// them 13500 / 765 (3016), 700 with a row of 30,000 edges 42200 / 209 (1728), 4000
+// with a row of 50,000 99300 / 630 (2651).  The lines: 500 rows of 100 to 129
+// edges 945 with long rows from 65 on, 1450 from 129 on; 1000 rows of 50 to 65
+// 1136 so, 1440 from 33 on.  The hub of 4000 by all waves 769, by one 931, the row
+// of 50,000 630 and 2349; ten rows of 1000 by a wave each 350, by all 615.
+constexpr int kLongEdges = 64, kWideEdges = 2048;
+constexpr int kRowSteps = 4;   // edges a lane has in flight on them
+constexpr int kWideRows = kSmallMaxM / (kWideEdges + 1);
 
 // a before b in the order (W / L, rep); r < 0: none.
 __device__ __forceinline__ bool cand_less(long long aw, long long al, int ar, long long bw,
@@ -58,6 +72,11 @@ struct Lds {
     unsigned short rep[N];               // smallest vertex of the reached cycle
     unsigned short layer[N];             // rebuild round (0xffff unattached); heads; alive
     unsigned char onc[N];                // 1 on a policy cycle, 3 on C
+    unsigned short longs[(M > 0 ? M : kSmallMaxM) / (kLongEdges + 1) + 1];   // long rows' vertices
+    unsigned short wides[kWideRows + 1];                                     // wide rows' vertices
+    unsigned nlong, nwide;
+    long long wk[1024 / 64];             // a wide row's best by wave: key, edge, head
+    int wp[1024 / 64], wh[1024 / 64];
     unsigned acc[2][4];                  // sweep: changed, broken, tight, certain (by parity)
     unsigned got[3];                     // rebuild rounds: vertices attached
     unsigned stall, over, cnt, flag;
@@ -91,6 +110,91 @@ struct View {
         return M > 0 && lds ? (int)S.c[e] : col[e0 + e] - v0;
     }
 };
+
+// The best edge of a row over a wave's lanes, ties to the lowest position (every
+// lane gets it; no edge: arg = INT32_MAX), from edge first on in steps of `step`
+// runs of 64 lanes with U edges each.  FIRST: by weight alone.  Else by the head's value too,
+// and the tight edges other than cur are counted as in the sweep.
+template <bool FIRST, typename WT, int N, int M, bool RATIO>
+__device__ __forceinline__ void wave_row(const View<WT, N, M, RATIO>& g, long long L, long long W,
+                                         int v, int first, int end, int step, int cur, long long own,
+                                         bool onC, long long& best, int& arg, int& bh,
+                                         unsigned& tight, unsigned& certain)
+{
+    constexpr int U = kRowSteps;
+    best = INT64_MAX;
+    arg = INT32_MAX;
+    bh = 0;
+    for (int eb = first + (threadIdx.x & 63); eb < end; eb += 64 * U * step) {
+        int x[U];
+        long long key[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = eb + 64 * u < end ? eb + 64 * u : end - 1;
+            x[u] = g.head(e);
+            key[u] = FIRST ? g.weight(e) : L * g.weight(e) - (RATIO ? W * g.time(e) : W);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (!FIRST) key[u] += (long long)g.S.E[x[u]] >> kBits;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = eb + 64 * u;
+            if (e >= end) break;
+            if (key[u] < best) {
+                best = key[u];
+                arg = e;
+                bh = x[u];
+            }
+            if (!FIRST && key[u] == own && e != cur) {
+                ++tight;
+                certain += x[u] == v || onC;
+            }
+        }
+    }
+    wave_argmin<long long, true>(best, arg, bh);
+}
+
+// done(v, best, arg, head) for every listed row, by every lane of the wave that
+// scanned it (of the first one for the wide rows).  All threads call it.
+template <bool FIRST, typename WT, int N, int M, bool RATIO, typename F>
+__device__ __forceinline__ void listed_rows(const View<WT, N, M, RATIO>& g, int nl, int nw,
+                                            long long L, long long W, unsigned& tight,
+                                            unsigned& certain, F&& done)
+{
+    Lds<N, M, RATIO>& S = g.S;
+    const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    for (int i = wave; i < nl; i += waves) {
+        const int v = S.longs[i];
+        long long best;
+        int arg, bh;
+        wave_row<FIRST>(g, L, W, v, S.rb[v], S.rb[v + 1], 1, S.pi[v], (long long)S.E[v] >> kBits,
+                        S.onc[v] == 3, best, arg, bh, tight, certain);
+        done(v, best, arg, bh);
+    }
+    for (int i = 0; i < nw; ++i) {
+        const int v = S.wides[i];
+        long long best;
+        int arg, bh;
+        wave_row<FIRST>(g, L, W, v, S.rb[v] + 64 * kRowSteps * wave, S.rb[v + 1], waves, S.pi[v],
+                        (long long)S.E[v] >> kBits, S.onc[v] == 3, best, arg, bh, tight, certain);
+        if ((threadIdx.x & 63) == 0) {
+            S.wk[wave] = best;
+            S.wp[wave] = arg;
+            S.wh[wave] = bh;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const int l = threadIdx.x < (unsigned)waves ? threadIdx.x : 0;
+            best = S.wk[l];
+            arg = S.wp[l];
+            bh = S.wh[l];
+            wave_argmin<long long, true>(best, arg, bh);
+            done(v, best, arg, bh);
+        }
+        __syncthreads();   // the next row reuses wk
+    }
+}
 
 // In-place chase of every vertex to s (see k_chase): at most n steps, each at
 // least one policy edge, so a vertex that has not arrived by then never does.
@@ -139,83 +243,15 @@ struct Run {
     bool tie;
 };
 
-// The whole solve; every thread returns the same Run.  row_ptr[0..n] holds the
-// rows' edge positions (e0 = row_ptr[0] when the CSR is known to be sound).
-template <typename WT, int N, int M, bool RATIO>
-__device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
-                          const int* __restrict__ row_ptr, const int* __restrict__ col,
-                          const WT* __restrict__ w, const int* __restrict__ tm, bool neg,
-                          const SmallOpts& o, const int* __restrict__ init, Run& R)
+// From the first sweep, or the warm start's policy, to the end.  LISTED: there
+// are nl long and nw wide rows.  (Without, their tests alone cost 2 to 8 %.)
+template <bool LISTED, typename WT, int N, int M, bool RATIO>
+__device__ __forceinline__ void iterate(const View<WT, N, M, RATIO>& g, int nl, int nw, int n, int e0,
+                                        const SmallOpts& o, const int* __restrict__ init, Run& R)
 {
+    Lds<N, M, RATIO>& S = g.S;
     const int t = threadIdx.x, B = blockDim.x;
     constexpr int VPT = kVpt<N>;
-    R = Run{};
-    R.status = OCM_OK;
-    R.s = 0;
-    R.L = 1;
-    // rows, edges, validation (as k_validate), the weight bound
-    if (t == 0) {
-        S.err = 0;
-        S.maxw = 0;
-        S.maxt = 1;
-        S.cap = 0;
-        S.stall = S.over = 0;
-        for (int p = 0; p < 2; ++p)
-            for (int i = 0; i < 4; ++i) S.acc[p][i] = 0;
-    }
-    __syncthreads();
-    {
-        unsigned err = 0;
-        for (int v = t; v < n; v += B) {
-            const int b = row_ptr[v], x = row_ptr[v + 1];
-            if (o.validate) {
-                if ((v == 0 && b != e0) || (v == n - 1 && x != e0 + m) || b < e0 || x > e0 + m || b > x)
-                    err |= kErrBadCsr;
-                else if (b == x) err |= kErrNoOut;
-            }
-            S.rb[v] = (unsigned short)(b - e0);
-            if (v == n - 1) S.rb[n] = (unsigned short)(x - e0);
-        }
-        unsigned long long mw = 0;
-        int mt = 1;
-        bool bad_t = false;
-        for (int e = t; e < m; e += B) {
-            const int h = col[e0 + e] - v0;
-            if (o.validate && (h < 0 || h >= n)) err |= kErrBadCsr;
-            const long long x = (long long)w[e0 + e];
-            const unsigned long long ax = uabs64(x);
-            mw = ax > mw ? ax : mw;
-            if (M > 0) {
-                S.c[e] = (unsigned short)h;
-                S.w[e] = (int)x;
-            }
-            if (RATIO) {
-                const int y = tm[e0 + e];
-                bad_t |= y < 1;
-                mt = y > mt ? y : mt;
-                if (M > 0) S.t[e] = y;
-            }
-        }
-        if (err) atomicOr(&S.err, err);
-        if (bad_t) atomicOr(&S.cap, 1u);
-        mw = wave_max_u64(mw);
-        if ((t & 63) == 0) atomicMax(&S.maxw, mw);
-        if (RATIO) atomicMax(&S.maxt, (unsigned)mt);
-    }
-    __syncthreads();
-    const unsigned long long maxw = S.maxw;
-    if (S.err & kErrBadCsr) R.status = OCM_E_BAD_CSR;
-    else if (S.err & kErrNoOut) R.status = OCM_E_NO_OUT_EDGE;
-    else if (S.cap) R.status = OCM_E_INVALID_ARG;
-    else if ((unsigned __int128)2 * (unsigned)n * maxw * S.maxt >= ((unsigned __int128)1 << 62) &&
-             o.bound)
-        R.status = OCM_E_OVERFLOW;
-    if (R.status != OCM_OK) {
-        R.tight = R.status == OCM_E_INVALID_ARG ? 1u : 0u;   // which argument: times
-        return;
-    }
-    const View<WT, N, M, RATIO> g{S, col, w, tm, v0, e0, neg, maxw <= (unsigned long long)INT32_MAX};
-
     if (init) {
         bool bad = false;
         for (int v = t; v < n; v += B) {
@@ -231,8 +267,15 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
         }
     } else {
         // R1: the lowest-position minimum-weight out-edge
+        unsigned none = 0;
+        if (LISTED) listed_rows<true>(g, nl, nw, 1, 0, none, none, [&](int v, long long, int arg, int bh) {
+            if ((t & 63) != 0) return;
+            S.pi[v] = (unsigned short)arg;
+            S.succ[v] = (unsigned short)bh;
+        });
         for (int v = t; v < n; v += B) {
             int arg = S.rb[v];
+            if (LISTED && (int)S.rb[v + 1] - arg > kLongEdges) continue;
             long long best = g.weight(arg);
             for (int e = arg + 1; e < (int)S.rb[v + 1]; ++e) {
                 const long long x = g.weight(e);
@@ -362,8 +405,41 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
                 // read after its barrier, and clears the next round's
                 if (t == 0 && k > 1) S.got[(k + 1) % 3] = 0;
                 unsigned got = 0;
+                for (int i = t >> 6; LISTED && i < nl + nw; i += B >> 6) {
+                    const int v = i < nl ? S.longs[i] : S.wides[i - nl];
+                    if (S.layer[v] != 0xffffu) continue;   // this wave's to write
+                    const int end = S.rb[v + 1];
+                    int at = -1, x = 0;
+                    for (int eb = S.rb[v]; eb < end && at < 0; eb += 64 * kRowSteps) {
+                        int h[kRowSteps];
+                        unsigned short ly[kRowSteps];
+#pragma unroll
+                        for (int u = 0; u < kRowSteps; ++u) {
+                            const int e = eb + 64 * u + (t & 63);
+                            h[u] = g.head(e < end ? e : end - 1);
+                        }
+#pragma unroll
+                        for (int u = 0; u < kRowSteps; ++u) ly[u] = S.layer[h[u]];
+#pragma unroll
+                        for (int u = kRowSteps - 1; u >= 0; --u) {
+                            const unsigned long long hit =
+                                __ballot((int)ly[u] < k && eb + 64 * u + (t & 63) < end);
+                            if (!hit) continue;
+                            const int l = __ffsll((long long)hit) - 1;
+                            at = eb + 64 * u + l;
+                            x = __shfl(h[u], l, 64);
+                        }
+                    }
+                    if (at >= 0 && (t & 63) == 0) {
+                        S.pi[v] = (unsigned short)at;
+                        S.succ[v] = (unsigned short)x;
+                        S.layer[v] = (unsigned short)k;
+                        ++got;
+                    }
+                }
                 for (int v = t; v < n; v += B) {
                     if (S.layer[v] != 0xffffu) continue;
+                    if (LISTED && (int)S.rb[v + 1] - (int)S.rb[v] > kLongEdges) continue;
                     for (int e = S.rb[v]; e < (int)S.rb[v + 1]; ++e) {
                         const int x = g.head(e);
                         if ((int)S.layer[x] < k) {
@@ -433,7 +509,8 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
                 long long best = INT64_MAX;
                 int arg = 0, bh = 0;
                 const int end = S.rb[v + 1];
-                for (int eb = S.rb[v]; eb < end; eb += 4) {
+                const bool listed = LISTED && end - (int)S.rb[v] > kLongEdges;
+                for (int eb = listed ? end : S.rb[v]; eb < end; eb += 4) {
                     // four edges in flight (past the row: its last edge again)
                     int x[4];
                     long long key[4];
@@ -460,12 +537,22 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
                     }
                 }
                 ch = best < own;
-                np[i] = ch ? arg : cur;
+                np[i] = listed ? -1 : ch ? arg : cur;
                 nh[i] = ch ? bh : (int)S.succ[v];
                 broke |= ch && onC;
             }
             changed += __popcll(__ballot(ch));
         }
+        // their policy is written at once: only the row's own scan reads it
+        if (LISTED) listed_rows<false>(g, nl, nw, L, W, tight, certain, [&](int v, long long best, int arg, int bh) {
+            if (best >= (long long)S.E[v] >> kBits) return;
+            ++changed;
+            broke |= S.onc[v] == 3;
+            if ((t & 63) == 0) {
+                S.pi[v] = (unsigned short)arg;
+                S.succ[v] = (unsigned short)bh;
+            }
+        });
         const bool any_t = __ballot(tight != 0) != 0, any_b = __ballot(broke) != 0;
         if (any_t) {
             tight = (unsigned)wave_sum_u64(tight);
@@ -494,6 +581,10 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
         for (int i = 0; i < VPT; ++i) {
             const int v = t + i * B;
             if (v < n) {
+                if (LISTED && np[i] < 0) {   // a listed row
+                    np[i] = S.pi[v];
+                    nh[i] = S.succ[v];
+                }
                 S.pi[v] = (unsigned short)np[i];
                 S.succ[v] = (unsigned short)nh[i];
                 if (!general) {
@@ -527,8 +618,29 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
         if (t == 0) S.flag = S.cnt = 0;
         __syncthreads();
         bool out = false, stay = false;
+        for (int i = t >> 6; LISTED && i < nl + nw; i += B >> 6) {
+            const int v = i < nl ? S.longs[i] : S.wides[i - nl];
+            if (!S.layer[v]) continue;   // this wave's to write
+            const long long own = (long long)S.E[v] >> kBits;
+            const int end = S.rb[v + 1];
+            bool alive = false;
+            for (int eb = S.rb[v]; eb < end && !alive; eb += 64) {
+                const int e = eb + (t & 63);
+                bool a = false;
+                if (e < end) {
+                    const int x = g.head(e);
+                    a = S.layer[x] && ((long long)S.E[x] >> kBits) + L * g.weight(e) -
+                                              (RATIO ? W * g.time(e) : W) ==
+                                          own;
+                }
+                alive = __ballot(a) != 0;
+            }
+            if (!alive && (t & 63) == 0) S.layer[v] = 0;
+            out |= !alive;
+            stay |= alive;
+        }
         for (int v = t; v < n; v += B) {
-            if (!S.layer[v]) continue;
+            if (!S.layer[v] || (LISTED && (int)S.rb[v + 1] - (int)S.rb[v] > kLongEdges)) continue;
             const long long own = (long long)S.E[v] >> kBits;
             bool alive = false;
             for (int e = S.rb[v]; e < (int)S.rb[v + 1] && !alive; ++e) {
@@ -549,6 +661,100 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
         if (S.flag == 0) break;
     }
     R.tie = true;
+}
+
+// The whole solve; every thread returns the same Run.  row_ptr[0..n] holds the
+// rows' edge positions (e0 = row_ptr[0] when the CSR is known to be sound).
+template <typename WT, int N, int M, bool RATIO>
+__device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
+                          const int* __restrict__ row_ptr, const int* __restrict__ col,
+                          const WT* __restrict__ w, const int* __restrict__ tm, bool neg,
+                          const SmallOpts& o, const int* __restrict__ init, Run& R)
+{
+    const int t = threadIdx.x, B = blockDim.x;
+    R = Run{};
+    R.status = OCM_OK;
+    R.s = 0;
+    R.L = 1;
+    // rows, edges, validation (as k_validate), the weight bound
+    if (t == 0) {
+        S.err = 0;
+        S.maxw = 0;
+        S.maxt = 1;
+        S.cap = 0;
+        S.nlong = S.nwide = 0;
+        S.stall = S.over = 0;
+        for (int p = 0; p < 2; ++p)
+            for (int i = 0; i < 4; ++i) S.acc[p][i] = 0;
+    }
+    __syncthreads();
+    {
+        unsigned err = 0;
+        for (int v = t; v < n; v += B) {
+            const int b = row_ptr[v], x = row_ptr[v + 1];
+            if (o.validate) {
+                if ((v == 0 && b != e0) || (v == n - 1 && x != e0 + m) || b < e0 || x > e0 + m || b > x)
+                    err |= kErrBadCsr;
+                else if (b == x) err |= kErrNoOut;
+            }
+            S.rb[v] = (unsigned short)(b - e0);
+            if (v == n - 1) S.rb[n] = (unsigned short)(x - e0);
+        }
+        unsigned long long mw = 0;
+        int mt = 1;
+        bool bad_t = false;
+        for (int e = t; e < m; e += B) {
+            const int h = col[e0 + e] - v0;
+            if (o.validate && (h < 0 || h >= n)) err |= kErrBadCsr;
+            const long long x = (long long)w[e0 + e];
+            const unsigned long long ax = uabs64(x);
+            mw = ax > mw ? ax : mw;
+            if (M > 0) {
+                S.c[e] = (unsigned short)h;
+                S.w[e] = (int)x;
+            }
+            if (RATIO) {
+                const int y = tm[e0 + e];
+                bad_t |= y < 1;
+                mt = y > mt ? y : mt;
+                if (M > 0) S.t[e] = y;
+            }
+        }
+        if (err) atomicOr(&S.err, err);
+        if (bad_t) atomicOr(&S.cap, 1u);
+        mw = wave_max_u64(mw);
+        if ((t & 63) == 0) atomicMax(&S.maxw, mw);
+        if (RATIO) atomicMax(&S.maxt, (unsigned)mt);
+    }
+    __syncthreads();
+    const unsigned long long maxw = S.maxw;
+    if (S.err & kErrBadCsr) R.status = OCM_E_BAD_CSR;
+    else if (S.err & kErrNoOut) R.status = OCM_E_NO_OUT_EDGE;
+    else if (S.cap) R.status = OCM_E_INVALID_ARG;
+    else if ((unsigned __int128)2 * (unsigned)n * maxw * S.maxt >= ((unsigned __int128)1 << 62) &&
+             o.bound)
+        R.status = OCM_E_OVERFLOW;
+    if (R.status != OCM_OK) {
+        R.tight = R.status == OCM_E_INVALID_ARG ? 1u : 0u;   // which argument: times
+        return;
+    }
+    const View<WT, N, M, RATIO> g{S, col, w, tm, v0, e0, neg, maxw <= (unsigned long long)INT32_MAX};
+
+    for (int v = t; v < n; v += B) {
+        const int len = (int)S.rb[v + 1] - (int)S.rb[v];
+        if (len <= kLongEdges) continue;
+        // (rows of an unchecked, unsound CSR may be more than there is room for)
+        const bool wide = len > kWideEdges;
+        const unsigned at = atomicAdd(wide ? &S.nwide : &S.nlong, 1u);
+        if (at < (wide ? sizeof S.wides : sizeof S.longs) / 2) (wide ? S.wides : S.longs)[at] = (unsigned short)v;
+        else atomicSub(wide ? &S.nwide : &S.nlong, 1u);
+    }
+    __syncthreads();
+    const int nl = __builtin_amdgcn_readfirstlane((int)S.nlong);
+    const int nw = __builtin_amdgcn_readfirstlane((int)S.nwide);
+
+    if (nl + nw > 0) iterate<true>(g, nl, nw, n, e0, o, init, R);
+    else iterate<false>(g, 0, 0, n, e0, o, init, R);
 }
 
 // Policy hops to s into out (the values are gone afterwards).

@@ -76,6 +76,60 @@ def test_long_rows(hubs, deg, monkeypatch):
     check(monkeypatch, synth.hub_graph(700, hubs, deg, 1, 4, -5, 5, np.int64, seed=[93, deg]))
 
 
+def rows(n, lens, wlo, whi, dtype, seed, layered=False):
+    """Short rows, and one of every length in lens.  layered: vertex v's way to
+    the light loop at 0 is v - 1, ..., and a long row's other heads lie behind
+    it, so that the row waits for its one edge through most of the rebuild."""
+    r = np.random.default_rng(seed)
+    deg = r.integers(2, 4, n)
+    at = (np.arange(len(lens)) + 1) * n // (len(lens) + 1)
+    deg[at] = lens
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    src = np.repeat(np.arange(n), deg)
+    w = r.integers(wlo, whi + 1, rp[-1]).astype(dtype)
+    if layered:
+        col = src + (r.random(rp[-1]) * (n - src)).astype(np.int64)
+        back = rp[:-1] + (r.random(n) * deg).astype(np.int64)
+        col[back] = np.arange(n) - 1
+        col[rp[0]:rp[1]] = (0, n - 1, 0)[:deg[0]]
+        w[src == col] = whi + 1
+        w[rp[0]] = wlo - 3
+    else:
+        col = r.integers(0, n, rp[-1])
+        col[rp[:-1] + (r.random(n) * deg).astype(np.int64)] = (np.arange(n) + 1) % n
+    return synth.Graph(rp.astype(np.int32), col.astype(np.int32), w)
+
+
+ROWS = [(500, (127, 128, 129)), (100, (2047, 1500)), (90, (3700,)), (900, (2047, 2048, 2049)), (1000, (3, 129, 300, 5000)),
+        (2000, (255, 256, 257, 511, 513, 2049, 6000)), (2048, (129,) * 60), (4000, (4000,)), (3000, (129, 2049, 9000, 40000)),
+        (200, (129,) * 150 + (2100,) * 20)]
+
+
+@pytest.mark.parametrize("n,lens", ROWS)
+@pytest.mark.parametrize("layered", [False, True])
+def test_rows_scanned_by_a_wave_or_the_workgroup(n, lens, layered, monkeypatch):
+    for wlo, whi, dtype, mode in ((0, 2, np.int32, "min"), (-2**20, 2**20, np.int64, "max"), (2**33, 2**33 + 9, np.int64, "min")):
+        g = rows(n, lens, wlo, whi, dtype, [103, n, len(lens)], layered)
+        r = check(monkeypatch, g, mode)
+        sol = native.solve(g.row_ptr, g.col, g.w, mode)
+        assert (r.p, r.q, r.iterations, r.cycle_edges.cpu().tolist(), r.tie) == \
+            (sol.p, sol.q, sol.iterations, sol.cycle.tolist(), bool(sol.tie))
+    check(monkeypatch, g, "min", t=np.random.default_rng(n).integers(1, 9, g.m).astype(np.int32))
+
+
+def test_rows_in_a_batch(monkeypatch):
+    gs = [rows(n, lens, -50, 50, np.int32, [104, n, k], k % 2 == 0) for k, (n, lens) in enumerate(ROWS) if n <= 2048 and sum(lens) < 25000]
+    u, vptr, eptr = synth.disjoint_union(gs)
+    arrays = dev(u.row_ptr, u.col, u.w)
+    got = []
+    for small in ("1", "0"):
+        monkeypatch.setenv("OCM_BATCH_SMALL", small)
+        r = ocm.cycle_mean_batched(*arrays, vptr, eptr)
+        assert r.status == [0] * len(gs)
+        got.append((r.p, r.q, r.iterations, r.flags, r.cycle_ptr, r.cycle_edges.cpu().tolist()))
+    assert got[0] == got[1]
+
+
 @pytest.mark.parametrize("seed", range(12))
 def test_ties(seed, monkeypatch):
     g = synth.random_digraph(100 + 150 * seed, 1, 3, 0, 2, np.int32, seed=[94, seed])
