@@ -712,7 +712,7 @@ __global__ __launch_bounds__(kWG) void k_chase(const int2* __restrict__ chunks, 
             fits &= chase_pack(((long long)e >> jb) + ((long long)r >> jb), h, jb, &e);
             chase_store<SC>(&Eg[me], e);
             if (h == me) {
-                atomicOr(stall, 1u);
+                set_flag(stall, 1u);
                 break;
             }
             if ((k & 7) == 0 &&
@@ -730,11 +730,11 @@ __global__ __launch_bounds__(kWG) void k_chase(const int2* __restrict__ chunks, 
         const bool open = __ballot(!done) != 0, prog = __ballot(done && !was) != 0;
         const bool over = __ballot(!fits) != 0, big = __ballot(wide) != 0;
         if ((threadIdx.x & 63) == 0) {
-            if (open) atomicOr(&ga.vact[4 * g + pass - 1], 1u);
-            if (pass == 2 && prog) atomicOr(&ga.vprog[4 * g + 1], 1u);
-            if (over) atomicOr(&ga.ovf[g], 1u);
+            if (open) set_flag(&ga.vact[4 * g + pass - 1], 1u);
+            if (pass == 2 && prog) set_flag(&ga.vprog[4 * g + 1], 1u);
+            if (over) set_flag(&ga.ovf[g], 1u);
             // sticky: from now on the sweeps gather the int64 values
-            if (big) atomicOr(&bc->wide32, 1u);
+            if (big) set_flag(&bc->wide32, 1u);
         }
     });
 }

@@ -262,6 +262,17 @@ __device__ __forceinline__ Jmp jmp_combine(Jmp q, const Jmp& r)
     return q;
 }
 
+// Sets bits of a word that many threads may set at once: each looks first, for
+// atomics on one word queue (a million vertices on policy cycles of their own
+// took a value phase of the 16^6 product from 0.25 to 10.5 ms).  Past it, the
+// bits are set for every later atomic of this thread's.
+__device__ __forceinline__ void set_flag(unsigned* p, unsigned bits)
+{
+    if ((__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bits) == bits) return;
+    const unsigned old = atomicOr(p, bits);   // the value read back orders it
+    asm volatile("" ::"v"(old));
+}
+
 // Value chase (k_chase): steps a vertex takes per pass.
 constexpr int kChaseSteps = 96;
 

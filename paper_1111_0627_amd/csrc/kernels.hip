@@ -533,7 +533,7 @@ void k_tiescan_tile(SweepArgs a, const WT* __restrict__ w)
                                                  changed ? bhead : a.succ[v0 + t], a.ctl->s, W, L,
                                                  &e);
         a.E[v0 + t] = e;
-        if (!fits) atomicOr(&a.ctl->fflags, kChaseOverflow);
+        if (!fits) set_flag(&a.ctl->fflags, kChaseOverflow);
     }
     unsigned long long sums[5] = {cnt, certain, nondec, changed, cbroken};
     block_sums_u64(sums);
@@ -709,7 +709,7 @@ __global__ __launch_bounds__(kWG) void k_sweep_filter(SweepArgs a, const WT* __r
         unsigned long long e;
         if (!chase_entry<WT, RATIO>(a, w, v0 + t, changed ? pos : cur, changed ? bhead : a.succ[v0 + t],
                                     a.ctl->s, W, L, &e))
-            atomicOr(&a.ctl->fflags, kChaseOverflow);
+            set_flag(&a.ctl->fflags, kChaseOverflow);
         a.E[v0 + t] = e;
     }
     unsigned long long sums[3] = {((unsigned long long)changed << 32) | (unsigned long long)(changed && onc),
@@ -922,7 +922,7 @@ __global__ __launch_bounds__(kWG) void k_giant_merge(SweepArgs a, const WT* __re
             if (!chase_entry<WT, RATIO>(a, w, v, wr ? parts[bi].pos : a.pi[v],
                                         wr ? parts[bi].head : a.succ[v], a.ctl->s, a.ctl->W,
                                         a.ctl->L, &e))
-                atomicOr(&a.ctl->fflags, kChaseOverflow);
+                set_flag(&a.ctl->fflags, kChaseOverflow);
             a.E[v] = e;
         }
     }
@@ -2870,7 +2870,7 @@ __global__ __launch_bounds__(kWG) void k_chase_init(int n, const int* __restrict
             E[v] = x;
         }
     }
-    if (!fits) atomicOr(&ctl->fflags, kChaseOverflow);
+    if (!fits) set_flag(&ctl->fflags, kChaseOverflow);
     __syncthreads();
     if (threadIdx.x != 0) return;
     unsigned long long tot;
@@ -2981,7 +2981,7 @@ __global__ __launch_bounds__(kWG) void k_chase(int n, int jb, unsigned long long
         fits &= chase_pack(((long long)e >> jb) + ((long long)r >> jb), h, jb, &e);
         chase_store<ST>(&E[v], e);
         if (h == (unsigned)v) {
-            atomicOr(&ctl->fflags, kChaseStall);
+            set_flag(&ctl->fflags, kChaseStall);
             break;
         }
         if ((k & 7) == 0 && (__hip_atomic_load(&ctl->fflags, __ATOMIC_RELAXED,
@@ -3021,10 +3021,7 @@ __global__ __launch_bounds__(kWG) void k_chase(int n, int jb, unsigned long long
     __syncthreads();
     if (threadIdx.x != 0) return;
     // flags are global before the arrival that lets the last workgroup read them
-    if (sflags) {
-        const unsigned old = atomicOr(&ctl->fflags, sflags);
-        asm volatile("" ::"v"(old));
-    }
+    if (sflags) set_flag(&ctl->fflags, sflags);
     unsigned long long tot;
     if (last_arrival(ctl, arrival_word(sleft, 0), &tot)) loop_after_chase(ctl, (unsigned)tot);
 }
