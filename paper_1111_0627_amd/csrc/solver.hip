@@ -1013,6 +1013,14 @@ int loop_pairs(const Ctx& c) { return c.prof.out ? 1 : c.n < (1 << 18) ? 4 : 2; 
 // few compute units.
 constexpr int kVertexRoundsN = 1 << 17;
 
+// Vertices left from which a warm start's rebuild pushes (and builds the reverse
+// CSR for it).  Below, a thread per vertex pulls a round faster than a push round
+// runs: whole warm starts from a poor policy, ms, pulls / pushes: torus of 450^2
+// 11.3 / 20.9, of 1500^2 147 / 195, ring of 300,000 33 / 89, 16^5 product 1.7 /
+// 3.0; from some 4M on a round of pulls takes longer: 24^5 product (8M) 12.8 /
+// 10.8, 16^6 22.2 / 15.1, and 15.0 / 12.0 from the optimum of weights that differ in one.
+constexpr unsigned kWarmPush = 1u << 22;
+
 // Runs the device-driven loop until it stops, from `start`: the general phases
 // (kLoopCycles: C, its lambda and the policy around it are found, then the
 // values), the values after them (kLoopRounds) or a sweep (kLoopSweep).  c.h
@@ -1028,8 +1036,8 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
     const int jb = ocm::chase_bits(c.n);
     const bool from_values = start != ocm::kLoopSweep;
     // a warm start's policy mostly reaches C already: its rebuilds do without
-    // the reverse CSR that pushes need
-    const bool small = c.n < kVertexRoundsN || c.warm;
+    // the reverse CSR that pushes need until a read finds kWarmPush vertices left
+    auto by_vertex = [&] { return c.n < kVertexRoundsN || (c.warm && !c.rev_built); };
     // on large graphs idle kernels cost more than a read (a chase of 65,536
     // workgroups that returns at once 15 us): the values and the loop are
     // queued once the rounds are over
@@ -1078,11 +1086,16 @@ ocm_status run_loop(Ctx& c, unsigned start, unsigned max_sweeps)
             ocm::launch_loop_select(c.n, w.rep, w.onc, w.pi, c.w, c.wtype, c.neg, c.t, w.wsum, w.lcnt,
                                     c.t ? w.tsum : nullptr, w.cyc, w.sel, w.ctl, c.low, c.st);
             ocm::launch_loop_conn_init(c.n, w.rep, c.low ? T : nullptr, w.onc, w.onC, w.abits[1],
-                                       w.abits[0], w.ctl, small ? 1 : 0, kPushMinUnattached, c.st);
+                                       w.abits[0], w.ctl, by_vertex() ? 1 : 0, kPushMinUnattached, c.st);
         }
         if (start == ocm::kLoopCycles && (mode == ocm::kLoopCycles || c.h.rmode != 0)) {
-            if (!small && !c.rev_built) build_reverse(c);
-            const int rounds = c.warm && kr == 0 ? 2 : kRoundsPerRead;
+            const bool first = mode == ocm::kLoopCycles;
+            if (first && c.warm && apart) return false;   // the read comes first
+            if (!c.rev_built &&
+                (!by_vertex() || (c.n >= kVertexRoundsN && !first && c.h.rleft >= kWarmPush)))
+                build_reverse(c);
+            const bool small = by_vertex();
+            const int rounds = c.warm && first ? 2 : kRoundsPerRead;
             for (int j = 0; j < rounds; ++j) {
                 ++kr;
                 if (small)

@@ -46,3 +46,26 @@ def test_pushes_after_a_pull(near, far, width):
     assert a.connect_rounds >= far // width
     # every in-edge of the layers attached while more than 65,536 vertices are left
     assert a.counters["push_in_edges"] >= far - 65536 - 2 * width
+
+
+def test_warm_start_with_millions_left():
+    near, far, width = 300_000, (1 << 22) + 200_001, 100_003
+    g = layers(near, far, width)
+    policy = 2 * torch.arange(near + far, device="cuda", dtype=torch.int32)
+    policy[1:near] += 1
+    a = ocm.min_cycle_mean(*g, init_policy=policy, **WHOLE)
+    same(a, ocm.min_cycle_mean(*g, init_policy=policy, connect="pull", **WHOLE))
+    assert a.connect_rounds >= far // width
+    assert a.counters["push_in_edges"] > 0
+
+
+def test_warm_start_with_some_left():
+    near, far, width = 150_000, 100_000, 1000
+    g = layers(near, far, width)
+    policy = 2 * torch.arange(near + far, device="cuda", dtype=torch.int32)
+    policy[1:near] += 1
+    for n_far in (far, 0):
+        if n_far == 0:
+            policy[near:] += 1   # everybody reaches C
+        a = ocm.min_cycle_mean(*g, init_policy=policy, **WHOLE)
+        same(a, ocm.min_cycle_mean(*g, init_policy=policy, connect="pull", **WHOLE))
