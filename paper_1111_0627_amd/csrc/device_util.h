@@ -275,6 +275,7 @@ __device__ __forceinline__ void set_flag(unsigned* p, unsigned bits)
 
 // Value chase (k_chase): steps a vertex takes per pass.
 constexpr int kChaseSteps = 96;
+constexpr int kChaseFew = 16, kChaseWaveSteps = 512;
 
 // A chase entry: the sum in the upper 64 - jb bits (signed), the vertex
 // reached below.  Returns false when the sum does not fit.

@@ -52,7 +52,7 @@ struct alignas(128) CtlLane {
     unsigned wide32;               // values: some value does not fit int32 (no int32 copy)
     unsigned ncrit;                // multichain tie check: policy cycles of optimal gain
     unsigned fpass;                // filtered sweep: edges whose value was gathered
-    unsigned pad_[1];
+    unsigned deep;                 // value chase: waves that most paths led on (see k_chase)
 };
 static_assert(sizeof(CtlLane) == 4 * kLaneWords, "one lane per 128-byte line");
 
@@ -94,6 +94,7 @@ struct alignas(128) Ctl {
     long long qbase, dbase, qlo, qhi;
     long long slo, shi, sL;        //   the scale's range, and the L its values were scaled by
     unsigned qshift, dshift, qvalid, dvalid;
+    unsigned fdeep;                // value chase: passes of few steps (see k_chase)
     unsigned lfail;                // cycles by records: a path or a cycle was too long
     CtlLane lane[kLanes];
 };

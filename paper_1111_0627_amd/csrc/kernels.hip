@@ -2785,7 +2785,15 @@ __global__ __launch_bounds__(kWG) void k_fill_u32(int64_t len, unsigned* __restr
 //     product: 960 -> 240 us.
 // A pass takes at most kChaseSteps steps per vertex (32 left a few deep
 // vertices of 2^22-vertex graphs for a second pass of 23 us behind a pass of
-// 190 us).  A pass that leaves vertices unfinished is followed by another one; one that finishes nobody
+// 190 us).  On large graphs most entries are still single edges when a vertex
+// meets them, and a policy of paths of thousands of edges cost 96 steps for all
+// (torus of 2000^2 after 1 % of the weights: 28.7 ms a solve, 20.3 by doubling):
+// once more than half of the waves had a quarter of their vertices on the way
+// after 32 steps (85 % of them on tori, up to 28 % on random and product graphs),
+// waves stop at kChaseFew steps with half of them on the way (at 32 with a
+// quarter, 64 with an eighth) from the next phase on, and the next pass finds
+// longer entries: 17.6 ms; 2^20 to 2^23 random vertices and products unchanged.
+// A pass that leaves vertices unfinished is followed by another one; one that finishes nobody
 // proves a stall: an unfinished vertex of C's component nearest to s has
 // reached a finished one and finishes with its next step.  A vertex that
 // reaches itself lies on another cycle, which proves it at once.
@@ -2797,7 +2805,7 @@ __global__ void k_loop_setup(Ctl* c, unsigned mode, unsigned opts, unsigned max_
         CtlLane& ln = c->lane[t];
         ln.changed = ln.tight = ln.certain = ln.nondec = 0;
         ln.cbroken = ln.overflow = ln.wide32 = ln.bad = 0;
-        ln.active = ln.active2 = ln.got = ln.left = ln.fpass = 0;
+        ln.active = ln.active2 = ln.got = ln.left = ln.fpass = ln.deep = 0;
         ln.rpack = 0;
     }
     if (t == 0) {
@@ -2895,7 +2903,7 @@ __global__ __launch_bounds__(kWG) void k_hop_init(int n, const int* __restrict__
 }
 
 // What follows a pass: `left` vertices are unfinished.
-__device__ void loop_after_chase(Ctl* c, unsigned left)
+__device__ void loop_after_chase(Ctl* c, int n, unsigned left)
 {
     const unsigned f = __hip_atomic_load(&c->fflags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((f & kChaseStall) || (left && left == c->jlast)) {
@@ -2917,13 +2925,18 @@ __device__ void loop_after_chase(Ctl* c, unsigned left)
     } else if ((f & kChaseWide) && (c->fopts & kLoopV32)) {
         loop_stop(c, kWhyWide);
     } else {
-        unsigned pass = 0;
+        unsigned pass = 0, deep = 0, dl[kLanes];
+#pragma unroll
+        for (int l = 0; l < kLanes; ++l)
+            dl[l] = __hip_atomic_load(&c->lane[l].deep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (int l = 0; l < kLanes; ++l) {
             CtlLane& ln = c->lane[l];
             pass += ln.fpass;
+            deep += dl[l];
             ln.changed = ln.tight = ln.certain = 0;
-            ln.cbroken = ln.fpass = 0;
+            ln.cbroken = ln.fpass = ln.deep = 0;
         }
+        c->fdeep = deep > (unsigned)n / 128;   // more than half of the waves
         // what the last sweep let through; the codes just written, and the next
         // phase's scale from the sampled range
         c->fpass = pass;
@@ -2965,15 +2978,17 @@ __global__ __launch_bounds__(kWG) void k_chase(int n, int jb, unsigned long long
                                                unsigned char* __restrict__ q8, Ctl* ctl)
 {
     // the step, the source and the own entry are on the way together
+    constexpr bool DEEP = LD == __HIP_MEMORY_SCOPE_WORKGROUP;
     const unsigned mode = ctl->fmode;
     const int s = ctl->s;
+    const bool few = DEEP && ctl->fdeep != 0;
     const unsigned long long jm = (1ull << jb) - 1;
     const int64_t v = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kWG + threadIdx.x;
     unsigned long long e = 0;
     if (v < n) e = chase_load<LD>(&E[v]);
     if (mode != kLoopChase) return;   // uniform: only the last arrival changes it
-    __shared__ unsigned sleft, sflags;
-    if (threadIdx.x == 0) sleft = sflags = 0;
+    __shared__ unsigned sleft, sflags, sdeep;
+    if (threadIdx.x == 0) sleft = sflags = sdeep = 0;
     __syncthreads();
     if (v >= n) e = (unsigned)s;
     bool fits = true;
@@ -2988,9 +3003,16 @@ __global__ __launch_bounds__(kWG) void k_chase(int n, int jb, unsigned long long
             set_flag(&ctl->fflags, kChaseStall);
             break;
         }
-        if ((k & 7) == 0 && (__hip_atomic_load(&ctl->fflags, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT) & kChaseStall))
+        if ((k & 7) != 0) continue;
+        if (__hip_atomic_load(&ctl->fflags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kChaseStall)
             break;
+        if (DEEP && k >= kChaseFew && (k & (k - 1)) == 0) {
+            const unsigned long long on = __ballot(true);
+            if (__popcll(on) * k > kChaseWaveSteps && (few || k == 2 * kChaseFew)) {
+                if (__ffsll((long long)on) - 1 == (int)(threadIdx.x & 63)) atomicAdd(&sdeep, 1u);
+                if (few) break;
+            }
+        }
     }
     const bool done = (e & jm) == (unsigned)s;
     bool wide = false;
@@ -3026,8 +3048,12 @@ __global__ __launch_bounds__(kWG) void k_chase(int n, int jb, unsigned long long
     if (threadIdx.x != 0) return;
     // flags are global before the arrival that lets the last workgroup read them
     if (sflags) set_flag(&ctl->fflags, sflags);
+    if (DEEP && sdeep) {
+        const unsigned old = atomicAdd(&my_lane(ctl).deep, sdeep);
+        asm volatile("" ::"v"(old));   // before the arrival
+    }
     unsigned long long tot;
-    if (last_arrival(ctl, arrival_word(sleft, 0), &tot)) loop_after_chase(ctl, (unsigned)tot);
+    if (last_arrival(ctl, arrival_word(sleft, 0), &tot)) loop_after_chase(ctl, n, (unsigned)tot);
 }
 
 __global__ void k_cycle_walk(int s, long long L, const int* __restrict__ pi,

@@ -216,3 +216,15 @@ def test_iteration_cap(cap, monkeypatch):
             ocm.min_cycle_mean(*dev, max_iters=cap, schedule=sched)
         assert e.value.status == ocm.OCM_E_NOT_CONVERGED
     assert ocm.min_cycle_mean(*dev, max_iters=need).iterations == need
+
+
+@pytest.mark.parametrize("a,b,whi", [(640, 512, 1000), (2100, 150, 1000), (700, 640, 3)])
+def test_deep_policies_in_passes_of_few_steps(a, b, whi):
+    """Tori of at least 2^18 vertices: most paths take hundreds of edges, so that
+    waves stop early from the second value phase on."""
+    n = a * b
+    v = np.arange(n)
+    col = np.stack([(v % a + 1) % a + v // a * a, v % a + (v // a + 1) % b * a], 1)
+    w = np.random.default_rng([75, a]).integers(1, whi + 1, (n, 2))
+    both(synth.Graph(2 * np.arange(n + 1, dtype=np.int32), col.astype(np.int32).reshape(-1), w.astype(np.int64).reshape(-1)),
+         "max" if whi == 3 else "min")
