@@ -2739,6 +2739,7 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
     BHIP(hipGetLastError());
 
     // validation: the union's CSR, the weight bound, and edges inside graphs
+    unsigned long long maxw = 0;
     {
         ocm::Ctl* vctl = (ocm::Ctl*)ws.vctl;
         ocm::launch_ctl_clear(vctl, ocm::kClrAll | ocm::kClrCount | ocm::kClrChanged, c.st);
@@ -2747,7 +2748,8 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
         BHIP(ocm::host_read_ctl(vctl, &hc, c.st));
         if (hc.err & ocm::kErrBadCsr) return bfail(OCM_E_BAD_CSR, "malformed CSR");
         if (hc.err & ocm::kErrNoOut) return bfail(OCM_E_NO_OUT_EDGE, "a vertex has no out-edge");
-        const unsigned __int128 bound = (unsigned __int128)2 * (unsigned)c.max_n * hc.maxabsw;
+        maxw = hc.maxabsw;
+        const unsigned __int128 bound = (unsigned __int128)2 * (unsigned)c.max_n * maxw;
         if (bound >= ((unsigned __int128)1 << 62))
             return bfail(OCM_E_OVERFLOW, "weights too large for int64 values");
         if (o.validate) {
@@ -2815,8 +2817,10 @@ ocm_status solve_batched(int64_t G, const int64_t* vptr, const int64_t* eptr, co
             if (!ns) continue;
             BHIP(hipMemcpyAsync(ws.small + at, small[k].data(), 4 * (size_t)ns, hipMemcpyHostToDevice,
                                 c.st));
+            int64_t most = 0;
+            for (int g : small[k]) most = std::max<int64_t>(most, vptr[g + 1] - vptr[g]);
             ocm::launch_small_batch(k, ws.small + at, ns, sb, c.row_ptr, c.col, c.w, c.wtype, neg, so,
-                                    c.st);
+                                    ocm::small_sums_may_not_fit(most, maxw), c.st);
             at += ns;
         }
         BHIP(hipGetLastError());

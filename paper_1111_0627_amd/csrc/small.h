@@ -57,9 +57,17 @@ struct SmallBatch {        // the batch's arrays, by graph and by union vertex
 int small_class(int64_t n, int64_t m, bool ratio);
 void launch_small_one(int n, int m, const int* row_ptr, const int* col, const void* w, int wtype,
                       const int* t, int neg, const SmallOpts& o, const SmallPtrs& p, hipStream_t st);
+// wide: some graph's sums may not fit the entries; those are solved again with
+// 64-bit values, and left to the loop only where a value leaves +-2^62.
 void launch_small_batch(int cls, const int* list, int nlist, const SmallBatch& b, const int* row_ptr,
                         const int* col, const void* w, int wtype, int neg, const SmallOpts& o,
-                        hipStream_t st);
+                        bool wide, hipStream_t st);
+// A sum over a path of a graph of n vertices with weights up to max|w| is at most
+// 2 n^2 max|w|; the entries hold less than 2^51.
+inline bool small_sums_may_not_fit(int64_t n, unsigned long long maxw)
+{
+    return (unsigned __int128)2 * (unsigned)n * (unsigned)n * maxw >= (unsigned __int128)1 << 51;
+}
 
 // ocm_min / ocm_max (neg) without the int128 fallback: a value that leaves int64
 // gives OCM_E_OVERFLOW, as in the batch.

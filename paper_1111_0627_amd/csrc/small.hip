@@ -87,7 +87,7 @@ struct Lds {
 };
 
 // The graph as the kernel reads it: edges [e0, e0 + m), vertices from v0.
-template <typename WT, int N, int M, bool RATIO>
+template <typename WT, int N, int M, bool RATIO, bool WIDE>
 struct View {
     Lds<N, M, RATIO>& S;
     const int* col;
@@ -109,14 +109,33 @@ struct View {
     {
         return M > 0 && lds ? (int)S.c[e] : col[e0 + e] - v0;
     }
+    // the value of a finished entry
+    __device__ __forceinline__ long long value(int v) const
+    {
+        return WIDE ? (long long)S.E[v] : (long long)S.E[v] >> kBits;
+    }
+    // v's entry for the edge e to h; false if its sum does not fit
+    __device__ __forceinline__ bool entry(int v, int s, long long L, long long W, int e, int h) const
+    {
+        if (WIDE) S.JM[v] = v == s ? (unsigned)s : (unsigned)h;
+        unsigned long long x = WIDE ? 0ull : (unsigned long long)(unsigned)s;
+        bool fits = true;
+        if (v != s) {
+            const long long d = L * weight(e) - (RATIO ? W * time(e) : W);
+            if (WIDE) x = (unsigned long long)d;
+            else fits = chase_pack(d, (unsigned)h, kBits, &x);
+        }
+        S.E[v] = x;
+        return fits;
+    }
 };
 
 // The best edge of a row over a wave's lanes, ties to the lowest position (every
 // lane gets it; no edge: arg = INT32_MAX), from edge first on in steps of `step`
 // runs of 64 lanes with U edges each.  FIRST: by weight alone.  Else by the head's value too,
 // and the tight edges other than cur are counted as in the sweep.
-template <bool FIRST, typename WT, int N, int M, bool RATIO>
-__device__ __forceinline__ void wave_row(const View<WT, N, M, RATIO>& g, long long L, long long W,
+template <bool FIRST, typename WT, int N, int M, bool RATIO, bool WIDE>
+__device__ __forceinline__ void wave_row(const View<WT, N, M, RATIO, WIDE>& g, long long L, long long W,
                                          int v, int first, int end, int step, int cur, long long own,
                                          bool onC, long long& best, int& arg, int& bh,
                                          unsigned& tight, unsigned& certain)
@@ -136,7 +155,7 @@ __device__ __forceinline__ void wave_row(const View<WT, N, M, RATIO>& g, long lo
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (!FIRST) key[u] += (long long)g.S.E[x[u]] >> kBits;
+            if (!FIRST) key[u] += g.value(x[u]);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int e = eb + 64 * u;
@@ -157,8 +176,8 @@ __device__ __forceinline__ void wave_row(const View<WT, N, M, RATIO>& g, long lo
 
 // done(v, best, arg, head) for every listed row, by every lane of the wave that
 // scanned it (of the first one for the wide rows).  All threads call it.
-template <bool FIRST, typename WT, int N, int M, bool RATIO, typename F>
-__device__ __forceinline__ void listed_rows(const View<WT, N, M, RATIO>& g, int nl, int nw,
+template <bool FIRST, typename WT, int N, int M, bool RATIO, bool WIDE, typename F>
+__device__ __forceinline__ void listed_rows(const View<WT, N, M, RATIO, WIDE>& g, int nl, int nw,
                                             long long L, long long W, unsigned& tight,
                                             unsigned& certain, F&& done)
 {
@@ -168,7 +187,7 @@ __device__ __forceinline__ void listed_rows(const View<WT, N, M, RATIO>& g, int 
         const int v = S.longs[i];
         long long best;
         int arg, bh;
-        wave_row<FIRST>(g, L, W, v, S.rb[v], S.rb[v + 1], 1, S.pi[v], (long long)S.E[v] >> kBits,
+        wave_row<FIRST>(g, L, W, v, S.rb[v], S.rb[v + 1], 1, S.pi[v], g.value(v),
                         S.onc[v] == 3, best, arg, bh, tight, certain);
         done(v, best, arg, bh);
     }
@@ -177,7 +196,7 @@ __device__ __forceinline__ void listed_rows(const View<WT, N, M, RATIO>& g, int 
         long long best;
         int arg, bh;
         wave_row<FIRST>(g, L, W, v, S.rb[v] + 64 * kRowSteps * wave, S.rb[v + 1], waves, S.pi[v],
-                        (long long)S.E[v] >> kBits, S.onc[v] == 3, best, arg, bh, tight, certain);
+                        g.value(v), S.onc[v] == 3, best, arg, bh, tight, certain);
         if ((threadIdx.x & 63) == 0) {
             S.wk[wave] = best;
             S.wp[wave] = arg;
@@ -202,9 +221,51 @@ __device__ __forceinline__ void listed_rows(const View<WT, N, M, RATIO>& g, int 
 template <int N>
 constexpr int kVpt = N == 4096 ? 4 : 2;   // vertices per thread at most
 
+// Values of 64 bits with the vertex reached beside them (JM): a pair cannot be
+// read whole while its owner writes it, so the vertices jump in rounds.
 template <int N, int M, bool RATIO>
+__device__ __forceinline__ void jump(Lds<N, M, RATIO>& S, int n, unsigned s)
+{
+    constexpr int VPT = kVpt<N>;
+    const int t = threadIdx.x, B = blockDim.x;
+    bool bad = false;
+    for (int span = 1;; span <<= 1) {
+        long long d[VPT];
+        unsigned j[VPT];
+        bool open = false;
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) {
+            const int v = t + i * B;
+            j[i] = v < n ? S.JM[v] : s;
+            if (j[i] == s) continue;
+            open = true;
+            bad |= __builtin_add_overflow((long long)S.E[v], (long long)S.E[j[i]], &d[i]);
+            j[i] = S.JM[j[i]] | 0x10000u;
+        }
+        if (!__syncthreads_or(open)) break;
+        if (span >= 2 * n) {   // uniform: a path of n edges has met s or never does
+            S.stall = 1;
+            break;
+        }
+#pragma unroll
+        for (int i = 0; i < VPT; ++i)
+            if (j[i] & 0x10000u) {
+                S.E[t + i * B] = (unsigned long long)d[i];
+                S.JM[t + i * B] = j[i] & 0xffffu;
+            }
+        __syncthreads();
+    }
+    for (int v = t; v < n; v += B) bad |= (long long)S.E[v] > kValLimit || (long long)S.E[v] < -kValLimit;
+    if (bad) S.over = 1;
+}
+
+template <bool WIDE, int N, int M, bool RATIO>
 __device__ __forceinline__ void chase(Lds<N, M, RATIO>& S, int n, unsigned s)
 {
+    if (WIDE) {
+        jump(S, n, s);
+        return;
+    }
     constexpr int WGS = __HIP_MEMORY_SCOPE_WORKGROUP, VPT = kVpt<N>;
     const int t = threadIdx.x, B = blockDim.x;
     unsigned long long e[VPT];
@@ -245,8 +306,8 @@ struct Run {
 
 // From the first sweep, or the warm start's policy, to the end.  LISTED: there
 // are nl long and nw wide rows.  (Without, their tests alone cost 2 to 8 %.)
-template <bool LISTED, typename WT, int N, int M, bool RATIO>
-__device__ __forceinline__ void iterate(const View<WT, N, M, RATIO>& g, int nl, int nw, int n, int e0,
+template <bool LISTED, typename WT, int N, int M, bool RATIO, bool WIDE>
+__device__ __forceinline__ void iterate(const View<WT, N, M, RATIO, WIDE>& g, int nl, int nw, int n, int e0,
                                         const SmallOpts& o, const int* __restrict__ init, Run& R)
 {
     Lds<N, M, RATIO>& S = g.S;
@@ -463,18 +524,13 @@ __device__ __forceinline__ void iterate(const View<WT, N, M, RATIO>& g, int nl, 
             }
             if (R.status != OCM_OK) break;
             for (int v = t; v < n; v += B) {
-                unsigned long long e = (unsigned)s;
-                const int p = S.pi[v];
-                if (v != s &&
-                    !chase_pack(L * g.weight(p) - (RATIO ? W * g.time(p) : W), S.succ[v], kBits, &e))
-                    S.over = 1;
-                S.E[v] = e;
+                if (!g.entry(v, s, L, W, S.pi[v], S.succ[v])) S.over = 1;
             }
             __syncthreads();
         }
         ++R.values;
         ++R.jumps;
-        chase(S, n, (unsigned)s);
+        chase<WIDE>(S, n, (unsigned)s);
         __syncthreads();
         if (S.stall) {
             if (general) {
@@ -503,7 +559,7 @@ __device__ __forceinline__ void iterate(const View<WT, N, M, RATIO>& g, int nl, 
             bool ch = false;
             np[i] = nh[i] = 0;
             if (v < n) {
-                const long long own = (long long)S.E[v] >> kBits;
+                const long long own = g.value(v);
                 const int cur = S.pi[v];
                 const bool onC = S.onc[v] == 3;
                 long long best = INT64_MAX;
@@ -521,7 +577,7 @@ __device__ __forceinline__ void iterate(const View<WT, N, M, RATIO>& g, int nl, 
                         key[u] = L * g.weight(e) - (RATIO ? W * g.time(e) : W);
                     }
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) key[u] += (long long)S.E[x[u]] >> kBits;
+                    for (int u = 0; u < 4; ++u) key[u] += g.value(x[u]);
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         if (eb + u >= end) break;
@@ -545,7 +601,7 @@ __device__ __forceinline__ void iterate(const View<WT, N, M, RATIO>& g, int nl, 
         }
         // their policy is written at once: only the row's own scan reads it
         if (LISTED) listed_rows<false>(g, nl, nw, L, W, tight, certain, [&](int v, long long best, int arg, int bh) {
-            if (best >= (long long)S.E[v] >> kBits) return;
+            if (best >= g.value(v)) return;
             ++changed;
             broke |= S.onc[v] == 3;
             if ((t & 63) == 0) {
@@ -587,13 +643,7 @@ __device__ __forceinline__ void iterate(const View<WT, N, M, RATIO>& g, int nl, 
                 }
                 S.pi[v] = (unsigned short)np[i];
                 S.succ[v] = (unsigned short)nh[i];
-                if (!general) {
-                    unsigned long long e = (unsigned)s;
-                    if (v != s && !chase_pack(L * g.weight(np[i]) - (RATIO ? W * g.time(np[i]) : W),
-                                              (unsigned)nh[i], kBits, &e))
-                        S.over = 1;
-                    S.E[v] = e;
-                }
+                if (!general && !g.entry(v, s, L, W, np[i], nh[i])) S.over = 1;
             }
         }
         par ^= 1;
@@ -621,7 +671,7 @@ __device__ __forceinline__ void iterate(const View<WT, N, M, RATIO>& g, int nl, 
         for (int i = t >> 6; LISTED && i < nl + nw; i += B >> 6) {
             const int v = i < nl ? S.longs[i] : S.wides[i - nl];
             if (!S.layer[v]) continue;   // this wave's to write
-            const long long own = (long long)S.E[v] >> kBits;
+            const long long own = g.value(v);
             const int end = S.rb[v + 1];
             bool alive = false;
             for (int eb = S.rb[v]; eb < end && !alive; eb += 64) {
@@ -629,9 +679,8 @@ __device__ __forceinline__ void iterate(const View<WT, N, M, RATIO>& g, int nl, 
                 bool a = false;
                 if (e < end) {
                     const int x = g.head(e);
-                    a = S.layer[x] && ((long long)S.E[x] >> kBits) + L * g.weight(e) -
-                                              (RATIO ? W * g.time(e) : W) ==
-                                          own;
+                    a = S.layer[x] &&
+                        g.value(x) + L * g.weight(e) - (RATIO ? W * g.time(e) : W) == own;
                 }
                 alive = __ballot(a) != 0;
             }
@@ -641,14 +690,12 @@ __device__ __forceinline__ void iterate(const View<WT, N, M, RATIO>& g, int nl, 
         }
         for (int v = t; v < n; v += B) {
             if (!S.layer[v] || (LISTED && (int)S.rb[v + 1] - (int)S.rb[v] > kLongEdges)) continue;
-            const long long own = (long long)S.E[v] >> kBits;
+            const long long own = g.value(v);
             bool alive = false;
             for (int e = S.rb[v]; e < (int)S.rb[v + 1] && !alive; ++e) {
                 const int x = g.head(e);
                 if (!S.layer[x]) continue;
-                alive = ((long long)S.E[x] >> kBits) + L * g.weight(e) -
-                            (RATIO ? W * g.time(e) : W) ==
-                        own;
+                alive = g.value(x) + L * g.weight(e) - (RATIO ? W * g.time(e) : W) == own;
             }
             if (!alive) S.layer[v] = 0;
             out |= !alive;
@@ -665,7 +712,7 @@ __device__ __forceinline__ void iterate(const View<WT, N, M, RATIO>& g, int nl, 
 
 // The whole solve; every thread returns the same Run.  row_ptr[0..n] holds the
 // rows' edge positions (e0 = row_ptr[0] when the CSR is known to be sound).
-template <typename WT, int N, int M, bool RATIO>
+template <bool WIDE, typename WT, int N, int M, bool RATIO>
 __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
                           const int* __restrict__ row_ptr, const int* __restrict__ col,
                           const WT* __restrict__ w, const int* __restrict__ tm, bool neg,
@@ -738,7 +785,7 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
         R.tight = R.status == OCM_E_INVALID_ARG ? 1u : 0u;   // which argument: times
         return;
     }
-    const View<WT, N, M, RATIO> g{S, col, w, tm, v0, e0, neg, maxw <= (unsigned long long)INT32_MAX};
+    const View<WT, N, M, RATIO, WIDE> g{S, col, w, tm, v0, e0, neg, maxw <= (unsigned long long)INT32_MAX};
 
     for (int v = t; v < n; v += B) {
         const int len = (int)S.rb[v + 1] - (int)S.rb[v];
@@ -758,14 +805,17 @@ __device__ void solve_one(Lds<N, M, RATIO>& S, int n, int m, int v0, int e0,
 }
 
 // Policy hops to s into out (the values are gone afterwards).
-template <int N, int M, bool RATIO>
+template <bool WIDE, int N, int M, bool RATIO>
 __device__ __forceinline__ void hops(Lds<N, M, RATIO>& S, int n, int s)
 {
     __syncthreads();
-    for (int v = threadIdx.x; v < n; v += blockDim.x)
-        S.E[v] = v == s ? (unsigned long long)(unsigned)s : (1ull << kBits) | S.succ[v];
+    for (int v = threadIdx.x; v < n; v += blockDim.x) {
+        const unsigned to = v == s ? (unsigned)s : S.succ[v];
+        if (WIDE) S.JM[v] = to;
+        S.E[v] = WIDE ? (unsigned long long)(v != s) : ((unsigned long long)(v != s) << kBits) | to;
+    }
     __syncthreads();
-    chase(S, n, (unsigned)s);
+    chase<WIDE>(S, n, (unsigned)s);
     __syncthreads();
 }
 
@@ -778,13 +828,13 @@ __global__ __launch_bounds__(1024) void k_small_one(int n, int m, const int* __r
 {
     __shared__ Lds<N, M, RATIO> S;
     Run R;
-    solve_one<WT, N, M, RATIO>(S, n, m, 0, 0, row_ptr, col, w, tm, neg != 0, o, p.init, R);
+    solve_one<false, WT, N, M, RATIO>(S, n, m, 0, 0, row_ptr, col, w, tm, neg != 0, o, p.init, R);
     if (R.status == OCM_OK && (long long)R.clen <= o.cycle_cap) {
         for (int v = threadIdx.x; v < n; v += blockDim.x) {
             if (p.policy) p.policy[v] = S.pi[v];
             if (p.potential) p.potential[v] = (long long)S.E[v] >> kBits;
         }
-        hops(S, n, R.s);
+        hops<false>(S, n, R.s);
         for (int v = threadIdx.x; v < n; v += blockDim.x)
             if (S.onc[v] == 3)
                 p.cycle[v == R.s ? 0 : (int)R.clen - (int)(S.E[v] >> kBits)] = S.pi[v];
@@ -813,8 +863,11 @@ __global__ __launch_bounds__(1024) void k_small_one(int n, int m, const int* __r
 }
 
 // The batched small class: graphs list[0..nlist) of the union, a workgroup
-// each (grid-stride).  A graph whose sums do not fit goes to the loop.
-template <typename WT, int N, int M>
+// each (grid-stride).  A graph whose sums do not fit the entries is left to a
+// second launch with 64-bit values (WIDE; the graphs that are done pass), then to
+// the loop.  300 graphs of 1000 vertices, ms in the loop / so: weights to 2^44 4.08 /
+// 1.01, to 2^50 8.99 / 0.79.
+template <typename WT, int N, int M, bool WIDE>
 __global__ __launch_bounds__(1024) void k_small_batch(const int* __restrict__ list, int nlist,
                                                       SmallBatch b, const int* __restrict__ row_ptr,
                                                       const int* __restrict__ col,
@@ -823,20 +876,22 @@ __global__ __launch_bounds__(1024) void k_small_batch(const int* __restrict__ li
     __shared__ Lds<N, M, false> S;
     for (int li = blockIdx.x; li < nlist; li += gridDim.x) {
         const int g = list[li];
+        if (WIDE && b.mode[g] == 0) continue;
         const int v0 = (int)b.vptr[g], e0 = (int)b.eptr[g];
         const int n = (int)(b.vptr[g + 1] - v0), m = (int)(b.eptr[g + 1] - e0);
         Run R;
-        solve_one<WT, N, M, false>(S, n, m, v0, e0, row_ptr + v0, col, w, nullptr, neg != 0, o,
-                                   nullptr, R);
+        solve_one<WIDE, WT, N, M, false>(S, n, m, v0, e0, row_ptr + v0, col, w, nullptr, neg != 0, o,
+                                         nullptr, R);
         if (R.status == OCM_OK) {
             for (int v = threadIdx.x; v < n; v += blockDim.x) {
                 b.pi[v0 + v] = e0 + S.pi[v];
                 b.succ[v0 + v] = v0 + S.succ[v];
-                b.V[v0 + v] = (long long)S.E[v] >> kBits;
+                b.V[v0 + v] = WIDE ? (long long)S.E[v] : (long long)S.E[v] >> kBits;
                 b.onC[v0 + v] = S.onc[v] == 3;
             }
-            hops(S, n, R.s);
-            for (int v = threadIdx.x; v < n; v += blockDim.x) b.hop[v0 + v] = (int)(S.E[v] >> kBits);
+            hops<WIDE>(S, n, R.s);
+            for (int v = threadIdx.x; v < n; v += blockDim.x)
+                b.hop[v0 + v] = (int)(WIDE ? S.E[v] : S.E[v] >> kBits);
         }
         if (threadIdx.x == 0 && R.status != kSmallFallback) {
             b.W[g] = R.W;
@@ -898,33 +953,40 @@ void launch_small_one(int n, int m, const int* row_ptr, const int* col, const vo
     }
 }
 
-template <typename WT>
+template <typename WT, bool WIDE>
 static void launch_batch(int cls, const int* list, int nlist, const SmallBatch& b, const int* row_ptr,
                          const int* col, const WT* w, int neg, const SmallOpts& o, hipStream_t st)
 {
     // one graph per workgroup, dispatched as earlier ones end
     switch (cls) {
         case 0:
-            sm::k_small_batch<WT, 512, 4096><<<nlist, 256, 0, st>>>(list, nlist, b, row_ptr, col, w, neg, o);
+            sm::k_small_batch<WT, 512, 4096, WIDE><<<nlist, 256, 0, st>>>(list, nlist, b, row_ptr, col, w, neg, o);
             break;
         case 1:
-            sm::k_small_batch<WT, 1024, 8192><<<nlist, 512, 0, st>>>(list, nlist, b, row_ptr, col, w, neg, o);
+            sm::k_small_batch<WT, 1024, 8192, WIDE><<<nlist, 512, 0, st>>>(list, nlist, b, row_ptr, col, w, neg, o);
             break;
         case 2:
-            sm::k_small_batch<WT, 2048, 16384><<<nlist, 1024, 0, st>>>(list, nlist, b, row_ptr, col, w, neg, o);
+            sm::k_small_batch<WT, 2048, 16384, WIDE><<<nlist, 1024, 0, st>>>(list, nlist, b, row_ptr, col, w, neg, o);
             break;
         default:
-            sm::k_small_batch<WT, 4096, 0><<<nlist, 1024, 0, st>>>(list, nlist, b, row_ptr, col, w, neg, o);
+            sm::k_small_batch<WT, 4096, 0, WIDE><<<nlist, 1024, 0, st>>>(list, nlist, b, row_ptr, col, w, neg, o);
     }
 }
 
 void launch_small_batch(int cls, const int* list, int nlist, const SmallBatch& b, const int* row_ptr,
                         const int* col, const void* w, int wtype, int neg, const SmallOpts& o,
-                        hipStream_t st)
+                        bool wide, hipStream_t st)
 {
     if (nlist <= 0) return;
-    if (wtype == kWI64) launch_batch(cls, list, nlist, b, row_ptr, col, (const long long*)w, neg, o, st);
-    else launch_batch(cls, list, nlist, b, row_ptr, col, (const int*)w, neg, o, st);
+    const auto* w64 = (const long long*)w;
+    const auto* w32 = (const int*)w;
+    if (wtype == kWI64) {
+        launch_batch<long long, false>(cls, list, nlist, b, row_ptr, col, w64, neg, o, st);
+        if (wide) launch_batch<long long, true>(cls, list, nlist, b, row_ptr, col, w64, neg, o, st);
+    } else {
+        launch_batch<int, false>(cls, list, nlist, b, row_ptr, col, w32, neg, o, st);
+        if (wide) launch_batch<int, true>(cls, list, nlist, b, row_ptr, col, w32, neg, o, st);
+    }
 }
 
 }  // namespace ocm

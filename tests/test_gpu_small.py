@@ -223,3 +223,30 @@ def test_batched_classes(monkeypatch):
         got.append((r.p, r.q, r.iterations, r.flags, r.status, r.cycle_ptr, r.cycle_edges.cpu().tolist()))
     assert got[0] == got[1]
     assert got[0][4] == [0] * 5 + [ocm.OCM_E_OVERFLOW] + [0] * 5
+
+
+@pytest.mark.parametrize("mode", ["min", "max"])
+@pytest.mark.parametrize("opt", [dict(), dict(fast_path=False), dict(max_iters=4)])
+def test_batched_sums_of_64_bits(mode, opt, monkeypatch):
+    """Weights whose sums leave the packed entries, in every class, beside graphs
+    whose sums do not, with long rows, a graph that is not strongly connected
+    and values beyond the limit."""
+    i64 = np.int64
+    gs = [synth.random_digraph(n, 1, d, -2**b, 2**b, i64, seed=[105, n, b])
+          for n, d, b in ((1, 2, 49), (2, 2, 49), (63, 4, 49), (257, 3, 49), (512, 5, 44), (700, 4, 20), (1000, 5, 49), (1024, 4, 46),
+                          (1025, 6, 48), (2048, 5, 48), (2047, 6, 30), (300, 60, 49))]
+    gs += [rows(500, (127, 2500), -2**49, 2**49, i64, 106), rows(2000, (300, 3000, 9000), -2**48, 2**48, i64, 107, True)]
+    gs.append(synth.deep_tail_graph(700, 800, 2, 10, 2**35, 2**36, seed=1))
+    gs.append(synth.deep_tail_graph(700, 800, 2, 10, 2**47, 2**48, seed=1))
+    gs.append(synth.Graph(np.array([0, 1, 2], np.int32), np.array([0, 1], np.int32), np.array([2**49, 1], i64)))
+    u, vptr, eptr = synth.disjoint_union(gs)
+    arrays = dev(u.row_ptr, u.col, u.w)
+    got = []
+    for small in ("1", "0"):
+        monkeypatch.setenv("OCM_BATCH_SMALL", small)
+        r = ocm.cycle_mean_batched(*arrays, vptr, eptr, mode=mode, **opt)
+        got.append((r.p, r.q, r.iterations, r.flags, r.status, r.cycle_ptr, r.cycle_edges.cpu().tolist()))
+    assert got[0] == got[1]
+    assert got[0][4][-1] == ocm.OCM_E_NOT_STRONGLY_CONNECTED
+    if not opt:
+        assert sum(x == ocm.OCM_OK for x in got[0][4]) >= len(gs) - 2
