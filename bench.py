@@ -95,6 +95,7 @@ def class_kernels(table, cls):
 # multichain files do not change its kernels).
 DIGEST_FILES = ("include/ocm.h", "paper_1111_0627_amd/csrc/kernels.h",
                 "paper_1111_0627_amd/csrc/device_util.h", "paper_1111_0627_amd/csrc/low.h",
+                "paper_1111_0627_amd/csrc/small.h", "paper_1111_0627_amd/csrc/small.hip",
                 "paper_1111_0627_amd/csrc/kernels.hip",
                 "paper_1111_0627_amd/csrc/solver.hip", "paper_1111_0627_amd/csrc/batch.hip")
 

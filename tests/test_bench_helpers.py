@@ -67,3 +67,19 @@ def test_stale_counter_files_are_not_used(tmp_path, monkeypatch):
     (tmp_path / "profiles" / "pmc_w.md").write_text("x\n```json\n" + json.dumps(blob) + "\n```\n")
     monkeypatch.setattr(bench, "ROOT", str(tmp_path))
     assert bench.load_pmc("w") is None
+
+
+def test_digest_covers_what_a_single_solve_is_built_from():
+    csrc = os.path.join(bench.SRC_ROOT, "paper_1111_0627_amd", "csrc")
+    need, seen = ["kernels.hip", "solver.hip", "small.hip"], set()
+    while need:
+        name = need.pop()
+        if name in seen:
+            continue
+        seen.add(name)
+        with open(os.path.join(csrc, name)) as f:
+            for line in f:
+                if line.startswith('#include "') and os.path.exists(os.path.join(csrc, line.split('"')[1])):
+                    need.append(line.split('"')[1])
+    digest = {os.path.basename(f) for f in bench.DIGEST_FILES}
+    assert seen <= digest, seen - digest
