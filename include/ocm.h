@@ -42,7 +42,9 @@
  * ocm_min / ocm_max on a graph of at least 131072 vertices also builds the
  * reverse CSR on a library-owned stream of the same device (created once,
  * default priority), ordered after the call's earlier work by an event; the
- * call waits for it before using it and before returning.
+ * call waits for it before using it and before returning.  The batched and the
+ * general calls do so too for graphs that they solve one after the other (at
+ * most four outside the small classes).
  *
  * Errors: functions return ocm_status; nothing aborts or throws across the
  * ABI.  ocm_last_error() returns a thread-local message for the last failure.

@@ -1638,8 +1638,8 @@ __global__ __launch_bounds__(kWG) void k_tie_init(int G, GArrays ga)
     }
 }
 
-// Graphs of at most kSmallN vertices and kSmallM edges never enter the loop:
-// a workgroup solves each whole (small.hip).
+// Graphs of at most kSmallN vertices and kSmallM edges are solved whole by a
+// workgroup each (small.hip); only those with a value beyond 2^62 enter the loop.
 constexpr int kSmallN = 2048;
 constexpr int kSmallM = 32768;
 
@@ -2647,6 +2647,10 @@ ocm_status exact_tie(BCtx& c, int64_t g, const int64_t* vptr, const int64_t* ept
 // are at most this many: an iteration of the loop is about 60 kernels whatever
 // it holds, a fast iteration of the solver two.  One component of 120,000
 // vertices (of a sparse graph of 200,000): 6.4 ms in the loop, 1.5 ms alone.
+// Batches, ms, loop / alone: two random graphs of 2500 vertices 2.4 / 0.9, four
+// 3.6 / 1.3; two of 50,000 7.4 / 3.3, four 8.9 / 5.9; two of 10^6 19.7 / 13.7, four
+// 24.0 / 20.7; four tori of 300^2 24.0 / 17.0, of 700^2 70.8 / 63.8: the loop takes
+// little longer for each further graph, so the gain ends beyond four large ones.
 constexpr int64_t kSoloGraphs = 4;
 
 ocm_status solve_solo(BCtx& c, int64_t g, const int64_t* vptr, const int64_t* eptr,

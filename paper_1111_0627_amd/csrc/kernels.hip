@@ -2793,10 +2793,10 @@ __global__ __launch_bounds__(kWG) void k_fill_u32(int64_t len, unsigned* __restr
 // waves stop at kChaseFew steps with half of them on the way (at 32 with a
 // quarter, 64 with an eighth) from the next phase on, and the next pass finds
 // longer entries: 17.6 ms; 2^20 to 2^23 random vertices and products unchanged.
-// A pass that leaves vertices unfinished is followed by another one; one that finishes nobody
-// proves a stall: an unfinished vertex of C's component nearest to s has
-// reached a finished one and finishes with its next step.  A vertex that
-// reaches itself lies on another cycle, which proves it at once.
+// A pass that leaves vertices unfinished is followed by another one; one that
+// finishes nobody proves a stall: an unfinished vertex of C's component nearest
+// to s has reached a finished one and finishes with its next step.  A vertex
+// that reaches itself lies on another cycle, which proves it at once.
 // ---------------------------------------------------------------------------
 __global__ void k_loop_setup(Ctl* c, unsigned mode, unsigned opts, unsigned max_sweeps)
 {
@@ -3805,7 +3805,10 @@ void launch_chase_init(int n, const int* col, const int* pi, const void* w, int 
 // reads may be late as long as writes go through: 2^20: 82 / 74 / 82, 300,007:
 // 30 / 28 / 33.  On large graphs written-through steps cost more than they
 // save: 2^22: 284 / 269 / 275, 2^23: 436 / 423 / 355, 16^6 product: 501 / 397 /
-// 259.
+// 259.  Whole solves between, ms, that line at 2^22 / 2^23: random 4.3M 27.1 /
+// 28.0, 5M 11.0 / 11.9, 6M 41.7 / 42.9, 7M 22.4 / 24.2, 24^5 product (8.0M) 10.1 /
+// 10.6, torus of 2200^2 132 / 152; at 2^21 / 2^22: random 2.1M 13.5 / 14.1, 3M 7.0
+// / 7.8, 4.1M 36.5 / 36.1, products of 2.6M and 3.0M the same.
 void launch_chase(int n, int jb, unsigned long long* E, long long* V, int* out32, unsigned char* q8,
                   Ctl* ctl, hipStream_t st)
 {
@@ -3953,7 +3956,10 @@ void launch_loop_low_cycles(int n, const int* col, const int* pi, int* succ, boo
     // edges; a pass of a few steps for all, then one that finishes the rest.
     // Scopes: written through and read fresh, or the walks around a cycle find
     // its lowest vertex late (2^22: over 256 steps); above 2^22 the first pass
-    // and the roots' cheaper steps win (16^6 product: 608 us against 899).
+    // and the roots' cheaper steps win (16^6 product: 608 us against 899).  Whole
+    // solves, ms, that line at 2^22 / 2^23: random 4.3M 27.1 / 27.4, 13^6 product
+    // (4.8M) 4.33 / 4.46, 24^5 (8.0M) 10.1 / 10.3; at 2^21 / 2^22: random 2.1M 13.9 /
+    // 14.1, 3M 7.8 / 7.8, torus of 1800^2 58.3 / 51.4.
     if (n < (1 << 18)) {
         k_low_next<A, A><<<grid, kWG, 0, st>>>(n, kLowSteps, 1, N, T, ctl);
         k_low_root<A, A><<<grid, kWG, 0, st>>>(n, T, cyc_list, ctl);

@@ -22,13 +22,14 @@ namespace sm {
 //     (value << kBits) | s.  A sweep reads the values, and after a barrier its
 //     threads write the next entries.
 //   * Classes (vertices, edges, threads in a batch; LDS): 512, 4096, 256 (36
-//     KB, 4 per CU); 1024, 8192, 512 (71 KB, 2 per CU); 2048, 16384, 1024 (142
-//     KB); 4096, edges in memory, 1024 (92 KB).  A single solve, alone on its
+//     KB, 4 per CU); 1024, 8192, 512 (72 KB, 2 per CU); 2048, 16384, 1024 (143
+//     KB); 4096, edges in memory, 1024 (94 KB).  A single solve, alone on its
 //     CU, takes 128 to 512 threads up to 512 vertices and 1024 beyond.
 //   * A thread walks its vertex's row, a wave the rows of more than kLongEdges
 //     edges, the whole workgroup those of more than kWideEdges: see below.
 // Sums that do not fit an entry (kBits for the vertex, 51 and a sign for the
-// sum) end the solve with kSmallFallback: the general path takes the graph.
+// sum) end the solve with kSmallFallback: the general path takes the graph, in a
+// batch first a second launch with wider entries.
 // ---------------------------------------------------------------------------
 constexpr int kBits = 12;
 constexpr unsigned long long kMask = (1ull << kBits) - 1;
