@@ -2256,7 +2256,11 @@ __global__ __launch_bounds__(kWG) void k_round_vertex(int k, int n, const int* _
 // marks left (a pull came first) every unattached vertex looks, which attaches
 // the same vertices by the same edges; the next round gets its marks either way
 // (as pull rounds, which leave none, a ring of a million vertices took 57.9 ms
-// over 2600 rounds, 33.1 so).
+// over 2600 rounds, 33.1 so).  Not while the frontier is more than a kMarkShare-th
+// of the vertices left: few rounds follow, and the marks are not worth it (batch of
+// 4096, ms: marks always 149.5, from a 4th down 147.9, a 16th 146.6, a 64th 146.4;
+// pushes of the rings are the same for all).
+constexpr unsigned long long kMarkShare = 16;
 template <bool GIANT>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_round_claim(
     int k, int n, const int* __restrict__ row_ptr, const int* __restrict__ col,
@@ -2270,9 +2274,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     __shared__ RoundLds L;
     __shared__ HeavyLds H;
     const bool left_marks = ctl->rmarks == (unsigned)k;
-    if (push) {
+    const bool all = single && !left_marks;
+    if (push && !(all && kMarkShare * ctl->rfront > ctl->rleft)) {
         const unsigned long long g =
-            claim_body<GIANT>(k, n, single && !left_marks, row_ptr, col, acur, anext, marks, pi, layer,
+            claim_body<GIANT>(k, n, all, row_ptr, col, acur, anext, marks, pi, layer,
                               nullptr, nullptr, nullptr, rin_ptr, rin, marks_next, pedges, L, &H);
         if (threadIdx.x == 0) round_close(ctl, k, g, policy, push_min, true);
     } else {
